@@ -29,6 +29,8 @@ import numpy as np  # noqa: E402
 
 # MI355X published peaks
 PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
+# the 128 x 128 fp32 tile runs six bf16 products per fp32 product
+PEAK_F32_TERMS_TFLOPS = PEAK_TFLOPS["bf16"] / 6
 PEAK_HBM_GBS = 8000.0
 # roofline.traffic (L2 <-> memory bytes per launch of the dominant kernel, from rocprofv3 FETCH_SIZE /
 # WRITE_SIZE runs scaled by a plain copy) is read from the traffic-record lines of the summaries under
@@ -181,7 +183,9 @@ def gemm_kernel_name(w, pgk, gen):
     bf = w.dtype == gen.BF16
     if (bm, bn) == (32, 32):
         return "pgk::gemm_tiny_f32_kernel", plan
-    layout = {(256, 256): "4, 2, 3, 2", (128, 128): "2, 2, 3, 2" if bf else "2, 2, 2, 1", (64, 64): "2, 2, 2, 2",
+    if not bf and (bm, bn) == (128, 128):
+        return "pgk::gemm_f32_terms_kernel<TermsCfg<false, 128, 128, 2>, 0, false>", plan
+    layout = {(256, 256): "4, 2, 3, 2", (128, 128): "2, 2, 3, 2", (64, 64): "2, 2, 2, 2",
               (256, 128): "4, 2, 3, 2", (128, 256): "2, 4, 3, 2", (32, 128): "1, 4, 2, 2", (128, 32): "4, 1, 2, 2"}[(bm, bn)]
     return f"MfmaCfg<{'true' if bf else 'false'}, {bm}, {bn}, {bk}, {layout}>, 0, false>", plan
 
@@ -194,14 +198,15 @@ def gemm_roofline(name, w, res, pgk, gen):
     dtype_key = "bf16" if w.dtype == gen.BF16 else "f32"
     achieved = w.flops / (res["call_ms_avg"] * 1e-3) / 1e12
     kernel, plan = gemm_kernel_name(w, pgk, gen)
+    peak = PEAK_F32_TERMS_TFLOPS if "f32_terms" in kernel else PEAK_TFLOPS[dtype_key]
     return {
         "bound": "mfma",
         "kernel": "pgk::gemm_mfma_kernel<" + kernel if kernel.startswith("MfmaCfg") else kernel,
         "plan": plan,
         "achieved": achieved,
-        "peak": PEAK_TFLOPS[dtype_key],
+        "peak": peak,
         "unit": "TFLOP/s",
-        "frac": achieved / PEAK_TFLOPS[dtype_key],
+        "frac": achieved / peak,
         "launch_ms_avg": res["call_ms_avg"],
         "launch_ms_median": res["call_ms_median"],
         "launch_ms_min": res["call_ms_min"],
@@ -226,8 +231,8 @@ def phase_budget(name, pgk, gen, torch, launches=6, sets=1, warmup=2):
     # tile, workgroups resident on one CU (registers and LDS of the instance), matrix-core flops per
     # cycle of one CU (published peak / 256 CUs / 2.4 GHz)
     bf16 = w.dtype == gen.BF16
-    bm, bn, bk, per_cu, cu_flops_per_cycle = (256, 256, 64, 1, 4096) if bf16 else (128, 128, 32, 2, 256)
-    issue_cycles = bm * bn * bk * 2 // cu_flops_per_cycle * per_cu   # per K tile, as one workgroup sees them
+    bm, bn, bk, per_cu, products = (256, 256, 64, 1, 1) if bf16 else (128, 128, 32, 2, 6)
+    issue_cycles = bm * bn * bk * 2 * products // 4096 * per_cu      # per K tile, as one workgroup sees them
     _, (dA, dB, dbias) = device_inputs(w, gen, torch)
     tiles_n = -(-w.N // bn)
     wgs = -(-w.M // bm) * tiles_n
@@ -287,7 +292,7 @@ def phase_budget(name, pgk, gen, torch, launches=6, sets=1, warmup=2):
     clk = float(np.median(clocks))
     ms = float(np.median(per_ms))
     achieved = w.flops / (ms * 1e-3) / 1e12
-    peak_at_clock = PEAK_TFLOPS["bf16" if bf16 else "f32"] * clk / 2.4
+    peak_at_clock = PEAK_TFLOPS["bf16"] / products * clk / 2.4
     return {
         "workload": DESCR[name], "workgroups": int(wgs), "rounds": rounds, "k_tiles": kt,
         "launches": launches, "buffer_sets": len(bufs),
@@ -440,7 +445,9 @@ def conv_main(args, name, pgk, gen, torch):
     fast = head["workspace_bytes"] > 0
     # the matrix-core path is priced against the matrix peak of its type, the bounds-checked
     # path (plain fp32 FMA) against the fp32 vector peak
-    peak = PEAK_TFLOPS[dtype_key] if fast else 157.3
+    # (fp32 with more than 64 output channels runs on the 128 x 128 tile)
+    terms = fast and dtype_key == "f32" and cw.Cout > 64
+    peak = PEAK_F32_TERMS_TFLOPS if terms else PEAK_TFLOPS[dtype_key] if fast else 157.3
     achieved = cw.flops / (head["call_ms_avg"] * 1e-3) / 1e12
     out = {
         "metric": "conv1d+epilogue TFLOP/s on 1 MI355X",
@@ -452,7 +459,7 @@ def conv_main(args, name, pgk, gen, torch):
                    "stride": cw.stride, "pad": cw.pad, "dilation": cw.dilation, "flops_per_step": cw.flops,
                    "algorithmic_bytes_per_step": cw.algorithmic_bytes, "workspace_bytes": head["workspace_bytes"]},
         "roofline": {"bound": "mfma" if fast else "alu",
-                     "kernel": "pgk::gemm_mfma_kernel on shifted views (+ pad and weight regrouping kernels)" if fast
+                     "kernel": ("pgk::gemm_f32_terms_kernel" if terms else "pgk::gemm_mfma_kernel") + " on shifted views (+ pad and weight regrouping kernels)" if fast
                                else "pgk::gemm_guarded_kernel reading the input in place",
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                      "launch_ms_avg": head["call_ms_avg"], "traffic": None,

@@ -1,0 +1,712 @@
+// fp32 GEMM on the bf16 matrix cores, with the fused epilogue, for gfx950 (MI355X): the kernel
+// template and its configurations.  Same operator, arguments and tile shapes as the kernels of
+// pgk_gemm_mfma_kernel.h (C = act(A*B + bias), optional row sums; PRAGMA Sections 1 and 4.2 name
+// it, the definition is the textbook one).
+//
+// What bounds an fp32 GEMM on this chip is the fp32 matrix instruction: 157 TFLOP/s, a sixteenth
+// of the bf16 one.  Here every operand value is taken apart into three bf16 values that add up to
+// it exactly (8 + 8 + 8 significand bits: x = h + m + l with h = x rounded to bf16, m = x - h cut off
+// after 8 bits, l the rest; the differences are exact in fp32), and a product is the sum of six bf16
+// products, accumulated in fp32:
+//     a b = ah bh + (ah bm + am bh) + (ah bl + al bh + am bm) + [am bl + al bm + al bl]
+// The bracket is left out: |m| <= 2^-8 |x| and |l| <= 2^-7 |m|, m of either sign, so it stays below
+// 2^-22 |a b| at worst, 2^-27 in the mean square, without a bias.  A product with an identity matrix
+// gives the other factor exactly.  Measured against 64-bit sums (2048 x 2048 outputs, A uniform in
+// [-1, 1), B normal), 2-norm of the error, the fp32 instruction / here: K = 32 1.03e-7 / 0.39e-7,
+// 256 2.87e-7 / 2.28e-7, 4096 1.15e-6 / 0.98e-6, 8192 1.62e-6 / 1.39e-6 (row sums 1.6e-6 / 1.4e-6).
+//
+// Rounding.  Inside the bf16 matrix instruction sums are cut off downwards, not rounded to nearest:
+// every output comes out a little low, as much again as its random error, and a sum over many
+// outputs (the row sums) would show it (256 x 256 x 65536: 1.9e-5 against the fp32 instruction's
+// 1.6e-6).  So odd rows of A and odd columns of B enter with their sign turned and the epilogue
+// turns it back, which costs nothing in either place: neighbouring outputs then err in opposite
+// directions.  And in the course of the K loop the sign of A (and of the accumulators) changes
+// twice, at a quarter and at three quarters of it, which takes a cut that is constant or grows
+// evenly out of every single output.
+//
+// Range.  bf16 has the exponents of fp32, so nothing overflows that fp32 holds, with two
+// exceptions, and both are found and made good inside the kernel: the tile is then computed again
+// with the fp32 matrix instruction (fallback below).
+//  * A value above the largest bf16 (3.39e38) rounds to infinity, and an infinity or NaN among the
+//    operands turns into NaN where fp32 would give an infinity.  Either way the accumulators it
+//    touches are not finite, so: any accumulator of the tile that is not finite.
+//  * The low terms of values below about 2^-110 fall under the smallest bf16.  Against values of the
+//    same row of A (column of B) of 2^-63 and more that is nothing; so: a thread that has seen
+//    only values below 2^-63 in its part of a row of A or a column of B (zeros alone do not count).
+//    2^-63 because a value reaches it exactly if one of the two upper bits of its exponent is set:
+//    the bitwise or of the values tells, at one operation per pair.
+//
+// How: a workgroup of four waves owns a BM x BN tile of C (waves 2 x 2), K in steps of 32.  While the
+// waves multiply the step in LDS, each thread splits its share of the fp32 values of the next one
+// (loaded into registers a step before) and loads the one after it, all in the shadow of the
+// matrix instructions; between two barriers the planes of bf16 values then go to LDS.  LDS holds one
+// step, 48 KiB for 128 x 128, and two workgroups share a CU: one multiplies while the other writes,
+// starts or stores.
+//  * Splitting in the copy and not at the operand fetch: every value is split once per workgroup
+//    instead of once per wave that reads it.
+//  * The differences are plain subtractions: v_dot2c_f32_bf16 would subtract without unpacking, but
+//    a matrix instruction next to one takes 36 cycles instead of 16 (measured).
+//  * 4096^3 with GELU 915 -> 645 us (213 TFLOP/s of fp32 products, 1280 of bf16 ones), 16 x [256 x 256 x
+//    65536] 1015 -> 748, 8192 x 8192 x 32 84 -> 71, 65536 x 128 x 1024 124 -> 93.  What bounds it: the matrix
+//    instructions alone, on these operands, run 500 us under the board's power limit; splitting
+//    and writing take issue slots next to them (72 % of the cycles are matrix instructions).
+//  * v_mfma_f32_16x16x32_bf16: with 32x32x16 two LDS stages of 16 k fit, a step takes 3724 cycles per
+//    pair of workgroups (3072 are matrix instructions), but the board's power limit then holds the
+//    clock at 1.63 GHz (4096^3 in 714 us).
+// LDS layout: fragments in the order the lanes read them -- sixteen rows x 32 k of one plane are
+// one contiguous KiB, lane (k chunk g, row r) reading 16 bytes of 256 g + ... (frag_pos) -- so that
+// operand reads need one address register; even rows before odd ones, XORed with the chunk, keeps
+// the reads and the writes (every other row, four k chunks at a time) free of bank conflicts.
+#ifndef PGK_GEMM_F32_TERMS_H
+#define PGK_GEMM_F32_TERMS_H
+
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+
+#include "pgk_device.h"
+#include "pgk_gemm_mfma_kernel.h"
+#include "pgk_kernels.h"
+
+namespace pgk {
+
+// f(IC<FROM>{}), ..., f(IC<TO - 1>{}): an unrolled loop whose index is a compile-time constant
+template <int FROM, int TO, typename F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (FROM < TO) {
+        f(IC<FROM>{});
+        static_for<FROM + 1, TO>(f);
+    }
+}
+
+template <bool BT_, int BM_, int BN_, int WAVES_PER_SIMD_>
+struct TermsCfg {
+    static constexpr bool BT = BT_;                    // B given as [N][K]
+    static constexpr int BM = BM_, BN = BN_, BK = 32;
+    static constexpr int WAVES_PER_SIMD = WAVES_PER_SIMD_;
+    static constexpr int WGM = 2, WGN = 2, NW = 4, NT = 256;
+    static constexpr int WM = BM / WGM, WN = BN / WGN;
+    static constexpr int TM16 = WM / 16, TN16 = WN / 16;       // 16 x 16 accumulator blocks per wave
+    static constexpr int PLANES = 3;
+    static constexpr int A_PLANE = BM * BK * 2, B_PLANE = BN * BK * 2;     // bytes of one plane
+    static constexpr int A_BYTES = PLANES * A_PLANE, B_BYTES = PLANES * B_PLANE;
+    // chunks of eight k values per thread: rows of A (of a transposed B), columns of a plain B
+    static constexpr int A_CH = BM * 4 / NT, B_CH = BN * 4 / NT;
+    static_assert(A_CH == 2 && B_CH == 2, "two neighbouring rows and columns per thread");
+    // the epilogue stages sixteen rows of a wave's part at a time
+    static constexpr int PIECE_BYTES = 16 * WN * 4;
+    static_assert(2 * PIECE_BYTES <= A_BYTES && 2 * PIECE_BYTES <= B_BYTES, "epilogue staging");
+};
+
+// The epilogue of a wave: its part of the tile, sixteen rows at a time, through a piece of LDS that
+// only this wave touches (LDS operations of one wave are carried out in order), stored as whole
+// row pieces of WN floats, 16 bytes per lane.  Accumulator layout and KINDs as in
+// pgk_gemm_mfma_kernel.h: lane (l16, grp) holds, of block (i, j), row 16 i + l16 and the columns
+// 16 j + 4 grp ..; HAS_BIAS false: partial products.
+template <int ACT, int KIND, typename Cfg, bool HAS_BIAS, bool STREAM>
+__device__ __forceinline__ void epilogue_terms(f32x4 (&acc)[Cfg::TM16][Cfg::TN16], const float* bias, const float* bias_row,
+                                               unsigned char* out_tile, size_t ld_bytes, int m_rem, int n_rem, int wm, int wn,
+                                               int lane, unsigned char* piece, float* rs_lds)
+{
+    constexpr int ROWB = Cfg::WN * 4;                     // bytes of a row piece
+    constexpr int UNITS = ROWB / 16;
+    constexpr int RPP = ROWB >= 256 ? 1 : 256 / ROWB;     // rows per 256-byte bank period
+    constexpr int CH = 16 * UNITS / 64;                   // chunks per lane and block
+    static_assert(ROWB >= 128 && (16 * UNITS) % 64 == 0, "row pieces of whole lines");
+    constexpr bool ROWSUM = KIND == EPI_ROWSUM || KIND == EPI_ROWSUM_MASKED;
+    const int grp = lane >> 4, row_in = lane & 15;
+    const int wkey = (row_in / RPP) % UNITS;
+    // the accumulators of outputs whose row and column are not both odd or both even have their sign turned
+    const float sign[2] = {row_in & 1 ? -1.0f : 1.0f, row_in & 1 ? 1.0f : -1.0f};
+#pragma unroll
+    for (int i = 0; i < Cfg::TM16; ++i) {
+        const int row = wm * Cfg::WM + 16 * i + row_in;   // row inside the tile
+        float rs = 0.0f, br = 0.0f;
+        if constexpr (KIND == EPI_ROWBIAS) br = bias_row[row];
+#pragma unroll
+        for (int j = 0; j < Cfg::TN16; ++j) {
+            const int colw = 16 * j + 4 * grp;            // column inside the wave's part
+            const int col = wn * Cfg::WN + colw;
+            f32x4 bv = {br, br, br, br};
+            if constexpr (HAS_BIAS && KIND != EPI_ROWBIAS) bv = *(const f32x4*)(bias + col);
+            int left = n_rem - col;
+            // (kept opaque: the comparisons are made where they are used, not held as lane masks)
+            if constexpr (KIND == EPI_ROWSUM_MASKED) asm volatile("" : "+v"(left));
+            f32x4 y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (HAS_BIAS) y[e] = activate<ACT>(__builtin_fmaf(acc[i][j][e], sign[e & 1], bv[e]));
+                else y[e] = __builtin_fmaf(acc[i][j][e], sign[e & 1], 0.0f);
+                if constexpr (KIND == EPI_ROWSUM) rs += y[e];
+                else if constexpr (KIND == EPI_ROWSUM_MASKED) rs += e < left ? y[e] : 0.0f;
+            }
+            *(f32x4*)(piece + row_in * ROWB + (((colw >> 2) ^ wkey) * 16)) = y;
+        }
+        if constexpr (ROWSUM) {
+            // the four lanes that share a row, in a fixed order
+            rs += __shfl_xor(rs, 16);
+            rs += __shfl_xor(rs, 32);
+            if (grp == 0) rs_lds[wn * Cfg::BM + row] = rs;
+        }
+        asm volatile("" ::: "memory");
+        u32x4 v[CH];
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+            const int c = lane + 64 * t;
+            const int r = c / UNITS, cc = c % UNITS;
+            v[t] = *(const u32x4*)(piece + r * ROWB + ((cc ^ ((r / RPP) % UNITS)) * 16));
+        }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+            const int c = lane + 64 * t;
+            const int r = c / UNITS, cc = c % UNITS;
+            const int trow = wm * Cfg::WM + 16 * i + r;
+            const int left = n_rem - (wn * Cfg::WN + cc * 4);     // elements of this chunk that exist
+            if (trow >= m_rem || left <= 0) continue;
+            unsigned char* at = out_tile + (size_t)trow * ld_bytes + (size_t)(wn * Cfg::WN) * 4 + (size_t)cc * 16;
+            if (left >= 4) {
+                if constexpr (STREAM) __builtin_nontemporal_store(v[t], (u32x4_align4*)at);
+                else *(u32x4_align4*)at = v[t];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    if (e >= left) break;
+                    ((unsigned int*)at)[e] = v[t][e];
+                }
+            }
+        }
+    }
+}
+
+template <typename Cfg, int VIEW, bool TIMED = false>
+__global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_kernel(const GemmArgs p, const int out_mode)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK;
+    constexpr int TM16 = Cfg::TM16, TN16 = Cfg::TN16, A_CH = Cfg::A_CH, B_CH = Cfg::B_CH;
+    constexpr bool BT = Cfg::BT;
+    constexpr int BIAS_N = BM > BN ? BM : BN;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_a[Cfg::A_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_b[Cfg::B_BYTES];
+    // row sums of the two wave columns, then the tile's column biases, then its row biases
+    __shared__ __attribute__((aligned(16))) float rs_buf[Cfg::WGN * BM + 2 * BIAS_N];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / Cfg::WGN, wn = wave % Cfg::WGN;
+    // phase stamp k of this workgroup: (cycles, 100 MHz ticks); see pgk_probe_gemm_phases
+    auto stamp = [&](int k) __attribute__((always_inline)) {
+        if constexpr (TIMED) {
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned long long cyc = __builtin_readcyclecounter();
+            const unsigned long long tick = __builtin_amdgcn_s_memrealtime();
+            if (wave == 0) {
+                unsigned long long* at = p.stamps + (size_t)blockIdx.x * kStampWords + 2 * k;
+                at[0] = cyc;
+                at[1] = tick;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    stamp(0);
+    if constexpr (TIMED) {
+        if (wave == 0) {
+            p.stamps[(size_t)blockIdx.x * kStampWords + 12] = (unsigned long long)__builtin_amdgcn_s_getreg(63492);   // HW_ID, 32 bits
+            p.stamps[(size_t)blockIdx.x * kStampWords + 13] = (unsigned long long)__builtin_amdgcn_s_getreg(63508);   // XCC_ID, 32 bits
+        }
+    }
+
+    // ---- which tile, batch entry and K slice this workgroup owns
+    const unsigned int tiles = (unsigned int)p.tiles_m * (unsigned int)p.tiles_n;
+    const unsigned int logical = xcd_remap(blockIdx.x, gridDim.x);
+    const unsigned int z = logical / tiles;
+    int tm, tn;
+    tile_coords(logical - z * tiles, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    const int b = (int)(z / (unsigned int)p.splits);
+    const int sp = (int)(z - (unsigned int)b * (unsigned int)p.splits);
+    const int k_begin = sp * p.k_slice;
+    const int k_end = (k_begin + p.k_slice < p.K) ? (k_begin + p.k_slice) : p.K;
+    const int KT = (k_end - k_begin + BK - 1) / BK;
+    const int k_last = (k_end - k_begin) - (KT - 1) * BK;        // k values of the last step that exist
+    // (see the same variable in pgk_gemm_mfma_kernel.h: skinny products start their K loops apart)
+    const int k_rot = (VIEW == VIEW_GEMM && p.k_rotate && k_last == BK)
+                          ? (int)((unsigned int)(p.batch > 1 ? b : tm + tn) % (unsigned int)KT) : 0;
+
+    const unsigned char* const Ag = (const unsigned char*)p.A +
+        ((size_t)b * (size_t)p.a_batch_stride + (size_t)tm * BM * p.K + (size_t)k_begin) * 4;
+    const unsigned char* b_src = (const unsigned char*)p.B;
+    int ldb = p.ldb;
+    long long b_batch_stride = p.b_batch_stride;
+    long long b_col0 = (long long)tn * BN;
+    if constexpr (VIEW == VIEW_CONV) {
+        b_col0 += p.b_col_shift;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            if (p.edge_B[e] && p.edge_tn[e] == tn) {
+                b_src = (const unsigned char*)p.edge_B[e];
+                ldb = p.edge_ldb;
+                b_batch_stride = p.edge_batch_stride;
+                b_col0 = 0;
+            }
+        }
+    }
+    const unsigned char* const Bg = b_src +
+        (BT ? ((long long)b * b_batch_stride + b_col0 * ldb + (long long)k_begin) * 4
+            : ((long long)b * b_batch_stride + (long long)k_begin * ldb + b_col0) * 4);
+    const size_t a_step = (size_t)BK * 4;
+    const size_t b_step = BT ? (size_t)BK * 4 : (size_t)BK * ldb * 4;
+    // one past the last byte of A and of B: what a partial last step, or a row's last columns, would
+    // read behind the array the buffer resource's size check cuts off (a convolution's copies and
+    // strips hold every column its tiles read, as they are laid out for that)
+    const unsigned char* const A_end = (const unsigned char*)p.A +
+        ((size_t)(p.batch - 1) * (size_t)p.a_batch_stride + (size_t)p.M * p.K) * 4;
+    const unsigned char* const B_end = (const unsigned char*)p.B +
+        ((size_t)(p.batch - 1) * (size_t)p.b_batch_stride + (size_t)(BT ? p.N : p.K) * p.ldb) * 4;
+    auto records = [](const unsigned char* base, const unsigned char* end) __attribute__((always_inline)) -> int {
+        const size_t left = (size_t)(end - base);
+        return left < 0xffffffffull ? (int)(unsigned int)left : (int)0xffffffffu;
+    };
+
+    const int m_rem = (p.M - tm * BM) < BM ? (p.M - tm * BM) : BM;
+    const int n_rem = (p.N - tn * BN) < BN ? (p.N - tn * BN) : BN;
+
+    constexpr bool BIAS_PER_ROW = VIEW == VIEW_CONV;
+    float bias_pre = 0.0f;
+    if (p.bias && out_mode == 0) {
+        if constexpr (BIAS_PER_ROW) { if (tid < m_rem) bias_pre = p.bias[(size_t)tm * BM + tid]; }
+        else if (tid < n_rem) bias_pre = p.bias[(size_t)tn * BN + tid];
+    }
+
+    // ---- what this thread copies: of A (and of a transposed B) the eight k values of chunk tid % 4 of
+    // two neighbouring rows; of a plain B the eight k rows 8 wave .. of two neighbouring columns.
+    // Rows and columns past the edge re-read the last ones.
+    const int my_row = 2 * (tid >> 2), my_chunk = tid & 3;
+    unsigned int voff_a[A_CH], voff_b[BT ? B_CH : 1];
+#pragma unroll
+    for (int t = 0; t < A_CH; ++t) {
+        const int r = my_row + t;
+        voff_a[t] = (unsigned int)(r < m_rem ? r : m_rem - 1) * (unsigned int)p.K * 4u + (unsigned int)my_chunk * 32u;
+    }
+    if constexpr (BT) {
+#pragma unroll
+        for (int t = 0; t < B_CH; ++t) {
+            const int r = my_row + t;
+            voff_b[t] = (unsigned int)(r < n_rem ? r : n_rem - 1) * (unsigned int)ldb * 4u + (unsigned int)my_chunk * 32u;
+        }
+    } else {
+        const int c = 2 * lane, last = (n_rem - 1) / 2 * 2;
+        voff_b[0] = (unsigned int)(8 * wave) * (unsigned int)ldb * 4u + (unsigned int)(c < n_rem ? c : last) * 4u;
+    }
+    const unsigned int b_row_bytes = (unsigned int)ldb * 4u;
+    // ... and where it goes in LDS (see "LDS layout")
+    auto frag_pos = [](int row, int g) __attribute__((always_inline)) {
+        return (row >> 4) * 1024 + g * 256 + (((((row & 15) >> 1) + 8 * (row & 1)) ^ (6 * g & 7)) * 16);
+    };
+    int wpos_a[A_CH], wpos_b[B_CH];
+#pragma unroll
+    for (int t = 0; t < A_CH; ++t) wpos_a[t] = frag_pos(my_row + t, my_chunk);
+#pragma unroll
+    for (int t = 0; t < B_CH; ++t) wpos_b[t] = BT ? frag_pos(my_row + t, my_chunk) : frag_pos(2 * lane + t, wave);
+
+    // ---- global -> registers, one step: ra[t] = eight k values of a row of A, rb[t] = of a column of B.
+    // Where the next step starts is running state, as in pgk_gemm_mfma_kernel.h.
+    float ra[A_CH][8], rb[B_CH][8];
+    size_t a_off = 0, b_off = 0;
+    int next_step = 0, b_row_step = 0, b_taps_done = 0;
+    long long tap_of_lane = 0;
+    if constexpr (VIEW == VIEW_CONV) {
+        const __attribute__((address_space(4))) long long* const tap_table =
+            (const __attribute__((address_space(4))) long long*)((const __attribute__((address_space(4))) char*)
+                __builtin_amdgcn_kernarg_segment_ptr() + offsetof(GemmArgs, b_tap_off));
+        tap_of_lane = tap_table[lane & 31];
+    }
+    auto tap_entry = [&](int t) __attribute__((always_inline)) -> long long {
+        const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)(unsigned long long)tap_of_lane, t);
+        const unsigned int hi = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)((unsigned long long)tap_of_lane >> 32), t);
+        return (long long)(((unsigned long long)hi << 32) | lo);
+    };
+    const long long b_tap_jump = VIEW == VIEW_CONV ? (long long)p.b_tap_step * 4 - (long long)p.b_tiles_per_tap * (long long)b_step : 0;
+    auto rewind = [&]() __attribute__((always_inline)) {
+        a_off = (size_t)k_rot * a_step;
+        b_off = VIEW == VIEW_CONV ? (p.b_use_tap_table ? (size_t)p.b_tap_off[0] : 0) : (size_t)k_rot * b_step;
+        next_step = k_rot;
+        b_row_step = b_taps_done = 0;
+    };
+    const unsigned char *abase = Ag, *bbase = Bg;
+    auto load_begin = [&]() __attribute__((always_inline)) {      // fixes where the step starts and moves on
+        abase = Ag + a_off;
+        bbase = Bg + b_off;
+        a_off += a_step;
+        b_off += b_step;
+        if constexpr (VIEW == VIEW_GEMM) {
+            if (++next_step == KT) { next_step = 0; a_off = 0; b_off = 0; }
+        } else {
+            const bool new_tap = ++b_row_step == p.b_tiles_per_tap;
+            b_row_step = new_tap ? 0 : b_row_step;
+            b_taps_done += new_tap ? 1 : 0;
+            // (the last advance comes after the final step: the index is kept inside the table)
+            const long long from_table = tap_entry(b_taps_done < 32 ? b_taps_done : 31);
+            const long long stepped = (long long)b_off + b_tap_jump;
+            b_off = new_tap ? (size_t)(p.b_use_tap_table ? from_table : stepped) : b_off;
+        }
+    };
+    auto four = [](auto rs, unsigned int off, float* x) __attribute__((always_inline)) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned int w = v[e];
+            x[e] = __builtin_bit_cast(float, w);
+        }
+    };
+    // chunk t of A: two instructions
+    auto load_a = [&](int t) __attribute__((always_inline)) {
+        auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)abase, 0, records(abase, A_end), 0x00020000);
+        four(rs, voff_a[t], ra[t]);
+        four(rs, voff_a[t] + 16, ra[t] + 4);
+    };
+    // part q (of 4 B_CH) of B: of a transposed B half a chunk every other time, of a plain B the
+    // k rows that part q completes when the parts are split in order (see `split`)
+    auto load_b = [&](auto q_tag) __attribute__((always_inline)) {
+        constexpr int q = decltype(q_tag)::value;
+        auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)bbase, 0, VIEW == VIEW_CONV ? (int)0xffffffffu : records(bbase, B_end), 0x00020000);
+        if constexpr (BT) {
+            if constexpr (q % 2 == 1) four(rs, voff_b[q / 4] + 16u * (q / 2 % 2), rb[q / 4] + 4 * (q / 2 % 2));
+        } else if constexpr (q % 2 == 1) {
+#pragma unroll
+            for (int e = q - 1; e <= q; ++e) {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, voff_b[0] + (unsigned int)e * b_row_bytes, 0, 0);
+                const unsigned int w0 = v[0], w1 = v[1];
+                rb[0][e] = __builtin_bit_cast(float, w0);
+                rb[1][e] = __builtin_bit_cast(float, w1);
+            }
+        }
+    };
+    auto load_step = [&]() __attribute__((always_inline)) {
+        load_begin();
+#pragma unroll
+        for (int t = 0; t < A_CH; ++t) load_a(t);
+        static_for<0, 4 * B_CH>(load_b);
+    };
+    // k values of a partial last step that do not exist: whatever was read in their place (the start
+    // of the next row; a NaN there must not reach this one) counts as zero
+    auto clear_k_tail = [&]() __attribute__((always_inline)) {
+        const int ka = k_last - 8 * my_chunk, kb = BT ? ka : k_last - 8 * wave;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+#pragma unroll
+            for (int t = 0; t < A_CH; ++t) ra[t][e] = e < ka ? ra[t][e] : 0.0f;
+#pragma unroll
+            for (int t = 0; t < B_CH; ++t) rb[t][e] = e < kb ? rb[t][e] : 0.0f;
+        }
+    };
+    auto meet = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // ---- the step in registers, split.  Part n is a pair of k values: of A's chunks one after the other,
+    // then of B's (of column pairs both columns at one k); OPS operations of two or three
+    // instructions each take it apart.
+    unsigned int a_seen[A_CH], b_seen[B_CH];      // the values this thread has seen, or-ed together
+#pragma unroll
+    for (int t = 0; t < A_CH; ++t) a_seen[t] = 0u;
+#pragma unroll
+    for (int t = 0; t < B_CH; ++t) b_seen[t] = 0u;
+    u32x4 pa[A_CH][3], pb[B_CH][3];               // the packed terms
+    constexpr int PARTS = 4 * (A_CH + B_CH), OPS = 5;
+    auto bits = [](float x) __attribute__((always_inline)) { return __builtin_bit_cast(unsigned int, x); };
+    auto value = [](unsigned int u) __attribute__((always_inline)) { return __builtin_bit_cast(float, u); };
+    float t0 = 0.0f, t1 = 0.0f;
+    auto split = [&](auto n_tag, auto op_tag) __attribute__((always_inline)) {
+        constexpr int n = decltype(n_tag)::value, op = decltype(op_tag)::value, nb = n - 4 * A_CH;
+        constexpr bool of_a = nb < 0;
+        constexpr int t = of_a ? n / 4 : BT ? nb / 4 : nb % 2, q = of_a ? n % 4 : BT ? nb % 4 : nb / 2;
+        float* x;
+        if constexpr (of_a) x = &ra[t][2 * q]; else x = &rb[t][2 * q];
+        auto put = [&](int plane, unsigned int w) __attribute__((always_inline)) {
+            if constexpr (of_a) pa[t][plane][q] = w; else pb[t][plane][q] = w;
+        };
+        if constexpr (op == 0) {
+            const unsigned int both = bits(x[0]) | bits(x[1]);
+            if constexpr (of_a) a_seen[t] |= both; else b_seen[t] |= both;
+            // odd rows and columns enter with their sign turned (see "Rounding")
+            if constexpr (t == 1) { x[0] = -x[0]; x[1] = -x[1]; }
+            const unsigned int h = pack_bf16x2(x[0], x[1]);
+            put(0, h);
+            t0 = value(h << 16);
+            t1 = value(h & 0xffff0000u);
+        } else if constexpr (op == 1) {
+            x[0] -= t0;
+            x[1] -= t1;
+        } else if constexpr (op == 2) {
+            put(1, __builtin_amdgcn_perm(bits(x[1]), bits(x[0]), 0x07060302u));       // the upper halves
+            t0 = value(bits(x[0]) & 0xffff0000u);
+            t1 = value(bits(x[1]) & 0xffff0000u);
+        } else if constexpr (op == 3) {
+            x[0] -= t0;
+            x[1] -= t1;
+        } else {
+            put(2, __builtin_amdgcn_perm(bits(x[1]), bits(x[0]), 0x07060302u));       // (at most eight bits are left)
+        }
+    };
+    auto write_step = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+#pragma unroll
+            for (int t = 0; t < A_CH; ++t) *(__attribute__((address_space(3))) u32x4*)PGK_LDS(lds_a + q * Cfg::A_PLANE + wpos_a[t]) = pa[t][q];
+#pragma unroll
+            for (int t = 0; t < B_CH; ++t) *(__attribute__((address_space(3))) u32x4*)PGK_LDS(lds_b + q * Cfg::B_PLANE + wpos_b[t]) = pb[t][q];
+        }
+    };
+
+    const int l16 = lane & 15, grp = lane >> 4;
+    // this lane's 16 bytes of a fragment
+    const int rpos = frag_pos(l16, grp);
+    const unsigned char* const as = lds_a + wm * TM16 * 1024 + rpos;
+    const unsigned char* const bs = lds_b + wn * TN16 * 1024 + rpos;
+
+    f32x4 acc[TM16][TN16];
+    auto clear_acc = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM16; ++i)
+#pragma unroll
+            for (int j = 0; j < TN16; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    clear_acc();
+
+    // ---- one step, in LDS; the step in registers (`next`) is split, the one after it (`ahead`) loaded.
+    // The instruction order is written out and pinned, slot by slot: one matrix instruction, then
+    // the operand fetches, the splitting and the loads that belong to the slot.
+    constexpr int PER_J = 6 * TM16, SLOTS = PER_J * TN16;
+    auto step = [&](auto next_tag, auto ahead_tag) __attribute__((always_inline)) {
+        constexpr bool NEXT = decltype(next_tag)::value != 0, AHEAD = decltype(ahead_tag)::value != 0;
+        bf16x8 fa[3][TM16], fb[2][3];
+        auto fetch_a = [&](int q, int i) __attribute__((always_inline)) { fa[q][i] = *(const __attribute__((address_space(3))) bf16x8*)PGK_LDS(as + q * Cfg::A_PLANE + i * 1024); };
+        auto fetch_b = [&](int j, int q) __attribute__((always_inline)) { fb[j & 1][q] = *(const __attribute__((address_space(3))) bf16x8*)PGK_LDS(bs + q * Cfg::B_PLANE + j * 1024); };
+        // (term of A, term of B) of the six products, the small ones first
+        constexpr int QA[6] = {0, 2, 1, 0, 1, 0}, QB[6] = {2, 0, 1, 1, 0, 0};
+        // the fragments of the first column block, in the order they are needed
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            fetch_b(0, QB[u]);
+#pragma unroll
+            for (int i = 0; i < TM16; ++i) fetch_a(QA[u], i);
+        }
+        if constexpr (AHEAD) load_begin();
+        // (a wave that multiplies goes before one that writes or starts: 694 -> 680 us on 4096^3)
+        __builtin_amdgcn_s_setprio(2);
+        __builtin_amdgcn_sched_barrier(0);
+        // the operations of the parts, in order, spread over the slots FIRST to LAST - 1
+        constexpr int TOTAL = OPS * PARTS, FIRST = SLOTS / 12, LAST = SLOTS - SLOTS / 24;
+        auto ops_before = [](int m) constexpr { return m <= FIRST ? 0 : m >= LAST ? TOTAL : (m - FIRST) * TOTAL / (LAST - FIRST); };
+        static_for<0, SLOTS>([&](auto m_tag) __attribute__((always_inline)) {
+            constexpr int m = decltype(m_tag)::value;
+            constexpr int j = m / PER_J, u = (m / TM16) % 6, i = m % TM16;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j & 1][QB[u]], fa[QA[u]][i], acc[i][j], 0, 0, 0);
+            // the next column block's fragments, into the other buffer
+            if constexpr (j + 1 < TN16 && m % PER_J >= TM16 && m % PER_J < TM16 + 3) fetch_b(j + 1, QB[m % PER_J - TM16]);
+            if constexpr (NEXT) {
+                static_for<ops_before(m), ops_before(m + 1)>([&](auto o_tag) __attribute__((always_inline)) {
+                    constexpr int o = decltype(o_tag)::value, part = o / OPS;
+                    split(IC<part>{}, IC<o % OPS>{});
+                    // a part's registers are free once it is split: what is to fill them next
+                    if constexpr (AHEAD && o % OPS == OPS - 1) {
+                        if constexpr (part < 4 * A_CH) { if constexpr (part % 4 == 3) load_a(part / 4); }
+                        else load_b(IC<part - 4 * A_CH>{});
+                    }
+                });
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto to_next = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_s_setprio(0);
+        meet();            // every wave has fetched its operands
+        write_step();
+        meet();            // the next step is in LDS
+    };
+
+    // prologue: step 0 in LDS, step 1 in registers
+    rewind();
+    load_step();
+    if (KT == 1 && k_last < BK) clear_k_tail();
+    static_for<0, OPS * PARTS>([&](auto o) __attribute__((always_inline)) { split(IC<decltype(o)::value / OPS>{}, IC<decltype(o)::value % OPS>{}); });
+    write_step();
+    if (KT > 1) load_step();
+    meet();
+    stamp(1);
+    // the sign of A changes twice, at a quarter and three quarters of the steps (see "Rounding"): from
+    // then on a thread's two rows change places, and with them their signs -- in the loads two steps
+    // before, in what is split and written and in the accumulators one step before
+    const int turn0 = KT >= 8 ? KT / 4 : -1, turn1 = KT >= 8 ? KT - KT / 4 : -1;
+    for (int kt = 0; kt + 2 < KT; ++kt) {
+        if (kt + 2 == turn0 || kt + 2 == turn1) {
+            const unsigned int o = voff_a[0];
+            voff_a[0] = voff_a[1];
+            voff_a[1] = o;
+        }
+        if (kt + 1 == turn0 || kt + 1 == turn1) {
+            const unsigned int o = a_seen[0];
+            a_seen[0] = a_seen[1];
+            a_seen[1] = o;
+        }
+        step(IC<1>{}, IC<1>{});
+        if (kt + 1 == turn0 || kt + 1 == turn1) {
+            const int o = wpos_a[0];
+            wpos_a[0] = wpos_a[1];
+            wpos_a[1] = o;
+#pragma unroll
+            for (int i = 0; i < TM16; ++i)
+#pragma unroll
+                for (int j = 0; j < TN16; ++j) acc[i][j] = -acc[i][j];
+        }
+        to_next();
+    }
+    if (KT > 1) {
+        if (k_last < BK) clear_k_tail();
+        step(IC<1>{}, IC<0>{});
+        to_next();
+    }
+    step(IC<0>{}, IC<0>{});
+    __builtin_amdgcn_s_setprio(0);
+
+    // ---- did the terms hold everything?  (see "Range")
+    {
+        int bad = 0;
+#pragma unroll
+        for (int t = 0; t < A_CH; ++t) bad |= (a_seen[t] & 0x7fffffffu) && !(a_seen[t] & 0x60000000u);
+#pragma unroll
+        for (int t = 0; t < B_CH; ++t) bad |= (b_seen[t] & 0x7fffffffu) && !(b_seen[t] & 0x60000000u);
+        float zero = 0.0f;            // 0 x anything finite; NaN otherwise
+#pragma unroll
+        for (int i = 0; i < TM16; ++i)
+#pragma unroll
+            for (int j = 0; j < TN16; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) zero = __builtin_fmaf(acc[i][j][e], 0.0f, zero);
+        bad |= zero != 0.0f;
+        if (__syncthreads_or(bad)) {
+            // the same tile with the fp32 matrix instruction.  LDS: sixteen rows x four k values of
+            // fp32 are 256 bytes, row r of k chunk c at 256 c + 16 r (BM x 32 floats fit the three planes).
+            clear_acc();
+            rewind();
+            for (int kt = 0; kt < KT; ++kt) {
+                load_step();
+                if (kt + 1 == KT && k_last < BK) clear_k_tail();
+                meet();
+                auto put = [](unsigned char* base, int row, int c, const float* x) __attribute__((always_inline)) {
+                    *(f32x4*)(base + (row >> 4) * 2048 + c * 256 + (row & 15) * 16) = f32x4{x[0], x[1], x[2], x[3]};
+                };
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int t = 0; t < A_CH; ++t) put(lds_a, my_row + t, 2 * my_chunk + h, &ra[t][4 * h]);
+#pragma unroll
+                    for (int t = 0; t < B_CH; ++t) {
+                        if constexpr (BT) put(lds_b, my_row + t, 2 * my_chunk + h, &rb[t][4 * h]);
+                        else put(lds_b, 2 * lane + t, 2 * wave + h, &rb[t][4 * h]);
+                    }
+                }
+                meet();
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    f32x4 xa[TM16], xb[TN16];
+                    const int at = (4 * h + grp) * 256 + l16 * 16;
+#pragma unroll
+                    for (int i = 0; i < TM16; ++i) xa[i] = *(const f32x4*)(lds_a + (wm * TM16 + i) * 2048 + at);
+#pragma unroll
+                    for (int j = 0; j < TN16; ++j) xb[j] = *(const f32x4*)(lds_b + (wn * TN16 + j) * 2048 + at);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int i = 0; i < TM16; ++i)
+#pragma unroll
+                            for (int j = 0; j < TN16; ++j)
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xb[j][e], xa[i][e], acc[i][j], 0, 0, 0);
+                }
+            }
+            meet();
+            // as the epilogue expects them
+#pragma unroll
+            for (int i = 0; i < TM16; ++i)
+#pragma unroll
+                for (int j = 0; j < TN16; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][j][e] = ((l16 ^ e) & 1) ? -acc[i][j][e] : acc[i][j][e];
+        }
+    }
+    stamp(2);          // end of the main loop (every wave is past its operand reads)
+
+    // ---- epilogue
+    unsigned char* const piece = (wave < 2 ? lds_a : lds_b) + (wave & 1) * Cfg::PIECE_BYTES;
+    if (out_mode == 1) {
+        // split-K pass 1: the partial products of this slice
+        unsigned char* w = (unsigned char*)(p.ws + ((size_t)b * p.splits + sp) * (size_t)p.M * (size_t)p.N +
+                                            (size_t)tm * BM * (size_t)p.N + (size_t)tn * BN);
+        epilogue_terms<ACT_NONE, EPI_PLAIN, Cfg, false, false>(acc, nullptr, nullptr, w, (size_t)p.N * 4, m_rem, n_rem, wm, wn, lane, piece, nullptr);
+        return;
+    }
+    float* const rs_lds = p.rs_part ? rs_buf : nullptr;
+    float* const bias_lds = rs_buf + Cfg::WGN * BM;
+    float* const bias_lds_row = bias_lds + BIAS_N;
+    if (tid < BIAS_N) {
+        bias_lds[tid] = BIAS_PER_ROW ? 0.0f : bias_pre;
+        if constexpr (BIAS_PER_ROW) bias_lds_row[tid] = bias_pre;
+    }
+    __syncthreads();
+    stamp(3);
+    unsigned char* c_tile = (unsigned char*)p.C + ((size_t)b * p.M * p.N + (size_t)tm * BM * (size_t)p.N + (size_t)tn * BN) * 4;
+    auto run_epilogue = [&](auto kind) __attribute__((always_inline)) {
+        constexpr int KIND = decltype(kind)::value;
+        const float* br = KIND == EPI_ROWBIAS ? bias_lds_row : nullptr;
+        switch (p.act) {
+        case ACT_RELU: epilogue_terms<ACT_RELU, KIND, Cfg, true, true>(acc, bias_lds, br, c_tile, (size_t)p.N * 4, m_rem, n_rem, wm, wn, lane, piece, rs_lds); break;
+        case ACT_GELU_TANH: epilogue_terms<ACT_GELU_TANH, KIND, Cfg, true, true>(acc, bias_lds, br, c_tile, (size_t)p.N * 4, m_rem, n_rem, wm, wn, lane, piece, rs_lds); break;
+        case ACT_SILU: epilogue_terms<ACT_SILU, KIND, Cfg, true, true>(acc, bias_lds, br, c_tile, (size_t)p.N * 4, m_rem, n_rem, wm, wn, lane, piece, rs_lds); break;
+        default: epilogue_terms<ACT_NONE, KIND, Cfg, true, true>(acc, bias_lds, br, c_tile, (size_t)p.N * 4, m_rem, n_rem, wm, wn, lane, piece, rs_lds); break;
+        }
+    };
+    if constexpr (VIEW == VIEW_CONV) {
+        if (p.bias) run_epilogue(IC<EPI_ROWBIAS>{});
+        else run_epilogue(IC<EPI_PLAIN>{});
+    } else {
+        if (!rs_lds) run_epilogue(IC<EPI_PLAIN>{});
+        else if (n_rem == BN) run_epilogue(IC<EPI_ROWSUM>{});
+        else run_epilogue(IC<EPI_ROWSUM_MASKED>{});
+    }
+    if (p.rs_part) {
+        __syncthreads();
+        if (tid < m_rem) {
+            // the wave columns' partial row sums, in order
+            p.rs_part[((size_t)b * p.tiles_n + tn) * (size_t)p.M + (size_t)tm * BM + tid] = rs_buf[tid] + rs_buf[BM + tid];
+        }
+    }
+    stamp(4);
+    if constexpr (TIMED) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        stamp(5);
+    }
+#endif
+}
+
+// 128 x 128 tiles: 48 KiB of LDS for operands, two workgroups per CU
+using CfgTerms = TermsCfg<false, 128, 128, 2>;
+using CfgTermsT = TermsCfg<true, 128, 128, 2>;
+
+template <typename Cfg, int VIEW, bool TIMED = false>
+static hipError_t launch_terms(const GemmArgs& a, int out_mode, hipStream_t s)
+{
+    const long long wgs = (long long)a.tiles_m * a.tiles_n * a.batch * a.splits;
+    if (wgs <= 0 || wgs > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (TIMED != (a.stamps != nullptr)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((gemm_f32_terms_kernel<Cfg, VIEW, TIMED>), dim3((unsigned int)wgs), dim3(Cfg::NT), 0, s, a, out_mode);
+    return hipGetLastError();
+}
+
+}  // namespace pgk
+#endif

@@ -1,5 +1,6 @@
 // Matrix-core GEMM kernels, plain operand views: instances, tile table and launcher.
 // The kernel template is in pgk_gemm_mfma_kernel.h.
+#include "pgk_gemm_f32_terms.h"
 #include "pgk_gemm_mfma_kernel.h"
 
 namespace pgk {
@@ -28,7 +29,7 @@ TileShape mfma_tile_shape(int dtype, int kind)
                                   : TileShape{CfgBF16::BM, CfgBF16::BN, CfgBF16::BK};
     }
     return kind == TILE_SMALL ? TileShape{CfgF32Small::BM, CfgF32Small::BN, CfgF32Small::BK}
-                              : TileShape{CfgF32::BM, CfgF32::BN, CfgF32::BK};
+                              : TileShape{CfgTerms::BM, CfgTerms::BN, CfgTerms::BK};
 }
 
 hipError_t launch_gemm_mfma(const GemmArgs& a, int dtype, int kind, int out_mode, hipStream_t s)
@@ -48,16 +49,16 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, int dtype, int kind, int out_mode
     if (kind == TILE_WIDE) return a.b_trans ? launch_cfg<CfgBF16WideT, VIEW_GEMM>(a, out_mode, s) : launch_cfg<CfgBF16Wide, VIEW_GEMM>(a, out_mode, s);
     if (a.b_trans) {
         if (dtype == DT_BF16) return small ? launch_cfg<CfgBF16SmallT, VIEW_GEMM>(a, out_mode, s) : launch_cfg<CfgBF16T, VIEW_GEMM>(a, out_mode, s);
-        return small ? launch_cfg<CfgF32SmallT, VIEW_GEMM>(a, out_mode, s) : launch_cfg<CfgF32T, VIEW_GEMM>(a, out_mode, s);
+        return small ? launch_cfg<CfgF32SmallT, VIEW_GEMM>(a, out_mode, s) : launch_gemm_f32_terms(a, out_mode, s);
     }
     if (dtype == DT_BF16) return small ? launch_cfg<CfgBF16Small, VIEW_GEMM>(a, out_mode, s) : launch_cfg<CfgBF16, VIEW_GEMM>(a, out_mode, s);
-    return small ? launch_cfg<CfgF32Small, VIEW_GEMM>(a, out_mode, s) : launch_cfg<CfgF32, VIEW_GEMM>(a, out_mode, s);
+    return small ? launch_cfg<CfgF32Small, VIEW_GEMM>(a, out_mode, s) : launch_gemm_f32_terms(a, out_mode, s);
 }
 
 hipError_t launch_gemm_mfma_timed(const GemmArgs& a, int dtype, hipStream_t s)
 {
     if (a.b_trans || a.bias_per_row || a.splits != 1 || !a.stamps) return hipErrorInvalidValue;
-    return dtype == DT_BF16 ? launch_cfg<CfgBF16, VIEW_GEMM, true>(a, 0, s) : launch_cfg<CfgF32, VIEW_GEMM, true>(a, 0, s);
+    return dtype == DT_BF16 ? launch_cfg<CfgBF16, VIEW_GEMM, true>(a, 0, s) : launch_gemm_f32_terms_timed(a, s);
 }
 
 }  // namespace pgk

@@ -19,7 +19,7 @@ hipError_t launch_gemm_mfma_conv(const GemmArgs& a, int dtype, int kind, int out
         }
     }
     switch (kind) {
-    case TILE_LARGE: return launch_cfg<CfgF32, VIEW_CONV>(a, out_mode, s);
+    case TILE_LARGE: return launch_gemm_f32_terms(a, out_mode, s);
     case TILE_SMALL: return launch_cfg<CfgF32Small, VIEW_CONV>(a, out_mode, s);
     case TILE_FLAT: return launch_cfg<CfgF32Flat, VIEW_CONV>(a, out_mode, s);
     default: return hipErrorInvalidValue;

@@ -1190,22 +1190,20 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_mfma_kernel
 // Large tiles for problems that fill the chip with them:
 //   bf16 256x256x64, eight waves of 64x128 (two per SIMD, so one wave's operand fetches
 //        and barrier waits overlap the other's MFMAs), A ring 3 + B ring 2 = 160 KiB LDS;
-//   fp32 128x128x32, four waves of 64x64, 64 KiB of LDS, two workgroups per CU.
+//   fp32 128x128x32: a kernel of its own, pgk_gemm_f32_terms.h.
 // Small tiles (a quarter of the area) for problems whose large-tile grid would leave
 // most of the 256 CUs idle:
 //   bf16 128x128x64, four waves of 64x64, 80 KiB of LDS, two workgroups per CU;
 //   fp32 64x64x32, four waves of 32x32, 32 KiB of LDS.
 using CfgBF16 = MfmaCfg<true, 256, 256, 64, 4, 2, 3, 2>;
-using CfgF32 = MfmaCfg<false, 128, 128, 32, 2, 2, 2, 1>;
 using CfgBF16Small = MfmaCfg<true, 128, 128, 64, 2, 2, 3, 2>;
 using CfgF32Small = MfmaCfg<false, 64, 64, 32, 2, 2, 2, 2>;
 // Halves of the large bf16 tile, eight waves of 64x64, for outputs whose last tile column (tall,
 // 256x128) or last tile row (wide, 128x256) would be at most half full with the large tile:
 using CfgBF16Tall = MfmaCfg<true, 256, 128, 64, 4, 2, 3, 2>;
 using CfgBF16Wide = MfmaCfg<true, 128, 256, 64, 2, 4, 3, 2>;
-// the same four for B given transposed ([N][K])
+// the same for B given transposed ([N][K])
 using CfgBF16T = MfmaCfgBt<true, 256, 256, 64, 4, 2, 3, 2>;
-using CfgF32T = MfmaCfgBt<false, 128, 128, 32, 2, 2, 2, 1>;
 using CfgBF16SmallT = MfmaCfgBt<true, 128, 128, 64, 2, 2, 3, 2>;
 using CfgF32SmallT = MfmaCfgBt<false, 64, 64, 32, 2, 2, 2, 2>;
 using CfgBF16TallT = MfmaCfgBt<true, 256, 128, 64, 4, 2, 3, 2>;

@@ -125,6 +125,11 @@ hipError_t launch_gemm_mfma_conv(const GemmArgs& a, int dtype, int kind, int out
 TileShape tiny_tile_shape();
 hipError_t launch_gemm_tiny(const GemmArgs& a, hipStream_t s);
 
+// The large fp32 tile, plain operand views and a convolution's, on the bf16 matrix cores
+// (pgk_gemm_f32_terms.h); reached through launch_gemm_mfma.
+hipError_t launch_gemm_f32_terms(const GemmArgs& a, int out_mode, hipStream_t s);
+hipError_t launch_gemm_f32_terms_timed(const GemmArgs& a, hipStream_t s);
+
 // The large tile of either type, plain operand views, out_mode 0, with phase stamps (a.stamps set).
 hipError_t launch_gemm_mfma_timed(const GemmArgs& a, int dtype, hipStream_t s);
 

@@ -1,0 +1,112 @@
+"""fp32 products on the bf16 matrix cores (the 128 x 128 fp32 tile): values split into three bf16
+terms, six products.  Compared element by element with the oracle under an a-priori bound, at the
+step counts where the loop changes shape, on ragged edges, with both layouts of B, and on values
+the terms cannot hold (the tile is then computed with the fp32 instruction)."""
+import numpy as np
+import pytest
+
+from paper_2511_06345_amd import inputs as gen
+from util import abs_inputs
+
+pytestmark = pytest.mark.gpu
+F32, NONE = gen.F32, gen.ACT_NONE
+
+
+@pytest.fixture(scope="module")
+def pgk():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2511_06345_amd import binding
+    binding.load_library()
+    return binding
+
+
+def call(pgk, A, B, bt, splits=None):
+    import torch
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(np.ascontiguousarray(np.swapaxes(B, 1, 2)) if bt else B).cuda()
+    if splits is None:
+        C, rs = pgk.gemm_fused(dA, dB, None, NONE, b_transposed=bt)
+    else:
+        C, rs = pgk.gemm_splitk(dA, dB, None, NONE, splits=splits, b_transposed=bt)
+    torch.cuda.synchronize()
+    return C.cpu().numpy(), rs.cpu().numpy()
+
+
+def bound(K):
+    """Largest error over sum |a||b|: a bf16 instruction cuts its accumulator at most twice per 32 k
+    (2^-23 of a partial sum each), there are six per 32 k, and the products left out are below
+    2^-22; the splitting itself is exact."""
+    return (12 * -(-K // 32) + 2) * 2.0 ** -23
+
+
+# (128 x 128 tiles: enough batch entries for 192 workgroups).  K: one step, its tail, two, three, the
+# last count without turns of the sign (7), the first with them (8, 9), more
+SHAPES = [(128, 128, 32, 192), (128, 128, 5, 192), (130, 140, 64, 60), (129, 131, 70, 60), (200, 136, 96, 60), (128, 256, 224, 100),
+          (256, 128, 256, 100), (250, 131, 259, 60), (128, 129, 288, 100), (131, 128, 516, 100)]
+
+
+@pytest.mark.parametrize("bt", [False, True])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_terms_meet_the_a_priori_bound(pgk, oracle, shape, bt):
+    M, N, K, batch = shape
+    assert pgk.gemm_plan(M, N, K, batch, F32, b_transposed=bt)["tile"] == (128, 128, 32)
+    A = gen.normal(gen.tensor_seed(95, 1, M + K), batch * M * K, 1.0).reshape(batch, M, K)
+    B = gen.normal(gen.tensor_seed(95, 2, N + K), batch * K * N, 1.0).reshape(batch, K, N)
+    ref, ref_rs = oracle.gemm_fused(A, B, None, NONE)
+    aa, ab, _ = abs_inputs(A, B, None, F32)
+    scale, scale_rs = oracle.gemm_fused(aa, ab, None, NONE)
+    for splits in (None, 2):
+        if splits and K < 64:
+            continue
+        C, rs = call(pgk, A, B, bt, splits)
+        assert np.all(np.abs(C - ref) <= bound(K) * scale), (shape, bt, splits)
+        assert np.all(np.abs(rs - ref_rs) <= (bound(K) + N * 2.0 ** -23) * scale_rs), (shape, bt, splits)
+
+
+@pytest.mark.parametrize("bt", [False, True])
+def test_values_the_terms_cannot_hold(pgk, oracle, bt):
+    """Infinities, NaNs, values above the largest bf16, rows and columns far below 2^-63 and down to
+    denormals: as the fp32 instruction gives them, in their rows and columns and nowhere else."""
+    M, N, K, batch = 256, 256, 288, 64
+    A = gen.normal(gen.tensor_seed(96, 1), batch * M * K, 1.0).reshape(batch, M, K)
+    B = gen.normal(gen.tensor_seed(96, 2), batch * K * N, 1.0).reshape(batch, K, N)
+    A[1, 5, 7] = np.inf
+    B[2, 11, 200] = -np.inf
+    A[3, 130, 287] = np.nan
+    A[4, 17, 9] = 3.4e38
+    A[5, 20] *= np.float32(1e-30)
+    A[6, 31] *= np.float32(1e-38)
+    B[7, :, 3] *= np.float32(1e-42)
+    A[8] *= np.float32(1e-33)
+    B[8] *= np.float32(1e30)
+    A[9, 40] = 0.0
+    ref, _ = oracle.gemm_fused(A, B, None, NONE)
+    aa, ab, _ = abs_inputs(A, B, None, F32)
+    scale, _ = oracle.gemm_fused(aa, ab, None, NONE)
+    C, _ = call(pgk, A, B, bt)
+    with np.errstate(over="ignore"):
+        want = ref.astype(np.float32)                   # (3.4e38 times more than one is an infinity in fp32)
+    finite = np.isfinite(want)
+    assert bool((np.isfinite(C) == finite).all()) and bool((np.isnan(C) == np.isnan(want)).all())
+    assert bool((C[np.isinf(want)] == want[np.isinf(want)]).all())
+    # (2^-149 per product: what fp32 sums of denormal products lose)
+    assert np.all(np.abs(C - ref)[finite] <= (bound(K) * scale + K * 2.0 ** -149)[finite])
+    assert np.all(C[9, 40] == 0.0)
+
+
+def test_identity_is_exact_and_row_sums_have_no_bias(pgk):
+    import torch
+    n = 2048
+    X = torch.empty((1, n, n), device="cuda").normal_(generator=torch.Generator("cuda").manual_seed(5))
+    eye = torch.eye(n, device="cuda")[None].contiguous()
+    assert torch.equal(pgk.gemm_fused(X, eye, None, NONE, rowsum=False)[0], X)
+    assert torch.equal(pgk.gemm_fused(eye, X, None, NONE, rowsum=False)[0], X)
+    # errors that are independent of each other weigh the same in a sum of outputs as in one output;
+    # a common part of them would weigh sqrt(N) = 45 times as much
+    W = torch.empty((1, n, n), device="cuda").normal_(generator=torch.Generator("cuda").manual_seed(6))
+    C, rs = pgk.gemm_fused(X, W, None, NONE)
+    ref = X[0].double() @ W[0].double()
+    err = float((C[0].double() - ref).norm() / ref.norm())
+    err_rs = float((rs[0].double() - ref.sum(1)).norm() / ref.sum(1).norm())
+    err_cs = float((C[0].double().sum(0) - ref.sum(0)).norm() / ref.sum(0).norm())
+    assert err < 2e-6 and err_rs < 2 * err and err_cs < 2 * err, (err, err_rs, err_cs)
