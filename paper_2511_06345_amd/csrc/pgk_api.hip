@@ -1101,7 +1101,13 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
         a.group_m = group_m_for(a.tiles_m, a.tiles_n);
         return pgk::launch_gemm_mfma(a, dtype, path.kind, 0, st) == hipSuccess ? PGK_OK : PGK_ERR_HIP;
     }
-    // bounds-checked kernel, input read in place
+    // few input channels: a kernel of its own (conv_few_channels_fits says where the line lies and why);
+    // what is left (long sums read in place because x is misaligned, short rows, little work) on the
+    // bounds-checked kernel, also reading the input in place
+    if (pgk::conv_few_channels_fits(B, Cin, Cout, Kw, stride, dilation, pl.Lout) &&
+        (long double)((pl.Lout + 142) / 128) * ((Cout + 127) / 128) * B <= 2.0e9L)
+        return pgk::launch_conv_few_channels(x, w, bias, y, B, (int)Cin, (int)L, (int)Cout, (int)Kw, (int)stride, (int)pad,
+                                             (int)dilation, (int)pl.Lout, act, dtype, st) == hipSuccess ? PGK_OK : PGK_ERR_HIP;
     const pgk::TileShape t = pgk::guarded_tile_shape();
     a.A = w; a.B = x;
     a.b_batch_stride = Cin * L;

@@ -180,6 +180,11 @@ hipError_t launch_conv_repack_weights(const void* w, void* wr, int Cout, int Cin
 hipError_t launch_conv_prepare(const void* x, void* strips, long long rows, int L, int W, int n_edges, const int* first_col,
                                const void* w, void* wr, int Cout, int Cin, int Kw, int dtype, hipStream_t s);
 constexpr int kMaxTableTaps = 32;
+// Convolution with few input channels, input read in place (pgk_conv_few.hip): whether the kernel takes
+// these sizes, and the launch (any alignment of the elements).
+bool conv_few_channels_fits(long long B, long long Cin, long long Cout, long long Kw, long long stride, long long dil, long long Lout);
+hipError_t launch_conv_few_channels(const void* x, const void* w, const float* bias, void* y, long long B, int Cin, int L, int Cout,
+                                    int Kw, int stride, int pad, int dil, int Lout, int act, int dtype, hipStream_t s);
 
 // Operand packing (pgk_pack.hip): dst[b][r][c] = src[b][r][c] inside the source, else 0 (dst rows of
 // cols_dst elements, a multiple of the 16-byte chunk).
