@@ -149,12 +149,13 @@ hipError_t launch_splitk_reduce(const float* ws, const float* bias, void* C, flo
                                 int nseg, int M, int N, int batch, int splits, int act, int dtype, hipStream_t s);
 
 // Maximum over the middle dimension of X viewed as [outer][red][inner]; see
-// pgk_reduce_max.hip.  The plan is pure host arithmetic: vector width (elements per
-// 16-byte load, or 1 for the unaligned fallback), lanes per row (inner == 1), number of
+// pgk_reduce_max.hip.  The plan is pure host arithmetic: vector width (elements per load), whether
+// the 16-byte loads have to do without alignment, lanes per row (inner == 1), number of
 // segments the reduced range is cut into and their length (in chunks for inner == 1, in
 // r otherwise), workgroups, and the number of (value, position) partials for the second
 // pass (0 when there is a single segment).
 struct ReducePlan {
+    bool unaligned;
     int vec, group, segs, per_seg, tiles_i;
     long long blocks;
     size_t partial_elems;

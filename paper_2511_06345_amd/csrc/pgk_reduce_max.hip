@@ -17,6 +17,8 @@
 // segment results in order.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "pgk_device.h"
 #include "pgk_kernels.h"
 
@@ -67,6 +69,15 @@ __device__ __forceinline__ void unpack(const u32x4& w, float (&x)[Elem<BF16>::VE
     }
 }
 
+// one 16-byte chunk, aligned or (UNALIGNED) starting on any element
+template <bool BF16, bool UNALIGNED>
+__device__ __forceinline__ u32x4 load_chunk(const unsigned char* at)
+{
+    using any_element = typename std::conditional<BF16, u32x4_align2, u32x4_align4>::type;
+    if constexpr (UNALIGNED) return __builtin_nontemporal_load((const any_element*)at);
+    else return __builtin_nontemporal_load((const u32x4*)at);
+}
+
 template <bool BF16>
 __device__ __forceinline__ float load_one(const void* X, size_t e)
 {
@@ -83,15 +94,17 @@ __device__ __forceinline__ void store_one(void* out, size_t e, float v)
 
 // ---------------------------------------------------------------------------------
 // inner == 1.  G lanes (one wave, or the whole workgroup of 256) sweep the chunks
-// [c0, c1) of one row; lane l takes chunks c0 + l, c0 + l + G, ...  VEC == 1 is the
-// fallback for rows that do not start on 16-byte boundaries (a "chunk" is one element).
+// [c0, c1) of one row; lane l takes chunks c0 + l, c0 + l + G, ...  LEAD: the rows do not all start on
+// 16-byte boundaries; the elements before a row's first boundary and those behind its last
+// whole chunk are taken one per lane (bf16 [2048, 50257]: 105 us with one element per load, 39 so).
 // Result: direct to out / idx when segs == 1, else to the segment partials.
-template <bool BF16, int VEC, int G>
+template <bool BF16, bool LEAD, int G>
 __global__ __launch_bounds__(256) void reduce_max_rows_kernel(const void* __restrict__ X, void* __restrict__ out,
                                                               int* __restrict__ idx, float* __restrict__ pv,
                                                               int* __restrict__ pi, long long outer, int red,
                                                               int segs, int chunks_per_seg)
 {
+    constexpr int VEC = Elem<BF16>::VEC;
     constexpr int ROWS = 256 / G;                 // rows (or row segments) per workgroup
     constexpr int UNROLL = 4;
     __shared__ float sv[4];
@@ -102,10 +115,14 @@ __global__ __launch_bounds__(256) void reduce_max_rows_kernel(const void* __rest
     const bool active = unit < outer * segs;      // whole groups only: uniform per wave
     const long long row = active ? unit / segs : 0;
     const int seg = active ? (int)(unit - row * segs) : 0;
-    const int nch = red / VEC;
+    const size_t row_base = (size_t)row * (size_t)red;
+    const unsigned char* const row_at = (const unsigned char*)X + row_base * Elem<BF16>::BYTES;
+    // elements before the first 16-byte boundary (red is larger than that), whole chunks, elements left
+    const int lead = LEAD ? (int)((0u - (unsigned int)(size_t)row_at) & 15u) / Elem<BF16>::BYTES : 0;
+    const int nch = (red - lead) / VEC;
+    const int rest = LEAD ? red - lead - nch * VEC : 0;
     const int c0 = seg * chunks_per_seg;
     const int c1 = active ? (c0 + chunks_per_seg < nch ? c0 + chunks_per_seg : nch) : c0;
-    const size_t row_base = (size_t)row * (size_t)red;
 
     float bv[VEC];
     int bk[VEC];                                  // sweep number of the best element per slot
@@ -113,42 +130,47 @@ __global__ __launch_bounds__(256) void reduce_max_rows_kernel(const void* __rest
     for (int e = 0; e < VEC; ++e) { bv[e] = kNegInf; bk[e] = 0; }
 
     int c = c0 + gl, k = 0;
-    if constexpr (VEC > 1) {
-        const u32x4* src = (const u32x4*)((const unsigned char*)X + row_base * Elem<BF16>::BYTES);
-        for (; c + (UNROLL - 1) * G < c1; c += UNROLL * G, k += UNROLL) {
-            u32x4 w[UNROLL];
+    const u32x4* src = (const u32x4*)(row_at + lead * Elem<BF16>::BYTES);
+    for (; c + (UNROLL - 1) * G < c1; c += UNROLL * G, k += UNROLL) {
+        u32x4 w[UNROLL];
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) w[u] = __builtin_nontemporal_load(src + c + u * G);
+        for (int u = 0; u < UNROLL; ++u) w[u] = __builtin_nontemporal_load(src + c + u * G);
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
-                float x[VEC];
-                unpack<BF16>(w[u], x);
-#pragma unroll
-                for (int e = 0; e < VEC; ++e)
-                    if (replaces(x[e], bv[e])) { bv[e] = x[e]; bk[e] = k + u; }
-            }
-        }
-        for (; c < c1; c += G, ++k) {
+        for (int u = 0; u < UNROLL; ++u) {
             float x[VEC];
-            unpack<BF16>(__builtin_nontemporal_load(src + c), x);
+            unpack<BF16>(w[u], x);
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
-                if (replaces(x[e], bv[e])) { bv[e] = x[e]; bk[e] = k; }
-        }
-    } else {
-        for (; c < c1; c += G, ++k) {
-            const float x = load_one<BF16>(X, row_base + c);
-            if (replaces(x, bv[0])) { bv[0] = x; bk[0] = k; }
+                if (replaces(x[e], bv[e])) { bv[e] = x[e]; bk[e] = k + u; }
         }
     }
-    // this lane's best: slot e of sweep k is element ((c0 + gl + k G) VEC + e) of the row
+    for (; c < c1; c += G, ++k) {
+        float x[VEC];
+        unpack<BF16>(__builtin_nontemporal_load(src + c), x);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+            if (replaces(x[e], bv[e])) { bv[e] = x[e]; bk[e] = k; }
+    }
+    // this lane's best: slot e of sweep k is element (lead + (c0 + gl + k G) VEC + e) of the row
     const bool any = c0 + gl < c1;
     float v = kNegInf;
     int p = kNoPos;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        const int pos = any ? (c0 + gl + bk[e] * G) * VEC + e : kNoPos;
+        const int pos = any ? lead + (c0 + gl + bk[e] * G) * VEC + e : kNoPos;
         if (beats(bv[e], pos, v, p)) { v = bv[e]; p = pos; }
+    }
+    if constexpr (LEAD) {
+        // the first segment's lanes take the elements before the chunks, the last segment's those behind
+        if (active && seg == 0 && gl < lead) {
+            const float x = load_one<BF16>(X, row_base + gl);
+            if (beats(x, gl, v, p)) { v = x; p = gl; }
+        }
+        if (active && seg == segs - 1 && gl < rest) {
+            const int pos = red - rest + gl;
+            const float x = load_one<BF16>(X, row_base + pos);
+            if (beats(x, pos, v, p)) { v = x; p = pos; }
+        }
     }
     // across the lanes of the wave
 #pragma unroll
@@ -179,13 +201,18 @@ __global__ __launch_bounds__(256) void reduce_max_rows_kernel(const void* __rest
 
 // ---------------------------------------------------------------------------------
 // inner > 1.  A workgroup owns 64 * VEC consecutive inner positions of one outer index
-// and the r range of one segment; wave w takes r = r0 + w, r0 + w + 4, ...
-template <bool BF16, int VEC>
+// and the r range of one segment; wave w takes r = r0 + w, r0 + w + 4, ...  UNALIGNED: rows of inner
+// elements that do not all start on 16-byte boundaries are read in 16-byte chunks all the same, from
+// any element on (fp32 [215, 6701, 135]: 752 us with one element per load, 139 so); the last lane's chunk
+// ends with the row (and overlaps the one before: the outputs
+// they share are written twice, with the same values).
+template <bool BF16, bool UNALIGNED>
 __global__ __launch_bounds__(256) void reduce_max_cols_kernel(const void* __restrict__ X, void* __restrict__ out,
                                                               int* __restrict__ idx, float* __restrict__ pv,
                                                               int* __restrict__ pi, long long outer, int red,
                                                               long long inner, int tiles_i, int segs, int r_per_seg)
 {
+    constexpr int VEC = Elem<BF16>::VEC;
     // loads in flight per lane: four for fp32; two for bf16, whose eight slots per load keep the
     // vector ALU busier (measured on [32, 4096, 4096] bf16: 6000 GB/s with two, 5700 with four, 5350 with eight)
     constexpr int UNROLL = BF16 ? 2 : 4;
@@ -196,8 +223,9 @@ __global__ __launch_bounds__(256) void reduce_max_cols_kernel(const void* __rest
     const int ti = (int)(u % tiles_i); u /= tiles_i;
     const int seg = (int)(u % segs);
     const long long o = u / segs;
-    const long long i0 = (long long)ti * (64 * VEC) + (long long)lane * VEC;
-    const bool in_range = i0 < inner;             // VEC > 1: inner is a multiple of VEC
+    const long long i_lane = (long long)ti * (64 * VEC) + (long long)lane * VEC;
+    const bool in_range = i_lane < inner;         // (aligned rows: inner is a multiple of VEC)
+    const long long i0 = UNALIGNED && i_lane + VEC > inner ? inner - VEC : i_lane;
     const int r0 = seg * r_per_seg;
     const int r1 = r0 + r_per_seg < red ? r0 + r_per_seg : red;
 
@@ -210,42 +238,33 @@ __global__ __launch_bounds__(256) void reduce_max_cols_kernel(const void* __rest
         const size_t base = ((size_t)o * (size_t)red) * (size_t)inner + (size_t)i0;   // element index of r = 0
         int r = r0 + wave;
         // the wave's first element starts the scan (so the loops need no "nothing seen yet" test)
-        if constexpr (VEC > 1) {
-            const unsigned char* src = (const unsigned char*)X + base * Elem<BF16>::BYTES;
-            const size_t rstride = (size_t)inner * Elem<BF16>::BYTES;
-            if (r < r1) {
-                unpack<BF16>(__builtin_nontemporal_load((const u32x4*)(src + (size_t)r * rstride)), bv);
+        const unsigned char* src = (const unsigned char*)X + base * Elem<BF16>::BYTES;
+        const size_t rstride = (size_t)inner * Elem<BF16>::BYTES;
+        if (r < r1) {
+            unpack<BF16>(load_chunk<BF16, UNALIGNED>(src + (size_t)r * rstride), bv);
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) bp[e] = r;
-                r += 4;
-            }
-            for (; r + (UNROLL - 1) * 4 < r1; r += UNROLL * 4) {
-                u32x4 w[UNROLL];
+            for (int e = 0; e < VEC; ++e) bp[e] = r;
+            r += 4;
+        }
+        for (; r + (UNROLL - 1) * 4 < r1; r += UNROLL * 4) {
+            u32x4 w[UNROLL];
 #pragma unroll
-                for (int q = 0; q < UNROLL; ++q)
-                    w[q] = __builtin_nontemporal_load((const u32x4*)(src + (size_t)(r + 4 * q) * rstride));
+            for (int q = 0; q < UNROLL; ++q) w[q] = load_chunk<BF16, UNALIGNED>(src + (size_t)(r + 4 * q) * rstride);
 #pragma unroll
-                for (int q = 0; q < UNROLL; ++q) {
-                    float x[VEC];
-                    unpack<BF16>(w[q], x);
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e)
-                        if (replaces(x[e], bv[e])) { bv[e] = x[e]; bp[e] = r + 4 * q; }
-                }
-            }
-            for (; r < r1; r += 4) {
+            for (int q = 0; q < UNROLL; ++q) {
                 float x[VEC];
-                unpack<BF16>(__builtin_nontemporal_load((const u32x4*)(src + (size_t)r * rstride)), x);
+                unpack<BF16>(w[q], x);
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
-                    if (replaces(x[e], bv[e])) { bv[e] = x[e]; bp[e] = r; }
+                    if (replaces(x[e], bv[e])) { bv[e] = x[e]; bp[e] = r + 4 * q; }
             }
-        } else {
-            if (r < r1) { bv[0] = load_one<BF16>(X, base + (size_t)r * (size_t)inner); bp[0] = r; r += 4; }
-            for (; r < r1; r += 4) {
-                const float x = load_one<BF16>(X, base + (size_t)r * (size_t)inner);
-                if (replaces(x, bv[0])) { bv[0] = x; bp[0] = r; }
-            }
+        }
+        for (; r < r1; r += 4) {
+            float x[VEC];
+            unpack<BF16>(load_chunk<BF16, UNALIGNED>(src + (size_t)r * rstride), x);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e)
+                if (replaces(x[e], bv[e])) { bv[e] = x[e]; bp[e] = r; }
         }
     }
     // waves 1..3 hand their results to wave 0
@@ -281,8 +300,11 @@ __global__ __launch_bounds__(256) void reduce_max_cols_kernel(const void* __rest
 // ---------------------------------------------------------------------------------
 // inner == 1, short rows (at most 128 chunks): a wave per row would leave most lanes idle,
 // so g = 1, 2, ... 32 lanes (a power of two, 1 << lg) share a row and a wave takes 64 / g
-// rows; every lane has at most four chunks, fetched together.  No segments.
-template <bool BF16, int VEC>
+// rows; every lane has at most four chunks, fetched together.  No segments.  VEC == 1: rows of at most 128
+// elements that do not start on 16-byte boundaries; UNALIGNED: longer ones, read in 16-byte chunks from
+// any element on, the elements behind the last whole chunk one by one by the lane whose chunk they
+// would be.
+template <bool BF16, int VEC, bool UNALIGNED>
 __global__ __launch_bounds__(256) void reduce_max_short_rows_kernel(const void* __restrict__ X, void* __restrict__ out,
                                                                     int* __restrict__ idx, long long outer, int red, int lg)
 {
@@ -302,7 +324,7 @@ __global__ __launch_bounds__(256) void reduce_max_short_rows_kernel(const void* 
         have[u] = active && c < nch;
         if constexpr (VEC > 1) {
             u32x4 w = {0u, 0u, 0u, 0u};
-            if (have[u]) w = __builtin_nontemporal_load((const u32x4*)((const unsigned char*)X + row_base * Elem<BF16>::BYTES) + c);
+            if (have[u]) w = load_chunk<BF16, UNALIGNED>((const unsigned char*)X + row_base * Elem<BF16>::BYTES + (size_t)c * 16);
             unpack<BF16>(w, x[u]);
         } else {
             x[u][0] = have[u] ? load_one<BF16>(X, row_base + c) : 0.0f;
@@ -317,6 +339,14 @@ __global__ __launch_bounds__(256) void reduce_max_short_rows_kernel(const void* 
         for (int e = 0; e < VEC; ++e) {
             const int pos = (gl + u * g) * VEC + e;
             if (have[u] && (p == kNoPos || replaces(x[u][e], v))) { v = x[u][e]; p = pos; }
+        }
+    }
+    if constexpr (UNALIGNED) {
+        if (active && gl == (nch & (g - 1))) {
+            for (int pos = nch * VEC; pos < red; ++pos) {
+                const float r = load_one<BF16>(X, row_base + pos);
+                if (p == kNoPos || replaces(r, v)) { v = r; p = pos; }
+            }
         }
     }
     // across the g lanes of the row
@@ -505,7 +535,10 @@ ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int 
     const int es = dtype == DT_BF16 ? 2 : 4;
     const int vec16 = 16 / es;
     if (inner == 1) {
-        pl.vec = (x_aligned && red % vec16 == 0) ? vec16 : 1;
+        // rows that do not all start on 16-byte boundaries: read in chunks all the same, except where
+        // they are so short that one element per lane is as good
+        pl.unaligned = !(x_aligned && red % vec16 == 0);
+        pl.vec = pl.unaligned && red <= kShortRowChunks ? 1 : vec16;
         const long long nch = red / pl.vec;
         if (nch <= kShortRowChunks) {              // very short rows: g lanes each, at most four chunks per lane
             int g = 1;
@@ -556,12 +589,15 @@ ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int 
         pl.segs = (int)((red + pl.per_seg - 1) / pl.per_seg);
         pl.blocks = (outer * pl.segs + 3) / 4;
     } else {
-        pl.vec = (x_aligned && inner % vec16 == 0) ? vec16 : 1;
+        pl.unaligned = !(x_aligned && inner % vec16 == 0);
+        pl.vec = vec16;
         pl.group = 256;
         pl.tiles_i = (int)((inner + 64 * pl.vec - 1) / (64 * pl.vec));
         const long long wg0 = outer * pl.tiles_i;
         pl.segs = 1;
-        if (wg0 < target_workgroups(dtype)) {
+        // (unaligned rows: from one workgroup per CU on the second pass costs more than the segments
+        // give, fp32 [42, 72, 1901], 336 workgroups: 13.7 us in one pass, 18.5 in two)
+        if (wg0 < (pl.unaligned ? 256 : target_workgroups(dtype))) {
             const long long want = (target_workgroups(dtype) + wg0 - 1) / wg0;
             const long long most = red / 32 > 0 ? red / 32 : 1;                 // eight r per wave at least
             pl.segs = (int)(want < most ? want : most);
@@ -583,10 +619,10 @@ hipError_t launch_reduce_max(const ReducePlan& pl, const void* X, void* out, int
     if (inner == 1 && pl.group < 64) {
         int lg = 0;
         while ((1 << lg) < pl.group) ++lg;
-#define PGK_SHORT(BF, VEC) \
-    hipLaunchKernelGGL((reduce_max_short_rows_kernel<BF, VEC>), grid, block, 0, s, X, out, idx, outer, (int)red, lg)
-        if (bf) { if (pl.vec > 1) PGK_SHORT(true, 8); else PGK_SHORT(true, 1); }
-        else { if (pl.vec > 1) PGK_SHORT(false, 4); else PGK_SHORT(false, 1); }
+#define PGK_SHORT(BF, VEC, UN) \
+    hipLaunchKernelGGL((reduce_max_short_rows_kernel<BF, VEC, UN>), grid, block, 0, s, X, out, idx, outer, (int)red, lg)
+        if (bf) { if (pl.vec == 1) PGK_SHORT(true, 1, false); else if (pl.unaligned) PGK_SHORT(true, 8, true); else PGK_SHORT(true, 8, false); }
+        else { if (pl.vec == 1) PGK_SHORT(false, 1, false); else if (pl.unaligned) PGK_SHORT(false, 4, true); else PGK_SHORT(false, 4, false); }
 #undef PGK_SHORT
     } else if (inner > 1 && pl.group == -1) {
         if (bf) hipLaunchKernelGGL(reduce_max_tiny_block_kernel<true>, grid, block, 0, s, X, out, idx, outer, (int)red, (int)inner);
@@ -595,21 +631,21 @@ hipError_t launch_reduce_max(const ReducePlan& pl, const void* X, void* out, int
         if (bf) hipLaunchKernelGGL(reduce_max_small_inner_kernel<true>, grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, (int)inner, pl.segs, pl.per_seg);
         else hipLaunchKernelGGL(reduce_max_small_inner_kernel<false>, grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, (int)inner, pl.segs, pl.per_seg);
     } else if (inner == 1) {
-#define PGK_ROWS(BF, VEC, G) \
-    hipLaunchKernelGGL((reduce_max_rows_kernel<BF, VEC, G>), grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, pl.segs, pl.per_seg)
+#define PGK_ROWS(BF, LEAD, G) \
+    hipLaunchKernelGGL((reduce_max_rows_kernel<BF, LEAD, G>), grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, pl.segs, pl.per_seg)
         if (bf) {
-            if (pl.vec > 1) { if (pl.group == 64) PGK_ROWS(true, 8, 64); else PGK_ROWS(true, 8, 256); }
-            else { if (pl.group == 64) PGK_ROWS(true, 1, 64); else PGK_ROWS(true, 1, 256); }
+            if (pl.unaligned) { if (pl.group == 64) PGK_ROWS(true, true, 64); else PGK_ROWS(true, true, 256); }
+            else { if (pl.group == 64) PGK_ROWS(true, false, 64); else PGK_ROWS(true, false, 256); }
         } else {
-            if (pl.vec > 1) { if (pl.group == 64) PGK_ROWS(false, 4, 64); else PGK_ROWS(false, 4, 256); }
-            else { if (pl.group == 64) PGK_ROWS(false, 1, 64); else PGK_ROWS(false, 1, 256); }
+            if (pl.unaligned) { if (pl.group == 64) PGK_ROWS(false, true, 64); else PGK_ROWS(false, true, 256); }
+            else { if (pl.group == 64) PGK_ROWS(false, false, 64); else PGK_ROWS(false, false, 256); }
         }
 #undef PGK_ROWS
     } else {
-#define PGK_COLS(BF, VEC) \
-    hipLaunchKernelGGL((reduce_max_cols_kernel<BF, VEC>), grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, inner, pl.tiles_i, pl.segs, pl.per_seg)
-        if (bf) { if (pl.vec > 1) PGK_COLS(true, 8); else PGK_COLS(true, 1); }
-        else { if (pl.vec > 1) PGK_COLS(false, 4); else PGK_COLS(false, 1); }
+#define PGK_COLS(BF, UN) \
+    hipLaunchKernelGGL((reduce_max_cols_kernel<BF, UN>), grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, inner, pl.tiles_i, pl.segs, pl.per_seg)
+        if (bf) { if (pl.unaligned) PGK_COLS(true, true); else PGK_COLS(true, false); }
+        else { if (pl.unaligned) PGK_COLS(false, true); else PGK_COLS(false, false); }
 #undef PGK_COLS
     }
     hipError_t e = hipGetLastError();

@@ -17,7 +17,7 @@ CASES = [(128, 1, 256, 16, 3, 1, 1, 1),          # two whole tiles, rows aligned
          (90, 3, 385, 70, 7, 1, 3, 1),           # three tiles and one position, K odd (21)
          (128, 2, 300, 5, 1, 1, 0, 1),           # one tap, fewer channels than waves
          (64, 1, 2600, 130, 10, 5, 2, 1),        # strided, two blocks of channels
-         (20, 15, 1700, 140, 3, 1, 2, 2),        # 45 products per sum, the kernel's longest
+         (40, 15, 1700, 140, 3, 1, 2, 2),        # 45 products per sum, the kernel's longest
          (43, 4, 768, 128, 6, 2, 5, 3),          # 24 products
          (70, 1, 1027, 512, 10, 1, 1, 1),        # every sixteenth channel (fp32, odd rows)
          (70, 1, 1027, 300, 16, 1, 1, 1)]        # ... with blocks only partly filled
