@@ -14,6 +14,8 @@
 // All are streaming copies.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "pgk_device.h"
 #include "pgk_kernels.h"
 
@@ -79,38 +81,77 @@ __device__ __forceinline__ void repack_weight_chunk(long long c, const T* __rest
 }
 
 // xc[c][b][ci][j] = x[b][ci][(j + h) * stride + phase - pad] (inside [0, L), ci < Cin; else 0) with
-// c = phase * shifts + h.  One thread per 16-byte chunk of the copies (rows of Lq elements, a
-// multiple of the chunk): element loads, one 16-byte store.  Also regroups the weights (padded to
-// Cin_pad channels) into wr.
-template <typename T>
-__global__ __launch_bounds__(256) void conv_phase_copies_kernel(const T* __restrict__ x, T* __restrict__ xc, long long B,
-                                                                int Cin, int Cin_pad, int L, int Lq, int pad, int stride,
-                                                                int shifts, long long total_chunks,
+// c = phase * shifts + h.  Bound by its traffic (the input once, the copies once).  A thread makes the
+// 16-byte chunk at one (row, j) of all stride * shifts copies, from one run of the input: for STRIDE 1
+// and 2, where that run lies inside the row, with 16-byte loads from any element on; else (STRIDE 0:
+// any other stride, and at the ends of rows) element by element.  bf16 [8, 512, 4096], two shifted copies:
+// 36 us with a thread per chunk of one copy and element loads, 20 so.  Also regroups the weights (padded
+// to Cin_pad channels) into wr.
+template <typename T, int STRIDE, int SHIFTS>
+__global__ __launch_bounds__(256) void conv_phase_copies_kernel(const T* __restrict__ x, T* __restrict__ xc, unsigned int rows,
+                                                                int Cin, int Cin_pad, int L, int Lq, int pad, int stride_any,
+                                                                unsigned int copy_blocks,
                                                                 const T* __restrict__ w, T* __restrict__ wr, int Cout, int Kw)
 {
     constexpr int EPC = 16 / (int)sizeof(T);
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    // the threads after the copies regroup the weights (same launch: a second one costs as much
+    // the workgroups after the copies regroup the weights (same launch: a second one costs as much
     // as either piece of work)
-    if (t >= total_chunks) { repack_weight_chunk<T>(t - total_chunks, w, wr, Cout, Cin, Cin_pad, Kw); return; }
-    const int cpr = Lq / EPC;                                // chunks per row
-    const long long row = t / cpr;                           // (c * B + b) * Cin_pad + ci
-    const int j0 = (int)(t - row * cpr) * EPC;
-    const int ci = (int)(row % Cin_pad);
-    const long long cb = row / Cin_pad;
-    const long long b = cb % B;
-    const int c = (int)(cb / B);
-    const int phase = c / shifts, h = c - phase * shifts;
-    const T* src = x + ((size_t)b * (size_t)Cin + (size_t)(ci < Cin ? ci : 0)) * (size_t)L;
-    T v[EPC];
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) {
-        const long long s = (long long)(j0 + e + h) * stride + phase - pad;
-        v[e] = (ci < Cin && s >= 0 && s < L) ? src[s] : T(0);
+    if (blockIdx.x >= copy_blocks) {
+        repack_weight_chunk<T>((long long)(blockIdx.x - copy_blocks) * 256 + threadIdx.x, w, wr, Cout, Cin, Cin_pad, Kw);
+        return;
     }
-    u32x4 out;
-    __builtin_memcpy(&out, v, 16);
-    *(u32x4*)(xc + (size_t)row * (size_t)Lq + j0) = out;
+    const int stride = STRIDE > 0 ? STRIDE : stride_any;
+    const unsigned int cpr = (unsigned int)(Lq / EPC);        // chunks per row
+    const unsigned long long chunk0 = (unsigned long long)blockIdx.x * 256u;
+    const unsigned int row0 = (unsigned int)(chunk0 / cpr), in0 = (unsigned int)(chunk0 - (unsigned long long)row0 * cpr) + threadIdx.x;
+    const unsigned int row = row0 + in0 / cpr;                // b * Cin_pad + ci
+    if (row >= rows) return;
+    const int j0 = (int)(in0 % cpr) * EPC;
+    const unsigned int b = row / (unsigned int)Cin_pad;
+    const int ci = (int)(row - b * (unsigned int)Cin_pad);
+    T* dst = xc + (size_t)row * (size_t)Lq + j0;
+    const size_t plane = (size_t)rows * (size_t)Lq;           // elements of one copy
+    const T* src = x + ((size_t)b * (size_t)Cin + (size_t)(ci < Cin ? ci : 0)) * (size_t)L;
+    const long long s0 = (long long)j0 * stride - pad;        // where the run starts
+    if constexpr (STRIDE > 0) {
+        constexpr int RUN = (EPC + SHIFTS - 1) * STRIDE;      // ... and its elements
+        if (ci < Cin && s0 >= 0 && s0 + RUN <= L) {
+            T v[RUN];
+            using chunk_at_element = typename std::conditional<sizeof(T) == 2, u32x4_align2, u32x4_align4>::type;
+#pragma unroll
+            for (int q = 0; q < STRIDE; ++q) {
+                const u32x4 c = *(const chunk_at_element*)(src + s0 + q * EPC);
+                __builtin_memcpy(v + q * EPC, &c, 16);
+            }
+#pragma unroll
+            for (int e = EPC * STRIDE; e < RUN; ++e) v[e] = src[s0 + e];
+#pragma unroll
+            for (int p = 0; p < STRIDE; ++p)
+#pragma unroll
+                for (int h = 0; h < SHIFTS; ++h) {
+                    T o[EPC];
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) o[e] = v[(e + h) * STRIDE + p];
+                    u32x4 out;
+                    __builtin_memcpy(&out, o, 16);
+                    *(u32x4*)(dst + (size_t)(p * SHIFTS + h) * plane) = out;
+                }
+            return;
+        }
+    }
+    for (int p = 0; p < stride; ++p)
+#pragma unroll
+        for (int h = 0; h < SHIFTS; ++h) {
+            T v[EPC];
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) {
+                const long long s = s0 + (long long)(e + h) * stride + p;
+                v[e] = (ci < Cin && s >= 0 && s < L) ? src[s] : T(0);
+            }
+            u32x4 out;
+            __builtin_memcpy(&out, v, 16);
+            *(u32x4*)(dst + (size_t)(p * SHIFTS + h) * plane) = out;
+        }
 }
 
 // Both preparations of the in-place path in one launch (each is a few microseconds of work;
@@ -183,17 +224,22 @@ hipError_t launch_conv_phase_copies(const void* x, void* xc, long long B, int Ci
     const int epc = dtype == DT_BF16 ? 8 : 4;
     if (Lq % epc != 0 || Cin_pad % epc != 0 || B <= 0) return hipErrorInvalidValue;
     if (((uintptr_t)xc | (uintptr_t)wr) % 16 != 0) return hipErrorInvalidValue;
-    const long long chunks = (long long)stride * shifts * B * Cin_pad * (Lq / epc);
+    if (shifts < 1 || shifts > 2 || (shifts == 2 && dtype != DT_BF16)) return hipErrorInvalidValue;
+    const long long rows = B * (long long)Cin_pad, chunks = rows * (Lq / epc);
+    const long long copy_blocks = (chunks + 255) / 256;
     const long long repack_chunks = (long long)Cout * Kw * (Cin_pad / epc);
-    const long long blocks = (chunks + repack_chunks + 255) / 256;
-    if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (dtype == DT_BF16)
-        hipLaunchKernelGGL(conv_phase_copies_kernel<unsigned short>, dim3((unsigned int)blocks), dim3(256), 0, s,
-                           (const unsigned short*)x, (unsigned short*)xc, B, Cin, Cin_pad, L, Lq, pad, stride, shifts, chunks,
-                           (const unsigned short*)w, (unsigned short*)wr, Cout, Kw);
-    else
-        hipLaunchKernelGGL(conv_phase_copies_kernel<float>, dim3((unsigned int)blocks), dim3(256), 0, s, (const float*)x,
-                           (float*)xc, B, Cin, Cin_pad, L, Lq, pad, stride, shifts, chunks, (const float*)w, (float*)wr, Cout, Kw);
+    const long long blocks = copy_blocks + (repack_chunks + 255) / 256;
+    if (rows > 0xffffffffLL || blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+#define PGK_COPIES(T, ST, SH)                                                                                            \
+    hipLaunchKernelGGL((conv_phase_copies_kernel<T, ST, SH>), dim3((unsigned int)blocks), dim3(256), 0, s, (const T*)x, (T*)xc, \
+                       (unsigned int)rows, Cin, Cin_pad, L, Lq, pad, stride, (unsigned int)copy_blocks, (const T*)w, (T*)wr, Cout, Kw)
+    if (dtype == DT_BF16) {
+        if (shifts == 2) { if (stride == 1) PGK_COPIES(unsigned short, 1, 2); else if (stride == 2) PGK_COPIES(unsigned short, 2, 2); else PGK_COPIES(unsigned short, 0, 2); }
+        else { if (stride == 1) PGK_COPIES(unsigned short, 1, 1); else if (stride == 2) PGK_COPIES(unsigned short, 2, 1); else PGK_COPIES(unsigned short, 0, 1); }
+    } else {
+        if (stride == 1) PGK_COPIES(float, 1, 1); else if (stride == 2) PGK_COPIES(float, 2, 1); else PGK_COPIES(float, 0, 1);
+    }
+#undef PGK_COPIES
     return hipGetLastError();
 }
 
