@@ -222,8 +222,11 @@ class _on_stream:
 
 
 def _stream_ptr(stream) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # the handle of torch.cuda.current_stream() without the Python object around it: 0.3 us, not 2.8, of a
+    # small call that takes 20 us of which the host bounds all
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ws_flags(A, B, rowsum: bool, b_transposed: bool) -> int:
