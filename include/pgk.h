@@ -94,7 +94,10 @@ typedef enum {
  * M, N, K, batch > 0.  Any shape is accepted; M, N and K need not be tile multiples.
  * (Tile shapes: 256 x 256, 128 x 128, 256 x 128, 128 x 256 for bfloat16, 128 x 128 and 64 x 64 for
  * float32, 128 x 32 and 32 x 128 for outputs of at most 32 columns or rows, and 32 x 32 tiles whose
- * waves split the K range for float32 problems of a few tiles and a short K; pgk_gemm_plan tells.)
+ * waves split the K range for float32 problems of a few tiles and a short K; pgk_gemm_plan tells.
+ * The 128 x 128 float32 tile runs on the bfloat16 matrix cores, each value as three exact bfloat16
+ * terms: results are as close to the exact ones as with the float32 instruction, which computes a
+ * tile again whose values the terms cannot hold.)
  * The matrix-core kernels read operands in place when their rows start on 4-byte boundaries
  * (float32 always; bfloat16 when K -- and, for B as [K][N], N -- is even).  Otherwise, when
  * the problem has at least 64^3 multiply-adds, the operands are first copied into the
@@ -252,8 +255,8 @@ int pgk_splitk_auto_splits(int64_t M, int64_t N, int64_t K, int64_t batch,
  *     idx  [outer][inner]       int32 device pointer, or NULL = positions not wanted
  *
  * outer, red, inner > 0; red at most 2^31 - 1024, outer * inner below 2^62, else
- * PGK_ERR_UNSUPPORTED.  Any shape and alignment is accepted (16-byte loads are used when
- * X is 16-byte aligned and the contiguous extent is a multiple of 16 bytes).  When there
+ * PGK_ERR_UNSUPPORTED.  Any shape and alignment is accepted (rows that do not start
+ * on 16-byte boundaries are read in aligned 16-byte chunks too).  When there
  * are few outputs and a long reduced dimension the range is reduced in segments and a
  * second small kernel combines them; the segment results (value, position) live in
  * `workspace`: pgk_reduce_max_workspace_bytes(...) bytes of device memory on a 4-byte
@@ -298,9 +301,9 @@ size_t pgk_reduce_max_workspace_bytes(int64_t outer, int64_t red, int64_t inner,
  * offsets), channels padded with zeros to a multiple of the K tile.  Both need `workspace`
  * (device memory, 256-byte aligned, contents destroyed) of pgk_conv1d_workspace_bytes(...)
  * bytes for the regrouped weights and the strips or copies.  Too small or NULL gives
- * PGK_ERR_WORKSPACE.  Every other case (a few input channels, tiny outputs) is computed by
- * a bounds-checked kernel that reads the input in place and needs no workspace (the query
- * then returns 0).
+ * PGK_ERR_WORKSPACE.  Every other case needs no workspace (the query then returns 0): few input
+ * channels under a large enough output run on a matrix-core kernel of their own, the rest (tiny
+ * outputs) on a bounds-checked kernel; both read the input in place.
  */
 int pgk_conv1d(const void* x, const void* w, const float* bias, void* y,
                int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw,

@@ -28,7 +28,8 @@
 //    operands sustain 2230 TFLOP/s with it against 1940 with 32 x 32 x 16, the
 //    8192^3 GEMM 764 against 837 us on the same machine.
 //  * fp32: v_mfma_f32_32x32x2_f32 (at a sixteenth of the bf16 rate the matrix
-//    pipes are not what the power limit sees).
+//    pipes are not what the power limit sees); the 128 x 128 fp32 tile has a
+//    kernel of its own on the bf16 matrix cores (pgk_gemm_f32_terms.h).
 //  * Workgroup ids are remapped so that each XCD (own L2) works on a compact
 //    group of tiles.
 #ifndef PGK_GEMM_MFMA_KERNEL_H
