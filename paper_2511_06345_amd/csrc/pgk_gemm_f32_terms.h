@@ -30,11 +30,10 @@
 //  * A value above the largest bf16 (3.39e38) rounds to infinity, and an infinity or NaN among the
 //    operands turns into NaN where fp32 would give an infinity.  Either way the accumulators it
 //    touches are not finite, so: any accumulator of the tile that is not finite.
-//  * The low terms of values below about 2^-110 fall under the smallest bf16.  Against values of the
-//    same row of A (column of B) of 2^-63 and more that is nothing; so: a thread that has seen
-//    only values below 2^-63 in its part of a row of A or a column of B (zeros alone do not count).
-//    2^-63 because a value reaches it exactly if one of the two upper bits of its exponent is set:
-//    the bitwise or of the values tells, at one operation per pair.
+//  * The low term of a value below about 2^-110 may fall under the smallest bf16 (denormals included, which
+//    the instruction takes as they are).  What a value leaves after two terms has eight significant
+//    bits; they lie in the upper half of the word, where they become the third term, unless that
+//    happens.  So: any such remainder with a bit in its lower half, at one operation per pair of values.
 //
 // How: a workgroup of four waves owns a BM x BN tile of C (waves 2 x 2), K in steps of 32.  While the
 // waves multiply the step in LDS, each thread splits its share of the fp32 values of the next one
@@ -411,11 +410,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     // ---- the step in registers, split.  Part n is a pair of k values: of A's chunks one after the other,
     // then of B's (of column pairs both columns at one k); OPS operations of two or three
     // instructions each take it apart.
-    unsigned int a_seen[A_CH], b_seen[B_CH];      // the values this thread has seen, or-ed together
-#pragma unroll
-    for (int t = 0; t < A_CH; ++t) a_seen[t] = 0u;
-#pragma unroll
-    for (int t = 0; t < B_CH; ++t) b_seen[t] = 0u;
+    unsigned int lost = 0u;                       // what the values leave after two terms, or-ed together
     u32x4 pa[A_CH][3], pb[B_CH][3];               // the packed terms
     constexpr int PARTS = 4 * (A_CH + B_CH), OPS = 5;
     auto bits = [](float x) __attribute__((always_inline)) { return __builtin_bit_cast(unsigned int, x); };
@@ -431,8 +426,6 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             if constexpr (of_a) pa[t][plane][q] = w; else pb[t][plane][q] = w;
         };
         if constexpr (op == 0) {
-            const unsigned int both = bits(x[0]) | bits(x[1]);
-            if constexpr (of_a) a_seen[t] |= both; else b_seen[t] |= both;
             // odd rows and columns enter with their sign turned (see "Rounding")
             if constexpr (t == 1) { x[0] = -x[0]; x[1] = -x[1]; }
             const unsigned int h = pack_bf16x2(x[0], x[1]);
@@ -451,6 +444,8 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             x[1] -= t1;
         } else {
             put(2, __builtin_amdgcn_perm(bits(x[1]), bits(x[0]), 0x07060302u));       // (at most eight bits are left)
+            lost |= bits(x[0]) | bits(x[1]);
+            asm volatile("" : "+v"(lost));        // (here and now: put off to the end of the step, all remainders stay live)
         }
     };
     auto write_step = [&]() __attribute__((always_inline)) {
@@ -549,11 +544,6 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             voff_a[0] = voff_a[1];
             voff_a[1] = o;
         }
-        if (kt + 1 == turn0 || kt + 1 == turn1) {
-            const unsigned int o = a_seen[0];
-            a_seen[0] = a_seen[1];
-            a_seen[1] = o;
-        }
         step(IC<1>{}, IC<1>{});
         if (kt + 1 == turn0 || kt + 1 == turn1) {
             const int o = wpos_a[0];
@@ -576,11 +566,6 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
 
     // ---- did the terms hold everything?  (see "Range")
     {
-        int bad = 0;
-#pragma unroll
-        for (int t = 0; t < A_CH; ++t) bad |= (a_seen[t] & 0x7fffffffu) && !(a_seen[t] & 0x60000000u);
-#pragma unroll
-        for (int t = 0; t < B_CH; ++t) bad |= (b_seen[t] & 0x7fffffffu) && !(b_seen[t] & 0x60000000u);
         float zero = 0.0f;            // 0 x anything finite; NaN otherwise
 #pragma unroll
         for (int i = 0; i < TM16; ++i)
@@ -588,7 +573,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             for (int j = 0; j < TN16; ++j)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) zero = __builtin_fmaf(acc[i][j][e], 0.0f, zero);
-        bad |= zero != 0.0f;
+        const int bad = (lost & 0xffffu) != 0u || zero != 0.0f;
         if (__syncthreads_or(bad)) {
             // the same tile with the fp32 matrix instruction.  LDS: sixteen rows x four k values of
             // fp32 are 256 bytes, row r of k chunk c at 256 c + 16 r (BM x 32 floats fit the three planes).

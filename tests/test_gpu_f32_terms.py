@@ -110,3 +110,64 @@ def test_identity_is_exact_and_row_sums_have_no_bias(pgk):
     err_rs = float((rs[0].double() - ref.sum(1)).norm() / ref.sum(1).norm())
     err_cs = float((C[0].double().sum(0) - ref.sum(0)).norm() / ref.sum(0).norm())
     assert err < 2e-6 and err_rs < 2 * err and err_cs < 2 * err, (err, err_rs, err_cs)
+
+
+def one_product_inputs(rows, cols, batch, seed):
+    """A [batch][rows][64], B [batch][64][cols] of normal float32 values whose products have one term each: row m of A holds
+    a value of 2^-60 ... 2^-122 at an even k, whose partners in B are as far above one, and a 1 beside it,
+    whose partners are zero.  In odd entries the values of A have twelve significant bits (their low
+    terms are denormal bf16 values and nothing is lost); odd rows are zero."""
+    d = np.exp2(-60.0 - np.arange(64)).astype(np.float32)
+    A, B = np.zeros((batch, rows, 64), np.float32), np.zeros((batch, 64, cols), np.float32)
+    v = gen.normal(gen.tensor_seed(seed, 1, rows), batch * rows, 1.0).reshape(batch, rows)
+    v[1::2] = (v[1::2].view(np.uint32) & np.uint32(0xfffff000)).view(np.float32)
+    m = np.arange(0, rows, 2)
+    A[:, m, m % 64] = v[:, m] * d[m % 64]
+    A[:, m, m % 64 + 1] = 1.0
+    B[:, ::2] = gen.normal(gen.tensor_seed(seed, 2, cols), batch * 32 * cols, 1.0).reshape(batch, 32, cols) / d[::2, None]
+    return A, B
+
+
+@pytest.mark.parametrize("bt", [False, True])
+@pytest.mark.parametrize("small_b", [False, True])
+@pytest.mark.parametrize("splits", [None, 2])
+def test_small_values_beside_ordinary_ones(pgk, oracle, splits, small_b, bt):
+    """Values whose low terms fall under the smallest bf16, in rows (columns) that hold ordinary values
+    too, against values as far above one: nothing else in the sum hides what a term loses."""
+    M, N, batch = 130, 140, 60
+    assert pgk.gemm_plan(M, N, 64, batch, F32, b_transposed=bt)["tile"] == (128, 128, 32)
+    if small_b:
+        A, B = one_product_inputs(N, M, batch, 98)
+        A, B = np.ascontiguousarray(np.swapaxes(B, 1, 2)), np.ascontiguousarray(np.swapaxes(A, 1, 2))
+    else:
+        A, B = one_product_inputs(M, N, batch, 98)
+    ref, _ = oracle.gemm_fused(A, B, None, NONE)
+    C, _ = call(pgk, A, B, bt, splits)
+    assert np.all(np.abs(C - ref) <= bound(64) * np.abs(ref))
+
+
+def test_small_values_in_a_convolution(pgk, oracle):
+    import torch
+    B, Cin, L, Cout = 8, 64, 4096, 130
+    assert pgk.conv1d_workspace_bytes(B, Cin, L, Cout, 3, 1, 1, 1, F32) > 0
+    wc, xc = one_product_inputs(Cout, L, B, 99)
+    w = np.zeros((Cout, Cin, 3), np.float32)
+    w[:, :, 1] = wc[0]
+    y = pgk.conv1d(torch.from_numpy(xc).cuda(), torch.from_numpy(w).cuda(), None, NONE, 1, 1, 1).cpu().numpy()
+    ref = oracle.conv1d(xc, w, None, NONE, 1, 1, 1)
+    assert np.all(np.abs(y - ref) <= bound(3 * Cin) * np.abs(ref))
+
+
+@pytest.mark.parametrize("power", [-66, -100, 60])
+def test_scaling_by_a_power_of_two_changes_no_bit(pgk, power):
+    """The terms hold values down to 2^-110 exactly: a factor of a power of two goes through the split, the
+    products and the sums unchanged, so a result that differs in any bit took another route."""
+    import torch
+    g = torch.Generator("cuda").manual_seed(7)
+    A = torch.randn((1, 1920, 200), generator=g, device="cuda")
+    A = torch.where(A.abs() < 2.0 ** -8, torch.full_like(A, 0.5), A)
+    B = torch.randn((1, 200, 2048), generator=g, device="cuda")
+    assert pgk.gemm_plan(1920, 2048, 200, 1, F32)["tile"] == (128, 128, 32)
+    C, _ = pgk.gemm_fused(A, B, None, NONE)
+    D, _ = pgk.gemm_fused(A * 2.0 ** power, B, None, NONE)
+    assert torch.equal(C * 2.0 ** power, D)
