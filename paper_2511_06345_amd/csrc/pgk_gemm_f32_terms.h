@@ -24,8 +24,8 @@
 // twice, at a quarter and at three quarters of it, which takes a cut that is constant or grows
 // evenly out of every single output.
 //
-// Range.  bf16 has the exponents of fp32, so nothing overflows that fp32 holds, with two
-// exceptions, and both are found and made good inside the kernel: the tile is then computed again
+// Range.  bf16 has the exponents of fp32, so nothing overflows that fp32 holds, with three
+// exceptions, and all are found and made good inside the kernel: the tile is then computed again
 // with the fp32 matrix instruction (fallback below).
 //  * A value above the largest bf16 (3.39e38) rounds to infinity, and an infinity or NaN among the
 //    operands turns into NaN where fp32 would give an infinity.  Either way the accumulators it
@@ -34,6 +34,8 @@
 //    the instruction takes as they are).  What a value leaves after two terms has eight significant
 //    bits; they lie in the upper half of the word, where they become the third term, unless that
 //    happens.  So: any such remainder with a bit in its lower half, at one operation per pair of values.
+//  * The small products of a sum that is itself next to nothing fall under the smallest float32, 2^-149: at most
+//    ten cuts of that size, 2^-26 of a result of 2^-119.  So: any accumulator below that, other than zero.
 //
 // How: a workgroup of four waves owns a BM x BN tile of C (waves 2 x 2), K in steps of 32.  While the
 // waves multiply the step in LDS, each thread splits its share of the fp32 values of the next one
@@ -567,13 +569,18 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     // ---- did the terms hold everything?  (see "Range")
     {
         float zero = 0.0f;            // 0 x anything finite; NaN otherwise
+        int smallest = 0;
 #pragma unroll
         for (int i = 0; i < TM16; ++i)
 #pragma unroll
             for (int j = 0; j < TN16; ++j)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) zero = __builtin_fmaf(acc[i][j][e], 0.0f, zero);
-        const int bad = (lost & 0xffffu) != 0u || zero != 0.0f;
+                for (int e = 0; e < 4; ++e) {
+                    zero = __builtin_fmaf(acc[i][j][e], 0.0f, zero);
+                    const int exponent = __builtin_amdgcn_frexp_expf(acc[i][j][e]);       // (0 for zero)
+                    smallest = exponent < smallest ? exponent : smallest;
+                }
+        const int bad = (lost & 0xffffu) != 0u || zero != 0.0f || smallest < -118;
         if (__syncthreads_or(bad)) {
             // the same tile with the fp32 matrix instruction.  LDS: sixteen rows x four k values of
             // fp32 are 256 bytes, row r of k chunk c at 256 c + 16 r (BM x 32 floats fit the three planes).

@@ -158,10 +158,12 @@ def test_small_values_in_a_convolution(pgk, oracle):
     assert np.all(np.abs(y - ref) <= bound(3 * Cin) * np.abs(ref))
 
 
-@pytest.mark.parametrize("power", [-66, -100, 60])
+@pytest.mark.parametrize("power", [-66, -80, 60])
 def test_scaling_by_a_power_of_two_changes_no_bit(pgk, power):
     """The terms hold values down to 2^-110 exactly: a factor of a power of two goes through the split, the
-    products and the sums unchanged, so a result that differs in any bit took another route."""
+    products and the sums unchanged, so a result that differs in any bit took another route.  (Not for results
+    below 2^-119, and of four million sums the smallest, by cancellation, is 2^-23 of an ordinary one: at a factor
+    of 2^-80 that leaves 2^-100.)"""
     import torch
     g = torch.Generator("cuda").manual_seed(7)
     A = torch.randn((1, 1920, 200), generator=g, device="cuda")
@@ -171,3 +173,18 @@ def test_scaling_by_a_power_of_two_changes_no_bit(pgk, power):
     C, _ = pgk.gemm_fused(A, B, None, NONE)
     D, _ = pgk.gemm_fused(A * 2.0 ** power, B, None, NONE)
     assert torch.equal(C * 2.0 ** power, D)
+
+
+@pytest.mark.parametrize("bt", [False, True])
+def test_results_near_the_smallest_normal_number(pgk, bt):
+    """Factors the terms hold exactly, products of 2^-126 to 2^-108: their small parts fall under the smallest
+    float32 inside the bf16 products."""
+    import torch
+    g = torch.Generator("cuda").manual_seed(8)
+    n = 2048
+    k = torch.arange(n, device="cuda")
+    A = torch.diag(torch.rand(n, generator=g, device="cuda").add_(1.0) * torch.exp2(-63.0 + (k % 18)))[None].contiguous()
+    B = torch.rand((1, n, n), generator=g, device="cuda").add_(1.0).mul_(2.0 ** -63)
+    C, _ = pgk.gemm_fused(A, B.transpose(1, 2).contiguous() if bt else B, None, NONE, b_transposed=bt)
+    ref = A[0].diagonal().double()[:, None] * B[0].double()
+    assert bool(((C[0].double() - ref).abs() <= bound(32) / 12 * ref).all())
