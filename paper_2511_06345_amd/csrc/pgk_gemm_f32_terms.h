@@ -403,6 +403,18 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             for (int t = 0; t < B_CH; ++t) rb[t][e] = e < kb ? rb[t][e] : 0.0f;
         }
     };
+    // columns past the edge that are loaded all the same -- the neighbour of an odd row's last column, in a
+    // convolution every position past the row's end -- hold other rows' values: zero, so that these do not
+    // decide how this tile is computed
+    const bool edge_cols = !BT && (VIEW == VIEW_CONV ? n_rem < BN : n_rem % 2 != 0);
+    auto clear_edge_cols = [&]() __attribute__((always_inline)) {
+        const int left = n_rem - 2 * lane;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            rb[0][e] = left > 0 ? rb[0][e] : 0.0f;
+            rb[1][e] = left > 1 ? rb[1][e] : 0.0f;
+        }
+    };
     auto meet = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -482,6 +494,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     auto step = [&](auto next_tag, auto ahead_tag) __attribute__((always_inline)) {
         constexpr bool NEXT = decltype(next_tag)::value != 0, AHEAD = decltype(ahead_tag)::value != 0;
         bf16x8 fa[3][TM16], fb[2][3];
+        if constexpr (NEXT && !BT) { if (edge_cols) clear_edge_cols(); }
         auto fetch_a = [&](int q, int i) __attribute__((always_inline)) { fa[q][i] = *(const __attribute__((address_space(3))) bf16x8*)PGK_LDS(as + q * Cfg::A_PLANE + i * 1024); };
         auto fetch_b = [&](int j, int q) __attribute__((always_inline)) { fb[j & 1][q] = *(const __attribute__((address_space(3))) bf16x8*)PGK_LDS(bs + q * Cfg::B_PLANE + j * 1024); };
         // (term of A, term of B) of the six products, the small ones first
@@ -531,6 +544,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     rewind();
     load_step();
     if (KT == 1 && k_last < BK) clear_k_tail();
+    if constexpr (!BT) { if (edge_cols) clear_edge_cols(); }
     static_for<0, OPS * PARTS>([&](auto o) __attribute__((always_inline)) { split(IC<decltype(o)::value / OPS>{}, IC<decltype(o)::value % OPS>{}); });
     write_step();
     if (KT > 1) load_step();

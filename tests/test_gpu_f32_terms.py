@@ -188,3 +188,35 @@ def test_results_near_the_smallest_normal_number(pgk, bt):
     C, _ = pgk.gemm_fused(A, B.transpose(1, 2).contiguous() if bt else B, None, NONE, b_transposed=bt)
     ref = A[0].diagonal().double()[:, None] * B[0].double()
     assert bool(((C[0].double() - ref).abs() <= bound(32) / 12 * ref).all())
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), 1.25e-38, 3.4e38])
+def test_columns_that_do_not_exist_leave_the_others_alone(pgk, value):
+    """An odd row length: the last column is loaded together with the element after it, which belongs to
+    the next row or the next batch entry.  Whatever that is, entry 0 gives the same bits."""
+    import torch
+    g = torch.Generator("cuda").manual_seed(9)
+    M, N, K, batch = 256, 131, 70, 60
+    assert pgk.gemm_plan(M, N, K, batch, F32)["tile"] == (128, 128, 32)
+    A = torch.randn((batch, M, K), generator=g, device="cuda")
+    B = torch.randn((batch, K, N), generator=g, device="cuda")
+    C, rs = pgk.gemm_fused(A, B, None, NONE)
+    B[1, 0, 0] = value
+    D, rt = pgk.gemm_fused(A, B, None, NONE)
+    assert torch.equal(C[0], D[0]) and torch.equal(rs[0], rt[0]) and torch.equal(C[2:], D[2:])
+
+
+@pytest.mark.parametrize("pad", [0, 1])
+def test_positions_that_do_not_exist_leave_the_others_alone(pgk, pad):
+    """The same of a convolution: the last tile of a row reads on into the next row's input or its padding."""
+    import torch
+    g = torch.Generator("cuda").manual_seed(10)
+    B, Cin, L, Cout = 8, 64, 4100, 128
+    x = torch.randn((B, Cin, L), generator=g, device="cuda")
+    w = torch.randn((Cout, Cin, 3), generator=g, device="cuda")
+    y = pgk.conv1d(x, w, None, NONE, 1, pad, 1)
+    x[1, :, 0] = float("nan")
+    x[2, 5, 7] = 1.25e-38
+    z = pgk.conv1d(x, w, None, NONE, 1, pad, 1)
+    assert torch.equal(y[0], z[0]) and torch.equal(y[3:], z[3:])
+    assert torch.equal(y[1:3, :, 128:], z[1:3, :, 128:])        # (all but the tiles that hold the two)
