@@ -95,9 +95,11 @@ typedef enum {
  * (Tile shapes: 256 x 256, 128 x 128, 256 x 128, 128 x 256 for bfloat16, 128 x 128 and 64 x 64 for
  * float32, 128 x 32 and 32 x 128 for outputs of at most 32 columns or rows, and 32 x 32 tiles whose
  * waves split the K range for float32 problems of a few tiles and a short K; pgk_gemm_plan tells.
- * The 128 x 128 float32 tile runs on the bfloat16 matrix cores, each value as three exact bfloat16
- * terms: results are as close to the exact ones as with the float32 instruction, which computes a
- * tile again whose values the terms cannot hold.)
+ * The 128 x 128 float32 tile runs on the bfloat16 matrix cores, each value as three bfloat16 terms that
+ * add up to it, a product without the terms' smallest three products (2^-24 of it at the very worst, 2^-27 in the
+ * root mean square); sums are rounded to nearest twice per 32 k, where the float32 instruction rounds
+ * every second k.  A tile with a value that three terms do not hold exactly (some below 2^-110), with a result
+ * below 2^-119 other than zero, or with one that is not finite is computed with the float32 instruction.)
  * The matrix-core kernels read operands in place when their rows start on 4-byte boundaries
  * (float32 always; bfloat16 when K -- and, for B as [K][N], N -- is even).  Otherwise, when
  * the problem has at least 64^3 multiply-adds, the operands are first copied into the

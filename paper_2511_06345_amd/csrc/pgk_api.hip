@@ -338,17 +338,18 @@ int auto_tile_kind(int64_t M, int64_t N, int64_t K, int dtype, int64_t units, bo
     int best = pgk::TILE_LARGE;
     if (K >= 1024 && wgs > kNumCUs) {      // (the fit does not hold for short K, where the epilogues weigh more)
         double best_time = 0.94 * estimated_rounds_time(M, N, K, dtype, units, pgk::TILE_LARGE);
-        // The fp32 constants were fitted when both fp32 tiles used the fp32 matrix instruction.  On the
-        // bf16 matrix cores a round of large tiles takes 0.70 ... 0.75 of that (4096 x 4096 x 4096, four
-        // rounds: 915 us, now 645), which moves the line between the tiles wherever the last round does its
-        // share of work.  75 shapes of 800 ... 5800 rows and columns (and 130 x 30000, 25 x [300 x 700]), K of 1000
-        // ... 4100, small against large tile: with a last round over a quarter of the CUs the large one is
-        // 1.01 ... 1.55 times as fast (4224 x 1552 x 3428 374 and 241 us, 2801 x 2000 x 2616 241 and 177, 2743 x
-        // 3344 x 3232 438 and 434); with a shorter one it is anything
-        // from 0.94 (4756 x 1672 x 3192, 394 and 421 us) to 1.40, and the former line stands.  The slice
+        // The fp32 constants (tile_cost) were fitted when both fp32 tiles used the fp32 matrix instruction.  On
+        // the bf16 matrix cores the large tile takes 0.77 of that (4096 x 4096 x 4096, four rounds: 916 us, now
+        // 700), which moves the line between the tiles wherever the last round does its share of work: shapes
+        // of 130 ... 6000 rows and columns (and 130 x 15000 ... 40000), K of 1024 ... 4096, batches up to 25, with a last round
+        // over a quarter of the CUs.  The factor is where both tiles take the same time: of the 791 shapes that 0.75
+        // gives to the large tile and 0.78 to the small one the ratio of their times has the median 0.995
+        // (0.89 ... 1.10), from 0.78 to 0.82 the large tile is 1.03 times as fast; over all that it is chosen for,
+        // 1.2 (0.94 for single shapes of 130 rows).  With a shorter last round it is anything
+        // from 0.94 to 1.40, and the former line stands.  The slice
         // counts of automatic splits, and with them the workspace a call needs, stay at the former fit.
         const long double last_round = std::fmod(wgs, (long double)kNumCUs);
-        if (dtype == PGK_DTYPE_F32 && (last_round == 0 || last_round > 0.25L * kNumCUs)) best_time *= 0.75;
+        if (dtype == PGK_DTYPE_F32 && (last_round == 0 || last_round > 0.25L * kNumCUs)) best_time *= 0.78;
         for (int kind : {pgk::TILE_SMALL, pgk::TILE_TALL, pgk::TILE_WIDE}) {
             if (!pgk::mfma_has_tile(dtype, kind, b_trans)) continue;
             const double t = estimated_rounds_time(M, N, K, dtype, units, kind);

@@ -5,24 +5,26 @@
 //
 // What bounds an fp32 GEMM on this chip is the fp32 matrix instruction: 157 TFLOP/s, a sixteenth
 // of the bf16 one.  Here every operand value is taken apart into three bf16 values that add up to
-// it exactly (8 + 8 + 8 significand bits: x = h + m + l with h = x rounded to bf16, m = x - h cut off
-// after 8 bits, l the rest; the differences are exact in fp32), and a product is the sum of six bf16
-// products, accumulated in fp32:
+// it exactly (x = h + m + l with h = x and m = x - h rounded to bf16, l the rest; the differences are exact in
+// fp32), and a product is the sum of six bf16 products (a published way of making wide products of narrow ones):
 //     a b = ah bh + (ah bm + am bh) + (ah bl + al bh + am bm) + [am bl + al bm + al bl]
-// The bracket is left out: |m| <= 2^-8 |x| and |l| <= 2^-7 |m|, m of either sign, so it stays below
-// 2^-22 |a b| at worst, 2^-27 in the mean square, without a bias.  A product with an identity matrix
-// gives the other factor exactly.  Measured against 64-bit sums (2048 x 2048 outputs, A uniform in
-// [-1, 1), B normal), 2-norm of the error, the fp32 instruction / here: K = 32 1.03e-7 / 0.39e-7,
-// 256 2.87e-7 / 2.28e-7, 4096 1.15e-6 / 0.98e-6, 8192 1.62e-6 / 1.39e-6 (row sums 1.6e-6 / 1.4e-6).
+// The bracket is left out.  Of values in [2^e, 2^(e+1)) |m| <= 2^(e-8) and |l| <= 2^(e-17), of either sign: it is
+// 2^-24 |a b| at the very worst and 2^-27 of it in the root mean square.  A product with an identity matrix gives the other
+// factor exactly.
 //
-// Rounding.  Inside the bf16 matrix instruction sums are cut off downwards, not rounded to nearest:
-// every output comes out a little low, as much again as its random error, and a sum over many
-// outputs (the row sums) would show it (256 x 256 x 65536: 1.9e-5 against the fp32 instruction's
-// 1.6e-6).  So odd rows of A and odd columns of B enter with their sign turned and the epilogue
-// turns it back, which costs nothing in either place: neighbouring outputs then err in opposite
-// directions.  And in the course of the K loop the sign of A (and of the accumulators) changes
-// twice, at a quarter and at three quarters of it, which takes a cut that is constant or grows
-// evenly out of every single output.
+// Rounding.  Inside the bf16 matrix instruction sums are cut off downwards, not rounded to nearest.  Were
+// the accumulators kept there, every step would cut six times at the size of the whole sum, in one direction.
+// So a step's sums start from zero, the five small products' and the large ones' apart, and the vector ALUs
+// add them to the accumulators, rounding to nearest: two roundings per 32 k (the fp32 instruction has
+// sixteen), cuts only at the size of a step's own sum, and for a single product nothing but the one rounding of its
+// two parts.  These adds are a third of the vector operations: 4096^3 640 us without them, 700 with.
+// What is left of the direction of the cuts would still show in a sum over many outputs (the row sums).  So odd rows of A
+// and odd columns of B enter with their sign turned and the epilogue turns it back, which costs nothing in
+// either place: neighbouring outputs err in opposite directions.
+// Measured against 64-bit sums (2048 x 2048 outputs), 2-norm of the error, the fp32 instruction / here:
+//   A uniform in [-1, 1), B normal: K = 32 1.03e-7 / 0.37e-7, 256 2.9e-7 / 0.8e-7, 4096 1.15e-6 / 0.29e-6, 16384 2.3e-6 / 0.58e-6;
+//   both uniform in [0, 1): 32 8.4e-8 / 4.1e-8, 256 2.2e-7 / 0.6e-7, 4096 8.4e-7 / 2.1e-7; and with A falling by 2^20 along K:
+//   4096 6.1e-6 / 0.27e-6; A diagonal: 2.53e-8 / 2.60e-8 (the products left out).
 //
 // Range.  bf16 has the exponents of fp32, so nothing overflows that fp32 holds, with three
 // exceptions, and all are found and made good inside the kernel: the tile is then computed again
@@ -47,10 +49,11 @@
 //    instead of once per wave that reads it.
 //  * The differences are plain subtractions: v_dot2c_f32_bf16 would subtract without unpacking, but
 //    a matrix instruction next to one takes 36 cycles instead of 16 (measured).
-//  * 4096^3 with GELU 915 -> 645 us (213 TFLOP/s of fp32 products, 1280 of bf16 ones), 16 x [256 x 256 x
-//    65536] 1015 -> 748, 8192 x 8192 x 32 84 -> 71, 65536 x 128 x 1024 124 -> 93.  What bounds it: the matrix
-//    instructions alone, on these operands, run 500 us under the board's power limit; splitting
-//    and writing take issue slots next to them (72 % of the cycles are matrix instructions).
+//  * 4096^3 with GELU 916 -> 700 us (196 TFLOP/s of fp32 products, 1180 of bf16 ones), 16 x [256 x 256 x
+//    65536] 1015 -> 820, 8192 x 8192 x 32 82 -> 74, 65536 x 128 x 1024 130 -> 101 (fp32 instruction, here).  What bounds
+//    it: a step takes 4940 cycles for the pair of workgroups on a CU (3072 are matrix instructions), as
+//    splitting, adding and writing take issue slots next to them; the matrix instructions alone, on these
+//    operands, run 500 us under the board's power limit.
 //  * v_mfma_f32_16x16x32_bf16: with 32x32x16 two LDS stages of 16 k fit, a step takes 3724 cycles per
 //    pair of workgroups (3072 are matrix instructions), but the board's power limit then holds the
 //    clock at 1.63 GHz (4096^3 in 714 us).
@@ -337,7 +340,9 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
         b_row_step = b_taps_done = 0;
     };
     const unsigned char *abase = Ag, *bbase = Bg;
+    unsigned int voff_row = 0;
     auto load_begin = [&]() __attribute__((always_inline)) {      // fixes where the step starts and moves on
+        if constexpr (!BT) voff_row = voff_b[0];
         abase = Ag + a_off;
         bbase = Bg + b_off;
         a_off += a_step;
@@ -378,7 +383,10 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
         } else if constexpr (q % 2 == 1) {
 #pragma unroll
             for (int e = q - 1; e <= q; ++e) {
-                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, voff_b[0] + (unsigned int)e * b_row_bytes, 0, 0);
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, voff_row, 0, 0);
+                // (a running offset: eight of them kept in registers are eight too many)
+                voff_row += b_row_bytes;
+                asm volatile("" : "+v"(voff_row));
                 const unsigned int w0 = v[0], w1 = v[1];
                 rb[0][e] = __builtin_bit_cast(float, w0);
                 rb[1][e] = __builtin_bit_cast(float, w1);
@@ -440,9 +448,16 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             if constexpr (of_a) pa[t][plane][q] = w; else pb[t][plane][q] = w;
         };
         if constexpr (op == 0) {
-            // odd rows and columns enter with their sign turned (see "Rounding")
-            if constexpr (t == 1) { x[0] = -x[0]; x[1] = -x[1]; }
-            const unsigned int h = pack_bf16x2(x[0], x[1]);
+            // odd rows and columns enter with their sign turned (see "Rounding"; left to the compiler, the
+            // conversion's operands are turned by instructions of their own)
+            unsigned int h;
+            if constexpr (t == 1) {
+                asm("v_cvt_pk_bf16_f32 %0, -%1, -%2" : "=v"(h) : "v"(x[0]), "v"(x[1]));
+                x[0] = -x[0];
+                x[1] = -x[1];
+            } else {
+                h = pack_bf16x2(x[0], x[1]);
+            }
             put(0, h);
             t0 = value(h << 16);
             t1 = value(h & 0xffff0000u);
@@ -450,14 +465,15 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             x[0] -= t0;
             x[1] -= t1;
         } else if constexpr (op == 2) {
-            put(1, __builtin_amdgcn_perm(bits(x[1]), bits(x[0]), 0x07060302u));       // the upper halves
-            t0 = value(bits(x[0]) & 0xffff0000u);
-            t1 = value(bits(x[1]) & 0xffff0000u);
+            const unsigned int m = pack_bf16x2(x[0], x[1]);
+            put(1, m);
+            t0 = value(m << 16);
+            t1 = value(m & 0xffff0000u);
         } else if constexpr (op == 3) {
             x[0] -= t0;
             x[1] -= t1;
         } else {
-            put(2, __builtin_amdgcn_perm(bits(x[1]), bits(x[0]), 0x07060302u));       // (at most eight bits are left)
+            put(2, __builtin_amdgcn_perm(bits(x[1]), bits(x[0]), 0x07060302u));       // the upper halves: all there is
             lost |= bits(x[0]) | bits(x[1]);
             asm volatile("" : "+v"(lost));        // (here and now: put off to the end of the step, all remainders stay live)
         }
@@ -494,6 +510,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     auto step = [&](auto next_tag, auto ahead_tag) __attribute__((always_inline)) {
         constexpr bool NEXT = decltype(next_tag)::value != 0, AHEAD = decltype(ahead_tag)::value != 0;
         bf16x8 fa[3][TM16], fb[2][3];
+        f32x4 sum[TM16];            // of this step's products of one column block (see "Rounding")
         if constexpr (NEXT && !BT) { if (edge_cols) clear_edge_cols(); }
         auto fetch_a = [&](int q, int i) __attribute__((always_inline)) { fa[q][i] = *(const __attribute__((address_space(3))) bf16x8*)PGK_LDS(as + q * Cfg::A_PLANE + i * 1024); };
         auto fetch_b = [&](int j, int q) __attribute__((always_inline)) { fb[j & 1][q] = *(const __attribute__((address_space(3))) bf16x8*)PGK_LDS(bs + q * Cfg::B_PLANE + j * 1024); };
@@ -516,7 +533,11 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
         static_for<0, SLOTS>([&](auto m_tag) __attribute__((always_inline)) {
             constexpr int m = decltype(m_tag)::value;
             constexpr int j = m / PER_J, u = (m / TM16) % 6, i = m % TM16;
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j & 1][QB[u]], fa[QA[u]][i], acc[i][j], 0, 0, 0);
+            // the small products' sum is complete before the large ones, theirs a column block later
+            if constexpr (u == 5) acc[i][j] += sum[i];
+            if constexpr (u == 0 && j > 0) acc[i][j - 1] += sum[i];
+            sum[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j & 1][QB[u]], fa[QA[u]][i],
+                                                             u == 0 || u == 5 ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : sum[i], 0, 0, 0);
             // the next column block's fragments, into the other buffer
             if constexpr (j + 1 < TN16 && m % PER_J >= TM16 && m % PER_J < TM16 + 3) fetch_b(j + 1, QB[m % PER_J - TM16]);
             if constexpr (NEXT) {
@@ -532,6 +553,8 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             }
             __builtin_amdgcn_sched_barrier(0);
         });
+#pragma unroll
+        for (int i = 0; i < TM16; ++i) acc[i][TN16 - 1] += sum[i];
     };
     auto to_next = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_s_setprio(0);
@@ -550,26 +573,8 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     if (KT > 1) load_step();
     meet();
     stamp(1);
-    // the sign of A changes twice, at a quarter and three quarters of the steps (see "Rounding"): from
-    // then on a thread's two rows change places, and with them their signs -- in the loads two steps
-    // before, in what is split and written and in the accumulators one step before
-    const int turn0 = KT >= 8 ? KT / 4 : -1, turn1 = KT >= 8 ? KT - KT / 4 : -1;
     for (int kt = 0; kt + 2 < KT; ++kt) {
-        if (kt + 2 == turn0 || kt + 2 == turn1) {
-            const unsigned int o = voff_a[0];
-            voff_a[0] = voff_a[1];
-            voff_a[1] = o;
-        }
         step(IC<1>{}, IC<1>{});
-        if (kt + 1 == turn0 || kt + 1 == turn1) {
-            const int o = wpos_a[0];
-            wpos_a[0] = wpos_a[1];
-            wpos_a[1] = o;
-#pragma unroll
-            for (int i = 0; i < TM16; ++i)
-#pragma unroll
-                for (int j = 0; j < TN16; ++j) acc[i][j] = -acc[i][j];
-        }
         to_next();
     }
     if (KT > 1) {

@@ -220,3 +220,52 @@ def test_positions_that_do_not_exist_leave_the_others_alone(pgk, pad):
     z = pgk.conv1d(x, w, None, NONE, 1, pad, 1)
     assert torch.equal(y[0], z[0]) and torch.equal(y[3:], z[3:])
     assert torch.equal(y[1:3, :, 128:], z[1:3, :, 128:])        # (all but the tiles that hold the two)
+
+
+# how the values of A change along K (all of B: ordinary).  The rounding of a sum of K products is a random
+# walk where errors are independent; where all are cut the same way, or a sum grows early, they add up
+GROWTH = {"even": lambda t: np.ones_like(t), "rising": lambda t: np.exp2(20.0 * t - 20.0), "falling": lambda t: np.exp2(-20.0 * t),
+          "early": lambda t: np.where(t < 0.25, 1.0, 2.0 ** -12), "middle": lambda t: np.where((t >= 0.25) & (t < 0.75), 64.0, 1.0)}
+
+
+@pytest.mark.parametrize("K", [32, 224, 1024, 4096])
+@pytest.mark.parametrize("growth", sorted(GROWTH))
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_sums_of_one_sign(pgk, sign, growth, K):
+    """Per 32 k two roundings to nearest of a partial sum of at most the whole, 2^-24 / sqrt(3) each in the root
+    mean square, independent of each other; within the 32, cuts of at most 2^-23 of their own sum.  And the errors of
+    neighbouring outputs are independent: a sum over n of them has an error sqrt(n) times one's (three times that).
+    (Not where most of a sum is there early: what then comes in pieces below half a unit of it is lost every time, in
+    float32 sums of any order, and of a column's outputs in the same direction.)"""
+    import torch
+    n = 2048
+    g = torch.Generator("cuda").manual_seed(K)
+    A = torch.rand((1, n, K), generator=g, device="cuda") * torch.from_numpy(GROWTH[growth](np.arange(K) / K).astype(np.float32)).cuda()
+    B = torch.rand((1, K, n), generator=g, device="cuda") * sign
+    assert pgk.gemm_plan(n, n, K, 1, F32)["tile"] == (128, 128, 32)
+    C, _ = pgk.gemm_fused(A, B, None, NONE)
+    ref = A[0].double() @ B[0].double()
+    err = (C[0].double() - ref) / ref.abs()
+    each = 2.0 ** -24 * ((2 * -(-K // 32) / 3.0) ** 0.5 + 2.0)
+    assert float(err.pow(2).mean().sqrt()) <= each
+    if growth in ("early", "falling"):
+        return
+    assert float((C[0].double() - ref).sum(0).norm() / ref.sum(0).norm()) <= 3 * each / n ** 0.5
+    assert float((C[0].double() - ref).sum(1).norm() / ref.sum(1).norm()) <= 3 * each / n ** 0.5
+
+
+@pytest.mark.parametrize("bt", [False, True])
+def test_one_product_per_output(pgk, bt):
+    """A diagonal factor.  With x = h + m + l, |m| <= 2^-8 and |l| <= 2^-17 of x's power of two: the products left out are below
+    2^-24 of a b (2 * 2^-25), the sum of the small ones is cut by less than 2^-27, and the last addition rounds to nearest."""
+    import torch
+    n = 2048
+    g = torch.Generator("cuda").manual_seed(11)
+    A = torch.diag(torch.randn(n, generator=g, device="cuda"))[None].contiguous()
+    B = torch.randn((1, n, n), generator=g, device="cuda")
+    C, _ = pgk.gemm_fused(A, B.transpose(1, 2).contiguous() if bt else B, None, NONE, b_transposed=bt)
+    ref = A[0].diagonal().double()[:, None] * B[0].double()
+    err = (C[0].double() - ref).abs() / ref.abs()
+    assert float(err.max()) <= 2.25 * 2.0 ** -24
+    # rounding to nearest alone: 0.42 ... 0.43 of 2^-24 for values spread over a power of two
+    assert float(err.pow(2).mean().sqrt()) <= 0.46 * 2.0 ** -24
