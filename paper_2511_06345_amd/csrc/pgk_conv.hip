@@ -14,6 +14,7 @@
 // All are streaming copies.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "pgk_device.h"
@@ -85,24 +86,29 @@ __device__ __forceinline__ void repack_weight_chunk(long long c, const T* __rest
 // 16-byte chunk at one (row, j) of all stride * shifts copies, from one run of the input: for STRIDE 1
 // and 2, where that run lies inside the row, with 16-byte loads from any element on; else (STRIDE 0:
 // any other stride, and at the ends of rows) element by element.  bf16 [8, 512, 4096], two shifted copies:
-// 36 us with a thread per chunk of one copy and element loads, 20 so.  Also regroups the weights (padded
+// 36 us with a thread per chunk of one copy and element loads, 20 so.  Large strides make few such threads with much
+// to do each: then `groups` of workgroups share the phases (see launch_conv_phase_copies).  Also regroups the weights (padded
 // to Cin_pad channels) into wr.
 template <typename T, int STRIDE, int SHIFTS>
 __global__ __launch_bounds__(256) void conv_phase_copies_kernel(const T* __restrict__ x, T* __restrict__ xc, unsigned int rows,
                                                                 int Cin, int Cin_pad, int L, int Lq, int pad, int stride_any,
-                                                                unsigned int copy_blocks,
+                                                                unsigned int copy_blocks, int groups,
                                                                 const T* __restrict__ w, T* __restrict__ wr, int Cout, int Kw)
 {
     constexpr int EPC = 16 / (int)sizeof(T);
     // the workgroups after the copies regroup the weights (same launch: a second one costs as much
     // as either piece of work)
-    if (blockIdx.x >= copy_blocks) {
-        repack_weight_chunk<T>((long long)(blockIdx.x - copy_blocks) * 256 + threadIdx.x, w, wr, Cout, Cin, Cin_pad, Kw);
+    if (blockIdx.x >= copy_blocks * groups) {
+        repack_weight_chunk<T>((long long)(blockIdx.x - copy_blocks * groups) * 256 + threadIdx.x, w, wr, Cout, Cin, Cin_pad, Kw);
         return;
     }
     const int stride = STRIDE > 0 ? STRIDE : stride_any;
+    // the phases of this workgroup
+    const int group = STRIDE > 0 ? 0 : (int)(blockIdx.x / copy_blocks), block = STRIDE > 0 ? (int)blockIdx.x : (int)(blockIdx.x % copy_blocks);
+    const int per = STRIDE > 0 ? STRIDE : (stride + groups - 1) / groups;
+    const int p0 = group * per, p1 = p0 + per < stride ? p0 + per : stride;
     const unsigned int cpr = (unsigned int)(Lq / EPC);        // chunks per row
-    const unsigned long long chunk0 = (unsigned long long)blockIdx.x * 256u;
+    const unsigned long long chunk0 = (unsigned long long)block * 256u;
     const unsigned int row0 = (unsigned int)(chunk0 / cpr), in0 = (unsigned int)(chunk0 - (unsigned long long)row0 * cpr) + threadIdx.x;
     const unsigned int row = row0 + in0 / cpr;                // b * Cin_pad + ci
     if (row >= rows) return;
@@ -139,7 +145,7 @@ __global__ __launch_bounds__(256) void conv_phase_copies_kernel(const T* __restr
             return;
         }
     }
-    for (int p = 0; p < stride; ++p)
+    for (int p = p0; p < p1; ++p)
 #pragma unroll
         for (int h = 0; h < SHIFTS; ++h) {
             T v[EPC];
@@ -228,11 +234,25 @@ hipError_t launch_conv_phase_copies(const void* x, void* xc, long long B, int Ci
     const long long rows = B * (long long)Cin_pad, chunks = rows * (Lq / epc);
     const long long copy_blocks = (chunks + 255) / 256;
     const long long repack_chunks = (long long)Cout * Kw * (Cin_pad / epc);
-    const long long blocks = copy_blocks + (repack_chunks + 255) / 256;
+    // Phases of one position lie side by side, so a thread that makes all of them reads its lines once -- if its
+    // wave's (stride KiB) survive in the caches until the last phase and there are enough such threads.  us per call,
+    // one group per phase / all phases in a thread:
+    //   up to 32: [8, 64, 16000] * [128, 64, 32] stride 16 fp32 118 / 89 (500 workgroups), bf16 85 / 72 (250), batch 1 bf16
+    //     33 / 56 (31), fp32 47 / 50 and 44 with four groups (62): groups until every CU has a workgroup, or two up to a stride of
+    //     8, where less is shared ([1, 512, 1000] stride 3 bf16 36.4 / 38.2);
+    //   up to 64: [16, 64, 16000] stride 48 fp32 336 / 211 (333), [1, 128, 64000] stride 64 bf16 184 / 114 (62), [1, 64, 16000] stride
+    //     48 fp32 48 / 75 (20); anything between one group and all of them is slower than the better one;
+    //   above: [16, 64, 19000] stride 65 bf16 125 / 257 (146), [1, 64, 48000] stride 160 fp32 62 / 151 (18), bf16 39 / 203 (9); the other
+    //     way round in bf16 with [8, 64, 48000] stride 160 (375 / 298).
+    const long long groups = stride <= 2    ? 1
+                             : stride <= 32 ? std::max<long long>(1, std::min<long long>(stride, (stride <= 8 ? 512 : 256) / copy_blocks))
+                             : stride <= 64 ? (copy_blocks >= 48 ? 1 : stride)
+                                            : stride;
+    const long long blocks = copy_blocks * groups + (repack_chunks + 255) / 256;
     if (rows > 0xffffffffLL || blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
 #define PGK_COPIES(T, ST, SH)                                                                                            \
     hipLaunchKernelGGL((conv_phase_copies_kernel<T, ST, SH>), dim3((unsigned int)blocks), dim3(256), 0, s, (const T*)x, (T*)xc, \
-                       (unsigned int)rows, Cin, Cin_pad, L, Lq, pad, stride, (unsigned int)copy_blocks, (const T*)w, (T*)wr, Cout, Kw)
+                       (unsigned int)rows, Cin, Cin_pad, L, Lq, pad, stride, (unsigned int)copy_blocks, (int)groups, (const T*)w, (T*)wr, Cout, Kw)
     if (dtype == DT_BF16) {
         if (shifts == 2) { if (stride == 1) PGK_COPIES(unsigned short, 1, 2); else if (stride == 2) PGK_COPIES(unsigned short, 2, 2); else PGK_COPIES(unsigned short, 0, 2); }
         else { if (stride == 1) PGK_COPIES(unsigned short, 1, 1); else if (stride == 2) PGK_COPIES(unsigned short, 2, 1); else PGK_COPIES(unsigned short, 0, 1); }
