@@ -205,17 +205,17 @@ __global__ __launch_bounds__(256) void reduce_max_rows_kernel(const void* __rest
 // elements that do not all start on 16-byte boundaries are read in 16-byte chunks all the same, from
 // any element on (fp32 [215, 6701, 135]: 752 us with one element per load, 139 so); the last lane's chunk
 // ends with the row (and overlaps the one before: the outputs
-// they share are written twice, with the same values).
-template <bool BF16, bool UNALIGNED>
+// they share are written twice, with the same values).  VEC == 1: one element per load, for the unaligned
+// problems that plan_reduce_max gives to it.
+template <bool BF16, int VEC, bool UNALIGNED>
 __global__ __launch_bounds__(256) void reduce_max_cols_kernel(const void* __restrict__ X, void* __restrict__ out,
                                                               int* __restrict__ idx, float* __restrict__ pv,
                                                               int* __restrict__ pi, long long outer, int red,
                                                               long long inner, int tiles_i, int segs, int r_per_seg)
 {
-    constexpr int VEC = Elem<BF16>::VEC;
     // loads in flight per lane: four for fp32; two for bf16, whose eight slots per load keep the
     // vector ALU busier (measured on [32, 4096, 4096] bf16: 6000 GB/s with two, 5700 with four, 5350 with eight)
-    constexpr int UNROLL = BF16 ? 2 : 4;
+    constexpr int UNROLL = BF16 && VEC > 1 ? 2 : 4;
     __shared__ float sv[3][64 * VEC];
     __shared__ int si[3][64 * VEC];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -240,20 +240,29 @@ __global__ __launch_bounds__(256) void reduce_max_cols_kernel(const void* __rest
         // the wave's first element starts the scan (so the loops need no "nothing seen yet" test)
         const unsigned char* src = (const unsigned char*)X + base * Elem<BF16>::BYTES;
         const size_t rstride = (size_t)inner * Elem<BF16>::BYTES;
+        using loaded = typename std::conditional<VEC == 1, float, u32x4>::type;
+        auto load = [&](int at) -> loaded {
+            if constexpr (VEC == 1) return load_one<BF16>(X, base + (size_t)at * (size_t)inner);
+            else return load_chunk<BF16, UNALIGNED>(src + (size_t)at * rstride);
+        };
+        auto values = [](const loaded& w, float (&x)[VEC]) {
+            if constexpr (VEC == 1) x[0] = w;
+            else unpack<BF16>(w, x);
+        };
         if (r < r1) {
-            unpack<BF16>(load_chunk<BF16, UNALIGNED>(src + (size_t)r * rstride), bv);
+            values(load(r), bv);
 #pragma unroll
             for (int e = 0; e < VEC; ++e) bp[e] = r;
             r += 4;
         }
         for (; r + (UNROLL - 1) * 4 < r1; r += UNROLL * 4) {
-            u32x4 w[UNROLL];
+            loaded w[UNROLL];
 #pragma unroll
-            for (int q = 0; q < UNROLL; ++q) w[q] = load_chunk<BF16, UNALIGNED>(src + (size_t)(r + 4 * q) * rstride);
+            for (int q = 0; q < UNROLL; ++q) w[q] = load(r + 4 * q);
 #pragma unroll
             for (int q = 0; q < UNROLL; ++q) {
                 float x[VEC];
-                unpack<BF16>(w[q], x);
+                values(w[q], x);
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
                     if (replaces(x[e], bv[e])) { bv[e] = x[e]; bp[e] = r + 4 * q; }
@@ -261,7 +270,7 @@ __global__ __launch_bounds__(256) void reduce_max_cols_kernel(const void* __rest
         }
         for (; r < r1; r += 4) {
             float x[VEC];
-            unpack<BF16>(load_chunk<BF16, UNALIGNED>(src + (size_t)r * rstride), x);
+            values(load(r), x);
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
                 if (replaces(x[e], bv[e])) { bv[e] = x[e]; bp[e] = r; }
@@ -590,16 +599,27 @@ ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int 
         pl.blocks = (outer * pl.segs + 3) / 4;
     } else {
         pl.unaligned = !(x_aligned && inner % vec16 == 0);
-        pl.vec = vec16;
+        // One element per load for unaligned rows while the problem is small: the chip is not full then, and
+        // 64 VEC positions per workgroup leave fewer and longer ones (fp32 [53, 67, 845] 10.1 us, in chunks 15.3;
+        // bf16 [580, 101, 83] 10.0 and 15.4); bf16 also with few positions per row, where most lanes have
+        // no chunk ([484, 279, 102] 19.3 and 22.9).  Of 20000 unaligned shapes 0.8 % stay more than
+        // 5 % behind one element per load everywhere, without these lines 5 %; the mean is 1.25 (bf16) and 1.38
+        // (fp32) times as fast as with one element everywhere.
+        const long double elements = (long double)outer * red * inner;
+        const bool single = pl.unaligned && (elements < (dtype == DT_BF16 ? 1.0e7L : 4.0e6L) ||
+                                             (dtype == DT_BF16 && inner <= 128 && red < 512));
+        pl.vec = single ? 1 : vec16;
         pl.group = 256;
         pl.tiles_i = (int)((inner + 64 * pl.vec - 1) / (64 * pl.vec));
         const long long wg0 = outer * pl.tiles_i;
         pl.segs = 1;
-        // (unaligned rows: from one workgroup per CU on the second pass costs more than the segments
-        // give, fp32 [42, 72, 1901], 336 workgroups: 13.7 us in one pass, 18.5 in two)
-        if (wg0 < (pl.unaligned ? 256 : target_workgroups(dtype))) {
+        if (wg0 < target_workgroups(dtype)) {
             const long long want = (target_workgroups(dtype) + wg0 - 1) / wg0;
-            const long long most = red / 32 > 0 ? red / 32 : 1;                 // eight r per wave at least
+            // eight r per wave at least; unaligned chunks sixteen, fp32 ones (less work each) thirty-two, else the second pass
+            // costs more than the segments give (fp32 [42, 72, 1901]: 13.7 us in one pass, 18.5 in two; [11, 135, 2959] 10.5
+            // and 15.8; bf16 [59, 254, 438], 26.9 and 16.0)
+            const long long least = !pl.unaligned || single ? 32 : dtype == DT_BF16 ? 64 : 128;
+            const long long most = red / least > 0 ? red / least : 1;
             pl.segs = (int)(want < most ? want : most);
         }
         pl.per_seg = (int)((red + pl.segs - 1) / pl.segs);
@@ -642,10 +662,10 @@ hipError_t launch_reduce_max(const ReducePlan& pl, const void* X, void* out, int
         }
 #undef PGK_ROWS
     } else {
-#define PGK_COLS(BF, UN) \
-    hipLaunchKernelGGL((reduce_max_cols_kernel<BF, UN>), grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, inner, pl.tiles_i, pl.segs, pl.per_seg)
-        if (bf) { if (pl.unaligned) PGK_COLS(true, true); else PGK_COLS(true, false); }
-        else { if (pl.unaligned) PGK_COLS(false, true); else PGK_COLS(false, false); }
+#define PGK_COLS(BF, VEC, UN) \
+    hipLaunchKernelGGL((reduce_max_cols_kernel<BF, VEC, UN>), grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, inner, pl.tiles_i, pl.segs, pl.per_seg)
+        if (bf) { if (pl.vec == 1) PGK_COLS(true, 1, true); else if (pl.unaligned) PGK_COLS(true, 8, true); else PGK_COLS(true, 8, false); }
+        else { if (pl.vec == 1) PGK_COLS(false, 1, true); else if (pl.unaligned) PGK_COLS(false, 4, true); else PGK_COLS(false, 4, false); }
 #undef PGK_COLS
     }
     hipError_t e = hipGetLastError();

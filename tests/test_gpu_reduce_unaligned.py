@@ -67,3 +67,20 @@ def test_unaligned_rows_special_values(pgk, oracle, dtype, shape):
     x = gen.f32_to_bf16_bits(x) if dtype == BF16 else x
     for start in (0, 1, 3):
         check(pgk, oracle, x, start, dtype)
+
+
+# unaligned rows of a strided reduction that are read in chunks because there is enough to do: segments of the
+# reduced range, one pass, a last lane whose chunk overlaps its neighbour's, lanes without a chunk, several tiles
+BIG_COLS = {F32: [(3, 5000, 321), (700, 63, 133), (300, 130, 259), (2, 9001, 241)],
+            BF16: [(3, 7000, 517), (600, 150, 129), (1100, 75, 131), (40, 250, 1025)]}
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("which", range(4))
+def test_unaligned_columns_in_chunks(pgk, oracle, dtype, which):
+    shape = BIG_COLS[dtype][which]
+    n = shape[0] * shape[1] * shape[2]
+    x = gen.uniform(gen.tensor_seed(98, 3, n), n, -1.0, 1.0)
+    x = (gen.f32_to_bf16_bits(x) if dtype == BF16 else x).reshape(shape)
+    for start in (0, 1):
+        check(pgk, oracle, x, start, dtype)
