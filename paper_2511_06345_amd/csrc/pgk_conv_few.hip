@@ -26,7 +26,7 @@ namespace pgk {
 
 namespace {
 
-constexpr int kTilePos = 128;                   // output positions per workgroup
+constexpr int kTilePos = 128;                   // output positions of a tile
 constexpr int kMaxLdsFloats = 20 * 1024;        // 80 KiB: at least two workgroups per CU
 
 struct FewArgs {
@@ -226,15 +226,22 @@ long long lds_floats(long long Cin, long long Kw, long long stride, long long di
 }  // namespace
 
 // Sums of up to 24 products, or up to 48 for at least 128 channels (which fill the blocks), the input of a
-// tile and the weights within 80 KiB of LDS, and at least 256 pairs of a tile and 128 channels (1024 for the
-// longer sums; bf16 [2, 4, 87346] * [128, 4, 7], 274 pairs: 18 us there, 21 here); with less to do the bounds-checked kernel's smaller tiles spread further ([4, 12, 9000] *
-// [128, 12, 7], stride 5: 19 us there, 29 here), and longer sums are its strength on few channels
-// ([4, 15, 20000] * [64, 15, 5]: 20 against 28).  Rows of fewer than 64 outputs would leave half a tile empty.
+// tile and the weights within 80 KiB of LDS, and enough pairs of a tile and 128 channels: 256, for more than 8
+// products 384 (bf16 [29, 1, 1260] * [281, 1, 16], stride 4, 261 pairs: 15.5 us here, 11.3 on the bounds-checked kernel), for the
+// longer sums 1024 (bf16 [2, 4, 87346] * [128, 4, 7], 274 pairs: 18 us there, 21 here); with less to do the bounds-checked
+// kernel's smaller tiles spread further ([4, 12, 9000] * [128, 12, 7], stride 5: 19 us there, 29 here), and longer sums are its
+// strength on few channels ([4, 15, 20000] * [64, 15, 5]: 20 against 28).  Cin * stride input values are copied into
+// LDS per position, element by element, and have to be shared by enough channels: not more than 32 of them, nor than
+// half the channels plus 4 (bf16 [5, 12, 67038] * [178, 12, 3], stride 5: 69 us here, 42 there; [24, 12, 106417] * [18, 12, 1], stride
+// 5: 110 and 43).  Rows of fewer than 64 outputs would leave half a tile empty.
+// Of 22500 shapes within the other limits the lines at 384 pairs, 32 values and half the channels take out 2760
+// (1300 slower here, 970 faster); 1.4 % of the rest are more than 5 % slower here than there, 6 % without these lines.
 bool conv_few_channels_fits(long long B, long long Cin, long long Cout, long long Kw, long long stride, long long dil, long long Lout)
 {
     if (Lout < 64 || Cin > 48 || Kw > 48 || stride > 4096 || dil > 4096) return false;
     const long long K = Cin * Kw, units = (Lout + kTilePos - 1) / kTilePos * ((Cout + 127) / 128);
-    if (K > 48 || (K > 24 && Cout < 128) || (long double)units * B < (K > 24 ? 1024.0L : 256.0L)) return false;
+    if (K > 48 || (K > 24 && Cout < 128) || (long double)units * B < (K > 24 ? 1024.0L : K > 8 ? 384.0L : 256.0L)) return false;
+    if (Cin * stride > 32 || Cin * stride > Cout / 2 + 4) return false;
     if (Lout * 4 * 128 >= (1LL << 32)) return false;          // a block's 32-bit offsets
     return lds_floats(Cin, Kw, stride, dil, 1, 128) <= kMaxLdsFloats;
 }

@@ -7,20 +7,42 @@ import pytest
 from paper_2511_06345_amd import inputs as gen
 from util import TOL, c_to_numpy, rel_err, to_device
 
-pytestmark = pytest.mark.gpu
+gpu = pytest.mark.gpu
 F32, BF16 = gen.F32, gen.BF16
 
-# B, Cin, L, Cout, Kw, stride, pad, dilation: at least 256 pairs of a tile and 128 channels each (1024
-# for sums of more than 24 products)
+# B, Cin, L, Cout, Kw, stride, pad, dilation
 CASES = [(128, 1, 256, 16, 3, 1, 1, 1),          # two whole tiles, rows aligned
-         (128, 1, 255, 33, 10, 1, 0, 1),         # an odd row length: windows moved, both ends cut
-         (90, 3, 385, 70, 7, 1, 3, 1),           # three tiles and one position, K odd (21)
+         (192, 1, 255, 33, 10, 1, 0, 1),         # an odd row length: windows moved, both ends cut
+         (96, 3, 385, 70, 7, 1, 3, 1),           # three tiles and one position, K odd (21)
          (128, 2, 300, 5, 1, 1, 0, 1),           # one tap, fewer channels than waves
          (64, 1, 2600, 130, 10, 5, 2, 1),        # strided, two blocks of channels
          (40, 15, 1700, 140, 3, 1, 2, 2),        # 45 products per sum, the kernel's longest
-         (43, 4, 768, 128, 6, 2, 5, 3),          # 24 products
-         (70, 1, 1027, 512, 10, 1, 1, 1),        # every sixteenth channel (fp32, odd rows)
-         (70, 1, 1027, 300, 16, 1, 1, 1)]        # ... with blocks only partly filled
+         (128, 4, 768, 128, 6, 2, 5, 3),         # 24 products
+         (24, 2, 1300, 32, 3, 1, 4096, 4096),    # a dilation that takes more than 64 KiB of LDS
+         (74, 1, 1027, 512, 10, 1, 1, 1),        # every sixteenth channel (fp32, odd rows)
+         (74, 1, 1027, 300, 16, 1, 1, 1)]        # ... with blocks only partly filled
+SIXTEENTH = CASES[-2:]
+
+
+def lout_of(case):
+    B, Cin, L, Cout, Kw, stride, pad, dil = case
+    return (L + 2 * pad - dil * (Kw - 1) - 1) // stride + 1
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_cases_are_within_the_rule(case):
+    """What the kernel asks for, restated: a case outside of it would run on the bounds-checked kernel."""
+    B, Cin, L, Cout, Kw, stride, pad, dil = case
+    K, Lout = Cin * Kw, lout_of(case)
+    pairs = -(-Lout // 128) * -(-Cout // 128) * B
+    assert Lout >= 64 and K <= 48 and (K <= 24 or Cout >= 128)
+    assert pairs >= (1024 if K > 24 else 384 if K > 8 else 256)
+    assert Cin * stride <= min(32, Cout // 2 + 4)
+    K2 = (K + 1) // 2 * 2
+    lds = Cin * ((128 + 14) * stride + (Kw - 1) * dil + 1) + K2 * 132 + 128 + K2
+    assert lds <= 20 * 1024 and (lds * 4 > 65536) == (dil == 4096)
+    sixteenth = Lout % 16 != 0 and Cout >= 256 and K2 <= 16 and Lout // 128 * -(-Cout // 512) * B >= 512
+    assert sixteenth == (case in SIXTEENTH)
 
 
 @pytest.fixture(scope="module")
@@ -32,6 +54,7 @@ def pgk():
     return binding
 
 
+@gpu
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("case", CASES)
 def test_few_channels_match_the_oracle_and_stay_in_bounds(pgk, oracle, dtype, case):
@@ -57,6 +80,7 @@ def test_few_channels_match_the_oracle_and_stay_in_bounds(pgk, oracle, dtype, ca
             assert bool((flat[:16 + start] == 7.0).all()) and bool((flat[16 + start + n:] == 7.0).all()), "wrote outside y"
 
 
+@gpu
 def test_few_channels_integers_are_exact_and_special_values_stay_in_place(pgk, oracle):
     """Small integers: every sum exact.  An infinity or NaN reaches the outputs whose window holds it
     and no other (the k that fills up a pair has a zero weight and must not meet it)."""
