@@ -31,6 +31,10 @@ WS_ROWSUM, WS_B_TRANSPOSED, WS_UNALIGNED = 1, 2, 4
 
 _lib = None
 
+# the handle of torch.cuda.current_stream() without the Python object around it: 0.3 us, not 2.8, of a small
+# call that takes 20 us of which the host bounds all.  Not a public name: None where torch does not have it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
 
 class PgkError(RuntimeError):
     def __init__(self, status: int, where: str):
@@ -224,9 +228,9 @@ class _on_stream:
 def _stream_ptr(stream) -> int:
     if stream is not None:
         return int(stream.cuda_stream)
-    # the handle of torch.cuda.current_stream() without the Python object around it: 0.3 us, not 2.8, of a
-    # small call that takes 20 us of which the host bounds all
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ws_flags(A, B, rowsum: bool, b_transposed: bool) -> int:

@@ -450,3 +450,13 @@ def test_plan_is_consistent_on_random_shapes(lib):
         else:
             assert p["tile"] == (64, 64, 16) and p["slices"] == 1, what
             assert M * N * K < 262144 or (M < 16 and N < 16 and K < 1024), what
+
+
+def test_the_current_stream_is_found_without_torchs_private_accessor(monkeypatch):
+    import types
+
+    import torch
+    from paper_2511_06345_amd import binding
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4711))
+    assert binding._stream_ptr(None) == 4711
