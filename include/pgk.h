@@ -257,8 +257,8 @@ int pgk_splitk_auto_splits(int64_t M, int64_t N, int64_t K, int64_t batch,
  *     idx  [outer][inner]       int32 device pointer, or NULL = positions not wanted
  *
  * outer, red, inner > 0; red at most 2^31 - 1024, outer * inner below 2^62, else
- * PGK_ERR_UNSUPPORTED.  Any shape and alignment is accepted (rows that do not start
- * on 16-byte boundaries are read in aligned 16-byte chunks too).  When there
+ * PGK_ERR_UNSUPPORTED.  Any shape and alignment is accepted (16-byte loads are used in all but
+ * small problems, also where rows do not start on 16-byte boundaries).  When there
  * are few outputs and a long reduced dimension the range is reduced in segments and a
  * second small kernel combines them; the segment results (value, position) live in
  * `workspace`: pgk_reduce_max_workspace_bytes(...) bytes of device memory on a 4-byte

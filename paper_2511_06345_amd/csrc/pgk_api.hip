@@ -148,6 +148,8 @@ bool large_tile_mostly_empty(int64_t M, int64_t N, int dtype)
 // workgroups on its busiest CU takes the share tail[j - 1] of a full one.  Fitted to GEMMs of
 // 2560^2 ... 8192^2 outputs with K = 1024 ... 4096 (e.g. bf16 4096^2 x 4096: 256 large tiles 104 us,
 // 1024 small ones 122 us, 512 half tiles 114 us; fp32: 1024 large 913 us, 4096 small 965 us).
+// The fp32 large tile of these figures, and of the ones beside auto_split and large_tile_mostly_empty, used the fp32
+// instruction; in three bf16 terms it takes 0.77 of them, which only auto_tile_kind counts so far.
 struct TileCost { int per_cu; double fixed, per_k; double tail[4]; };
 
 TileCost tile_cost(int dtype, int kind)

@@ -14,7 +14,7 @@ namespace pgk {
 // load(0) + load(1) + ... + load(n - 1), added in that order, up to eight loads in flight.  These passes
 // are bound by the latency of their loads, and a loop of load and add pays it once per summand.  Whole call
 // in a graph, before and after: 256 x 256 x 256 float32 7.5 and 6.6 us, 1 x 4096 x 4096 bf16 14.1 and
-// 13.3, 32 x 8192 x 8192 bf16 with row sums 34.1 and 29.3, 8 x 11008 x 4096 bf16 19.5 and 19.0.  The
+// 13.3, 32 x 8192 x 8192 bf16 with row sums 34.1 and 29.3 (8 x 11008 x 4096 bf16 the same within the noise).  The
 // batches are of fixed sizes: one of eight guarded by s < n leaves a branch around each load, and two to
 // four slices were slower for it (768 x 768 x 3072 bf16 21.0 and 23.1).
 template <int BATCH, typename V, typename F>

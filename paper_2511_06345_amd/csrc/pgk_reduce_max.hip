@@ -4,8 +4,10 @@
 // formula, so this is the plain definition).  IEEE comparison: +0 and -0 tie and the
 // earlier one is returned; a NaN in the slice gives that NaN and the first NaN's position.
 //
-// The kernels are streaming kernels bound by HBM bandwidth: every element is read once
-// with 16-byte loads, several loads in flight per lane.
+// The kernels are streaming kernels bound by HBM bandwidth: every element is read once, with 16-byte loads
+// and several of them in flight per lane.  Where rows do not start on 16-byte boundaries, long ones are
+// read in aligned chunks with the elements at their ends apart, shorter and strided ones in chunks from any element on,
+// and small problems one element per load (plan_reduce_max).
 //   * inner == 1 (the reduced dimension is contiguous): a wave (short rows) or a
 //     256-thread workgroup (long rows) sweeps one row in 16-byte chunks; lanes are
 //     combined with cross-lane shuffles, waves through LDS.
