@@ -33,14 +33,14 @@ def call(pgk, A, B, bt, splits=None):
 
 
 def bound(K):
-    """Largest error over sum |a||b|: a bf16 instruction cuts its accumulator at most twice per 32 k
-    (2^-23 of a partial sum each), there are six per 32 k, and the products left out are below
-    2^-22; the splitting itself is exact."""
+    """Largest error over sum |a||b| if every bf16 instruction (six per 32 k) cut the whole partial sum twice, by 2^-23
+    each, and the products left out came to 2^-22.  The kernel rounds a whole partial sum twice per 32 k, to nearest,
+    and leaves out 2^-24: this is what no result may miss, the tests of single kinds of data ask for more."""
     return (12 * -(-K // 32) + 2) * 2.0 ** -23
 
 
-# (128 x 128 tiles: enough batch entries for 192 workgroups).  K: one step, its tail, two, three, the
-# last count without turns of the sign (7), the first with them (8, 9), more
+# (128 x 128 tiles: enough batch entries for 192 workgroups).  K: one step, its tail, two and three steps (the
+# loop has none, then one in its middle), more, and their tails
 SHAPES = [(128, 128, 32, 192), (128, 128, 5, 192), (130, 140, 64, 60), (129, 131, 70, 60), (200, 136, 96, 60), (128, 256, 224, 100),
           (256, 128, 256, 100), (250, 131, 259, 60), (128, 129, 288, 100), (131, 128, 516, 100)]
 

@@ -28,8 +28,8 @@ def test_values(shape, tile, shift, bt):
     A = torch.randn(batch * M * K + shift, generator=g, device="cuda")[shift:].view(batch, M, K)
     B = torch.randn(batch, *((N, K) if bt else (K, N)), generator=g, device="cuda")
     C, rs = pgk.gemm_fused(A, B, None, 0, b_transposed=bt)
-    # a sum of K products in float32: at most K roundings of 2^-24 (the fp32 instruction), or twelve
-    # cuts of 2^-23 per 32 k (the bf16 one), of sum |a||b|; the row sums add N more roundings
+    # a sum of K products in float32: at most K roundings of 2^-24 of sum |a||b| (the fp32 instruction; in bf16
+    # terms two per 32 k and a few at the size of 32 products); the row sums add N more roundings
     per_sum = (K + 2) * 2.0 ** -24
     for b in range(batch):
         a, w = A[b].double(), (B[b].t() if bt else B[b]).contiguous().double()
