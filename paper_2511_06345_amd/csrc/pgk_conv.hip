@@ -238,16 +238,20 @@ hipError_t launch_conv_phase_copies(const void* x, void* xc, long long B, int Ci
     // wave's (stride KiB) survive in the caches until the last phase and there are enough such threads.  us per call,
     // one group per phase / all phases in a thread:
     //   up to 32: [8, 64, 16000] * [128, 64, 32] stride 16 fp32 118 / 89 (500 workgroups), bf16 85 / 72 (250), batch 1 bf16
-    //     33 / 56 (31), fp32 47 / 50 and 44 with four groups (62): groups until every CU has a workgroup, or two up to a stride of
-    //     8, where less is shared ([1, 512, 1000] stride 3 bf16 36.4 / 38.2);
+    //     33 / 56 (31), fp32 47 / 50 and 44 with four groups (62): groups until every CU has a workgroup;
+    //   up to 8 less is shared, and what counts is that loads are in flight everywhere: groups until there are 2048 or 4096
+    //     workgroups, in bf16 up to 4 one per phase.  11800 shapes of strides 3 to 8, share that is more than 5 % slower than with one per phase
+    //     and mean gain over it: fp32 with 512 workgroups as the aim 3.9 % and 1.09, with 4096 1.5 % and 1.09, bf16 14.3 % and 1.005, and
+    //     3.7 % and 1.02 (bf16 [9, 35, 4921] stride 4 17.9 us, with all phases in a thread 25.5);
     //   up to 64: [16, 64, 16000] stride 48 fp32 336 / 211 (333), [1, 128, 64000] stride 64 bf16 184 / 114 (62), [1, 64, 16000] stride
     //     48 fp32 48 / 75 (20); anything between one group and all of them is slower than the better one;
     //   above: [16, 64, 19000] stride 65 bf16 125 / 257 (146), [1, 64, 48000] stride 160 fp32 62 / 151 (18), bf16 39 / 203 (9); the other
     //     way round in bf16 with [8, 64, 48000] stride 160 (375 / 298).
-    const long long groups = stride <= 2    ? 1
-                             : stride <= 32 ? std::max<long long>(1, std::min<long long>(stride, (stride <= 8 ? 512 : 256) / copy_blocks))
-                             : stride <= 64 ? (copy_blocks >= 48 ? 1 : stride)
-                                            : stride;
+    const long long enough = stride > 8 ? 256 : dtype == DT_BF16 || stride <= 4 ? 4096 : 2048;
+    const long long groups = stride <= 2                                          ? 1
+                             : (dtype == DT_BF16 && stride <= 4) || stride > 64 ? stride
+                             : stride <= 32 ? std::max<long long>(1, std::min<long long>(stride, enough / copy_blocks))
+                                            : (copy_blocks >= 48 ? 1 : stride);
     const long long blocks = copy_blocks * groups + (repack_chunks + 255) / 256;
     if (rows > 0xffffffffLL || blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
 #define PGK_COPIES(T, ST, SH)                                                                                            \
