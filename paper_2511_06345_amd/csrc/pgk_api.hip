@@ -57,34 +57,6 @@ size_t round_up256(size_t v) { return (v + 255) / 256 * 256; }
 int64_t chunk_elems(int dtype) { return dtype == PGK_DTYPE_BF16 ? 8 : 4; }
 int64_t round_up64(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
-// What the matrix-core kernels take as it is: operand rows that start on 4-byte boundaries (K
-// elements for A and a transposed B; the row length ldb of a plain B, which is N unless the
-// caller has padded it).  M, N and K need not be tile multiples, and the output rows may have any
-// length.  An
-// output below 16 x 16 is left to the bounds-checked kernel, which wastes less, unless K is
-// long (then the matrix-core route splits the K range over the chip).
-bool mfma_shape_ok(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans = false, int64_t ldb = 0)
-{
-    const pgk::TileShape t = pgk::mfma_tile_shape(dtype, false);
-    const int64_t es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
-    if (!ldb) ldb = b_trans ? K : N;
-    if ((K * es) % 4 || (ldb * es) % 4) return false;
-    if (M < 16 && N < 16 && K < 1024) return false;
-    // per-lane 32-bit byte offsets inside one tile
-    if ((int64_t)t.bm * K * es >= (1LL << 32)) return false;
-    if ((b_trans ? (int64_t)t.bn * K : (int64_t)t.bk * ldb) * es >= (1LL << 32)) return false;
-    return true;
-}
-
-// Operand rows that would start off 4-byte boundaries (bf16: an odd K, or an odd N for a plain
-// B): the operands are first copied into buffers with rows padded with zeros to whole 16-byte
-// chunks.  Worth it from about 64^3 multiply-adds on.
-bool needs_packing(int64_t N, int64_t K, int dtype, bool b_trans)
-{
-    const int64_t es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
-    return (K * es) % 4 != 0 || (!b_trans && (N * es) % 4 != 0);
-}
-
 // Outputs with at most 32 columns or rows: the skinny tiles (narrow 128 x 32, flat 32 x 128), on
 // which such a product stays bound by the stream of its large operand instead of by matrix work
 // on padding (bf16 16384 x 16 x 16384: 137 us on 128 x 128 tiles).  The narrow tile exists for a
@@ -96,6 +68,61 @@ int skinny_tile_kind(int64_t M, int64_t N)
     if (N <= 32 && M > 32) return pgk::TILE_NARROW;
     if (M <= 32 && N <= 32) return pgk::TILE_FLAT;
     return -1;
+}
+
+// Operand rows that would start off 4-byte boundaries (bf16: an odd K, or an odd N for a plain B), which
+// the direct-to-LDS copies do not take.
+struct OddRows { bool a, b; };
+OddRows odd_rows(int64_t K, int dtype, bool b_trans, int64_t ldb)
+{
+    const int64_t es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
+    return {(K * es) % 4 != 0, ((b_trans ? K : ldb) * es) % 4 != 0};
+}
+
+// Whether such operands are copied through registers (pgk_gemm_mfma_reg.hip) or first into rows padded
+// to whole chunks (pack_dims).  Loads and LDS writes of its own cost the main loop about a fifth of its time
+// on the large tile (one operand odd; 4096 x 4096 x 4096 direct 102 us, A 108, B 107, with rows off the grid 114 and 121),
+// and as much again as the product takes where both are odd, which the large tile has no registers for; a copy costs
+// its two passes over memory and a launch.  So, in microseconds: the share lost of a product at 1100 TFLOP/s
+// against copies at 5.5 TB/s and four per launch.  Copied first / through registers: 512 x 50257 x 768 80 / 62 us,
+// 1024 x 4095 x 1024 27 / 25, 1024 x 2048 x 255 (B transposed) 19 / 12, 4096 x 4095 x 4096 115 / 120, 2048 x 2047 x 2048 31 / 43.
+// Skinny outputs, whose tiles have no such instance, are copied first, and problems of less than 2^25
+// multiply-adds keep to the workspace they have always asked for.
+bool reg_copies(int64_t M, int64_t N, int64_t K, OddRows odd)
+{
+    if (skinny_tile_kind(M, N) >= 0 || (long double)M * N * K < 33554432.0L) return false;
+    const double product = 2.0 * (double)M * (double)N * (double)K / 1.1e9;
+    const double lost = odd.a && odd.b ? 1.2 : odd.a ? 0.13 : 0.2;
+    const double bytes = 4.0 * (double)K * ((odd.a ? (double)M : 0.0) + (odd.b ? (double)N : 0.0));
+    return lost * product < bytes / 5.5e6 + 4.0 * ((odd.a ? 1 : 0) + (odd.b ? 1 : 0));
+}
+
+// What the matrix-core kernels take as it is: operand rows that start on 4-byte boundaries (K
+// elements for A and a transposed B; the row length ldb of a plain B, which is N unless the
+// caller has padded it), bf16 rows on any element where reg_copies allows.  M, N and K need not be tile multiples, and the output rows may have any
+// length.  An
+// output below 16 x 16 is left to the bounds-checked kernel, which wastes less, unless K is
+// long (then the matrix-core route splits the K range over the chip).
+bool mfma_shape_ok(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans = false, int64_t ldb = 0)
+{
+    const pgk::TileShape t = pgk::mfma_tile_shape(dtype, false);
+    const int64_t es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
+    if (!ldb) ldb = b_trans ? K : N;
+    const OddRows odd = odd_rows(K, dtype, b_trans, ldb);
+    if ((odd.a || odd.b) && !reg_copies(M, N, K, odd)) return false;
+    if (M < 16 && N < 16 && K < 1024) return false;
+    // per-lane 32-bit byte offsets inside one tile
+    if ((int64_t)t.bm * K * es >= (1LL << 32)) return false;
+    if ((b_trans ? (int64_t)t.bn * K : (int64_t)t.bk * ldb) * es >= (1LL << 32)) return false;
+    return true;
+}
+
+// Odd rows that no kernel takes as they are: the operands are first copied into buffers with rows
+// padded with zeros to whole 16-byte chunks.  Worth it from about 64^3 multiply-adds on.
+bool needs_packing(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans)
+{
+    const OddRows odd = odd_rows(K, dtype, b_trans, N);
+    return (odd.a || odd.b) && !reg_copies(M, N, K, odd);
 }
 
 // The dimensions the kernels see for a problem that is packed first: K and the row length of B,
@@ -111,7 +138,7 @@ PackDims pack_dims(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans, boo
 {
     const PackDims as_is{false, K, 0, false, b_trans};
     const bool transpose_b = !b_trans && skinny_tile_kind(M, N) == pgk::TILE_NARROW;
-    if (!transpose_b && !misaligned && !needs_packing(N, K, dtype, b_trans)) return as_is;
+    if (!transpose_b && !misaligned && !needs_packing(M, N, K, dtype, b_trans)) return as_is;
     if ((long double)M * N * K < 262144.0L) return as_is;
     const int64_t epc = chunk_elems(dtype), es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
     PackDims d{true, ((K * es) % 4 || misaligned) ? round_up64(K, epc) : K, 0, transpose_b, b_trans || transpose_b};
@@ -372,6 +399,9 @@ Path choose_path(bool aligned, int64_t M, int64_t N, int64_t K, int dtype, int64
     if (!ok) return Path{false, false, pgk::guarded_tile_shape()};
     int kind = kind_forced >= 0 ? kind_forced : auto_tile_kind(M, N, K, dtype, units, b_trans, ldb);
     if (!pgk::mfma_has_tile(dtype, kind, b_trans)) kind = pgk::TILE_SMALL;      // (the narrow tile with a plain B)
+    // (the large tile does not exist with both operands copied through registers)
+    const OddRows odd = odd_rows(K, dtype, b_trans, ldb ? ldb : N);
+    if ((odd.a || odd.b) && !pgk::mfma_reg_has_tile(kind, odd.a, odd.b, b_trans)) kind = pgk::TILE_TALL;
     return Path{true, kind, pgk::mfma_tile_shape(dtype, kind)};
 }
 
@@ -382,9 +412,12 @@ void set_ldb(GemmArgs& a, int64_t ldb)
     a.b_batch_stride = (long long)(a.b_trans ? a.N : a.K) * ldb;
 }
 
-// call when the views are final: the rows of a plain B that are not whole chunks
+// call when the views are final: rows off 4-byte boundaries, rows of a plain B that are not whole chunks
 void mark_ragged_rows(GemmArgs& a, int dtype)
 {
+    const OddRows odd = odd_rows(a.K, dtype, a.b_trans != 0, a.ldb);
+    a.reg_a = odd.a ? 1 : 0;
+    a.reg_b = odd.b ? 1 : 0;
     a.b_tail_bounded = (!a.b_trans && a.ldb % chunk_elems(dtype) != 0) ? 1 : 0;
 }
 
@@ -908,7 +941,9 @@ struct ConvPlan {
     //           offset (k dil div stride) - h, with h = 1 where that offset would be odd in bf16;
     //   else:   a zero-padded copy of the whole input with rows of Lp elements (Lp = 0: the
     //           input as it is -- no padding and aligned rows)
-    bool strips;
+    //           (reg: tile bases off 4-byte boundaries -- bf16 with an odd dilation, padding or row
+    //           length -- are copied through registers)
+    bool strips, reg;
     int n_edges;
     int edge_tn[3];
     int edge_first_col[3];
@@ -949,8 +984,17 @@ ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw
     pl.tile = pgk::mfma_tile_shape(dtype, pl.kind);
     const int64_t bn = pl.tile.bn, halo = (Kw - 1) * dilation;
     const bool shifts_even = dtype == PGK_DTYPE_F32 || dilation % 2 == 0 || Kw == 1;
+    // (bf16: every tile base on a 4-byte boundary)
+    const bool bases_even = shifts_even && (L * es) % 4 == 0 && (pad * es) % 4 == 0;
+    // Through registers the main loop loses a fifth of its time (reg_copies), the alternative is two shifted copies of
+    // the input: even at 3000 products per output position and channel ([8, 512, 4096] x [512, 512, 3] 69 us
+    // with the copies, 63 without).
+    const bool reg = !bases_even && pl.kind != pgk::TILE_FLAT && Cout * Kw <= 3000;
+    // Reading the input in place needs the halo and the padding to be no wider than a tile.
+    const bool strips = ((bases_even && (pl.Lout % epc == 0 || pl.kind != pgk::TILE_FLAT)) || reg) && halo <= bn && pad <= bn &&
+                        (long double)B * Cin * 3 * ((bn + halo) / 256 + 2) < 2.0e9L;
 
-    if (stride == 1 && Cin % t.bk == 0 && shifts_even) {
+    if (stride == 1 && Cin % t.bk == 0 && (shifts_even || strips)) {
         // the input as it is, or one zero-padded copy of it; taps a constant column step apart
         const int64_t K = Cin * Kw;
         const bool needs_copy = pad > 0 || L % epc != 0 || pl.Lout % epc != 0;
@@ -958,18 +1002,17 @@ ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw
         if ((int64_t)t.bm * K * es >= (1LL << 32) || (int64_t)t.bk * Lp * es + dilation * Kw * es >= (1LL << 32)) return pl;
         pl.fast = true;
         pl.w_bytes = round_up((size_t)(Cout * K * es), 256);
-        // Reading the input in place needs every tile base 4-byte aligned (rows and shifts), the
-        // halo and the padding no wider than a tile.
-        pl.strips = pl.Lout % epc == 0 && halo <= bn && pad <= bn && (L * es) % 4 == 0 && (pad * es) % 4 == 0 &&
-                    (long double)B * Cin * 3 * ((bn + halo) / 256 + 2) < 2.0e9L;
+        pl.strips = strips;
+        pl.reg = reg && strips;
         if (pl.strips) {
             const int64_t tiles_n = (pl.Lout + bn - 1) / bn;
             pl.edge_w = (int64_t)round_up((size_t)(bn + halo), (size_t)epc);
             pl.n_edges = 0;
-            if (pad > 0) {
+            // (the last tile column reads whole 16-byte chunks, past the row's end where the output length is none)
+            if (pad > 0 || pl.Lout % epc != 0) {
                 const int64_t r0 = pl.Lout > pad ? (pl.Lout - pad) / bn : 0;     // first tile column reading past the end
                 for (int64_t tn = 0; tn < tiles_n; ++tn)
-                    if (tn == 0 || tn >= r0) {
+                    if ((tn == 0 && pad > 0) || tn >= r0) {
                         pl.edge_tn[pl.n_edges] = (int)tn;
                         pl.edge_first_col[pl.n_edges] = (int)(tn * bn - pad);
                         ++pl.n_edges;
@@ -1045,7 +1088,7 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
     // The weights are always regrouped into the workspace, y and the bias may start on any element;
     // only an input that the kernels read in place has to start on a 16-byte boundary.
     const bool reads_x_in_place = pl.strips || (!pl.table && pl.Lp == 0);
-    if (pl.fast && reads_x_in_place && !aligned16(x)) pl.fast = false;
+    if (pl.fast && reads_x_in_place && !pl.reg && !aligned16(x)) pl.fast = false;
 
     GemmArgs a{};
     a.bias = bias; a.C = y; a.ws = nullptr; a.rs_part = nullptr;
@@ -1100,12 +1143,14 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
                 ldb = pl.Lp;
             }
         }
-        const Path path = choose_path(aligned16(wr) && aligned16(bsrc), Cout, pl.Lout, cin_k * Kw, dtype, B, pl.kind, false, ldb);
+        const Path path = pl.reg ? Path{true, pl.kind, pl.tile}
+                                 : choose_path(aligned16(wr) && aligned16(bsrc), Cout, pl.Lout, cin_k * Kw, dtype, B, pl.kind, false, ldb);
         if (!path.mfma) return PGK_ERR_UNSUPPORTED;   // the plan has checked what the kernel needs
         a.A = wr; a.B = bsrc;
         a.a_batch_stride = 0;
         a.b_batch_stride = cin_k * ldb;
         a.ldb = (int)ldb;
+        a.reg_b = pl.reg ? 1 : 0;
         a.b_tiles_per_tap = (int)(cin_k / path.tile.bk);
         a.b_tap_step = (int)dilation;
         a.k_slice = a.K;
@@ -1177,7 +1222,8 @@ int pgk_probe_gemm_phases(const void* A, const void* B, const float* bias, void*
     if (rc != PGK_OK) return rc;
     if (!stamps || (reinterpret_cast<uintptr_t>(stamps) & 7u)) return PGK_ERR_INVALID_ARG;
     const pgk::TileShape t = pgk::mfma_tile_shape(dtype, pgk::TILE_LARGE);
-    if (!aligned16(A) || !aligned16(B) || !mfma_shape_ok(M, N, K, dtype) || needs_packing(N, K, dtype, false))
+    if (!aligned16(A) || !aligned16(B) || !mfma_shape_ok(M, N, K, dtype) || odd_rows(K, dtype, false, N).a ||
+        odd_rows(K, dtype, false, N).b)
         return PGK_ERR_UNSUPPORTED;
     const int64_t tiles_m = (M + t.bm - 1) / t.bm, tiles_n = (N + t.bn - 1) / t.bn;
     if ((long double)tiles_m * tiles_n > 1.0e6L) return PGK_ERR_UNSUPPORTED;

@@ -35,6 +35,7 @@ TileShape mfma_tile_shape(int dtype, int kind)
 hipError_t launch_gemm_mfma(const GemmArgs& a, int dtype, int kind, int out_mode, hipStream_t s)
 {
     if (!mfma_has_tile(dtype, kind, a.b_trans != 0)) return hipErrorInvalidValue;
+    if (a.reg_a || a.reg_b) return dtype == DT_BF16 ? launch_gemm_mfma_reg(a, kind, out_mode, s) : hipErrorInvalidValue;
     // a convolution's operand views (one bias per row marks them) have instances of their own
     if (a.bias_per_row) return launch_gemm_mfma_conv(a, dtype, kind, out_mode, s);
     if (a.b_tiles_per_tap != 0x7fffffff || a.b_col_shift != 0 || a.edge_B[0] || a.b_use_tap_table) return hipErrorInvalidValue;

@@ -45,9 +45,13 @@
 
 namespace pgk {
 
-template <bool BT_, bool BF16_, int BM_, int BN_, int BK_, int WGM_, int WGN_, int A_STAGES_, int WAVES_PER_SIMD_>
+template <bool BT_, bool BF16_, int BM_, int BN_, int BK_, int WGM_, int WGN_, int A_STAGES_, int WAVES_PER_SIMD_,
+          bool REG_A_ = false, bool REG_B_ = false>
 struct MfmaCfgBase {
     static constexpr bool BF16 = BF16_;
+    // bf16 operands whose rows start on 2-byte boundaries only, which the direct-to-LDS copies do not
+    // take: their tiles go through registers (see "Copies through registers" in the kernel)
+    static constexpr bool REG_A = REG_A_, REG_B = REG_B_;
     // B given transposed, [N][K] with K contiguous (a linear layer's weight as stored): its
     // tile then sits in LDS like the A tile, [BN][BK], and is fetched like it
     static constexpr bool BT = BT_;
@@ -96,6 +100,11 @@ struct MfmaCfg : MfmaCfgBase<false, BF16_, BM_, BN_, BK_, WGM_, WGN_, A_STAGES_,
 // ... and B given transposed, [N][K]
 template <bool BF16_, int BM_, int BN_, int BK_, int WGM_, int WGN_, int A_STAGES_, int WAVES_PER_SIMD_>
 struct MfmaCfgBt : MfmaCfgBase<true, BF16_, BM_, BN_, BK_, WGM_, WGN_, A_STAGES_, WAVES_PER_SIMD_> {};
+// ... bf16 with A and / or B copied through registers
+template <bool BT_, int BM_, int BN_, int BK_, int WGM_, int WGN_, int A_STAGES_, int WAVES_PER_SIMD_, bool REG_A_, bool REG_B_>
+struct MfmaCfgReg : MfmaCfgBase<BT_, true, BM_, BN_, BK_, WGM_, WGN_, A_STAGES_, WAVES_PER_SIMD_, REG_A_, REG_B_> {
+    static_assert(A_STAGES_ == 3 || (REG_A_ && REG_B_), "the two-deep A ring's copies are interleaved with B's");
+};
 
 // A tile: rows of CPR chunks; 16 consecutive rows read the same logical chunk
 // at once, so the 16 chunk slots of a 256-byte bank period must all differ.
@@ -204,6 +213,11 @@ __device__ __forceinline__ void epilogue_to_lds16(f32x4 (&acc)[Cfg::TM16][Cfg::T
 // four units a wave writes at once, and the row pieces it reads back, fall in different banks.
 // Row sums as in the workgroup-wide form: per-wave partials to rs_lds, combined by the caller
 // after a barrier.
+// Output rows that start off the 128-byte grid (an N that is no multiple of 64) share lines between waves and
+// workgroups, and plain stores, which L2 puts together, are the better ones there (512 x 50257 x 768 64 -> 62 us); the
+// instances for odd operand rows, whose output is mostly like that, store so.  (Chunks moved onto the
+// 16-byte grid first, from three LDS reads each: 75 us.  A branch in the other instances costs their epilogue more
+// than it gains: 16384 x 1024 x 4096 104 -> 105 us.)
 template <int ACT, int KIND, typename Cfg, bool HAS_BIAS = true>
 __device__ __forceinline__ void epilogue_wave16(f32x4 (&acc)[Cfg::TM16][Cfg::TN16], const float* bias,
                                                 const float* bias_row, unsigned char* out_tile, size_t ld_bytes,
@@ -278,7 +292,8 @@ __device__ __forceinline__ void epilogue_wave16(f32x4 (&acc)[Cfg::TM16][Cfg::TN1
             if (trow >= m_rem || left <= 0) continue;
             unsigned char* at = out_tile + (size_t)trow * ld_bytes + (size_t)(wn * Cfg::WN) * 2 + (size_t)cc * 16;
             if (left >= 8) {
-                __builtin_nontemporal_store(v[t], (chunk_at_element*)at);
+                if constexpr (Cfg::REG_A || Cfg::REG_B) *(chunk_at_element*)at = v[t];
+                else __builtin_nontemporal_store(v[t], (chunk_at_element*)at);
             } else {
 #pragma unroll
                 for (int e = 0; e < 7; ++e) {
@@ -642,6 +657,12 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_mfma_kernel
     // of the K range after its last tile (a rotated loop starts at tile k_rot and wraps around).
     size_t a_next_off = (size_t)k_rot * a_step;
     int a_next_tile = k_rot;
+    auto a_moves_on = [&]() __attribute__((always_inline)) {
+        a_next_off += a_step;
+        if constexpr (VIEW == VIEW_GEMM) {
+            if (++a_next_tile == KT) { a_next_tile = 0; a_next_off = 0; }
+        }
+    };
     auto copy_a_op = [&](int kt, auto st, int t, bool bounded) __attribute__((always_inline)) {
         (void)kt;
         unsigned char* la = lds_a(st) + wave * (Cfg::A_CPW * 1024);
@@ -649,12 +670,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_mfma_kernel
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, records(base, A_end, bounded), 0x00020000),
             PGK_LDS(la + t * 1024), 16, voff_a[t], 0, 0, 0);
-        if (t == Cfg::A_CPW - 1) {        // the tile's last piece: move on to the next tile
-            a_next_off += a_step;
-            if constexpr (VIEW == VIEW_GEMM) {
-                if (++a_next_tile == KT) { a_next_tile = 0; a_next_off = 0; }
-            }
-        }
+        if (t == Cfg::A_CPW - 1) a_moves_on();        // the tile's last piece
     };
     // B tiles likewise: b_step further down -- in a convolution's view, after every
     // b_tiles_per_tap tiles the rows start over and the columns move on by b_tap_step elements
@@ -678,6 +694,22 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_mfma_kernel
     size_t b_next_off = VIEW == VIEW_CONV ? (p.b_use_tap_table ? (size_t)p.b_tap_off[0] : 0) : (size_t)k_rot * b_step;
     int b_next_row_tile = 0, b_taps_done = 0, b_next_tile = k_rot;
     const long long b_tap_jump = VIEW == VIEW_CONV ? (long long)p.b_tap_step * ES - (long long)p.b_tiles_per_tap * (long long)b_step : 0;
+    auto b_moves_on = [&]() __attribute__((always_inline)) {
+        b_next_off += b_step;
+        if constexpr (VIEW == VIEW_GEMM) {
+            if (++b_next_tile == KT) { b_next_tile = 0; b_next_off = 0; }
+        } else {
+            // (written without branches: a branch here would cut the pinned instruction
+            // sequence of the tile into basic blocks)
+            const bool new_tap = ++b_next_row_tile == p.b_tiles_per_tap;
+            b_next_row_tile = new_tap ? 0 : b_next_row_tile;
+            b_taps_done += new_tap ? 1 : 0;
+            // (the last advance comes after the final tile: the index is kept inside the table)
+            const long long from_table = tap_entry(b_taps_done < 32 ? b_taps_done : 31);
+            const long long stepped = (long long)b_next_off + b_tap_jump;
+            b_next_off = new_tap ? (size_t)(p.b_use_tap_table ? from_table : stepped) : b_next_off;
+        }
+    };
     auto copy_b_op = [&](int kt, auto st, int t, bool bounded) __attribute__((always_inline)) {
         unsigned char* lb = lds_b(st) + wave * (Cfg::B_CPW * 1024);
         (void)kt;
@@ -685,22 +717,72 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_mfma_kernel
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, records(base, B_end, bounded), 0x00020000),
             PGK_LDS(lb + t * 1024), 16, voff_b[t], 0, 0, 0);
-        if (t == Cfg::B_CPW - 1) {        // the tile's last piece: move on to the next tile
-            b_next_off += b_step;
-            if constexpr (VIEW == VIEW_GEMM) {
-                if (++b_next_tile == KT) { b_next_tile = 0; b_next_off = 0; }
-            } else {
-                // (written without branches: a branch here would cut the pinned instruction
-                // sequence of the tile into basic blocks)
-                const bool new_tap = ++b_next_row_tile == p.b_tiles_per_tap;
-                b_next_row_tile = new_tap ? 0 : b_next_row_tile;
-                b_taps_done += new_tap ? 1 : 0;
-                // (the last advance comes after the final tile: the index is kept inside the table)
-                const long long from_table = tap_entry(b_taps_done < 32 ? b_taps_done : 31);
-                const long long stepped = (long long)b_next_off + b_tap_jump;
-                b_next_off = new_tap ? (size_t)(p.b_use_tap_table ? from_table : stepped) : b_next_off;
-            }
+        if (t == Cfg::B_CPW - 1) b_moves_on();        // the tile's last piece
+    };
+    // Copies through registers (REG_A, REG_B): the same 16-byte pieces, lane by lane, as 16-byte
+    // loads from element-aligned addresses and LDS writes.  A tile is loaded after the barrier of
+    // the tile two before it and written in the last step but one of the tile before it, so the loads have most of a
+    // tile's matrix instructions to land; one tile of an operand is in registers at a time.
+    // `bounded` (the last K tile): a piece that would run past the array's end is read further
+    // down, ending there, and moved into place when it is written; one that lies behind the end as a
+    // whole is read anywhere and cleared (zero_k_tail).
+    // The loads and LDS writes take issue slots and the rows off the 16-byte grid extra requests: a fifth
+    // of the large tile's main loop (4096 x 4095 x 4096 97 -> 121 us); what they spare is a padded copy of the operand
+    // (512 x 50257 x 768 83 -> 62 us).
+    u32x4 ra[Cfg::REG_A ? Cfg::A_CPW : 1], rb[Cfg::REG_B ? Cfg::B_CPW : 1];
+    const unsigned char *ra_base = Ag, *rb_base = Bg;         // where the tile in registers starts
+    auto past_end = [](const unsigned char* base, const unsigned char* end, unsigned int off) __attribute__((always_inline)) -> long long {
+        const long long over = (long long)off + 16 - (long long)(end - base);
+        return over > 0 ? over : 0;
+    };
+    auto reg_load = [&](const unsigned char* base, const unsigned char* end, unsigned int off, bool bounded) __attribute__((always_inline)) -> u32x4 {
+        const unsigned char* at = base + off;
+        if (bounded) at -= past_end(base, end, off);
+        return *(const u32x4_align2*)at;
+    };
+    auto in_place = [&](u32x4 v, const unsigned char* base, const unsigned char* end, unsigned int off, bool bounded) __attribute__((always_inline)) -> u32x4 {
+        if (bounded) {
+            const long long over = past_end(base, end, off);
+            const unsigned int bits = over < 16 ? 8u * (unsigned int)over : 0u;
+            unsigned long long lo = ((unsigned long long)v[1] << 32) | v[0], hi = ((unsigned long long)v[3] << 32) | v[2];
+            const unsigned int sh = bits & 63u;
+            const unsigned long long from_hi = sh ? hi << (64u - sh) : 0ull;
+            lo = bits >= 64u ? hi >> sh : (lo >> sh) | from_hi;
+            hi = bits >= 64u ? 0ull : hi >> sh;
+            v = u32x4{(unsigned int)lo, (unsigned int)(lo >> 32), (unsigned int)hi, (unsigned int)(hi >> 32)};
         }
+        return v;
+    };
+    constexpr int REG_PIECES = (Cfg::REG_A ? Cfg::A_CPW : 0) + (Cfg::REG_B ? Cfg::B_CPW : 0);
+    // piece q of the REG_PIECES of a tile (A's first)
+    auto load_op = [&](int q, bool bounded) __attribute__((always_inline)) {
+        if constexpr (Cfg::REG_A) {
+            if (q < Cfg::A_CPW) {
+                ra_base = Ag + a_next_off;
+                ra[q] = reg_load(ra_base, A_end, voff_a[q], bounded);
+                if (q == Cfg::A_CPW - 1) a_moves_on();
+                return;
+            }
+            q -= Cfg::A_CPW;
+        }
+        if constexpr (Cfg::REG_B) {
+            rb_base = Bg + b_next_off;
+            rb[q] = reg_load(rb_base, B_end, voff_b[q], bounded);
+            if (q == Cfg::B_CPW - 1) b_moves_on();
+        }
+    };
+    auto write_op = [&](auto sta, auto stb, int q, bool bounded) __attribute__((always_inline)) {
+        if constexpr (Cfg::REG_A) {
+            if (q < Cfg::A_CPW) {
+                *(__attribute__((address_space(3))) u32x4*)PGK_LDS(lds_a(sta) + (wave * Cfg::A_CPW + q) * 1024 + lane * 16) =
+                    in_place(ra[q], ra_base, A_end, voff_a[q], bounded);
+                return;
+            }
+            q -= Cfg::A_CPW;
+        }
+        if constexpr (Cfg::REG_B)
+            *(__attribute__((address_space(3))) u32x4*)PGK_LDS(lds_b(stb) + (wave * Cfg::B_CPW + q) * 1024 + lane * 16) =
+                in_place(rb[q], rb_base, B_end, voff_b[q], bounded);
     };
     auto copy_a = [&](int kt, auto st) __attribute__((always_inline)) {
 #pragma unroll
@@ -923,7 +1005,8 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_mfma_kernel
     };
     // With a three-deep A ring the A copy issued in this tile's first step is for the
     // tile after next and may still be in flight when the next tile is awaited.
-    constexpr int STEADY_IN_FLIGHT = (SA - 2) * Cfg::A_CPW;
+    // (Tiles loaded into registers have been written, and so awaited, before that.)
+    constexpr int STEADY_IN_FLIGHT = Cfg::REG_A ? 0 : (SA - 2) * Cfg::A_CPW;
 
     // One K tile: A operands from A stage kt % SA, B operands from B stage kt % 2.  ("Step": a
     // sub-step for bf16.)
@@ -963,8 +1046,10 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_mfma_kernel
         for (int s = 0; s < NS; ++s) {
             const bool last = s + 1 == NS;
             // which copy (if any) is issued during this step
-            const bool early = s == 0 && (SA == 3 ? has_a : has_next);    // A(kt+2) or B(kt+1)
-            const bool late = last && has_next && (SA == 3 ? has_b : has_a);  // B(kt+2) or A(kt+2)
+            const bool early = s == 0 && (SA == 3 ? has_a && !Cfg::REG_A : has_next && !Cfg::REG_B);           // A(kt+2) or B(kt+1)
+            const bool late = last && has_next && (SA == 3 ? has_b && !Cfg::REG_B : has_a && !Cfg::REG_A);     // B(kt+2) or A(kt+2)
+            const bool reg_load_now = REG_PIECES > 0 && last && has_next && has_b;     // tile kt+2 into registers
+            const bool reg_write_now = REG_PIECES > 0 && s + 2 == NS && has_next;      // tile kt+1 from registers
             const int n_copy = early ? (SA == 3 ? Cfg::A_CPW : Cfg::B_CPW)
                              : late ? (SA == 3 ? Cfg::B_CPW : Cfg::A_CPW) : 0;
             const bool fetch = !last || has_next;
@@ -1000,15 +1085,42 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_mfma_kernel
                         else copy_a_op(kt + 2, sta, t, b2);
                     }
                 }
+                if constexpr (REG_PIECES > 0) {
+                    constexpr int W0 = N_MFMA / 2;       // the writes go into the second half of their step
+#pragma unroll
+                    for (int q = 0; q < REG_PIECES; ++q) {
+                        if (reg_load_now && q >= (m * REG_PIECES) / N_MFMA && q < ((m + 1) * REG_PIECES) / N_MFMA)
+                            load_op(q, !STEADY && k_partial && kt + 3 == KT);
+                        if (reg_write_now && m >= W0 && q >= ((m - W0) * REG_PIECES) / (N_MFMA - W0) && q < ((m + 1 - W0) * REG_PIECES) / (N_MFMA - W0))
+                            write_op(NextA{}, NextB{}, q, !STEADY && k_partial && kt + 2 == KT);
+                    }
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
 
     // prologue: tile 0 in full; what a tile body expects to find in flight follows
-    copy_a(0, IC<0>{});
-    copy_b(0, IC<0>{});
-    if constexpr (SA == 3) {
+    if constexpr (!Cfg::REG_A) copy_a(0, IC<0>{});
+    if constexpr (!Cfg::REG_B) copy_b(0, IC<0>{});
+    if constexpr (REG_PIECES > 0) {
+        const bool only = k_partial && KT == 1;
+#pragma unroll
+        for (int q = 0; q < REG_PIECES; ++q) load_op(q, only);
+        if constexpr (!Cfg::REG_A) { if (KT > 1) copy_a(1, IC<1>{}); }
+#pragma unroll
+        for (int q = 0; q < REG_PIECES; ++q) write_op(IC<0>{}, IC<0>{}, q, only);
+        if (KT > 1) {
+            wait_copies_and_sync(IC<STEADY_IN_FLIGHT>{});
+            if constexpr (!Cfg::REG_B) copy_b(1, IC<1>{});
+#pragma unroll
+            for (int q = 0; q < REG_PIECES; ++q) load_op(q, k_partial && KT == 2);
+        } else if (k_partial) {
+            wait_clear_and_sync(IC<0>{}, IC<0>{});
+        } else {
+            wait_copies_and_sync(IC<0>{});
+        }
+    } else if constexpr (SA == 3) {
         if (KT > 1) {
             copy_a(1, IC<1>{});
             wait_copies_and_sync(IC<Cfg::A_CPW>{});

@@ -30,6 +30,7 @@ struct GemmArgs {
     long long a_batch_stride, b_batch_stride;   // elements between batch entries of A and of B
     int ldb;                 // elements between rows of B
     int b_trans;             // 1: B is given transposed, [batch][N][ldb >= K], K contiguous
+    int reg_a, reg_b;        // 1: bf16 rows of A / B off 4-byte boundaries: copied through registers (pgk_gemm_mfma_reg.hip)
     int k_rotate;            // 1: each workgroup starts its K loop at a tile of its own (plain GEMM views, whole K tiles only)
     int b_tail_bounded;      // 1: rows of a plain B are not whole 16-byte chunks: the copies of the last K tile stop at the end of B
     int bias_per_row;        // 0: bias[N] added to columns; 1: bias[M] added to rows (a convolution's views: the
@@ -77,6 +78,7 @@ inline void fill_plain_views(GemmArgs& a)
     a.ldb = a.N;
     a.b_trans = 0;
     a.b_tail_bounded = 0;
+    a.reg_a = a.reg_b = 0;
     a.k_rotate = 0;
     a.bias_per_row = 0;
     a.b_tiles_per_tap = 0x7fffffff;
@@ -119,6 +121,11 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, int dtype, int kind, int out_mode
 // entries, B tiles walking tap after tap, edge strips; B as [K][N], out_mode 0); reached through
 // launch_gemm_mfma.
 hipError_t launch_gemm_mfma_conv(const GemmArgs& a, int dtype, int kind, int out_mode, hipStream_t s);
+
+// bf16 operands off 4-byte boundaries (a.reg_a, a.reg_b): which tiles there are, and the launch (plain
+// views and a convolution's); reached through launch_gemm_mfma.
+bool mfma_reg_has_tile(int kind, bool reg_a, bool reg_b, bool b_trans);
+hipError_t launch_gemm_mfma_reg(const GemmArgs& a, int kind, int out_mode, hipStream_t s);
 
 // fp32, 32 x 32 tiles, K split over the four waves of a workgroup (out_mode 0; K, N, ldb multiples
 // of 4, A and B on 16-byte boundaries); reached through launch_gemm_mfma with TILE_TINY.

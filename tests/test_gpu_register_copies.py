@@ -1,0 +1,89 @@
+"""bf16 operands whose rows start on 2-byte boundaries only, copied through registers: odd K, odd N of
+a plain B, both, and a convolution's taps at odd offsets, at the edges of tiles, with a partial last
+K tile and none, one K tile to many, batches, and values behind the operands that must not be read
+into a result."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_06345_amd.inputs import ACT_NONE, ACT_SILU, BF16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pgk():
+    from paper_2511_06345_amd import binding
+    binding.load_library()
+    return binding
+
+
+def _inside(values, offset=0):
+    """The values as the middle of a buffer of NaN, `offset` elements from a 16-byte boundary on."""
+    buf = torch.full((values.numel() + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    view = buf[32 + offset:32 + offset + values.numel()].view(values.shape)
+    view.copy_(values)
+    return view
+
+
+# integer values below 8 keep every sum exact in float32 (49 K < 2^24): the outputs are those of 64-bit
+# sums rounded once to bf16, whatever the order
+@pytest.mark.parametrize("M,N,K,batch,bt", [
+    (512, 2049, 64, 1, False),       # odd N, one whole K tile
+    (300, 1501, 128, 2, False),      # odd N, whole K tiles, a batch whose entries start on odd elements
+    (257, 4097, 190, 1, False),      # odd N, partial K tile
+    (1024, 2304, 67, 1, False),      # odd K: A alone
+    (1000, 2303, 129, 1, False),     # both; one K value in the last tile
+    (2047, 1025, 703, 1, False),     # both, many tiles
+    (130, 2100, 255, 3, True),       # transposed B, odd K
+    (1024, 2048, 1023, 1, True),
+    (33, 33, 40001, 1, True),        # split along K
+    (64, 2051, 1000, 1, False),      # few rows
+])
+def test_odd_rows_exact(pgk, M, N, K, batch, bt):
+    need = pgk.gemm_fused_workspace_bytes(M, N, K, batch, BF16, pgk.WS_B_TRANSPOSED if bt else 0)
+    slices = pgk.gemm_plan(M, N, K, batch, BF16, bt)["slices"]
+    assert need == (0 if slices == 1 else -(-slices * batch * M * N * 4 // 256) * 256), "no copies of operands"
+    g = torch.Generator(device="cuda").manual_seed(M * N + K)
+    A = torch.randint(-7, 8, (batch, M, K), generator=g, device="cuda").to(torch.bfloat16)
+    B = torch.randint(-7, 8, (batch, N, K) if bt else (batch, K, N), generator=g, device="cuda").to(torch.bfloat16)
+    call = pgk.gemm_fused_bt if bt else pgk.gemm_fused
+    C, rs = call(_inside(A), _inside(B), None, ACT_NONE, rowsum=True)
+    ref = torch.stack([A[b].double() @ (B[b].double().t() if bt else B[b].double()) for b in range(batch)])
+    assert torch.equal(C, ref.to(torch.bfloat16))
+    # (row sums of integers: exact while below 2^24)
+    if 49 * K * N < 2 ** 24 * 16:
+        assert torch.allclose(rs.double(), ref.sum(-1), rtol=1e-6, atol=0.5)
+
+
+@pytest.mark.parametrize("B,Cin,L,Cout,Kw,pad,dil", [
+    (2, 64, 1000, 64, 3, 1, 1), (1, 128, 4096, 256, 3, 1, 1), (2, 64, 777, 100, 5, 2, 1), (1, 64, 513, 48, 4, 0, 1),
+    (3, 192, 300, 130, 3, 3, 3), (1, 64, 129, 64, 7, 3, 1), (1, 64, 2001, 512, 1, 0, 1), (2, 64, 640, 64, 3, 101, 1),
+])
+def test_convolution_taps_at_odd_offsets_exact(pgk, B, Cin, L, Cout, Kw, pad, dil):
+    g = torch.Generator(device="cuda").manual_seed(L + Cout)
+    x = torch.randint(-7, 8, (B, Cin, L), generator=g, device="cuda").to(torch.bfloat16)
+    w = torch.randint(-7, 8, (Cout, Cin, Kw), generator=g, device="cuda").to(torch.bfloat16)
+    bias = torch.randint(-7, 8, (Cout,), generator=g, device="cuda").float()
+    y = pgk.conv1d(_inside(x), _inside(w), bias, ACT_NONE, 1, pad, dil)
+    Lout = y.shape[2]
+    xp = torch.nn.functional.pad(x.double(), (pad, pad))
+    ref = bias.double().view(1, -1, 1).expand(B, -1, Lout).clone()
+    for b in range(B):
+        for k in range(Kw):
+            ref[b] += w[:, :, k].double() @ xp[b, :, k * dil:k * dil + Lout].contiguous()
+    assert torch.equal(y, ref.to(torch.bfloat16))
+
+
+def test_activation_against_64_bits(pgk):
+    rng = np.random.default_rng(7)
+    M, N, K = 129, 1021, 515
+    A = torch.from_numpy(rng.uniform(-1, 1, (1, M, K)).astype(np.float32)).to(torch.bfloat16)
+    B = torch.from_numpy((rng.standard_normal((1, K, N)) / K ** 0.5).astype(np.float32)).to(torch.bfloat16)
+    bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32))
+    C, _ = pgk.gemm_fused(A.cuda(), B.cuda(), bias.cuda(), ACT_SILU, rowsum=False)
+    x = A.double() @ B.double() + bias.double()
+    ref = x * torch.sigmoid(x)
+    err = (C.cpu().double() - ref).abs() / torch.maximum(ref.abs(), ref.pow(2).mean().sqrt())
+    # half a unit of the stored bf16 (2^-9) and the float32 sums
+    assert err.max() < 2.0 ** -8
