@@ -101,10 +101,14 @@ typedef enum {
  * every second k.  A tile with a value that three terms do not hold exactly (some below 2^-110), with a result
  * below 2^-119 other than zero, or with one that is not finite is computed with the float32 instruction.)
  * The matrix-core kernels read operands in place when their rows start on 4-byte boundaries
- * (float32 always; bfloat16 when K -- and, for B as [K][N], N -- is even).  Otherwise, when
+ * (float32 always; bfloat16 when K -- and, for B as [K][N], N -- is even).  Otherwise, from 2^25
+ * multiply-adds on, tiles are copied through registers where that costs less than the copies that follow
+ * (short K, or one operand only); else, when
  * the problem has at least 64^3 multiply-adds, the operands are first copied into the
  * workspace with rows padded with zeros to whole 16-byte chunks (up to batch*(M*K' + K'*N')
- * elements, K' and N' the next multiples of 8).  C, bias and rowsum are always used in place,
+ * elements, K' and N' the next multiples of 8).  Products of at most 32 rows by 256 columns and more run, over
+ * the range where that is the faster way, on a kernel whose workgroups take all of K: one pass, operands in
+ * place at any alignment of their elements, row sums per 16 (B transposed) or up to 128 columns.  C, bias and rowsum are always used in place,
  * whatever N is and wherever they start (element alignment).  A B given as [K][N] with at
  * most 32 columns (under an output of more than 32 rows) is likewise copied first, in
  * transposed form, so that the product can run on the 128 x 32 tile, and so is an A or B
@@ -215,7 +219,7 @@ int pgk_gemm_splitk_bt(const void* A, const void* Bt, const float* bias, void* C
  *   out[0]  1 = matrix-core kernel, 0 = bounds-checked kernel
  *   out[1..3]  tile rows, tile columns, K tile
  *   out[4]  K slices (1 = one pass; more = the automatic two-pass split)
- *   out[5]  workgroups of the GEMM launch
+ *   out[5]  workgroups of the GEMM launch (few rows, one pass: the 32 x 128 tiles that its narrower workgroups make up)
  * Returns PGK_OK, or the error pgk_gemm_fused would return for these sizes; out == NULL is
  * PGK_ERR_INVALID_ARG.  Nothing is launched.
  */

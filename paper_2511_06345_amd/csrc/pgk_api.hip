@@ -487,6 +487,39 @@ size_t split_part_bytes(int64_t M, int64_t N, int64_t batch, bool rowsum)
     return (rowsum && nseg > 1) ? (size_t)batch * (size_t)nseg * (size_t)M * sizeof(float) : 0;
 }
 
+// Products of few rows whose workgroups take all of K, in one launch (pgk_gemm_stream.hip): where that beat
+// the skinny tiles with their K slices over 66 shapes of 1 ... 32 rows, 256 ... 32768 columns and K of 256 ... 16384 (whole calls
+// in a graph; slices / one launch).  B transposed, up to 16 rows: 8 x 11008 x 4096 bf16 19.7 / 17.5 us, fp32 41.5 / 35.2,
+// 1 x 4096 x 4096 13.9 / 7.4, 9 x 258 x 640 fp32 13.0 / 5.7; a long K needs many columns (10 x 896 x 7667 21 / 25), many
+// columns favour the wide tiles (16 x 32768 x 8192 102 / 105, 16 x 23934 x 704 10 / 18).  B plain: 8 x 11008 x 4096 bf16 19.7 / 18.4, fp32
+// 40.3 / 32.7, 12 x 5376 x 1024 8.8 / 6.4, 3 x 704 x 640 fp32 12.9 / 5.4; the K of one workgroup may not be too long (3 x 5888 x
+// 14784 64 / 105).  bf16 with odd rows spares the padded copy of B as well and wins up to 32 rows: 23 x 12131 x 5554
+// 70 / 43, 27 x 13225 x 1216 27 / 15, 12 x 2496 x 5383 transposed 31 / 13.  A second row block (17 ... 32 rows) loses otherwise.
+bool stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, pgk::StreamPlan* pl)
+{
+    if (M > 32) return false;
+    if (K < 64 || K > (1 << 24) || N < 256) return false;
+    const bool odd = dtype == PGK_DTYPE_BF16 && (K % 2 != 0 || (!b_trans && N % 2 != 0));
+    if (M > 16 && (b_trans || !odd)) return false;
+    if (b_trans) {
+        if (N > 16384 || (K > 2048 && N < (odd ? 2048 : 4096))) return false;
+        pl->blocks = 1;
+        pl->waves = 8;
+    } else if (dtype == PGK_DTYPE_BF16) {
+        if (odd ? (N < 2048 && K > 4096) : (N <= 4096 && K > 1024)) return false;
+        pl->blocks = N >= 16384 ? 8 : 4;      // (98 against 117 us for 16 x 32768 x 8192; 21 against 18 for 8 x 11008 x 4096)
+        pl->waves = 4;
+    } else {
+        if (K > 1024 && (N <= 4096 || K > N)) return false;
+        pl->blocks = N >= 4096 ? 4 : 2;
+        pl->waves = 4;
+    }
+    const int64_t cols = 16 * pl->blocks, groups = (N + cols - 1) / cols;
+    if (groups * batch > kMaxDim) return false;
+    pl->groups = (int)groups;
+    return true;
+}
+
 // What pgk_gemm_fused does with a problem: the kernel and tile of the single-pass route, and
 // whether the K range is split instead (then `slices` and the tile that goes with them).
 struct FusedPlan {
@@ -544,6 +577,8 @@ FusedPlan plan_fused(bool aligned, int64_t M, int64_t N, int64_t K, int64_t batc
 // workspace out inside the calls.
 struct WsNeeds {
     bool ok;                 // sizes are representable
+    bool stream;             // fused call: the kernel for few rows
+    pgk::StreamPlan sp;
     PackDims d;
     bool pack_a, pack_b;
     FusedPlan fp;            // fused call only
@@ -583,6 +618,13 @@ WsNeeds fused_needs(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, b
                     bool b_mis)
 {
     WsNeeds w{};
+    if (stream_plan(M, N, K, batch, dtype, b_trans, &w.sp)) {
+        w.ok = w.stream = true;
+        w.d = PackDims{false, K, 0, false, b_trans};
+        w.rs_part = (want_rowsum && w.sp.groups > 1) ? (size_t)batch * (size_t)w.sp.groups * (size_t)M * sizeof(float) : 0;
+        lay_out(w);
+        return w;
+    }
     w.ok = pack_needs(w, M, N, K, batch, dtype, b_trans, a_mis, b_mis);
     if (!w.ok) return w;
     // the problem as the kernels see it
@@ -691,6 +733,10 @@ int gemm_fused_impl(const void* A, const void* B, const float* bias, void* C, fl
     const WsNeeds w = fused_needs(M, N, K, batch, dtype, b_trans, rowsum != nullptr, a_mis, b_mis);
     rc = check_workspace(w, workspace, workspace_bytes);
     if (rc != PGK_OK) return rc;
+    if (w.stream)
+        return pgk::launch_gemm_stream(w.sp, A, B, bias, C, rowsum, w.rs_part ? static_cast<float*>(workspace) : nullptr, (int)M,
+                                       (int)N, (int)K, (int)batch, act, dtype, b_trans, static_cast<hipStream_t>(stream)) == hipSuccess
+                   ? PGK_OK : PGK_ERR_HIP;
     const FusedPlan& fp = w.fp;
     const Path& path = fp.path;
     const int64_t tiles_m = (M + path.tile.bm - 1) / path.tile.bm;
@@ -789,6 +835,17 @@ int pgk_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int
     const void* ok = reinterpret_cast<const void*>(uintptr_t{256});   // stands for any 16-byte aligned pointer
     const int rc = validate_common(ok, ok, ok, M, N, K, batch, PGK_ACT_NONE, dtype);
     if (rc != PGK_OK) return rc;
+    if (pgk::StreamPlan sp; stream_plan(M, N, K, batch, dtype, b_transposed != 0, &sp)) {
+        // (its workgroups are narrower than a tile; the query answers with the tiles they make up)
+        const pgk::TileShape t = pgk::mfma_tile_shape(dtype, pgk::TILE_FLAT);
+        const long double tiles = (long double)((N + t.bn - 1) / t.bn) * batch;
+        if (tiles > 2.0e9L) return PGK_ERR_UNSUPPORTED;
+        out[0] = 1;
+        out[1] = t.bm; out[2] = t.bn; out[3] = t.bk;
+        out[4] = 1;
+        out[5] = (int32_t)tiles;
+        return PGK_OK;
+    }
     const PackDims d = pack_dims(M, N, K, dtype, b_transposed != 0);      // as pgk_gemm_fused sees the problem
     K = d.k;
     const FusedPlan fp = plan_fused(true, M, N, K, batch, dtype, d.b_trans, d.ldb);

@@ -140,6 +140,13 @@ hipError_t launch_gemm_f32_terms_timed(const GemmArgs& a, hipStream_t s);
 // The large tile of either type, plain operand views, out_mode 0, with phase stamps (a.stamps set).
 hipError_t launch_gemm_mfma_timed(const GemmArgs& a, int dtype, hipStream_t s);
 
+// Products of at most 32 rows, all of K in one workgroup (pgk_gemm_stream.hip): blocks of sixteen
+// columns and waves of a workgroup, and how many workgroups cover N.  Any alignment of the elements.
+struct StreamPlan { int blocks, waves, groups; };
+// part: batch * groups * M floats, unused without row sums or with one group
+hipError_t launch_gemm_stream(const StreamPlan& pl, const void* A, const void* B, const float* bias, void* C, float* rowsum,
+                              float* part, int M, int N, int K, int batch, int act, int dtype, bool b_trans, hipStream_t s);
+
 // Bounds-checked kernel for every other shape.
 hipError_t launch_gemm_guarded(const GemmArgs& a, int dtype, int out_mode, hipStream_t s);
 
