@@ -32,10 +32,10 @@ def _one_pass(pgk, M, N, K, batch, dtype, bt):
         pgk.gemm_plan(M, N, K, batch, dtype, bt)["slices"] == 1
 
 
-BT = [(1, 256, 64), (8, 4097, 128), (15, 301, 129), (16, 1000, 1023), (7, 4111, 2056), (3, 272, 65), (2, 5000, 136), (16, 4096, 100)]
-PLAIN = {BF16: [(1, 256, 64), (16, 4100, 33 * 32), (5, 4224, 1000), (9, 16384, 72), (15, 16500, 100), (3, 300, 1024),
-                (31, 257, 65), (17, 2049, 96), (32, 16387, 71), (24, 4103, 259)],
-         F32: [(1, 256, 64), (16, 257, 100), (8, 4097, 1040), (3, 4160, 2052), (9, 301, 1023), (15, 4099, 67), (2, 258, 515)]}
+BT = [(1, 256, 64), (8, 4097, 128), (15, 301, 129), (16, 1000, 1023), (7, 4111, 2056), (3, 272, 65), (2, 5000, 136), (16, 4096, 100), (5, 4098, 8200)]
+PLAIN = {BF16: [(1, 256, 64), (16, 4100, 33 * 32), (5, 4224, 1000), (9, 16385, 72), (15, 16501, 100), (3, 300, 1024),
+                (31, 257, 65), (6, 2051, 8201), (20, 2101, 9000), (17, 2049, 96), (32, 16387, 71), (24, 4103, 259)],
+         F32: [(1, 256, 64), (16, 257, 100), (8, 4097, 1040), (3, 4160, 2052), (9, 301, 1023), (15, 4099, 67), (2, 258, 515), (3, 8260, 8200)]}
 CASES = [(d, *s, True) for d in (F32, BF16) for s in BT] + [(d, *s, False) for d in (F32, BF16) for s in PLAIN[d]]
 
 
