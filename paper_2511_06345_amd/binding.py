@@ -7,7 +7,10 @@ library is missing the import of a function fails loudly.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
+import functools
+import math
 import os
 from typing import Optional, Tuple
 
@@ -34,6 +37,8 @@ _lib = None
 # the handle of torch.cuda.current_stream() without the Python object around it: 0.3 us, not 2.8, of a small
 # call that takes 20 us of which the host bounds all.  Not a public name: None where torch does not have it.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+# likewise the current device's number (0.1 us, not 0.3)
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 
 
 class PgkError(RuntimeError):
@@ -117,14 +122,19 @@ def splitk_workspace_bytes(M: int, N: int, K: int, batch: int, dtype: int, split
     return int(load_library().pgk_splitk_workspace_bytes(M, N, K, batch, dtype, splits))
 
 
+# The size queries are pure host arithmetic on the sizes; a program asks about the same few again and again (0.1 us,
+# not 0.7, of a small call).
+@functools.lru_cache(maxsize=4096)
 def gemm_splitk_workspace_bytes(M: int, N: int, K: int, batch: int, dtype: int, splits: int = 0, flags: int = 0) -> int:
     return int(load_library().pgk_gemm_splitk_workspace_bytes(M, N, K, batch, dtype, splits, flags))
 
 
+@functools.lru_cache(maxsize=4096)
 def gemm_fused_workspace_bytes(M: int, N: int, K: int, batch: int, dtype: int, flags: int = 0) -> int:
     return int(load_library().pgk_gemm_fused_workspace_bytes(M, N, K, batch, dtype, flags))
 
 
+@functools.lru_cache(maxsize=4096)
 def reduce_max_workspace_bytes(outer: int, red: int, inner: int, dtype: int) -> int:
     return int(load_library().pgk_reduce_max_workspace_bytes(outer, red, inner, dtype))
 
@@ -143,25 +153,26 @@ def gemm_plan(M: int, N: int, K: int, batch: int, dtype: int, b_transposed: bool
 
 
 def _shape(A: torch.Tensor, B: torch.Tensor, b_transposed: bool = False) -> Tuple[int, int, int, int, int]:
-    if A.dim() == 2:
-        A = A.unsqueeze(0)
-    if B.dim() == 2:
-        B = B.unsqueeze(0)
+    a, b = A.shape, B.shape
+    if len(a) == 2:
+        a = (1, *a)
+    if len(b) == 2:
+        b = (1, *b)
     kdim, ndim = (2, 1) if b_transposed else (1, 2)
-    if A.dim() != 3 or B.dim() != 3 or A.shape[0] != B.shape[0] or A.shape[2] != B.shape[kdim]:
+    if len(a) != 3 or len(b) != 3 or a[0] != b[0] or a[2] != b[kdim]:
         raise ValueError("expected A [batch, M, K] and B [batch, K, N] (transposed: [batch, N, K])")
     if not (A.is_cuda and B.is_cuda and A.is_contiguous() and B.is_contiguous()):
         raise ValueError("A and B must be contiguous device tensors")
-    if A.device != B.device:
+    if A.get_device() != B.get_device():
         raise ValueError("A and B must live on the same device")
-    if A.dtype == torch.float32 and B.dtype == torch.float32:
+    type_a = A.dtype
+    if type_a == torch.float32 and B.dtype == type_a:
         dtype = F32
-    elif A.dtype == torch.bfloat16 and B.dtype == torch.bfloat16:
+    elif type_a == torch.bfloat16 and B.dtype == type_a:
         dtype = BF16
     else:
         raise TypeError("A and B must both be float32 or both bfloat16")
-    batch, M, K = A.shape
-    return int(batch), int(M), int(B.shape[ndim]), int(K), dtype
+    return a[0], a[1], b[ndim], a[2], dtype
 
 
 def _check_bias(bias: Optional[torch.Tensor], N: int, device=None) -> int:
@@ -208,21 +219,14 @@ def _check_workspace(ws: Optional[torch.Tensor], need: int, device) -> Tuple[Opt
     return ws.data_ptr(), ws.numel()
 
 
-class _on_stream:
+_current_stream = contextlib.nullcontext()
+
+
+def _on_stream(stream):
     """Temporaries the binding allocates itself (outputs, workspaces) must belong, in torch's
     caching allocator, to the stream the kernels run on: allocated under that stream, a block
     freed on return is not handed out again before the queued kernels are done."""
-
-    def __init__(self, stream):
-        self.ctx = torch.cuda.stream(stream) if stream is not None else None
-
-    def __enter__(self):
-        if self.ctx is not None:
-            self.ctx.__enter__()
-
-    def __exit__(self, *exc):
-        if self.ctx is not None:
-            self.ctx.__exit__(*exc)
+    return _current_stream if stream is None else torch.cuda.stream(stream)
 
 
 def _stream_ptr(stream) -> int:
@@ -230,7 +234,7 @@ def _stream_ptr(stream) -> int:
         return int(stream.cuda_stream)
     if _raw_stream is None:
         return int(torch.cuda.current_stream().cuda_stream)
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_current_device())
 
 
 def _ws_flags(A, B, rowsum: bool, b_transposed: bool) -> int:
@@ -352,14 +356,11 @@ def reduce_max(X: torch.Tensor, dim: int, want_idx: bool = True, out: Optional[t
         dtype = BF16
     else:
         raise TypeError("X must be float32 or bfloat16")
-    dim = dim % X.dim()
-    outer = inner = 1
-    for d in X.shape[:dim]:
-        outer *= int(d)
-    for d in X.shape[dim + 1:]:
-        inner *= int(d)
-    red = int(X.shape[dim])
-    shape = tuple(X.shape[:dim]) + tuple(X.shape[dim + 1:])
+    sizes = tuple(X.shape)
+    dim = dim % len(sizes)
+    before, after = sizes[:dim], sizes[dim + 1:]
+    outer, red, inner = math.prod(before), sizes[dim], math.prod(after)
+    shape = before + after
     dev = X.device
     need = reduce_max_workspace_bytes(outer, red, inner, dtype)
     with _on_stream(stream):
@@ -443,10 +444,12 @@ def probe_stream_read(src: torch.Tensor, sink: torch.Tensor, stream=None) -> int
     return nbytes
 
 
+@functools.lru_cache(maxsize=4096)
 def conv1d_out_len(L: int, Kw: int, stride: int = 1, pad: int = 0, dilation: int = 1) -> int:
     return int(load_library().pgk_conv1d_out_len(L, Kw, stride, pad, dilation))
 
 
+@functools.lru_cache(maxsize=4096)
 def conv1d_workspace_bytes(B: int, Cin: int, L: int, Cout: int, Kw: int, stride: int, pad: int, dilation: int,
                            dtype: int) -> int:
     return int(load_library().pgk_conv1d_workspace_bytes(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype))
@@ -469,8 +472,8 @@ def conv1d(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor], act: 
         dtype = BF16
     else:
         raise TypeError("x and w must both be float32 or both bfloat16")
-    B, Cin, L = (int(d) for d in x.shape)
-    Cout, _, Kw = (int(d) for d in w.shape)
+    B, Cin, L = x.shape
+    Cout, _, Kw = w.shape
     Lout = conv1d_out_len(L, Kw, stride, pad, dilation)
     if Lout <= 0:
         raise ValueError("the convolution has no output for these sizes")
