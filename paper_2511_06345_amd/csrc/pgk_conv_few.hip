@@ -60,7 +60,11 @@ __device__ __forceinline__ int channel_slot(int c, int every)
 }
 
 // STEPS > 0: Cin * Kw of at most 2 STEPS, weights of a block in registers for all its tiles.
-template <bool BF16, int ACT, int STEPS>
+// STREAM: non-temporal stores.  With every sixteenth channel a row's runs are whole 64-byte pieces, and past L2 they go
+// out faster ([8, 1, 160000] * [512, 1, 10], stride 5: 137 us with plain stores, 116 so); with every fourth a run starts on any 16
+// bytes and L2 has to put lines together (15999 positions of 2 channels 64 us with plain stores, 109 so); rows on
+// the 64-byte grid are even (32000 positions 109 and 111, bf16 120000 53 and 58, 64 channels of 160000 77 and 69).
+template <bool BF16, int ACT, int STEPS, bool STREAM = false>
 __global__ __launch_bounds__(256, 4) void conv_few_channels_kernel(const FewArgs p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -200,7 +204,7 @@ __global__ __launch_bounds__(256, 4) void conv_few_channels_kernel(const FewArgs
                     } else {
                         if (whole) {
                             const f32x4 v = {y[0], y[1], y[2], y[3]};
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rows, lane_off, row_off, 0);
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rows, lane_off, row_off, STREAM ? 2 : 0);
                         } else {
 #pragma unroll
                             for (int q = 0; q < 4; ++q)
@@ -259,7 +263,7 @@ hipError_t launch_conv_few_channels(const void* x, const void* w, const float* b
     // than four workgroups per CU (windows start up to fifteen positions early).
     // Every sixteenth channel: fp32 rows that do not start on 64-byte boundaries, where there are enough
     // channels to fill half of such a block, the products do not weigh and two workgroups per CU are left
-    // (8 x 512 rows of 31999: 184 -> 145 us; 300 rows of 14747, 116 workgroups: 15 -> 20 us).  bf16 stores are
+    // (8 x 512 rows of 31999: 184 -> 145 us, 116 with non-temporal stores; 300 rows of 14747, 116 workgroups: 15 -> 20 us).  bf16 stores are
     // 8 bytes a lane, and 31999 positions as fast as 32000 with every fourth (84 us).
     const long long es = dtype == DT_BF16 ? 2 : 4;
     const bool rows_aligned = (Lout * es) % 64 == 0 && (reinterpret_cast<uintptr_t>(y) % 64) == 0;
@@ -284,7 +288,9 @@ hipError_t launch_conv_few_channels(const void* x, const void* w, const float* b
     const size_t lds = (size_t)lds_floats(Cin, Kw, stride, dil, tiles, ch) * sizeof(float);
     const dim3 grid((unsigned int)wgs), block(256);
 #define PGK_FEW(BF, ACT)                                                                                       \
-    if (a.K2 <= 8) hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 4>), grid, block, lds, s, a);          \
+    if (a.every == 16 && a.K2 <= 8) hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 4, !BF>), grid, block, lds, s, a);        \
+    else if (a.every == 16) hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 8, !BF>), grid, block, lds, s, a);    \
+    else if (a.K2 <= 8) hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 4>), grid, block, lds, s, a);     \
     else if (a.K2 <= 16) hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 8>), grid, block, lds, s, a);    \
     else hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 0>), grid, block, lds, s, a)
 #define PGK_FEW_ACT(BF)                                                   \
