@@ -298,11 +298,11 @@ size_t pgk_reduce_max_workspace_bytes(int64_t outer, int64_t red, int64_t inner,
  * ways (where the kernels read x itself, x must start on a 16-byte boundary; w, bias and y may
  * start on any element).
  * Stride 1, Cin a multiple of the K tile (32 float32 / 64 bfloat16) and, for bfloat16, an even
- * dilation (or Kw = 1): the views are taken of the input itself -- only the tile columns at the
- * ends of the rows read small zero-padded strips -- or (also whenever Lout is not a multiple of
- * 16 bytes of elements) of one zero-padded copy of it.  Otherwise
- * -- stride > 1, any Cin of at least half a K tile's multiple (Cin >= its round-up / 2), odd
- * dilation in bfloat16 -- with Kw <= 32: the views are taken of copies of the input, one per
+ * dilation (or Kw = 1) or Cout of more than 32 and Cout * Kw of at most 3000: the views are taken of the input itself --
+ * only the tile columns at the ends of the rows read small zero-padded strips -- or (padding wider than a tile; up to 32
+ * output channels and Lout no multiple of 16 bytes of elements) of one zero-padded copy of it.  Otherwise
+ * -- stride > 1, any Cin of at least half a K tile's multiple (Cin >= its round-up / 2), other odd
+ * dilations in bfloat16 -- with Kw <= 32: the views are taken of copies of the input, one per
  * phase of the stride (and a second one shifted by one element for bfloat16 taps at odd
  * offsets), channels padded with zeros to a multiple of the K tile.  Both need `workspace`
  * (device memory, 256-byte aligned, contents destroyed) of pgk_conv1d_workspace_bytes(...)

@@ -1144,9 +1144,15 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
     const int64_t es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
     if ((long double)B * Cout * pl.Lout >= 4.6e18L || (long double)B * Cin * L >= 4.6e18L) return PGK_ERR_UNSUPPORTED;
     // The weights are always regrouped into the workspace, y and the bias may start on any element;
-    // only an input that the kernels read in place has to start on a 16-byte boundary.
+    // only an input that the kernels read in place has to start on a 16-byte boundary -- not where it is copied
+    // through registers, which take any element, nor where the outputs are no whole chunks, whose tile bases lie off
+    // that boundary anyway: the direct copies take 4-byte ones, the registers the rest.
     const bool reads_x_in_place = pl.strips || (!pl.table && pl.Lp == 0);
-    if (pl.fast && reads_x_in_place && !pl.reg && !aligned16(x)) pl.fast = false;
+    const bool ragged_strips = pl.strips && pl.Lout % (16 / es) != 0;
+    if (pl.fast && reads_x_in_place && !pl.reg && !aligned16(x)) {
+        if (!ragged_strips) pl.fast = false;
+        else if (reinterpret_cast<uintptr_t>(x) & 3u) pl.reg = true;
+    }
 
     GemmArgs a{};
     a.bias = bias; a.C = y; a.ws = nullptr; a.rs_part = nullptr;
@@ -1202,7 +1208,7 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
             }
         }
         const Path path = pl.reg ? Path{true, pl.kind, pl.tile}
-                                 : choose_path(aligned16(wr) && aligned16(bsrc), Cout, pl.Lout, cin_k * Kw, dtype, B, pl.kind, false, ldb);
+                                 : choose_path(aligned16(wr) && (ragged_strips || aligned16(bsrc)), Cout, pl.Lout, cin_k * Kw, dtype, B, pl.kind, false, ldb);
         if (!path.mfma) return PGK_ERR_UNSUPPORTED;   // the plan has checked what the kernel needs
         a.A = wr; a.B = bsrc;
         a.a_batch_stride = 0;

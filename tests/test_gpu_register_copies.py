@@ -20,7 +20,7 @@ def pgk():
 
 def _inside(values, offset=0):
     """The values as the middle of a buffer of NaN, `offset` elements from a 16-byte boundary on."""
-    buf = torch.full((values.numel() + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    buf = torch.full((values.numel() + 64,), float("nan"), dtype=values.dtype, device="cuda")
     view = buf[32 + offset:32 + offset + values.numel()].view(values.shape)
     view.copy_(values)
     return view
@@ -54,6 +54,19 @@ def test_odd_rows_exact(pgk, M, N, K, batch, bt):
     # (row sums of integers: exact while below 2^24)
     if 49 * K * N < 2 ** 24 * 16:
         assert torch.allclose(rs.double(), ref.sum(-1), rtol=1e-6, atol=0.5)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("offset", [1, 2, 3])
+@pytest.mark.parametrize("B,Cin,L,Cout,Kw,pad,dil", [(2, 64, 1001, 64, 3, 2, 2), (1, 64, 1002, 128, 1, 0, 1), (1, 128, 515, 256, 3, 1, 1)])
+def test_convolution_of_an_input_on_any_element_exact(pgk, dtype, offset, B, Cin, L, Cout, Kw, pad, dil):
+    g = torch.Generator(device="cuda").manual_seed(L)
+    x = torch.randint(-7, 8, (B, Cin, L), generator=g, device="cuda").to(dtype)
+    w = torch.randint(-7, 8, (Cout, Cin, Kw), generator=g, device="cuda").to(dtype)
+    y = pgk.conv1d(_inside(x, offset), w, None, ACT_NONE, 1, pad, dil)
+    xp = torch.nn.functional.pad(x.double(), (pad, pad))
+    ref = torch.stack([sum(w[:, :, k].double() @ xp[b, :, k * dil:k * dil + y.shape[2]].contiguous() for k in range(Kw)) for b in range(B)])
+    assert torch.equal(y, ref.to(dtype))
 
 
 @pytest.mark.parametrize("B,Cin,L,Cout,Kw,pad,dil", [
