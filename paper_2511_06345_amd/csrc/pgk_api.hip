@@ -239,6 +239,10 @@ AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype)
     auto slices_for = [&](long double n_tiles, long double goal) {
         int64_t n = 1;
         while (n < s_max && n_tiles * n < 0.95L * goal) ++n;      // (250 tiles: two slices, not three)
+        // The goal is also what the chip holds at once (but for skinny tiles): a few workgroups more run as a round of
+        // their own, and one slice less, in one round, is done sooner (in slices by the goal / one less: fp32 8 x [256 x 384 x 64992] 923 / 646 us,
+        // 700 x 900 x 9000 122 / 94, bf16 10 x [512 x 500 x 20000] 200 / 135).
+        if (skinny_tile_kind(M, N) < 0 && n >= 4 && n_tiles * n > goal) --n;
         return n;
     };
     int64_t s = slices_for(tiles, target);
@@ -258,8 +262,13 @@ AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype)
                                           : dtype == PGK_DTYPE_BF16 && other == pgk::TILE_LARGE ? 1.0L
                                                                                                  : 2.0L) * kNumCUs;
         const int64_t s_other = slices_for(tiles_of(other), other_target);
+        // (A large tile that fits in one round is better than the model has it.  bf16: 8 x [256 x 384 x 64992] on small
+        // tiles, estimated at 0.89 of it, 184 us, on large ones 167.  fp32, whose fit is that of the fp32 instruction: the factor
+        // of auto_tile_kind; 9 x [256 x 130 x 53517] 409 and 366, 16 x [128 x 192 x 24994] 194 and 173.)
+        const bool one_round = kind == pgk::TILE_LARGE && tiles * s <= target;
+        const double margin = !one_round ? 0.94 : dtype == PGK_DTYPE_BF16 ? 0.88 : 0.78;
         const bool other_allowed = other == pgk::TILE_SMALL || !large_tile_mostly_empty(M, N, dtype);
-        if (other_allowed && K / s >= 1024 && K / s_other >= 1024 && estimate(other, s_other) < 0.94 * estimate(kind, s)) {
+        if (other_allowed && K / s >= 1024 && K / s_other >= 1024 && estimate(other, s_other) < margin * estimate(kind, s)) {
             kind = other;
             s = s_other;
         }
