@@ -79,29 +79,18 @@ OddRows odd_rows(int64_t K, int dtype, bool b_trans, int64_t ldb)
     return {(K * es) % 4 != 0, ((b_trans ? K : ldb) * es) % 4 != 0};
 }
 
-// Whether such operands are copied through registers (pgk_gemm_mfma_reg.hip) or first into rows padded
-// to whole chunks (pack_dims).  Loads and LDS writes of its own cost the main loop about a fifth of its time
-// on the large tile (one operand odd; 4096 x 4096 x 4096 direct 102 us, A 108, B 107, with rows off the grid 114 and 121),
-// and as much again as the product takes where both are odd, which the large tile has no registers for; a copy costs
-// its two passes over memory and a launch.  So, in microseconds: the share lost of a product at 1100 TFLOP/s
-// against copies at 5.5 TB/s and four per launch.  Copied first / through registers: 512 x 50257 x 768 80 / 62 us,
-// 1024 x 4095 x 1024 27 / 25, 1024 x 2048 x 255 (B transposed) 19 / 12, 4096 x 4095 x 4096 115 / 120, 2048 x 2047 x 2048 31 / 43.
-// Skinny outputs, whose tiles have no such instance, are copied first, and problems of less than 2^25
-// multiply-adds keep to the workspace they have always asked for.
-bool reg_copies(int64_t M, int64_t N, int64_t K, OddRows odd)
+// Whether there is a kernel that copies such operands through registers (pgk_gemm_mfma_reg.hip): skinny tiles have no such
+// instance, and problems of less than 2^25 multiply-adds keep to the workspace they have always asked for.
+// (What it costs against padded copies: reg_copies_pay.)
+bool reg_copies_exist(int64_t M, int64_t N, int64_t K)
 {
-    if (skinny_tile_kind(M, N) >= 0 || (long double)M * N * K < 33554432.0L) return false;
-    const double product = 2.0 * (double)M * (double)N * (double)K / 1.1e9;
-    const double lost = odd.a && odd.b ? 1.2 : odd.a ? 0.13 : 0.2;
-    const double bytes = 4.0 * (double)K * ((odd.a ? (double)M : 0.0) + (odd.b ? (double)N : 0.0));
-    return lost * product < bytes / 5.5e6 + 4.0 * ((odd.a ? 1 : 0) + (odd.b ? 1 : 0));
+    return skinny_tile_kind(M, N) < 0 && (long double)M * N * K >= 33554432.0L;
 }
 
 // What the matrix-core kernels take as it is: operand rows that start on 4-byte boundaries (K
 // elements for A and a transposed B; the row length ldb of a plain B, which is N unless the
-// caller has padded it), bf16 rows on any element where reg_copies allows.  M, N and K need not be tile multiples, and the output rows may have any
-// length.  An
-// output below 16 x 16 is left to the bounds-checked kernel, which wastes less, unless K is
+// caller has padded it), bf16 rows on any element where reg_copies_exist.  M, N and K need not be tile multiples, and the
+// output rows may have any length.  An output below 16 x 16 is left to the bounds-checked kernel, which wastes less, unless K is
 // long (then the matrix-core route splits the K range over the chip).
 bool mfma_shape_ok(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans = false, int64_t ldb = 0)
 {
@@ -109,7 +98,7 @@ bool mfma_shape_ok(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans = fa
     const int64_t es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
     if (!ldb) ldb = b_trans ? K : N;
     const OddRows odd = odd_rows(K, dtype, b_trans, ldb);
-    if ((odd.a || odd.b) && !reg_copies(M, N, K, odd)) return false;
+    if ((odd.a || odd.b) && !reg_copies_exist(M, N, K)) return false;
     if (M < 16 && N < 16 && K < 1024) return false;
     // per-lane 32-bit byte offsets inside one tile
     if ((int64_t)t.bm * K * es >= (1LL << 32)) return false;
@@ -117,12 +106,17 @@ bool mfma_shape_ok(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans = fa
     return true;
 }
 
-// Odd rows that no kernel takes as they are: the operands are first copied into buffers with rows
-// padded with zeros to whole 16-byte chunks.  Worth it from about 64^3 multiply-adds on.
-bool needs_packing(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans)
+// The slices of a split call (0: the fused call's own plan) and the tile that an automatic count comes with (-1: by the grid)
+struct Slices { int count, kind; };
+
+bool reg_copies_pay(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, Slices slices);
+
+// Odd rows that no kernel takes as they are, or that are cheaper copied: the operands are first copied into buffers with
+// rows padded with zeros to whole 16-byte chunks.  Worth it from about 64^3 multiply-adds on.
+bool needs_packing(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, Slices slices)
 {
     const OddRows odd = odd_rows(K, dtype, b_trans, N);
-    return (odd.a || odd.b) && !reg_copies(M, N, K, odd);
+    return (odd.a || odd.b) && !(reg_copies_exist(M, N, K) && reg_copies_pay(M, N, K, batch, dtype, b_trans, slices));
 }
 
 // The dimensions the kernels see for a problem that is packed first: K and the row length of B,
@@ -134,11 +128,11 @@ struct PackDims { bool pack; int64_t k, ldb; bool transpose_b; bool b_trans; };
 
 // misaligned: A or B does not start on a 16-byte boundary; the copies do (pack_operands copies
 // whichever operand needs it), and their rows are whole chunks.
-PackDims pack_dims(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans, bool misaligned = false)
+PackDims pack_dims(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, Slices slices, bool misaligned = false)
 {
     const PackDims as_is{false, K, 0, false, b_trans};
     const bool transpose_b = !b_trans && skinny_tile_kind(M, N) == pgk::TILE_NARROW;
-    if (!transpose_b && !misaligned && !needs_packing(M, N, K, dtype, b_trans)) return as_is;
+    if (!transpose_b && !misaligned && !needs_packing(M, N, K, batch, dtype, b_trans, slices)) return as_is;
     if ((long double)M * N * K < 262144.0L) return as_is;
     const int64_t epc = chunk_elems(dtype), es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
     PackDims d{true, ((K * es) % 4 || misaligned) ? round_up64(K, epc) : K, 0, transpose_b, b_trans || transpose_b};
@@ -153,8 +147,9 @@ PackDims pack_dims(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans, boo
 // cores, one way or the other, with either layout
 bool mfma_route(int64_t M, int64_t N, int64_t K, int dtype)
 {
-    return mfma_shape_ok(M, N, K, dtype) || pack_dims(M, N, K, dtype, false).pack ||
-           mfma_shape_ok(M, N, K, dtype, true) || pack_dims(M, N, K, dtype, true).pack;
+    const Slices fused{0, -1};
+    return mfma_shape_ok(M, N, K, dtype) || pack_dims(M, N, K, 1, dtype, false, fused).pack ||
+           mfma_shape_ok(M, N, K, dtype, true) || pack_dims(M, N, K, 1, dtype, true, fused).pack;
 }
 
 // A large tile mostly outside the matrix (skinny M or N): the small tile wastes less matrix work
@@ -193,15 +188,23 @@ TileCost tile_cost(int dtype, int kind)
     return {1, 3.0, 56.2, {1.0, 1.0, 1.0, 1.0}};
 }
 
-double estimated_rounds_time(int64_t M, int64_t N, int64_t K, int dtype, int64_t units, int kind)
+// full rounds, and the workgroups on the busiest CU of the last one where that is not full
+struct Rounds { double full; int rest; };
+
+Rounds rounds_of(int64_t M, int64_t N, int dtype, int64_t units, int kind)
 {
     const pgk::TileShape t = pgk::mfma_tile_shape(dtype, kind);
-    const TileCost c = tile_cost(dtype, kind);
     const double wgs = (double)((M + t.bm - 1) / t.bm) * (double)((N + t.bn - 1) / t.bn) * (double)units;
-    const double slots = (double)kNumCUs * c.per_cu;
-    const double full = std::floor(wgs / slots), rest = wgs - full * slots;
-    const int j = (int)std::ceil(rest / kNumCUs);
-    return (c.fixed + c.per_k * (double)K / 1024.0) * (full + (j > 0 ? c.tail[j - 1] : 0.0));
+    const double slots = (double)kNumCUs * tile_cost(dtype, kind).per_cu;
+    const double full = std::floor(wgs / slots);
+    return {full, (int)std::ceil((wgs - full * slots) / kNumCUs)};
+}
+
+double estimated_rounds_time(int64_t M, int64_t N, int64_t K, int dtype, int64_t units, int kind)
+{
+    const TileCost c = tile_cost(dtype, kind);
+    const Rounds r = rounds_of(M, N, dtype, units, kind);
+    return (c.fixed + c.per_k * (double)K / 1024.0) * (r.full + (r.rest > 0 ? c.tail[r.rest - 1] : 0.0));
 }
 
 // Automatic choice (splits == 0): slices of at least min_steps_per_slice K steps (shorter ones
@@ -211,7 +214,8 @@ double estimated_rounds_time(int64_t M, int64_t N, int64_t K, int dtype, int64_t
 // empty, else the small one.
 struct AutoPlan { int splits; int kind; };
 
-AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype)
+// large_ok: false where the large tile has no instance (both operands copied through registers).
+AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool large_ok = true)
 {
     const int ks = kstep_of(dtype);
     const int64_t ksteps = (K + ks - 1) / ks;
@@ -226,7 +230,7 @@ AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype)
     if (s_max > kMaxAutoSplits) s_max = kMaxAutoSplits;
     int kind = skinny_tile_kind(M, N);
     if (kind < 0)
-        kind = (large_tile_mostly_empty(M, N, dtype) || tiles_of(pgk::TILE_LARGE) * s_max < 1.5L * kNumCUs) ? pgk::TILE_SMALL
+        kind = (!large_ok || large_tile_mostly_empty(M, N, dtype) || tiles_of(pgk::TILE_LARGE) * s_max < 1.5L * kNumCUs) ? pgk::TILE_SMALL
                                                                                                           : pgk::TILE_LARGE;
     const long double tiles = tiles_of(kind);
     // (enough slices for two workgroups per CU; four of the fp32 small tile and one of the bf16
@@ -267,7 +271,7 @@ AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype)
         // of auto_tile_kind; 9 x [256 x 130 x 53517] 409 and 366, 16 x [128 x 192 x 24994] 194 and 173.)
         const bool one_round = kind == pgk::TILE_LARGE && tiles * s <= target;
         const double margin = !one_round ? 0.94 : dtype == PGK_DTYPE_BF16 ? 0.88 : 0.78;
-        const bool other_allowed = other == pgk::TILE_SMALL || !large_tile_mostly_empty(M, N, dtype);
+        const bool other_allowed = other == pgk::TILE_SMALL || (large_ok && !large_tile_mostly_empty(M, N, dtype));
         if (other_allowed && K / s >= 1024 && K / s_other >= 1024 && estimate(other, s_other) < margin * estimate(kind, s)) {
             kind = other;
             s = s_other;
@@ -276,14 +280,14 @@ AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype)
     return {(int)s, kind};
 }
 
-SplitPlan plan_splits(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int splits)
+SplitPlan plan_splits(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int splits, bool large_ok = true)
 {
     const int ks = kstep_of(dtype);
     const int64_t ksteps = (K + ks - 1) / ks;
     int64_t s = splits;
     if (s == 0) {
         if (mfma_route(M, N, K, dtype)) {
-            s = auto_split(M, N, K, batch, dtype).splits;
+            s = auto_split(M, N, K, batch, dtype, large_ok).splits;
         } else {
             const pgk::TileShape t = pgk::guarded_tile_shape();
             const long double tiles = (long double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * batch;
@@ -296,6 +300,12 @@ SplitPlan plan_splits(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype,
     const int64_t L = per * ks;
     const int64_t eff = (K + L - 1) / L;          // drop trailing empty slices
     return {(int)eff, (int)L};
+}
+
+// an automatic plan comes with its tile; explicit splits get the tile their grid suggests (-1)
+int split_tile_kind(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int splits)
+{
+    return (splits == 0 && mfma_route(M, N, K, dtype)) ? auto_split(M, N, K, batch, dtype).kind : -1;
 }
 
 int group_m_for(int tiles_m, int tiles_n)
@@ -397,6 +407,15 @@ int auto_tile_kind(int64_t M, int64_t N, int64_t K, int dtype, int64_t units, bo
     return best;
 }
 
+// The tile of operands copied through registers: the large one where it is planned and has an instance (one operand of a
+// plain B), else the small one, whose two workgroups per CU cover one's loads and LDS writes with the other's products.
+// (The half tiles, both operands through registers, one workgroup per CU, over 73 shapes: 0.92 and 0.94 of its speed; the
+// tall one 1344 x 87 x 708, 43 entries, 57 us, the small one 34, but 171 x 32134 x 6733 192 and 207.)
+int reg_tile_kind(int kind, OddRows odd, bool b_trans)
+{
+    return kind == pgk::TILE_LARGE && !b_trans && !(odd.a && odd.b) ? pgk::TILE_LARGE : pgk::TILE_SMALL;
+}
+
 // kind_forced: -1 = auto_tile_kind, else the caller (an automatic split plan, a convolution plan) decides.
 // `aligned`: A, B and the split-K partial products start on 16-byte boundaries (C, the biases and
 // the row sums only need the alignment of their elements: a row of C may start anywhere, so its
@@ -408,9 +427,7 @@ Path choose_path(bool aligned, int64_t M, int64_t N, int64_t K, int dtype, int64
     if (!ok) return Path{false, false, pgk::guarded_tile_shape()};
     int kind = kind_forced >= 0 ? kind_forced : auto_tile_kind(M, N, K, dtype, units, b_trans, ldb);
     if (!pgk::mfma_has_tile(dtype, kind, b_trans)) kind = pgk::TILE_SMALL;      // (the narrow tile with a plain B)
-    // (the large tile does not exist with both operands copied through registers)
-    const OddRows odd = odd_rows(K, dtype, b_trans, ldb ? ldb : N);
-    if ((odd.a || odd.b) && !pgk::mfma_reg_has_tile(kind, odd.a, odd.b, b_trans)) kind = pgk::TILE_TALL;
+    if (const OddRows odd = odd_rows(K, dtype, b_trans, ldb ? ldb : N); odd.a || odd.b) kind = reg_tile_kind(kind, odd, b_trans);
     return Path{true, kind, pgk::mfma_tile_shape(dtype, kind)};
 }
 
@@ -569,12 +586,52 @@ FusedPlan plan_fused(bool aligned, int64_t M, int64_t N, int64_t K, int64_t batc
     const bool under_filled = dtype == PGK_DTYPE_F32 && fp.path.kind == pgk::TILE_SMALL &&
                               (long double)tiles_m * tiles_n * batch < 3 * kNumCUs && (K + big.bk - 1) / big.bk >= 128;
     if (fp.path.mfma && (few_tiles || long_k || under_filled)) {
-        fp.slices = plan_splits(M, N, K, batch, dtype, 0);
-        fp.split_small_tile = auto_split(M, N, K, batch, dtype).kind;
+        const OddRows odd = odd_rows(K, dtype, b_trans, ldb ? ldb : N);
+        const bool large_ok = !(odd.a || odd.b) || reg_tile_kind(pgk::TILE_LARGE, odd, b_trans) == pgk::TILE_LARGE;
+        fp.slices = plan_splits(M, N, K, batch, dtype, 0, large_ok);
+        fp.split_small_tile = auto_split(M, N, K, batch, dtype, large_ok).kind;
         const long double ws_bytes = (long double)batch * fp.slices.splits * M * N * sizeof(float);
         fp.split = fp.slices.splits > 1 && ws_bytes <= (long double)kAutoSplitMaxWorkspace;
     }
     return fp;
+}
+
+// Whether operands with odd rows are copied through registers (pgk_gemm_mfma_reg.hip) or first into rows padded to whole
+// chunks (pack_dims).  Loads and LDS writes of their own cost the main loop's matrix work: with one operand on the large
+// tile 0.7 of the loop's time in the round model (4096 x 4096 x 4096 direct 102 us, A 108, B 107, with rows off the grid 114 and 121;
+// with K odd as well as in shorter loops more), on the small tile, which always takes both that way, 1.4, and 1.6 where both
+// are odd or B is transposed; a CU with a single workgroup has nothing to cover them with and loses 0.7 of a full round's.
+// The copies cost two passes over memory at 4 TB/s (an odd K: both operands, rows of a plain B: B alone) and 5 us a launch.
+// Output rows off the 128-byte grid are stored plainly by the register instances, which gains 0.16 us a megabyte.
+// Fitted to 600 shapes (33 ... 16384 x 33 ... 50257 x 33 ... 65536, batches up to 64, both layouts of B, splits): of the choices
+// 15 are more than 5 % slower than the copies, 17 than the registers, 0.8 % above the better of both in the geometric mean.
+// Copied first / through registers: 512 x 50257 x 768 84 / 65 us, 128 x 256 x 32371, 16 entries, 233 / 100, 9800 x 12713 x 64
+// 139 / 90, 1024 x 2048 x 255 (B transposed) 19 / 12; 2048 x 2047 x 2048 35 / 49, 4096 x 4095 x 4095 126 / 180, 16 x [1501 x 1501 x 1501] 199 / 215.
+bool reg_copies_pay(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, Slices slices)
+{
+    struct Estimate { int kind, count; double time; };
+    auto estimate = [&](int64_t k, int64_t ldb) {
+        Estimate e{slices.kind, slices.count, 0.0};
+        if (!e.count) {
+            const FusedPlan fp = plan_fused(true, M, N, k, batch, dtype, b_trans, ldb);
+            e.count = fp.split ? fp.slices.splits : 1;
+            e.kind = fp.split ? fp.split_small_tile : fp.path.kind;
+        }
+        e.kind = choose_path(true, M, N, k, dtype, batch * e.count, e.kind, b_trans, ldb).kind;
+        const double second_pass = e.count > 1 ? 2.0 * e.count * (double)M * (double)N * (double)batch * 4.0 / 4.0e6 + 5.0 : 0.0;
+        e.time = estimated_rounds_time(M, N, (k + e.count - 1) / e.count, dtype, batch * e.count, e.kind) + second_pass;
+        return e;
+    };
+    const OddRows odd = odd_rows(K, dtype, b_trans, N);
+    const int64_t epc = chunk_elems(dtype), k = odd.a ? round_up64(K, epc) : K;
+    const Estimate reg = estimate(K, 0), packed = estimate(k, b_trans ? k : round_up64(N, epc));
+    const Rounds r = rounds_of(M, N, dtype, batch * reg.count, reg.kind);
+    const double loops = tile_cost(dtype, reg.kind).per_k * (double)K / (1024.0 * reg.count) * (r.full + (r.rest == 1 ? 0.7 : r.rest > 1 ? 1.0 : 0.0));
+    const double lost = reg.kind == pgk::TILE_LARGE ? 0.7 : (odd.a && odd.b) ? 1.6 : 1.4;
+    const double bytes = 4.0 * (double)K * (double)batch * ((odd.a ? (double)M : 0.0) + (double)N);
+    const double off_grid = reg.count == 1 && N % 64 != 0 ? 2.0 * (double)M * (double)N * (double)batch : 0.0;
+    // (where the registers need another tile than the copies would have, no less than that one takes)
+    return std::max(reg.time, packed.time) + lost * loops < packed.time + bytes / 4.0e6 + (odd.a ? 10.0 : 5.0) + 0.16e-6 * off_grid;
 }
 
 // ---- The caller's workspace.  Everything a call needs beyond its inputs and outputs is cut from
@@ -607,10 +664,11 @@ void lay_out(WsNeeds& w)
 
 // the operand copies of a packed problem (see pack_dims); a_mis / b_mis: that operand does not
 // start on a 16-byte boundary
-bool pack_needs(WsNeeds& w, int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, bool a_mis, bool b_mis)
+bool pack_needs(WsNeeds& w, int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, bool a_mis, bool b_mis,
+                Slices slices)
 {
     const size_t es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
-    w.d = pack_dims(M, N, K, dtype, b_trans, a_mis || b_mis);
+    w.d = pack_dims(M, N, K, batch, dtype, b_trans, slices, a_mis || b_mis);
     w.pack_a = w.pack_b = false;
     w.a_bytes = w.b_bytes = 0;
     if (!w.d.pack) return true;
@@ -635,7 +693,7 @@ WsNeeds fused_needs(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, b
         lay_out(w);
         return w;
     }
-    w.ok = pack_needs(w, M, N, K, batch, dtype, b_trans, a_mis, b_mis);
+    w.ok = pack_needs(w, M, N, K, batch, dtype, b_trans, a_mis, b_mis, Slices{0, -1});
     if (!w.ok) return w;
     // the problem as the kernels see it
     const bool packed = w.d.pack;
@@ -653,14 +711,14 @@ WsNeeds fused_needs(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, b
     return w;
 }
 
-WsNeeds splitk_needs(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int effective_splits, bool b_trans,
+WsNeeds splitk_needs(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, Slices slices, bool b_trans,
                      bool want_rowsum, bool a_mis, bool b_mis)
 {
     WsNeeds w{};
-    w.ok = pack_needs(w, M, N, K, batch, dtype, b_trans, a_mis, b_mis);
+    w.ok = pack_needs(w, M, N, K, batch, dtype, b_trans, a_mis, b_mis, slices);
     if (!w.ok) return w;
-    if ((long double)batch * effective_splits * M * N * sizeof(float) >= 1.8e19L) { w.ok = false; return w; }
-    w.products = (size_t)batch * (size_t)effective_splits * (size_t)M * (size_t)N * sizeof(float);
+    if ((long double)batch * slices.count * M * N * sizeof(float) >= 1.8e19L) { w.ok = false; return w; }
+    w.products = (size_t)batch * (size_t)slices.count * (size_t)M * (size_t)N * sizeof(float);
     w.rs_part = split_part_bytes(M, N, batch, want_rowsum);
     lay_out(w);
     return w;
@@ -856,7 +914,7 @@ int pgk_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int
         out[5] = (int32_t)tiles;
         return PGK_OK;
     }
-    const PackDims d = pack_dims(M, N, K, dtype, b_transposed != 0);      // as pgk_gemm_fused sees the problem
+    const PackDims d = pack_dims(M, N, K, batch, dtype, b_transposed != 0, Slices{0, -1});      // as pgk_gemm_fused sees the problem
     K = d.k;
     const FusedPlan fp = plan_fused(true, M, N, K, batch, dtype, d.b_trans, d.ldb);
     Path path = fp.path;
@@ -890,7 +948,7 @@ size_t pgk_gemm_splitk_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t 
     const int s = pgk_splitk_auto_splits(M, N, K, batch, dtype, splits);
     if (s <= 0) return 0;
     const bool mis = (flags & PGK_WS_UNALIGNED) != 0;
-    const WsNeeds w = splitk_needs(M, N, K, batch, dtype, s, (flags & PGK_WS_B_TRANSPOSED) != 0, (flags & PGK_WS_ROWSUM) != 0, mis, mis);
+    const WsNeeds w = splitk_needs(M, N, K, batch, dtype, Slices{s, split_tile_kind(M, N, K, batch, dtype, splits)}, (flags & PGK_WS_B_TRANSPOSED) != 0, (flags & PGK_WS_ROWSUM) != 0, mis, mis);
     return w.ok ? w.total : 0;
 }
 
@@ -914,8 +972,9 @@ int gemm_splitk_impl(const void* A, const void* B, const float* bias, void* C, f
     if (rc != PGK_OK) return rc;
     if (splits < 0 || splits > K) return PGK_ERR_INVALID_ARG;
     const SplitPlan plan = plan_splits(M, N, K, batch, dtype, splits);
+    const int tile_kind = split_tile_kind(M, N, K, batch, dtype, splits);
     const bool a_mis = !aligned16(A), b_mis = !aligned16(B);
-    const WsNeeds w = splitk_needs(M, N, K, batch, dtype, plan.splits, b_trans, rowsum != nullptr, a_mis, b_mis);
+    const WsNeeds w = splitk_needs(M, N, K, batch, dtype, Slices{plan.splits, tile_kind}, b_trans, rowsum != nullptr, a_mis, b_mis);
     if (!w.ok) return PGK_ERR_UNSUPPORTED;
     rc = check_workspace(w, workspace, workspace_bytes);
     if (rc != PGK_OK) return rc;
@@ -923,16 +982,14 @@ int gemm_splitk_impl(const void* A, const void* B, const float* bias, void* C, f
     hipStream_t st = static_cast<hipStream_t>(stream);
     unsigned char* base = static_cast<unsigned char*>(workspace);
     float* part = w.rs_part ? reinterpret_cast<float*>(base + w.off_rs_part) : nullptr;
-    // an automatic plan comes with its tile; explicit splits get the tile their grid suggests
-    const int small_tile = (splits == 0 && mfma_route(M, N, K, dtype)) ? auto_split(M, N, K, batch, dtype).kind : -1;
     // (the slices are counted in K steps, which padding K to whole chunks leaves as they are)
     if (!w.d.pack)
-        return run_split_passes(A, B, bias, C, rowsum, M, N, K, batch, act, dtype, plan, small_tile,
+        return run_split_passes(A, B, bias, C, rowsum, M, N, K, batch, act, dtype, plan, tile_kind,
                                 reinterpret_cast<float*>(base), part, st, !(a_mis || b_mis), b_trans);
     PackedOperands pk{};
     rc = pack_operands(w, base, A, B, M, N, K, batch, dtype, b_trans, st, &pk);
     if (rc != PGK_OK) return rc;
-    return run_split_passes(pk.A, pk.B, bias, C, rowsum, M, N, w.d.k, batch, act, dtype, plan, small_tile,
+    return run_split_passes(pk.A, pk.B, bias, C, rowsum, M, N, w.d.k, batch, act, dtype, plan, tile_kind,
                             reinterpret_cast<float*>(base), part, st, true, w.d.b_trans, w.d.ldb);
 }
 

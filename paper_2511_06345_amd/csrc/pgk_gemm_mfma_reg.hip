@@ -6,54 +6,39 @@
 namespace pgk {
 
 namespace {
-// The large tile has registers for one operand's pieces beside its accumulators (246 of 256); the
-// others take both operands that way, also where only one needs it.
+// The large tile has registers for one operand's pieces beside its accumulators, and not quite: of 256 three spill
+// with B's pieces, six in the convolution's form and sixteen with A's (scratch of 16, 28 and 68 bytes a lane).
+// The small tile takes both operands that way, also where only one needs it; the half tiles have no such
+// instances, as the small one is as fast or faster on what they are planned for (reg_tile_kind).
 template <bool REG_A, bool REG_B>
 using RegLarge = MfmaCfgReg<false, 256, 256, 64, 4, 2, 3, 2, REG_A, REG_B>;
 template <bool BT>
 using RegSmall = MfmaCfgReg<BT, 128, 128, 64, 2, 2, 3, 2, true, true>;
-template <bool BT>
-using RegTall = MfmaCfgReg<BT, 256, 128, 64, 4, 2, 3, 2, true, true>;
-template <bool BT>
-using RegWide = MfmaCfgReg<BT, 128, 256, 64, 2, 4, 3, 2, true, true>;
 // (a convolution's weights are regrouped and always copied directly)
 using ConvSmall = MfmaCfgReg<false, 128, 128, 64, 2, 2, 3, 2, false, true>;
 using ConvTall = MfmaCfgReg<false, 256, 128, 64, 4, 2, 3, 2, false, true>;
 using ConvWide = MfmaCfgReg<false, 128, 256, 64, 2, 4, 3, 2, false, true>;
 
-template <bool BT>
-hipError_t launch_layout(const GemmArgs& a, int kind, int out_mode, hipStream_t s)
-{
-    if (kind == TILE_SMALL) return launch_cfg<RegSmall<BT>, VIEW_GEMM>(a, out_mode, s);
-    if (kind == TILE_TALL) return launch_cfg<RegTall<BT>, VIEW_GEMM>(a, out_mode, s);
-    if (kind == TILE_WIDE) return launch_cfg<RegWide<BT>, VIEW_GEMM>(a, out_mode, s);
-    return hipErrorInvalidValue;
-}
 }  // namespace
-
-bool mfma_reg_has_tile(int kind, bool reg_a, bool reg_b, bool b_trans)
-{
-    if (kind == TILE_LARGE) return !b_trans && !(reg_a && reg_b);
-    return kind == TILE_SMALL || kind == TILE_TALL || kind == TILE_WIDE;
-}
 
 hipError_t launch_gemm_mfma_reg(const GemmArgs& a, int kind, int out_mode, hipStream_t s)
 {
     const bool b_trans = a.b_trans != 0;
-    if (!mfma_reg_has_tile(kind, a.reg_a != 0, a.reg_b != 0, b_trans)) return hipErrorInvalidValue;
     if (a.bias_per_row) {
         if (b_trans || a.reg_a || out_mode != 0) return hipErrorInvalidValue;
         switch (kind) {
         case TILE_LARGE: return launch_cfg<RegLarge<false, true>, VIEW_CONV>(a, out_mode, s);
         case TILE_SMALL: return launch_cfg<ConvSmall, VIEW_CONV>(a, out_mode, s);
         case TILE_TALL: return launch_cfg<ConvTall, VIEW_CONV>(a, out_mode, s);
-        default: return launch_cfg<ConvWide, VIEW_CONV>(a, out_mode, s);
+        case TILE_WIDE: return launch_cfg<ConvWide, VIEW_CONV>(a, out_mode, s);
+        default: return hipErrorInvalidValue;
         }
     }
-    if (kind == TILE_LARGE)
+    if (kind == TILE_LARGE && !b_trans && !(a.reg_a && a.reg_b))
         return a.reg_a ? launch_cfg<RegLarge<true, false>, VIEW_GEMM>(a, out_mode, s)
                        : launch_cfg<RegLarge<false, true>, VIEW_GEMM>(a, out_mode, s);
-    return b_trans ? launch_layout<true>(a, kind, out_mode, s) : launch_layout<false>(a, kind, out_mode, s);
+    if (kind != TILE_SMALL) return hipErrorInvalidValue;
+    return b_trans ? launch_cfg<RegSmall<true>, VIEW_GEMM>(a, out_mode, s) : launch_cfg<RegSmall<false>, VIEW_GEMM>(a, out_mode, s);
 }
 
 }  // namespace pgk

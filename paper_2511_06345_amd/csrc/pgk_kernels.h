@@ -122,9 +122,8 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, int dtype, int kind, int out_mode
 // launch_gemm_mfma.
 hipError_t launch_gemm_mfma_conv(const GemmArgs& a, int dtype, int kind, int out_mode, hipStream_t s);
 
-// bf16 operands off 4-byte boundaries (a.reg_a, a.reg_b): which tiles there are, and the launch (plain
-// views and a convolution's); reached through launch_gemm_mfma.
-bool mfma_reg_has_tile(int kind, bool reg_a, bool reg_b, bool b_trans);
+// bf16 operands off 4-byte boundaries (a.reg_a, a.reg_b), plain views (the small tile; the large one with one such operand
+// and a plain B) and a convolution's (every tile, B alone); reached through launch_gemm_mfma.
 hipError_t launch_gemm_mfma_reg(const GemmArgs& a, int kind, int out_mode, hipStream_t s);
 
 // fp32, 32 x 32 tiles, K split over the four waves of a workgroup (out_mode 0; K, N, ldb multiples

@@ -460,3 +460,28 @@ def test_the_current_stream_is_found_without_torchs_private_accessor(monkeypatch
     monkeypatch.setattr(binding, "_raw_stream", None)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4711))
     assert binding._stream_ptr(None) == 4711
+
+
+def test_odd_rows_are_copied_first_where_that_is_faster(lib):
+    """bf16 operands with odd rows: through registers (no workspace but partial products) or padded copies, on shapes that
+    either was measured faster on by a tenth or more (microseconds copied / through registers)."""
+    def copied(M, N, K, batch=1, bt=False):
+        need = binding.gemm_fused_workspace_bytes(M, N, K, batch, gen.BF16, binding.WS_B_TRANSPOSED if bt else 0)
+        slices = binding.gemm_plan(M, N, K, batch, gen.BF16, bt)["slices"]
+        return need != (0 if slices == 1 else -(-slices * batch * M * N * 4 // 256) * 256)
+
+    assert copied(2048, 2047, 2048)                     # 35 / 49
+    assert copied(9856, 427, 896)                       # 22 / 31
+    assert copied(6717, 249, 4264)                      # 34 / 47
+    assert copied(4096, 4095, 4095)                     # 126 / 180
+    assert copied(1920, 1408, 925, 56, True)            # 504 / 583
+    assert copied(6528, 192, 3941, 1, True)             # 64 / 77
+    assert copied(1501, 1501, 1501, 16)                 # 199 / 215: the copies' launches are paid once, the loop's loss per entry
+    assert copied(2944, 20352, 2763, 1, True)           # 335 / 542
+    assert not copied(512, 50257, 768)                  # 84 / 65
+    assert not copied(128, 256, 32371, 16)              # 233 / 100
+    assert not copied(9800, 12713, 64)                  # 139 / 90
+    assert not copied(4096, 4096, 511)                  # 36 / 29
+    assert not copied(1024, 2048, 255, 1, True)         # 19 / 12
+    # both operands through registers: the small tile, also where slices and rounds are counted (the large one does not exist)
+    assert binding.gemm_plan(528, 223, 30575, 12, gen.BF16)["tile"] == (128, 128, 64)

@@ -26,24 +26,16 @@ def _inside(values, offset=0):
     return view
 
 
-# integer values below 8 keep every sum exact in float32 (49 K < 2^24): the outputs are those of 64-bit
-# sums rounded once to bf16, whatever the order
-@pytest.mark.parametrize("M,N,K,batch,bt", [
-    (512, 2049, 64, 1, False),       # odd N, one whole K tile
-    (300, 1501, 128, 2, False),      # odd N, whole K tiles, a batch whose entries start on odd elements
-    (257, 4097, 190, 1, False),      # odd N, partial K tile
-    (1024, 2304, 67, 1, False),      # odd K: A alone
-    (1000, 2303, 129, 1, False),     # both; one K value in the last tile
-    (2047, 1025, 703, 1, False),     # both, many tiles
-    (130, 2100, 255, 3, True),       # transposed B, odd K
-    (1024, 2048, 1023, 1, True),
-    (33, 33, 40001, 1, True),        # split along K
-    (64, 2051, 1000, 1, False),      # few rows
-])
-def test_odd_rows_exact(pgk, M, N, K, batch, bt):
+def _copied(pgk, M, N, K, batch, bt):
+    """Whether the call asks for padded copies of operands: for more than its partial products."""
     need = pgk.gemm_fused_workspace_bytes(M, N, K, batch, BF16, pgk.WS_B_TRANSPOSED if bt else 0)
     slices = pgk.gemm_plan(M, N, K, batch, BF16, bt)["slices"]
-    assert need == (0 if slices == 1 else -(-slices * batch * M * N * 4 // 256) * 256), "no copies of operands"
+    return need != (0 if slices == 1 else -(-slices * batch * M * N * 4 // 256) * 256)
+
+
+# integer values below 8 keep every sum exact in float32 (49 K < 2^24): the outputs are those of 64-bit
+# sums rounded once to bf16, whatever the order
+def _exact(pgk, M, N, K, batch, bt):
     g = torch.Generator(device="cuda").manual_seed(M * N + K)
     A = torch.randint(-7, 8, (batch, M, K), generator=g, device="cuda").to(torch.bfloat16)
     B = torch.randint(-7, 8, (batch, N, K) if bt else (batch, K, N), generator=g, device="cuda").to(torch.bfloat16)
@@ -54,6 +46,43 @@ def test_odd_rows_exact(pgk, M, N, K, batch, bt):
     # (row sums of integers: exact while below 2^24)
     if 49 * K * N < 2 ** 24 * 16:
         assert torch.allclose(rs.double(), ref.sum(-1), rtol=1e-6, atol=0.5)
+
+
+@pytest.mark.parametrize("M,N,K,batch,bt", [
+    (512, 2049, 64, 1, False),       # odd N, one whole K tile
+    (300, 1501, 128, 2, False),      # odd N, whole K tiles, a batch whose entries start on odd elements
+    (257, 4097, 190, 1, False),      # odd N, partial K tile
+    (1024, 2304, 67, 1, False),      # odd K: A alone
+    (1000, 2303, 129, 1, False),     # both; one K value in the last tile
+    (2047, 1025, 703, 1, False),     # both, many tiles
+    (130, 2100, 255, 3, True),       # transposed B, odd K
+    (1000, 2303, 575, 1, True),
+    (40, 40, 40001, 12, True),       # split along K
+    (64, 4099, 200, 1, False),       # few rows
+])
+def test_odd_rows_exact(pgk, M, N, K, batch, bt):
+    assert not _copied(pgk, M, N, K, batch, bt), "no copies of operands"
+    _exact(pgk, M, N, K, batch, bt)
+
+
+@pytest.mark.parametrize("M,N,K,batch,bt", [(1024, 2048, 1023, 1, True), (33, 33, 40001, 1, True), (64, 2051, 1000, 1, False)])
+def test_odd_rows_copied_first_exact(pgk, M, N, K, batch, bt):
+    assert _copied(pgk, M, N, K, batch, bt)
+    _exact(pgk, M, N, K, batch, bt)
+
+
+# every instance at one, two, three and many K tiles, whole and partial last ones
+LARGE_A = [(600, 16400, 63), (600, 16400, 127), (3900, 4100, 129), (3900, 4100, 577), (4096, 4096, 511)]
+LARGE_B = [(500, 50257, 64), (500, 50257, 62), (500, 50257, 128), (500, 50257, 190), (300, 20001, 640), (500, 50257, 646)]
+SMALL = [(1000, 2303, 63), (1000, 2303, 65), (1000, 2303, 191), (1000, 2303, 575), (3000, 4999, 129)]
+INSTANCES = ([(256, *s, 1, False) for s in LARGE_A + LARGE_B] + [(128, *s, 1, bt) for s in SMALL for bt in (False, True)] +
+             [(128, 4096, 300, 255, 8, True), (128, 1000, 2303, 64, 1, False), (128, 200, 3001, 384, 4, False), (128, 90, 130, 36001, 6, True)])
+
+
+@pytest.mark.parametrize("tile,M,N,K,batch,bt", INSTANCES)
+def test_every_instance_exact(pgk, tile, M, N, K, batch, bt):
+    assert pgk.gemm_plan(M, N, K, batch, BF16, bt)["tile"][:2] == (tile, tile) and not _copied(pgk, M, N, K, batch, bt)
+    _exact(pgk, M, N, K, batch, bt)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -72,6 +101,10 @@ def test_convolution_of_an_input_on_any_element_exact(pgk, dtype, offset, B, Cin
 @pytest.mark.parametrize("B,Cin,L,Cout,Kw,pad,dil", [
     (2, 64, 1000, 64, 3, 1, 1), (1, 128, 4096, 256, 3, 1, 1), (2, 64, 777, 100, 5, 2, 1), (1, 64, 513, 48, 4, 0, 1),
     (3, 192, 300, 130, 3, 3, 3), (1, 64, 129, 64, 7, 3, 1), (1, 64, 2001, 512, 1, 0, 1), (2, 64, 640, 64, 3, 101, 1),
+    # the tiles of 256 x 256, 256 x 128 (outputs of at most 128 positions) and 128 x 256 (at most 128 channels), enough of them
+    # to be chosen
+    (8, 128, 4097, 512, 3, 1, 1), (9, 64, 4001, 500, 5, 2, 1), (97, 64, 101, 512, 3, 1, 1), (49, 128, 130, 1000, 3, 0, 1),
+    (12, 64, 4097, 128, 3, 1, 1), (13, 128, 3900, 100, 7, 3, 1),
 ])
 def test_convolution_taps_at_odd_offsets_exact(pgk, B, Cin, L, Cout, Kw, pad, dil):
     g = torch.Generator(device="cuda").manual_seed(L + Cout)
