@@ -542,9 +542,8 @@ bool stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool
     // 11008 x 8192 fp32 8.0e-7 with four waves, 6.5e-7 in slices.  (The time is the same with four, eight or sixteen.)
     pl->waves = K > 8192 ? 16 : b_trans || K > 1024 ? 8 : 4;
     const int64_t cols = 16 * pl->blocks, groups = (N + cols - 1) / cols;
-    if (groups * batch > kMaxDim) return false;
-    pl->groups = (int)groups;
-    return true;
+    pl->groups = (int)std::min<int64_t>(groups, kMaxDim);
+    return pgk::stream_launch_fits(*pl, batch);
 }
 
 // What pgk_gemm_fused does with a problem: the kernel and tile of the single-pass route, and

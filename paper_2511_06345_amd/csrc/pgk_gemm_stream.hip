@@ -418,7 +418,7 @@ hipError_t launch_gemm_stream(const StreamPlan& pl, const void* A, const void* B
                               float* part, int M, int N, int K, int batch, int act, int dtype, bool b_trans, hipStream_t s)
 {
     const long long wgs = (long long)pl.groups * batch;
-    if (M < 1 || M > 32 || wgs <= 0 || wgs > 0x7fffffffLL || N < (b_trans ? 1 : pl.blocks) || K < 8) return hipErrorInvalidValue;
+    if (M < 1 || M > 32 || wgs <= 0 || !stream_launch_fits(pl, batch) || N < (b_trans ? 1 : pl.blocks) || K < 8) return hipErrorInvalidValue;
     if ((long long)pl.groups * 16 * pl.blocks < N) return hipErrorInvalidValue;
     const StreamArgs a{A, B, bias, C, !rowsum ? nullptr : pl.groups == 1 ? rowsum : part, M, N, K, act, pl.groups};
     const unsigned int g = (unsigned int)wgs;

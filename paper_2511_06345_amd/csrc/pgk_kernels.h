@@ -142,6 +142,11 @@ hipError_t launch_gemm_mfma_timed(const GemmArgs& a, int dtype, hipStream_t s);
 // Products of at most 32 rows, all of K in one workgroup (pgk_gemm_stream.hip): blocks of sixteen
 // columns and waves of a workgroup, and how many workgroups cover N.  Any alignment of the elements.
 struct StreamPlan { int blocks, waves, groups; };
+// a launch takes fewer than 2^32 threads
+inline bool stream_launch_fits(const StreamPlan& pl, long long batch)
+{
+    return (long double)pl.groups * (long double)batch * pl.waves * 64.0L < 4294967296.0L;
+}
 // part: batch * groups * M floats, unused without row sums or with one group
 hipError_t launch_gemm_stream(const StreamPlan& pl, const void* A, const void* B, const float* bias, void* C, float* rowsum,
                               float* part, int M, int N, int K, int batch, int act, int dtype, bool b_trans, hipStream_t s);

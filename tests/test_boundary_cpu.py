@@ -485,3 +485,15 @@ def test_odd_rows_are_copied_first_where_that_is_faster(lib):
     assert not copied(1024, 2048, 255, 1, True)         # 19 / 12
     # both operands through registers: the small tile, also where slices and rounds are counted (the large one does not exist)
     assert binding.gemm_plan(528, 223, 30575, 12, gen.BF16)["tile"] == (128, 128, 64)
+
+
+def test_few_rows_stay_below_the_launch_limit(lib):
+    """One launch has fewer than 2^32 threads: more entries than that go to the tiles (which copy odd bf16 rows first)."""
+    q = binding.gemm_fused_workspace_bytes
+    # five workgroups of 256 threads per entry
+    last = (2 ** 32 - 1) // (5 * 256)
+    assert q(16, 257, 64, last, gen.BF16) == 0
+    assert q(16, 257, 64, last + 1, gen.BF16) > 0
+    # transposed B, sixteen workgroups of 512
+    for dtype in (gen.F32, gen.BF16):
+        assert q(16, 256, 64, 2 ** 32 // (16 * 512), dtype, binding.WS_B_TRANSPOSED | binding.WS_UNALIGNED) > 0
