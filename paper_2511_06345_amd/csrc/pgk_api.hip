@@ -527,6 +527,8 @@ bool stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool
     if (K < 64 || K > 16384 || N < 256) return false;
     const bool odd = dtype == PGK_DTYPE_BF16 && (K % 2 != 0 || (!b_trans && N % 2 != 0));
     if (M > 16 && (b_trans || !odd)) return false;
+    // fp32 sums are in chains no longer than in the slices of the tiles (below)
+    if (dtype == PGK_DTYPE_F32 && K > 4096 && (b_trans || N < 10240)) return false;
     if (b_trans) {
         if (N > 16384 || (K < 1024 && N > 8192) || (K > 2048 && N < (odd ? 2048 : 4096))) return false;
         pl->blocks = 1;
@@ -538,8 +540,10 @@ bool stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool
         if (K > 1024 && (N <= 4096 || K > N)) return false;
         pl->blocks = N >= 4096 ? 4 : 2;
     }
-    // A wave's sum runs over K / waves products, and in chains no longer than the slices' were the error is no larger: 8 x
-    // 11008 x 8192 fp32 8.0e-7 with four waves, 6.5e-7 in slices.  (The time is the same with four, eight or sixteen.)
+    // A wave's sum runs over K / waves products, and the error grows with the length of that chain (fp32 8 x 4096 x 8192 4.2e-7
+    // in 16 slices, 5.8e-7 in eight waves).  The tiles' slices are 16 K tiles or longer, 512 products of fp32 and 1024 of bf16, and from
+    // 10240 columns on at most six of them; the waves' chains are at most 512 of fp32 up to a K of 4096 and 1024 above, and 1024 of
+    // bf16.  (Sixteen waves for a longer K, fp32, B transposed, 5312 x 5851: 45 us, eight 41, in slices 37.)
     pl->waves = K > 8192 ? 16 : b_trans || K > 1024 ? 8 : 4;
     const int64_t cols = 16 * pl->blocks, groups = (N + cols - 1) / cols;
     pl->groups = (int)std::min<int64_t>(groups, kMaxDim);
