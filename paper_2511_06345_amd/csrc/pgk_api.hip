@@ -513,36 +513,51 @@ size_t split_part_bytes(int64_t M, int64_t N, int64_t batch, bool rowsum)
     return (rowsum && nseg > 1) ? (size_t)batch * (size_t)nseg * (size_t)M * sizeof(float) : 0;
 }
 
-// Products of few rows whose workgroups take all of K, in one launch (pgk_gemm_stream.hip): where that beat
-// the skinny tiles with their K slices over 66 shapes of 1 ... 32 rows, 256 ... 32768 columns and K of 256 ... 16384 (whole calls
-// in a graph; slices / one launch).  B transposed, up to 16 rows: 8 x 11008 x 4096 bf16 19.7 / 17.5 us, fp32 41.5 / 35.2,
-// 1 x 4096 x 4096 13.9 / 7.4, 9 x 258 x 640 fp32 13.0 / 5.7; a long K needs many columns (10 x 896 x 7667 21 / 25), many
-// columns favour the wide tiles (16 x 32768 x 8192 102 / 105, 16 x 23934 x 704 10 / 18).  B plain: 8 x 11008 x 4096 bf16 19.7 / 18.4, fp32
-// 40.3 / 32.7, 12 x 5376 x 1024 8.8 / 6.4, 3 x 704 x 640 fp32 12.9 / 5.4; the K of one workgroup may not be too long (3 x 5888 x
-// 14784 64 / 105).  bf16 with odd rows spares the padded copy of B as well and wins up to 32 rows: 23 x 12131 x 5554
-// 70 / 43, 27 x 13225 x 1216 27 / 15, 12 x 2496 x 5383 transposed 31 / 13.  A second row block (17 ... 32 rows) loses otherwise.
+// Products of few rows whose workgroups take all of K, in one launch (pgk_gemm_stream.hip): where that beat the skinny
+// tiles with their K slices and second launch over 800 shapes of 1 ... 32 rows, 256 ... 32768 columns, K of 64 ... 16384, up to 450 entries (whole
+// calls in a graph, operands from memory; tiles / one launch).  `tiles`: the workgroups that the tiles have before K is split.
+// Many of them fill the chip by themselves, and the narrow workgroups of a transposed B then cost more than they spare.
+//  * B transposed, up to 16 rows.  8 x 11008 x 4096 bf16 19.7 / 17.5 us, fp32 41.5 / 35.2, 1 x 4096 x 4096 13.9 / 7.4.  The limits of `tiles`: fp32
+//    3 x 1053 x 1536 23 / 14 at 63, 6 x 2240 x 2042 27 / 20 at 216, 11 x 1152 x 1200 34 / 37 at 288, 4 x 4669 x 726 30 / 19 at 111, 10 x 640 x 320 27 / 48 at 695,
+//    11 x 1664 x 192 8.1 / 7.3 at 91, 13 x 4688 x 127 8 / 13 at 111; bf16 12 x 6784 x 1024 18 / 14 at 159, 13 x 4405 x 1280 28 / 31 at 315, 3 x 5201 x 896 11 / 8 at 82, 12
+//    x 4672 x 650 12.5 / 14.7 at 148, 2 x 960 x 448 7.9 / 6.9 at 48, 6 x 704 x 448 8 / 12 at 84, 12 x 8064 x 320 38 / 211 at 2898; with odd rows 12 x 2449 x 811 32 / 22 at
+//    180, 8 x 3810 x 545 56 / 59 at 630, 5 x 1920 x 121 9.6 / 6.0 at 45, 10 x 1313 x 89 12.5 / 15.6 at 165.  Short rows of bf16 are too little for a step of 128:
+//    10 x 3008 x 192 4.9 / 5.6.  A long K needs many columns (10 x 896 x 7667 21 / 25); fp32 beyond 4096 is even at best (5312 x 11136
+//    51 / 67), as are wide ones (15 x 12506 x 3431 48 / 59).
+//  * B plain, bf16, up to 16 rows.  8 x 11008 x 4096 19.7 / 18.4, 9 x 13248 x 2624 25 / 17, 13 x 2616 x 832, 5 entries, 11.7 / 10.1; longer K loses (7 x
+//    5120 x 7808 27 / 43), many tiles are even (4 x 2176 x 344, 36 entries, 15.5 / 13.9; 2 x 6768 x 1308, 7 entries, 30 / 38).
+//  * ... with odd rows, up to 32 rows: it spares the padded copy of B as well.  23 x 12131 x 5554 70 / 43, 10 x 1728 x 221, 63 entries,
+//    37 / 16; few columns under a long K lose (32 x 3072 x 4429 31 / 39, 26 x 4509 x 8104 53 / 59; 9 x 8027 x 12583 110 / 81).
+//  * B plain, fp32, up to 16 rows.  12 x 5376 x 1024 8.8 / 6.4, 6 x 2176 x 295, 3 entries, 11 / 5.6; 1 x 3072 x 958, 12 entries, 41 / 38 at 288, 7 x 2281 x 448,
+//    70 entries, 60 / 82; K beyond 1024: 9 x 10752 x 2179 29 / 24, 8 x 25481 x 1600 41 / 42; beyond 2048: rows on 64 bytes and 10240 ... 16384
+//    columns (8 x 11008 x 4096 40.3 / 32.7, 14 x 13248 x 4224 54 / 44; 15 x 12933 x 4352 48 / 57, 9 x 5228 x 4672 29 / 43, 13 x 18048 x 2210 40 / 47).
+// Beyond a K of 8192 only odd rows gain (bf16, B transposed, 6 x 14592 x 8704 55 / 59; fp32 9 x 12544 x 10368 94 / 105). A second
+// row block (17 ... 32 rows) loses but for odd rows.
 bool stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, pgk::StreamPlan* pl)
 {
-    if (M > 32) return false;
-    if (K < 64 || K > 16384 || N < 256) return false;
-    const bool odd = dtype == PGK_DTYPE_BF16 && (K % 2 != 0 || (!b_trans && N % 2 != 0));
+    const bool f32 = dtype == PGK_DTYPE_F32;
+    const bool odd = !f32 && (K % 2 != 0 || (!b_trans && N % 2 != 0));
+    if (M > 32 || K < 64 || K > (odd ? 16384 : 8192) || N < 256) return false;
     if (M > 16 && (b_trans || !odd)) return false;
-    // fp32 sums are in chains no longer than in the slices of the tiles (below)
-    if (dtype == PGK_DTYPE_F32 && K > 4096 && (b_trans || N < 10240)) return false;
+    const int64_t tiles = (N + 127) / 128 * batch;
     if (b_trans) {
-        if (N > 16384 || (K < 1024 && N > 8192) || (K > 2048 && N < (odd ? 2048 : 4096))) return false;
+        if (!f32 && !odd && K < 256) return false;
+        const int64_t most = odd ? (K >= 512 ? 192 : 128) : f32 ? (K >= 1024 ? 192 : K >= 256 ? 128 : 64) : K >= 1024 ? 160 : K >= 512 ? 96 : 48;
+        if (tiles > most || N > 16384 || (K < 1024 && N > 8192)) return false;
+        if (K > 2048 && N < (odd ? 2048 : 4096)) return false;
+        if (f32 && (K > 4096 || (K > 2048 && N > 12288))) return false;
         pl->blocks = 1;
-    } else if (dtype == PGK_DTYPE_BF16) {
-        if (odd ? (N < 2048 && K > 4096) : (N <= 4096 && K > 1024)) return false;
-        if (!odd && (K > 8192 || N >= 16384)) return false;      // (9 x 27220 x 896 14 / 16)
+    } else if (!f32) {
+        if (odd ? K > 4096 && (N < 4096 || 5 * N < 3 * K) : tiles >= 128 || K > 4096 || (N <= 4096 && K > 1024)) return false;
         pl->blocks = N >= 16384 && K <= 8192 ? 8 : 4;   // (98 against 117 us for 16 x 32768 x 8192; 21 against 18 for 8 x 11008 x 4096)
     } else {
-        if (K > 1024 && (N <= 4096 || K > N)) return false;
+        if (tiles > 320 || N > 32768 || (K > 1024 && (N <= 4096 || N > 16384))) return false;
+        if (K > 2048 && (N < 10240 || N % 16 != 0)) return false;
         pl->blocks = N >= 4096 ? 4 : 2;
     }
     // A wave's sum runs over K / waves products, and the error grows with the length of that chain (fp32 8 x 4096 x 8192 4.2e-7
     // in 16 slices, 5.8e-7 in eight waves).  The tiles' slices are 16 K tiles or longer, 512 products of fp32 and 1024 of bf16, and from
-    // 10240 columns on at most six of them; the waves' chains are at most 512 of fp32 up to a K of 4096 and 1024 above, and 1024 of
+    // 10240 columns on at most seven of them; the waves' chains are at most 512 of fp32 up to a K of 4096 and 1024 above, and 1024 of
     // bf16.  (Sixteen waves for a longer K, fp32, B transposed, 5312 x 5851: 45 us, eight 41, in slices 37.)
     pl->waves = K > 8192 ? 16 : b_trans || K > 1024 ? 8 : 4;
     const int64_t cols = 16 * pl->blocks, groups = (N + cols - 1) / cols;

@@ -497,3 +497,38 @@ def test_few_rows_stay_below_the_launch_limit(lib):
     # transposed B, sixteen workgroups of 512
     for dtype in (gen.F32, gen.BF16):
         assert q(16, 256, 64, 2 ** 32 // (16 * 512), dtype, binding.WS_B_TRANSPOSED | binding.WS_UNALIGNED) > 0
+
+
+def test_few_rows_go_to_the_faster_kernel(lib):
+    """Products of few rows: all of K in a workgroup (no workspace for unaligned operands) or the tiles, on shapes that either
+    was measured faster on (microseconds tiles / one launch)."""
+    def one_launch(dtype, M, N, K, batch=1, bt=False):
+        return binding.gemm_fused_workspace_bytes(M, N, K, batch, dtype, binding.WS_UNALIGNED | (binding.WS_B_TRANSPOSED if bt else 0)) == 0
+
+    F32, BF16 = gen.F32, gen.BF16
+    for shape in ((BF16, 8, 11008, 4096, 1, True),      # 19.7 / 17.5
+                  (F32, 8, 11008, 4096, 1, True),       # 41.5 / 35.2
+                  (F32, 8, 11008, 4096),                # 40.3 / 32.7
+                  (BF16, 23, 12131, 5554),              # 70 / 43
+                  (BF16, 10, 1728, 221, 63),            # 37 / 16
+                  (BF16, 5, 5201, 896, 2, True),        # 11 / 8
+                  (BF16, 12, 2449, 811, 9, True),       # 32 / 22
+                  (F32, 3, 1053, 1536, 7, True),        # 23 / 14
+                  (F32, 9, 277, 384, 28, True),         # 12 / 7
+                  (F32, 6, 2176, 295, 3)):              # 11 / 6
+        assert one_launch(*shape), shape
+    for shape in ((BF16, 12, 8064, 320, 46, True),      # 38 / 211
+                  (BF16, 3, 7168, 67, 52, True),        # 46 / 213
+                  (BF16, 10, 3008, 192, 1, True),       # 4.9 / 5.6
+                  (F32, 15, 3746, 194, 212, True),      # 187 / 467
+                  (F32, 11, 1243, 64, 368, True),       # 39 / 157
+                  (F32, 7, 2281, 448, 70),              # 60 / 82
+                  (BF16, 7, 5120, 7808),                # 27 / 43
+                  (BF16, 10, 6220, 7104, 8),            # 140 / 212
+                  (BF16, 32, 3072, 4429),               # 31 / 39
+                  (F32, 4, 4492, 14843, 1, True),       # 50 / 82
+                  (F32, 15, 4608, 3857),                # 26 / 40
+                  (F32, 9, 12544, 10368),               # 94 / 105
+                  (BF16, 6, 14592, 8704, 1, True),      # 55 / 59
+                  (F32, 11, 9216, 8998)):               # 64 / 95
+        assert not one_launch(*shape), shape

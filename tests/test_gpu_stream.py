@@ -32,20 +32,24 @@ def _one_pass(pgk, M, N, K, batch, dtype, bt):
         pgk.gemm_plan(M, N, K, batch, dtype, bt)["slices"] == 1
 
 
-BT = [(1, 256, 64), (8, 4097, 128), (15, 301, 129), (16, 1000, 1023), (7, 4111, 2056), (3, 272, 65), (2, 5000, 136), (16, 4096, 100), (5, 4098, 8200), (5, 4098, 4096)]
+BT = [(1, 256, 64), (8, 4097, 128), (15, 301, 129), (16, 1000, 1023), (7, 4111, 2056), (3, 272, 65), (2, 5000, 136), (16, 4096, 100), (5, 4098, 8200), (5, 4098, 4096),
+      (8, 1500, 128), (2, 1501, 264), (5, 4098, 8201), (16, 1000, 300)]
 PLAIN = {BF16: [(1, 256, 64), (16, 4100, 33 * 32), (5, 4224, 1000), (9, 16385, 72), (15, 16501, 100), (3, 300, 1024),
-                (31, 257, 65), (6, 2051, 8201), (20, 2101, 9000), (17, 2049, 96), (32, 16387, 71), (24, 4103, 259)],
-         F32: [(1, 256, 64), (16, 257, 100), (8, 4097, 1040), (3, 4160, 2052), (9, 301, 1023), (15, 4099, 67), (2, 258, 515), (3, 8260, 8200), (3, 10240, 8200)]}
+                (31, 257, 65), (6, 2051, 8201), (20, 2101, 9000), (17, 2049, 96), (32, 16387, 71), (24, 4103, 259), (6, 6151, 8201), (20, 6101, 9000)],
+         F32: [(1, 256, 64), (16, 257, 100), (8, 4097, 1040), (3, 4160, 2052), (9, 301, 1023), (15, 4099, 67), (2, 258, 515), (3, 8260, 8200), (3, 10240, 8192), (7, 10256, 2052)]}
 CASES = [(d, *s, True) for d in (F32, BF16) for s in BT] + [(d, *s, False) for d in (F32, BF16) for s in PLAIN[d]]
-# of these, left to the tiles
-OUTSIDE = {(F32, 5, 4098, 8200, True), (F32, 3, 8260, 8200, False)}
+# of these, left to the tiles: whatever the batch, and with three entries
+OUTSIDE = {(F32, 5, 4098, 8200, True), (F32, 5, 4098, 8201, True), (BF16, 5, 4098, 8200, True), (F32, 3, 8260, 8200, False), (F32, 3, 4160, 2052, False), (BF16, 6, 2051, 8201, False), (BF16, 20, 2101, 9000, False),
+           (BF16, 8, 4097, 128, True), (BF16, 2, 5000, 136, True), (BF16, 16, 4096, 100, True), (BF16, 8, 1500, 128, True)}
+OUTSIDE_BATCHED = {(F32, 8, 4097, 128, True), (F32, 2, 5000, 136, True), (F32, 16, 4096, 100, True)}
 
 
 @pytest.mark.parametrize("dtype,M,N,K,bt", CASES)
 @pytest.mark.parametrize("batch,offset", [(1, 0), (3, 1)])
 def test_integers_exact(pgk, dtype, M, N, K, bt, batch, offset):
     # |sum| <= 49 K < 2^24: exact in any order
-    assert _one_pass(pgk, M, N, K, batch, dtype, bt) == ((dtype, M, N, K, bt) not in OUTSIDE)
+    outside = OUTSIDE | OUTSIDE_BATCHED if batch > 1 else OUTSIDE
+    assert _one_pass(pgk, M, N, K, batch, dtype, bt) == ((dtype, M, N, K, bt) not in outside)
     g = torch.Generator(device="cuda").manual_seed(M + N * K)
     A = torch.randint(-7, 8, (batch, M, K), generator=g, device="cuda").to(TYPES[dtype])
     B = torch.randint(-7, 8, (batch, N, K) if bt else (batch, K, N), generator=g, device="cuda").to(TYPES[dtype])
