@@ -108,7 +108,8 @@ typedef enum {
  * workspace with rows padded with zeros to whole 16-byte chunks (up to batch*(M*K' + K'*N')
  * elements, K' and N' the next multiples of 8).  Products of at most 32 rows by 256 columns and more run, over
  * the range where that is the faster way, on a kernel whose workgroups take all of K: one pass, operands in
- * place at any alignment of their elements, row sums per 16 (B transposed) or up to 128 columns.  C, bias and rowsum are always used in place,
+ * place at any alignment of their elements, row sums per 16 (B transposed) or up to 128 columns (with a smaller
+ * workspace that holds the row sums of the 32 x 128 tiles, per 128 columns, those run instead).  C, bias and rowsum are always used in place,
  * whatever N is and wherever they start (element alignment).  A B given as [K][N] with at
  * most 32 columns (under an output of more than 32 rows) is likewise copied first, in
  * transposed form, so that the product can run on the 128 x 32 tile, and so is an A or B

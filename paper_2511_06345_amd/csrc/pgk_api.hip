@@ -700,11 +700,12 @@ bool pack_needs(WsNeeds& w, int64_t M, int64_t N, int64_t K, int64_t batch, int 
     return true;
 }
 
+// allow_stream: false = the tiles in any case
 WsNeeds fused_needs(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, bool want_rowsum, bool a_mis,
-                    bool b_mis)
+                    bool b_mis, bool allow_stream = true)
 {
     WsNeeds w{};
-    if (stream_plan(M, N, K, batch, dtype, b_trans, &w.sp)) {
+    if (allow_stream && stream_plan(M, N, K, batch, dtype, b_trans, &w.sp)) {
         w.ok = w.stream = true;
         w.d = PackDims{false, K, 0, false, b_trans};
         w.rs_part = (want_rowsum && w.sp.groups > 1) ? (size_t)batch * (size_t)w.sp.groups * (size_t)M * sizeof(float) : 0;
@@ -740,6 +741,17 @@ WsNeeds splitk_needs(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, 
     w.rs_part = split_part_bytes(M, N, batch, want_rowsum);
     lay_out(w);
     return w;
+}
+
+// What a fused call with `workspace_bytes` does.  The kernel for few rows has row sums per 16 to 128 columns where the tiles
+// have them per 128: a workspace with room for the tiles' alone is still enough, and the tiles run.
+WsNeeds fused_needs_within(size_t workspace_bytes, int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans,
+                           bool want_rowsum, bool a_mis, bool b_mis)
+{
+    const WsNeeds w = fused_needs(M, N, K, batch, dtype, b_trans, want_rowsum, a_mis, b_mis);
+    if (!w.stream || w.total <= workspace_bytes) return w;
+    const WsNeeds tiles = fused_needs(M, N, K, batch, dtype, b_trans, want_rowsum, a_mis, b_mis, false);
+    return tiles.ok && tiles.total <= workspace_bytes ? tiles : w;
 }
 
 bool sizes_valid(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype)
@@ -816,7 +828,7 @@ int gemm_fused_impl(const void* A, const void* B, const float* bias, void* C, fl
     int rc = validate_common(A, B, C, M, N, K, batch, act, dtype);
     if (rc != PGK_OK) return rc;
     const bool a_mis = !aligned16(A), b_mis = !aligned16(B);
-    const WsNeeds w = fused_needs(M, N, K, batch, dtype, b_trans, rowsum != nullptr, a_mis, b_mis);
+    const WsNeeds w = fused_needs_within(workspace ? workspace_bytes : 0, M, N, K, batch, dtype, b_trans, rowsum != nullptr, a_mis, b_mis);
     rc = check_workspace(w, workspace, workspace_bytes);
     if (rc != PGK_OK) return rc;
     if (w.stream)
@@ -894,7 +906,7 @@ int pgk_gemm_fused_static(const void* A, const void* B, const float* bias, void*
     int rc = validate_common(A, B, C, M, N, K, batch, act, dtype);
     if (rc != PGK_OK) return rc;
     // the need is known on the host: refuse before touching the device
-    const WsNeeds w = fused_needs(M, N, K, batch, dtype, false, rowsum != nullptr, !aligned16(A), !aligned16(B));
+    const WsNeeds w = fused_needs_within(kStaticScratchBytes, M, N, K, batch, dtype, false, rowsum != nullptr, !aligned16(A), !aligned16(B));
     if (!w.ok) return PGK_ERR_UNSUPPORTED;
     if (w.total > kStaticScratchBytes) return PGK_ERR_WORKSPACE;
     void* ws = nullptr;

@@ -532,3 +532,10 @@ def test_few_rows_go_to_the_faster_kernel(lib):
                   (BF16, 6, 14592, 8704, 1, True),      # 55 / 59
                   (F32, 11, 9216, 8998)):               # 64 / 95
         assert not one_launch(*shape), shape
+
+
+def test_row_sums_of_few_rows_and_many_entries_fit_the_fixed_workspace(lib):
+    """Row sums per 128 columns, as the tiles have them, where there are many entries: what pgk_gemm_fused_static takes."""
+    q = binding.gemm_fused_workspace_bytes
+    assert q(16, 2048, 64, 2048, gen.F32, binding.WS_ROWSUM) == 2048 * 16 * 16 * 4
+    assert q(16, 2048, 128, 4096, gen.BF16, binding.WS_ROWSUM) == 4096 * 16 * 16 * 4 == binding.gemm_fused_static_max_bytes()

@@ -102,3 +102,25 @@ def test_against_64_bits(pgk, dtype, bt, act):
     assert err < (2.0 ** -16 if dtype == F32 else 2.0 ** -8)
     rs_err = (rs[0].double() - ref.sum(-1)).abs().max() / ref.abs().sum(-1).max()
     assert rs_err < 2.0 ** -18
+
+
+def _integers(M, N, K, batch, dtype, seed=5):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    A = torch.randint(-7, 8, (batch, M, K), generator=g, device="cuda").to(TYPES[dtype])
+    B = torch.randint(-7, 8, (batch, K, N), generator=g, device="cuda").to(TYPES[dtype])
+    return A, B, torch.bmm(A.double(), B.double())
+
+
+@pytest.mark.parametrize("dtype,M,N,K,bt", [(F32, 16, 2048, 64, False), (F32, 16, 2048, 128, True), (BF16, 16, 2048, 128, False), (BF16, 3, 600, 512, True)])
+def test_a_workspace_for_the_tiles_row_sums_is_enough(pgk, dtype, M, N, K, bt):
+    flags = pgk.WS_ROWSUM | (pgk.WS_B_TRANSPOSED if bt else 0)
+    tiles = -(-(-(-N // 128)) * M * 4 // 256) * 256          # row sums per 128 columns
+    assert _one_pass(pgk, M, N, K, 1, dtype, bt) and pgk.gemm_fused_workspace_bytes(M, N, K, 1, dtype, flags) > tiles
+    A, B, ref = _integers(M, N, K, 1, dtype)
+    call, B = (pgk.gemm_fused_bt, B.transpose(1, 2).contiguous()) if bt else (pgk.gemm_fused, B)
+    ws = torch.full((tiles + 256,), 255, dtype=torch.uint8, device="cuda")
+    C, rs = call(A, B, None, ACT_NONE, rowsum=True, workspace=ws[:tiles])
+    assert torch.equal(C.double(), ref.to(TYPES[dtype]).double()) and torch.equal(rs.double(), ref.sum(-1))
+    assert bool((ws[tiles:] == 255).all())
+    with pytest.raises(pgk.PgkError):
+        call(A, B, None, ACT_NONE, rowsum=True, workspace=ws[:tiles - 256])
