@@ -214,8 +214,8 @@ double estimated_rounds_time(int64_t M, int64_t N, int64_t K, int dtype, int64_t
 // empty, else the small one.
 struct AutoPlan { int splits; int kind; };
 
-// large_ok: false where the large tile has no instance (both operands copied through registers).
-AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool large_ok = true)
+// fit_round: slices and large tiles are counted so that a grid fits one round where it can (see auto_split).
+AutoPlan count_slices(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool fit_round)
 {
     const int ks = kstep_of(dtype);
     const int64_t ksteps = (K + ks - 1) / ks;
@@ -230,7 +230,7 @@ AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, b
     if (s_max > kMaxAutoSplits) s_max = kMaxAutoSplits;
     int kind = skinny_tile_kind(M, N);
     if (kind < 0)
-        kind = (!large_ok || large_tile_mostly_empty(M, N, dtype) || tiles_of(pgk::TILE_LARGE) * s_max < 1.5L * kNumCUs) ? pgk::TILE_SMALL
+        kind = (large_tile_mostly_empty(M, N, dtype) || tiles_of(pgk::TILE_LARGE) * s_max < 1.5L * kNumCUs) ? pgk::TILE_SMALL
                                                                                                           : pgk::TILE_LARGE;
     const long double tiles = tiles_of(kind);
     // (enough slices for two workgroups per CU; four of the fp32 small tile and one of the bf16
@@ -244,9 +244,8 @@ AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, b
         int64_t n = 1;
         while (n < s_max && n_tiles * n < 0.95L * goal) ++n;      // (250 tiles: two slices, not three)
         // The goal is also what the chip holds at once (but for skinny tiles): a few workgroups more run as a round of
-        // their own, and one slice less, in one round, is done sooner (in slices by the goal / one less: fp32 8 x [256 x 384 x 64992] 923 / 646 us,
-        // 700 x 900 x 9000 122 / 94, bf16 10 x [512 x 500 x 20000] 200 / 135).
-        if (skinny_tile_kind(M, N) < 0 && n >= 4 && n_tiles * n > goal) --n;
+        // their own, and one slice less, in one round, is done sooner.
+        if (fit_round && skinny_tile_kind(M, N) < 0 && n >= 4 && n_tiles * n > goal) --n;
         return n;
     };
     int64_t s = slices_for(tiles, target);
@@ -269,9 +268,9 @@ AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, b
         // (A large tile that fits in one round is better than the model has it.  bf16: 8 x [256 x 384 x 64992] on small
         // tiles, estimated at 0.89 of it, 184 us, on large ones 167.  fp32, whose fit is that of the fp32 instruction: the factor
         // of auto_tile_kind; 9 x [256 x 130 x 53517] 409 and 366, 16 x [128 x 192 x 24994] 194 and 173.)
-        const bool one_round = kind == pgk::TILE_LARGE && tiles * s <= target;
+        const bool one_round = fit_round && kind == pgk::TILE_LARGE && tiles * s <= target;
         const double margin = !one_round ? 0.94 : dtype == PGK_DTYPE_BF16 ? 0.88 : 0.78;
-        const bool other_allowed = other == pgk::TILE_SMALL || (large_ok && !large_tile_mostly_empty(M, N, dtype));
+        const bool other_allowed = other == pgk::TILE_SMALL || !large_tile_mostly_empty(M, N, dtype);
         if (other_allowed && K / s >= 1024 && K / s_other >= 1024 && estimate(other, s_other) < margin * estimate(kind, s)) {
             kind = other;
             s = s_other;
@@ -280,14 +279,25 @@ AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, b
     return {(int)s, kind};
 }
 
-SplitPlan plan_splits(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int splits, bool large_ok = true)
+// Slices and large tiles that fit one round are faster (fp32 8 x [256 x 384 x 64992], 6 slices of small tiles or 10 of large ones, 923 / 646 us,
+// bf16 10 x [512 x 500 x 20000], 4 or 6, 200 / 135), and taken where no sum gets less exact by them: with no fewer slices, whose
+// chains of sums would be longer (512 x 178 x 19776, 13 entries, error 1.33e-6 in four slices, 1.55e-6 in three), and not from the fp32 large tile,
+// which computes in bf16 terms, to the small one, whose sums are those of the fp32 instruction (320 x 157 x 8029, 11 entries, 1.7e-7 and 6.7e-7).
+AutoPlan auto_split(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype)
+{
+    const AutoPlan plain = count_slices(M, N, K, batch, dtype, false), fitted = count_slices(M, N, K, batch, dtype, true);
+    const bool rounder = dtype == PGK_DTYPE_F32 && plain.kind == pgk::TILE_LARGE && fitted.kind != pgk::TILE_LARGE;
+    return fitted.splits >= plain.splits && !rounder ? fitted : plain;
+}
+
+SplitPlan plan_splits(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int splits)
 {
     const int ks = kstep_of(dtype);
     const int64_t ksteps = (K + ks - 1) / ks;
     int64_t s = splits;
     if (s == 0) {
         if (mfma_route(M, N, K, dtype)) {
-            s = auto_split(M, N, K, batch, dtype, large_ok).splits;
+            s = auto_split(M, N, K, batch, dtype).splits;
         } else {
             const pgk::TileShape t = pgk::guarded_tile_shape();
             const long double tiles = (long double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * batch;
@@ -410,7 +420,8 @@ int auto_tile_kind(int64_t M, int64_t N, int64_t K, int dtype, int64_t units, bo
 // The tile of operands copied through registers: the large one where it is planned and has an instance (one operand of a
 // plain B), else the small one, whose two workgroups per CU cover one's loads and LDS writes with the other's products.
 // (The half tiles, both operands through registers, one workgroup per CU, over 73 shapes: 0.92 and 0.94 of its speed; the
-// tall one 1344 x 87 x 708, 43 entries, 57 us, the small one 34, but 171 x 32134 x 6733 192 and 207.)
+// tall one 1344 x 87 x 708, 43 entries, 57 us, the small one 34, but 171 x 32134 x 6733 192 and 207.)  Slices that are planned for large tiles stay as they are: fewer would be
+// longer chains of sums; whether such a grid pays is reg_copies_pay's business.
 int reg_tile_kind(int kind, OddRows odd, bool b_trans)
 {
     return kind == pgk::TILE_LARGE && !b_trans && !(odd.a && odd.b) ? pgk::TILE_LARGE : pgk::TILE_SMALL;
@@ -604,10 +615,8 @@ FusedPlan plan_fused(bool aligned, int64_t M, int64_t N, int64_t K, int64_t batc
     const bool under_filled = dtype == PGK_DTYPE_F32 && fp.path.kind == pgk::TILE_SMALL &&
                               (long double)tiles_m * tiles_n * batch < 3 * kNumCUs && (K + big.bk - 1) / big.bk >= 128;
     if (fp.path.mfma && (few_tiles || long_k || under_filled)) {
-        const OddRows odd = odd_rows(K, dtype, b_trans, ldb ? ldb : N);
-        const bool large_ok = !(odd.a || odd.b) || reg_tile_kind(pgk::TILE_LARGE, odd, b_trans) == pgk::TILE_LARGE;
-        fp.slices = plan_splits(M, N, K, batch, dtype, 0, large_ok);
-        fp.split_small_tile = auto_split(M, N, K, batch, dtype, large_ok).kind;
+        fp.slices = plan_splits(M, N, K, batch, dtype, 0);
+        fp.split_small_tile = auto_split(M, N, K, batch, dtype).kind;
         const long double ws_bytes = (long double)batch * fp.slices.splits * M * N * sizeof(float);
         fp.split = fp.slices.splits > 1 && ws_bytes <= (long double)kAutoSplitMaxWorkspace;
     }

@@ -539,3 +539,25 @@ def test_row_sums_of_few_rows_and_many_entries_fit_the_fixed_workspace(lib):
     q = binding.gemm_fused_workspace_bytes
     assert q(16, 2048, 64, 2048, gen.F32, binding.WS_ROWSUM) == 2048 * 16 * 16 * 4
     assert q(16, 2048, 128, 4096, gen.BF16, binding.WS_ROWSUM) == 4096 * 16 * 16 * 4 == binding.gemm_fused_static_max_bytes()
+
+
+def test_automatic_slices_are_not_made_longer_to_fit_one_round(lib):
+    """A plan that fits one round is taken where its sums are in chains no longer than those of the smallest count of slices that
+    fills the chip, and not from the fp32 large tile to the small one, whose sums are less exact."""
+    F32, BF16 = gen.F32, gen.BF16
+
+    def plan(dtype, *shape, bt=False):
+        p = binding.gemm_plan(*shape, dtype, b_transposed=bt)
+        return p["tile"][:2], p["slices"]
+
+    assert plan(F32, 512, 178, 19776, 13) == ((64, 64), 4)
+    assert plan(F32, 448, 156, 10112, 15) == ((64, 64), 4)
+    assert plan(F32, 700, 900, 9000, 1) == ((128, 128), 11)
+    assert plan(F32, 320, 157, 8029, 11) == ((128, 128), 8)
+    assert plan(BF16, 256, 443, 15618, 10, bt=True) == ((128, 128), 7)
+    assert plan(BF16, 128, 384, 43264, 16) == ((128, 128), 11)
+    # no longer chains: large tiles in one round
+    assert plan(F32, 256, 384, 64992, 8) == ((128, 128), 10)
+    assert plan(BF16, 512, 500, 20000, 10) == ((256, 256), 6)
+    # odd rows through registers, on small tiles: the slices of the large ones
+    assert plan(BF16, 256, 256, 58097, 10, bt=True) == ((128, 128), 25)
