@@ -122,21 +122,24 @@ def splitk_workspace_bytes(M: int, N: int, K: int, batch: int, dtype: int, split
     return int(load_library().pgk_splitk_workspace_bytes(M, N, K, batch, dtype, splits))
 
 
-# The size queries are pure host arithmetic on the sizes; a program asks about the same few again and again (0.1 us,
-# not 0.7, of a small call).
-@functools.lru_cache(maxsize=4096)
 def gemm_splitk_workspace_bytes(M: int, N: int, K: int, batch: int, dtype: int, splits: int = 0, flags: int = 0) -> int:
     return int(load_library().pgk_gemm_splitk_workspace_bytes(M, N, K, batch, dtype, splits, flags))
 
 
-@functools.lru_cache(maxsize=4096)
 def gemm_fused_workspace_bytes(M: int, N: int, K: int, batch: int, dtype: int, flags: int = 0) -> int:
     return int(load_library().pgk_gemm_fused_workspace_bytes(M, N, K, batch, dtype, flags))
 
 
-@functools.lru_cache(maxsize=4096)
 def reduce_max_workspace_bytes(outer: int, red: int, inner: int, dtype: int) -> int:
     return int(load_library().pgk_reduce_max_workspace_bytes(outer, red, inner, dtype))
+
+
+# The size queries are pure host arithmetic on the sizes; a program calls with the same few again and again (0.1 us,
+# not 0.7, of a small call).  For plain ints only: whatever else the library takes for an integer may be equal to one that it
+# does not take (256.0), or change (a tensor).
+_fused_bytes = functools.lru_cache(maxsize=4096)(gemm_fused_workspace_bytes)
+_splitk_bytes = functools.lru_cache(maxsize=4096)(gemm_splitk_workspace_bytes)
+_reduce_bytes = functools.lru_cache(maxsize=4096)(reduce_max_workspace_bytes)
 
 
 def splitk_auto_splits(M: int, N: int, K: int, batch: int, dtype: int, splits: int = 0) -> int:
@@ -261,7 +264,7 @@ def gemm_fused(A: torch.Tensor, B: torch.Tensor, bias: Optional[torch.Tensor], a
     batch, M, N, K, dtype = _shape(A, B, b_transposed)
     entry = lib.pgk_gemm_fused_bt if b_transposed else lib.pgk_gemm_fused
     dev = A.device
-    need = gemm_fused_workspace_bytes(M, N, K, batch, dtype, _ws_flags(A, B, rowsum, b_transposed))
+    need = _fused_bytes(M, N, K, batch, dtype, _ws_flags(A, B, rowsum, b_transposed))
     with _on_stream(stream):
         if workspace is None and need:
             workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
@@ -317,7 +320,8 @@ def gemm_splitk(A: torch.Tensor, B: torch.Tensor, bias: Optional[torch.Tensor], 
     batch, M, N, K, dtype = _shape(A, B, b_transposed)
     entry = lib.pgk_gemm_splitk_bt if b_transposed else lib.pgk_gemm_splitk
     dev = A.device
-    need = gemm_splitk_workspace_bytes(M, N, K, batch, dtype, splits, _ws_flags(A, B, rowsum, b_transposed))
+    query = _splitk_bytes if type(splits) is int else gemm_splitk_workspace_bytes
+    need = query(M, N, K, batch, dtype, splits, _ws_flags(A, B, rowsum, b_transposed))
     with _on_stream(stream):
         if workspace is None:
             workspace = torch.empty((max(need, 16),), dtype=torch.uint8, device=dev)
@@ -362,7 +366,7 @@ def reduce_max(X: torch.Tensor, dim: int, want_idx: bool = True, out: Optional[t
     outer, red, inner = math.prod(before), sizes[dim], math.prod(after)
     shape = before + after
     dev = X.device
-    need = reduce_max_workspace_bytes(outer, red, inner, dtype)
+    need = _reduce_bytes(outer, red, inner, dtype)
     with _on_stream(stream):
         if workspace is None and need:
             workspace = torch.empty((need,), dtype=torch.uint8, device=dev)
@@ -444,15 +448,17 @@ def probe_stream_read(src: torch.Tensor, sink: torch.Tensor, stream=None) -> int
     return nbytes
 
 
-@functools.lru_cache(maxsize=4096)
 def conv1d_out_len(L: int, Kw: int, stride: int = 1, pad: int = 0, dilation: int = 1) -> int:
     return int(load_library().pgk_conv1d_out_len(L, Kw, stride, pad, dilation))
 
 
-@functools.lru_cache(maxsize=4096)
 def conv1d_workspace_bytes(B: int, Cin: int, L: int, Cout: int, Kw: int, stride: int, pad: int, dilation: int,
                            dtype: int) -> int:
     return int(load_library().pgk_conv1d_workspace_bytes(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype))
+
+
+_conv1d_len = functools.lru_cache(maxsize=4096)(conv1d_out_len)
+_conv1d_bytes = functools.lru_cache(maxsize=4096)(conv1d_workspace_bytes)
 
 
 def conv1d(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor], act: int = ACT_NONE, stride: int = 1,
@@ -474,11 +480,12 @@ def conv1d(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor], act: 
         raise TypeError("x and w must both be float32 or both bfloat16")
     B, Cin, L = x.shape
     Cout, _, Kw = w.shape
-    Lout = conv1d_out_len(L, Kw, stride, pad, dilation)
+    plain = type(stride) is int and type(pad) is int and type(dilation) is int
+    Lout = (_conv1d_len if plain else conv1d_out_len)(L, Kw, stride, pad, dilation)
     if Lout <= 0:
         raise ValueError("the convolution has no output for these sizes")
     dev = x.device
-    need = conv1d_workspace_bytes(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype)
+    need = (_conv1d_bytes if plain else conv1d_workspace_bytes)(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype)
     with _on_stream(stream):
         if workspace is None and need:
             workspace = torch.empty((need,), dtype=torch.uint8, device=dev)

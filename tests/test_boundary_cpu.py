@@ -561,3 +561,20 @@ def test_automatic_slices_are_not_made_longer_to_fit_one_round(lib):
     assert plan(BF16, 512, 500, 20000, 10) == ((256, 256), 6)
     # odd rows through registers, on small tiles: the slices of the large ones
     assert plan(BF16, 256, 256, 58097, 10, bt=True) == ((128, 128), 25)
+
+
+def test_size_queries_answer_for_the_values_they_are_given(lib):
+    """Numbers equal to an integer asked about before, and integers that change: refused, or answered anew."""
+    import torch
+    for query, sizes in ((binding.gemm_fused_workspace_bytes, (256, 256, 4096, 1, gen.F32)),
+                         (binding.gemm_splitk_workspace_bytes, (256, 256, 4096, 1, gen.F32)),
+                         (binding.reduce_max_workspace_bytes, (4, 1 << 20, 1, gen.F32)),
+                         (binding.conv1d_out_len, (1000, 3)),
+                         (binding.conv1d_workspace_bytes, (2, 64, 1000, 64, 3, 1, 1, 1, gen.F32))):
+        value = query(*sizes)
+        with pytest.raises(ctypes.ArgumentError):
+            query(float(sizes[0]), *sizes[1:])
+        size = torch.tensor(sizes[0])
+        assert query(size, *sizes[1:]) == value
+        size += 4096
+        assert query(size, *sizes[1:]) == query(sizes[0] + 4096, *sizes[1:]) != value
