@@ -560,7 +560,7 @@ bool stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool
         pl->blocks = 1;
     } else if (!f32) {
         if (odd ? K > 4096 && (N < 4096 || 5 * N < 3 * K) : tiles >= 128 || K > 4096 || (N <= 4096 && K > 1024)) return false;
-        pl->blocks = N >= 16384 && K <= 8192 ? 8 : 4;   // (98 against 117 us for 16 x 32768 x 8192; 21 against 18 for 8 x 11008 x 4096)
+        pl->blocks = N >= 16384 && K <= 8192 ? 8 : 4;   // (8 / 4: 24 x 16387 x 4095 58 / 78 us, 16 x 11008 x 4095 38 / 31; 15001 x 2048 19 / 21)
     } else {
         if (tiles > 320 || N > 32768 || (K > 1024 && (N <= 4096 || N > 16384))) return false;
         if (K > 2048 && (N < 10240 || N % 16 != 0)) return false;

@@ -250,6 +250,24 @@ bool conv_few_channels_fits(long long B, long long Cin, long long Cout, long lon
     return lds_floats(Cin, Kw, stride, dil, 1, 128) <= kMaxLdsFloats;
 }
 
+namespace {
+// (every sixteenth channel: fp32 with at most 16 products only)
+template <bool BF16, int ACT>
+void launch_few(const FewArgs& a, dim3 grid, size_t lds, hipStream_t s)
+{
+    const dim3 block(256);
+    if constexpr (!BF16)
+        if (a.every == 16) {
+            if (a.K2 <= 8) hipLaunchKernelGGL((conv_few_channels_kernel<BF16, ACT, 4, true>), grid, block, lds, s, a);
+            else hipLaunchKernelGGL((conv_few_channels_kernel<BF16, ACT, 8, true>), grid, block, lds, s, a);
+            return;
+        }
+    if (a.K2 <= 8) hipLaunchKernelGGL((conv_few_channels_kernel<BF16, ACT, 4>), grid, block, lds, s, a);
+    else if (a.K2 <= 16) hipLaunchKernelGGL((conv_few_channels_kernel<BF16, ACT, 8>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((conv_few_channels_kernel<BF16, ACT, 0>), grid, block, lds, s, a);
+}
+}  // namespace
+
 hipError_t launch_conv_few_channels(const void* x, const void* w, const float* bias, void* y, long long B, int Cin, int L, int Cout,
                                     int Kw, int stride, int pad, int dil, int Lout, int act, int dtype, hipStream_t s)
 {
@@ -286,23 +304,16 @@ hipError_t launch_conv_few_channels(const void* x, const void* w, const float* b
     const long long wgs = wgs_of();
     if (wgs <= 0 || wgs > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t lds = (size_t)lds_floats(Cin, Kw, stride, dil, tiles, ch) * sizeof(float);
-    const dim3 grid((unsigned int)wgs), block(256);
-#define PGK_FEW(BF, ACT)                                                                                       \
-    if (a.every == 16 && a.K2 <= 8) hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 4, !BF>), grid, block, lds, s, a);        \
-    else if (a.every == 16) hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 8, !BF>), grid, block, lds, s, a);    \
-    else if (a.K2 <= 8) hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 4>), grid, block, lds, s, a);     \
-    else if (a.K2 <= 16) hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 8>), grid, block, lds, s, a);    \
-    else hipLaunchKernelGGL((conv_few_channels_kernel<BF, ACT, 0>), grid, block, lds, s, a)
-#define PGK_FEW_ACT(BF)                                                   \
-    switch (act) {                                                        \
-    case ACT_RELU: PGK_FEW(BF, ACT_RELU); break;                          \
-    case ACT_GELU_TANH: PGK_FEW(BF, ACT_GELU_TANH); break;                \
-    case ACT_SILU: PGK_FEW(BF, ACT_SILU); break;                          \
-    default: PGK_FEW(BF, ACT_NONE); break;                                \
+    const dim3 grid((unsigned int)wgs);
+#define PGK_FEW_ACT(BF)                                                      \
+    switch (act) {                                                           \
+    case ACT_RELU: launch_few<BF, ACT_RELU>(a, grid, lds, s); break;         \
+    case ACT_GELU_TANH: launch_few<BF, ACT_GELU_TANH>(a, grid, lds, s); break; \
+    case ACT_SILU: launch_few<BF, ACT_SILU>(a, grid, lds, s); break;         \
+    default: launch_few<BF, ACT_NONE>(a, grid, lds, s); break;               \
     }
     if (dtype == DT_BF16) { PGK_FEW_ACT(true) } else { PGK_FEW_ACT(false) }
 #undef PGK_FEW_ACT
-#undef PGK_FEW
     return hipGetLastError();
 }
 

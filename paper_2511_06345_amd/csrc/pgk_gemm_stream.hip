@@ -391,15 +391,17 @@ __global__ __launch_bounds__(256) void stream_rowsum_kernel(const float* __restr
     if (lane == 0) rowsum[i] = s;
 }
 
-// (sixteen waves of the widest lanes would not have the registers, and four are for a plain B only)
+// (what stream_plan asks for: eight waves but with two blocks; sixteen, bf16 beyond a K of 8192, for which eight blocks would not
+// have the registers; four, a plain B up to a K of 1024)
 template <bool BF16, bool BT, int MB, int BLOCKS>
 hipError_t launch_waves(const StreamArgs& a, int waves, unsigned int wgs, hipStream_t s)
 {
-    if (waves == 8) {
-        hipLaunchKernelGGL((gemm_stream_kernel<BF16, BT, MB, BLOCKS, 8>), dim3(wgs), dim3(512), 0, s, a);
-        return hipGetLastError();
-    }
-    if constexpr (BLOCKS < 8)
+    if constexpr (BLOCKS != 2)
+        if (waves == 8) {
+            hipLaunchKernelGGL((gemm_stream_kernel<BF16, BT, MB, BLOCKS, 8>), dim3(wgs), dim3(512), 0, s, a);
+            return hipGetLastError();
+        }
+    if constexpr (BF16 && BLOCKS < 8)
         if (waves == 16) {
             hipLaunchKernelGGL((gemm_stream_kernel<BF16, BT, MB, BLOCKS, 16>), dim3(wgs), dim3(1024), 0, s, a);
             return hipGetLastError();
