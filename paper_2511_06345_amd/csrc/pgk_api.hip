@@ -1149,10 +1149,19 @@ ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw
     const bool shifts_even = dtype == PGK_DTYPE_F32 || dilation % 2 == 0 || Kw == 1;
     // (bf16: every tile base on a 4-byte boundary)
     const bool bases_even = shifts_even && (L * es) % 4 == 0 && (pad * es) % 4 == 0;
-    // Through registers the main loop loses a fifth of its time (reg_copies), the alternative is two shifted copies of
-    // the input: even at 3000 products per output position and channel ([8, 512, 4096] x [512, 512, 3] 69 us
-    // with the copies, 63 without).
-    const bool reg = !bases_even && pl.kind != pgk::TILE_FLAT && Cout * Kw <= 3000;
+    // Otherwise tiles are copied through registers, or first into copies of the input (two shifted ones; a padded one where
+    // the taps' offsets are even).  The registers cost 0.35 of the loop in the round model on the large tile, 0.5 on the small one, 0.7 on half
+    // tiles, and 0.6 of a full round's with a single workgroup on a CU; the copies three passes over the input at 3.5 TB/s.
+    // Fitted to 464 convolutions of up to 3000 products per output position and input channel (beyond, the copies): of the choices six are more
+    // than 5 % slower than the copies, none than the registers.  Copies / registers: [8, 512, 4096] x [512, 512, 3] 66 / 58 us, [8, 128, 54071] x
+    // [256, 128, 1] 193 / 103; [7, 384, 1656] x [265, 384, 10] 65 / 83, [2, 448, 576] x [234, 448, 5] 26 / 33.
+    auto reg_pays = [&]() {
+        const Rounds r = rounds_of(Cout, pl.Lout, dtype, B, pl.kind);
+        const double loops = tile_cost(dtype, pl.kind).per_k * (double)Cin * (double)Kw / 1024.0 * (r.full + (r.rest == 1 ? 0.6 : r.rest > 1 ? 1.0 : 0.0));
+        const double lost = pl.kind == pgk::TILE_LARGE ? 0.35 : pl.kind == pgk::TILE_SMALL ? 0.5 : 0.7;
+        return lost * loops < 6.0 * (double)B * (double)Cin * (double)L / 3.5e6 + 1.5;
+    };
+    const bool reg = !bases_even && pl.kind != pgk::TILE_FLAT && Cout * Kw <= 3000 && reg_pays();
     // Reading the input in place needs the halo and the padding to be no wider than a tile.
     const bool strips = ((bases_even && (pl.Lout % epc == 0 || pl.kind != pgk::TILE_FLAT)) || reg) && halo <= bn && pad <= bn &&
                         (long double)B * Cin * 3 * ((bn + halo) / 256 + 2) < 2.0e9L;

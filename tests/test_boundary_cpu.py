@@ -578,3 +578,20 @@ def test_size_queries_answer_for_the_values_they_are_given(lib):
         assert query(size, *sizes[1:]) == value
         size += 4096
         assert query(size, *sizes[1:]) == query(sizes[0] + 4096, *sizes[1:]) != value
+
+
+def test_odd_convolutions_copy_the_input_where_that_is_faster(lib):
+    """bf16 taps, padding or rows at odd offsets: the input in place (workspace for weights and the rows' ends) or copies of it, on
+    shapes that either was measured faster on (microseconds copies / in place)."""
+    def in_place(B, Cin, L, Cout, Kw, pad=0, dilation=1):
+        weights = -(-Cout * Cin * Kw * 2 // 256) * 256
+        return binding.conv1d_workspace_bytes(B, Cin, L, Cout, Kw, 1, pad, dilation, gen.BF16) - weights < B * Cin * L * 2
+
+    assert in_place(8, 512, 4096, 512, 3, 1)            # 66 / 58
+    assert in_place(8, 128, 54071, 256, 1)              # 193 / 103
+    assert in_place(10, 192, 65149, 157, 5, 0, 2)       # 463 / 339
+    assert in_place(9, 384, 7552, 64, 3, 1)             # 66 / 52
+    assert not in_place(7, 384, 1656, 265, 10)          # 65 / 83
+    assert not in_place(2, 448, 576, 234, 5, 2)         # 26 / 33
+    assert not in_place(3, 384, 3758, 128, 10, 4)       # 46 / 53
+    assert not in_place(5, 384, 2048, 261, 10, 9, 2)    # 49 / 64
