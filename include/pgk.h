@@ -102,9 +102,8 @@ typedef enum {
  * below 2^-119 other than zero, or with one that is not finite is computed with the float32 instruction.)
  * The matrix-core kernels read operands in place when their rows start on 4-byte boundaries
  * (float32 always; bfloat16 when K -- and, for B as [K][N], N -- is even).  Otherwise, from 2^25
- * multiply-adds on, tiles are copied through registers where that costs less than the copies that follow
- * (short K, or one operand only); else, when
- * the problem has at least 64^3 multiply-adds, the operands are first copied into the
+ * multiply-adds on, tiles are copied through registers where that is estimated to cost less than the copies that
+ * follow (short K, large operands for their outputs, grids of many workgroups); else, when the problem has at least 64^3 multiply-adds, the operands are first copied into the
  * workspace with rows padded with zeros to whole 16-byte chunks (up to batch*(M*K' + K'*N')
  * elements, K' and N' the next multiples of 8).  Products of at most 32 rows by 256 columns and more run, over
  * the range where that is the faster way, on a kernel whose workgroups take all of K: one pass, operands in
@@ -220,7 +219,9 @@ int pgk_gemm_splitk_bt(const void* A, const void* Bt, const float* bias, void* C
  *   out[0]  1 = matrix-core kernel, 0 = bounds-checked kernel
  *   out[1..3]  tile rows, tile columns, K tile
  *   out[4]  K slices (1 = one pass; more = the automatic two-pass split)
- *   out[5]  workgroups of the GEMM launch (few rows, one pass: the 32 x 128 tiles that its narrower workgroups make up)
+ *   out[5]  workgroups of the GEMM launch
+ * Few rows on the kernel whose workgroups take all of K are answered with the 32 x 128 tiles that those narrower workgroups make
+ * up, in one pass; from 64^3 multiply-adds on, a workspace query with PGK_WS_UNALIGNED that is 0 tells them from the tiles.
  * Returns PGK_OK, or the error pgk_gemm_fused would return for these sizes; out == NULL is
  * PGK_ERR_INVALID_ARG.  Nothing is launched.
  */
@@ -295,17 +296,21 @@ size_t pgk_reduce_max_workspace_bytes(int64_t outer, int64_t red, int64_t inner,
  * within the index ranges of pgk_gemm_fused (else PGK_ERR_INVALID_ARG / PGK_ERR_UNSUPPORTED).
  *
  * The convolution runs on the matrix cores as a sum over the taps of GEMMs on shifted views of
- * the input (no unfolded copy of the input is made) when Lout is at least 16, in one of two
- * ways (where the kernels read x itself, x must start on a 16-byte boundary; w, bias and y may
- * start on any element).
- * Stride 1, Cin a multiple of the K tile (32 float32 / 64 bfloat16) and, for bfloat16, an even
- * dilation (or Kw = 1) or Cout of more than 32 and Cout * Kw of at most 3000: the views are taken of the input itself --
- * only the tile columns at the ends of the rows read small zero-padded strips -- or (padding wider than a tile; up to 32
- * output channels and Lout no multiple of 16 bytes of elements) of one zero-padded copy of it.  Otherwise
- * -- stride > 1, any Cin of at least half a K tile's multiple (Cin >= its round-up / 2), other odd
- * dilations in bfloat16 -- with Kw <= 32: the views are taken of copies of the input, one per
- * phase of the stride (and a second one shifted by one element for bfloat16 taps at odd
- * offsets), channels padded with zeros to a multiple of the K tile.  Both need `workspace`
+ * the input (no unfolded copy of the input is made) when Lout is at least 16, in one of three
+ * ways.  w, bias and y may start on any element.
+ *  1. Stride 1, Cin a multiple of the K tile (32 float32 / 64 bfloat16), padding and (Kw - 1) * dilation no wider
+ *     than an output tile: the views are taken of the input itself, and only the tile columns at the ends of the rows
+ *     read small zero-padded strips.  Bfloat16 whose dilation (with Kw > 1), padding or L is odd, so that tiles start off
+ *     4-byte boundaries: where Cout is above 32, Cout * Kw at most 3000 and copying tiles through registers costs less
+ *     than the copies of 2 or 3.  Float32, and bfloat16 with all of them even: also where Lout is no multiple of 16 bytes of
+ *     elements, if Cout is above 32.  x may start on any element where tiles go through registers or Lout is no
+ *     such multiple; otherwise an x off a 16-byte boundary takes the bounds-checked kernel.
+ *  2. Such a stride and Cin in the other cases, but with a dilation that is even or of no consequence (float32, Kw = 1): of one
+ *     zero-padded copy of the input (of the input itself, on a 16-byte boundary, where there is nothing to pad).
+ *  3. Otherwise -- stride > 1, any Cin of at least half a K tile's multiple (Cin >= its round-up / 2), odd
+ *     dilations in bfloat16 -- with Kw <= 32: of copies of the input, one per phase of the stride (and a second one
+ *     shifted by one element for bfloat16 taps at odd offsets), channels padded with zeros to a multiple of the K tile.
+ * These need `workspace`
  * (device memory, 256-byte aligned, contents destroyed) of pgk_conv1d_workspace_bytes(...)
  * bytes for the regrouped weights and the strips or copies.  Too small or NULL gives
  * PGK_ERR_WORKSPACE.  Every other case needs no workspace (the query then returns 0): few input
