@@ -63,7 +63,9 @@ __device__ __forceinline__ int channel_slot(int c, int every)
 // STREAM: non-temporal stores.  With every sixteenth channel a row's runs are whole 64-byte pieces, and past L2 they go
 // out faster ([8, 1, 160000] * [512, 1, 10], stride 5: 137 us with plain stores, 116 so); with every fourth a run starts on any 16
 // bytes and L2 has to put lines together (15999 positions of 2 channels 64 us with plain stores, 109 so); rows on
-// the 64-byte grid are even (32000 positions 109 and 111, bf16 120000 53 and 58, 64 channels of 160000 77 and 69).
+// the 64-byte grid are even (32000 positions 109 and 111, bf16 120000 53 and 58, 64 channels of 160000 77 and 69).  For outputs beyond
+// what the last-level cache of 256 MiB takes only, which plain stores end in: 13 x 384 rows of 13325 (266 MB) 51 us with plain stores, 61 so,
+// 14 x 384 of 7188 (155 MB) 34 and 41; 9 x 320 of 27050 (312 MB) 89 and 81, 15 x 320 of 24766 (476 MB) 131 and 105.
 template <bool BF16, int ACT, int STEPS, bool STREAM = false>
 __global__ __launch_bounds__(256, 4) void conv_few_channels_kernel(const FewArgs p)
 {
@@ -251,13 +253,13 @@ bool conv_few_channels_fits(long long B, long long Cin, long long Cout, long lon
 }
 
 namespace {
-// (every sixteenth channel: fp32 with at most 16 products only)
+// (non-temporal stores: every sixteenth channel, which is fp32 with at most 16 products only)
 template <bool BF16, int ACT>
-void launch_few(const FewArgs& a, dim3 grid, size_t lds, hipStream_t s)
+void launch_few(const FewArgs& a, bool stream, dim3 grid, size_t lds, hipStream_t s)
 {
     const dim3 block(256);
     if constexpr (!BF16)
-        if (a.every == 16) {
+        if (stream) {
             if (a.K2 <= 8) hipLaunchKernelGGL((conv_few_channels_kernel<BF16, ACT, 4, true>), grid, block, lds, s, a);
             else hipLaunchKernelGGL((conv_few_channels_kernel<BF16, ACT, 8, true>), grid, block, lds, s, a);
             return;
@@ -305,12 +307,13 @@ hipError_t launch_conv_few_channels(const void* x, const void* w, const float* b
     if (wgs <= 0 || wgs > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t lds = (size_t)lds_floats(Cin, Kw, stride, dil, tiles, ch) * sizeof(float);
     const dim3 grid((unsigned int)wgs);
+    const bool stream = a.every == 16 && (long double)B * Cout * Lout * es > 300.0e6L;
 #define PGK_FEW_ACT(BF)                                                      \
     switch (act) {                                                           \
-    case ACT_RELU: launch_few<BF, ACT_RELU>(a, grid, lds, s); break;         \
-    case ACT_GELU_TANH: launch_few<BF, ACT_GELU_TANH>(a, grid, lds, s); break; \
-    case ACT_SILU: launch_few<BF, ACT_SILU>(a, grid, lds, s); break;         \
-    default: launch_few<BF, ACT_NONE>(a, grid, lds, s); break;               \
+    case ACT_RELU: launch_few<BF, ACT_RELU>(a, stream, grid, lds, s); break;         \
+    case ACT_GELU_TANH: launch_few<BF, ACT_GELU_TANH>(a, stream, grid, lds, s); break; \
+    case ACT_SILU: launch_few<BF, ACT_SILU>(a, stream, grid, lds, s); break;         \
+    default: launch_few<BF, ACT_NONE>(a, stream, grid, lds, s); break;               \
     }
     if (dtype == DT_BF16) { PGK_FEW_ACT(true) } else { PGK_FEW_ACT(false) }
 #undef PGK_FEW_ACT

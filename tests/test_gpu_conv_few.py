@@ -97,3 +97,27 @@ def test_few_channels_integers_are_exact_and_special_values_stay_in_place(pgk, o
     want = np.zeros((B, 700), dtype=bool)
     want[3, :4] = want[7, 696:] = True
     assert np.array_equal(bad.any(axis=1), want)
+
+
+@gpu
+@pytest.mark.parametrize("case", [(11, 1, 30001, 256, 3, 1, 0, 1), (11, 1, 30001, 256, 10, 1, 4, 1), (7, 2, 118003, 512, 7, 5, 3, 1)])
+def test_outputs_beyond_the_last_level_cache_are_exact(pgk, case):
+    """fp32, every sixteenth channel and more than 300 MB of output: non-temporal stores.  Small integers: every sum exact."""
+    import torch
+    B, Cin, L, Cout, Kw, stride, pad, dil = case
+    Lout = lout_of(case)
+    assert B * Cout * Lout * 4 > 300e6 and Lout % 16 != 0 and Lout // 128 * -(-Cout // 512) * B >= 512
+    g = torch.Generator(device="cuda").manual_seed(L)
+    x = torch.randint(-7, 8, (B, Cin, L), generator=g, device="cuda").float()
+    w = torch.randint(-7, 8, (Cout, Cin, Kw), generator=g, device="cuda").float()
+    bias = torch.randint(-7, 8, (Cout,), generator=g, device="cuda").float()
+    n = B * Cout * Lout
+    flat = torch.full((n + 64,), 7.5, device="cuda")
+    y = flat[17:17 + n].view(B, Cout, Lout)
+    pgk.conv1d(x, w, bias, gen.ACT_NONE, stride, pad, dil, out=y)
+    assert bool((flat[:17] == 7.5).all()) and bool((flat[17 + n:] == 7.5).all()), "wrote outside y"
+    xp = torch.nn.functional.pad(x.double(), (pad, pad))
+    span = (Lout - 1) * stride + 1
+    for b in range(B):
+        ref = bias.double().view(-1, 1) + sum(w[:, :, k].double() @ xp[b, :, k * dil:k * dil + span:stride].contiguous() for k in range(Kw))
+        assert torch.equal(y[b].double(), ref), b
