@@ -1,6 +1,5 @@
 // Fixed-order reductions that follow the GEMM kernels:
-//  * rowsum_combine: adds the per-tile-column row-sum partials in tile order, what each addition rounds off
-//    carried along and added last (Knuth's two-sum);
+//  * rowsum_combine: adds the per-tile-column row-sum partials in tile order, in 64 bits;
 //  * splitk_reduce: second pass of the split-K path -- adds the K-slice partial
 //    products in slice order, then bias, activation, store and row sum.
 // No atomics: equal inputs give bit-equal outputs.  Both read each
@@ -40,22 +39,9 @@ __device__ __forceinline__ V ordered_sum(int n, F&& load)
     return sum;
 }
 
-// A sum and what its additions have rounded off.  The partials are one after another for each row, so their number, which
-// goes by the tile's width, would otherwise show in the error (256 x 44864 x 3079, bf16 with odd rows: 176 columns of 256
-// 2.1e-7, 351 of 128 2.8e-7); the kernel waits for its loads either way.
-struct CarriedSum {
-    float sum, lost;
-    __device__ __forceinline__ CarriedSum& operator+=(const CarriedSum& o)
-    {
-        const float s = sum + o.sum, part = s - sum;
-        lost += (sum - (s - part)) + (o.sum - part);
-        sum = s;
-        return *this;
-    }
-    // (infinities and NaN are those of the plain sum: `lost` is NaN then)
-    __device__ __forceinline__ float value() const { return __builtin_isfinite(sum) ? sum + lost : sum; }
-};
-
+// In 64 bits: the partials are added one after another for each row, so their number, which goes by the tile's width,
+// would otherwise show in the error (256 x 44864 x 3079, bf16 with odd rows: 176 columns of 256 2.1e-7, 351 of 128 2.8e-7; in 64 bits
+// 2.8e-8).  The kernel waits for its loads: as fast as 32-bit sums, where carrying what those round off took a microsecond more.
 __global__ __launch_bounds__(256) void rowsum_combine_kernel(const float* __restrict__ part,
                                                              float* __restrict__ rowsum,
                                                              int M, int batch, int tiles_n)
@@ -65,8 +51,7 @@ __global__ __launch_bounds__(256) void rowsum_combine_kernel(const float* __rest
     if (i >= total) return;
     const size_t b = i / M, m = i - b * M;
     const float* src = part + b * (size_t)tiles_n * M + m;
-    const CarriedSum sum = ordered_sum<CarriedSum>(tiles_n, [&](int t) { return CarriedSum{src[(size_t)t * M], 0.0f}; });
-    rowsum[i] = sum.value();
+    rowsum[i] = (float)ordered_sum<double>(tiles_n, [&](int t) { return (double)src[(size_t)t * M]; });
 }
 
 hipError_t launch_rowsum_combine(const float* part, float* rowsum, int M, int batch, int tiles_n,
