@@ -100,7 +100,7 @@ def test_few_channels_integers_are_exact_and_special_values_stay_in_place(pgk, o
 
 
 @gpu
-@pytest.mark.parametrize("case", [(11, 1, 30001, 256, 3, 1, 0, 1), (11, 1, 30001, 256, 10, 1, 4, 1), (7, 2, 118003, 512, 7, 5, 3, 1)])
+@pytest.mark.parametrize("case", [(11, 1, 30001, 256, 3, 1, 0, 1), (11, 1, 30002, 256, 10, 1, 4, 1), (7, 2, 118003, 512, 7, 5, 3, 1)])
 def test_outputs_beyond_the_last_level_cache_are_exact(pgk, case):
     """fp32, every sixteenth channel and more than 300 MB of output: non-temporal stores.  Small integers: every sum exact."""
     import torch
