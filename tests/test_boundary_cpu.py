@@ -595,3 +595,17 @@ def test_odd_convolutions_copy_the_input_where_that_is_faster(lib):
     assert not in_place(2, 448, 576, 234, 5, 2)         # 26 / 33
     assert not in_place(3, 384, 3758, 128, 10, 4)       # 46 / 53
     assert not in_place(5, 384, 2048, 261, 10, 9, 2)    # 49 / 64
+
+
+def test_kernels_that_spill_registers_are_known(lib):
+    """The build's resource table: the large bf16 tile with an operand copied through registers spills a few, no other
+    kernel any."""
+    import json
+
+    from paper_2511_06345_amd import build
+    if not os.path.exists(build.RESOURCES):
+        pytest.skip("no resource table: the library was not built here")
+    with open(build.RESOURCES) as f:
+        table = json.load(f)
+    spilled = {name: use["vgpr_spills"] for name, use in table.items() if use.get("vgpr_spills")}
+    assert all("MfmaCfgReg<false, 256, 256, 64" in name and n <= 16 for name, n in spilled.items()), spilled
