@@ -27,11 +27,13 @@ __device__ __forceinline__ void ordered_batch(V& sum, int& s, F&& load)
     for (int q = 0; q < BATCH; ++q) sum += v[q];
     s += BATCH;
 }
-template <typename V, typename F>
+template <typename V, int FIRST = 8, typename F>
 __device__ __forceinline__ V ordered_sum(int n, F&& load)
 {
     V sum = load(0);
     int s = 1;
+    if constexpr (FIRST > 8)
+        while (n - s >= FIRST) ordered_batch<FIRST>(sum, s, load);
     while (n - s >= 8) ordered_batch<8>(sum, s, load);
     if (n - s >= 4) ordered_batch<4>(sum, s, load);
     if (n - s >= 2) ordered_batch<2>(sum, s, load);
@@ -41,7 +43,9 @@ __device__ __forceinline__ V ordered_sum(int n, F&& load)
 
 // In 64 bits: the partials are added one after another for each row, so their number, which goes by the tile's width,
 // would otherwise show in the error (256 x 44864 x 3079, bf16 with odd rows: 176 columns of 256 2.1e-7, 351 of 128 2.8e-7; in 64 bits
-// 2.8e-8).  The kernel waits for its loads: as fast as 32-bit sums, where carrying what those round off took a microsecond more.
+// 2.8e-8).  Slower than 32-bit additions where few rows have hundreds of tile columns, which sixteen loads in flight more than make
+// up for (whole calls, 32 bits / 64 bits / with sixteen loads: 100 x 30000 x 512 fp32 42.5, 43.2, 39.7 us, 300 x 40000 x 256 bf16 35.0, 35.2,
+// 32.8, 64 x 50000 x 200 fp32 50.0, 50.8, 39.1); added in pairs 43.0, 35.9 and 51.4.
 __global__ __launch_bounds__(256) void rowsum_combine_kernel(const float* __restrict__ part,
                                                              float* __restrict__ rowsum,
                                                              int M, int batch, int tiles_n)
@@ -51,7 +55,7 @@ __global__ __launch_bounds__(256) void rowsum_combine_kernel(const float* __rest
     if (i >= total) return;
     const size_t b = i / M, m = i - b * M;
     const float* src = part + b * (size_t)tiles_n * M + m;
-    rowsum[i] = (float)ordered_sum<double>(tiles_n, [&](int t) { return (double)src[(size_t)t * M]; });
+    rowsum[i] = (float)ordered_sum<double, 16>(tiles_n, [&](int t) { return (double)src[(size_t)t * M]; });
 }
 
 hipError_t launch_rowsum_combine(const float* part, float* rowsum, int M, int batch, int tiles_n,

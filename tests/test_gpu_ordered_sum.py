@@ -33,7 +33,7 @@ def test_slices(splits, N):
     _check(A, B, bias, C, rs)
 
 
-@pytest.mark.parametrize("tiles", [1, 2, 4, 8, 9, 12, 16, 17])
+@pytest.mark.parametrize("tiles", [1, 2, 4, 8, 9, 12, 16, 17, 18, 32, 33, 48])
 def test_row_sum_partials(tiles):
     M, N, K = 512, 64 * tiles, 128
     A, B, bias = _ints((1, M, K), 4, torch.float32), _ints((1, K, N), 5, torch.float32), _ints((N,), 6, torch.float32)
@@ -56,8 +56,8 @@ def test_row_sum_partials_that_are_not_finite():
 
 @pytest.mark.parametrize("dtype,bt", [(torch.float32, False), (torch.bfloat16, True)])
 def test_row_sums_of_many_tile_columns_are_rounded_once(dtype, bt):
-    # non-negative whole numbers: sums inside a tile stay below 2^24 and are exact, those of a row do not, and what each addition of
-    # a partial rounds off (a whole number again) is carried, so the result is the exact sum rounded once
+    # non-negative whole numbers: sums inside a tile stay below 2^24 and are exact, those of a row do not, and the partials are
+    # added in 64 bits, exactly, so the result is the exact sum rounded once
     M, N, K = 512, 64 * 301, 255
     g = torch.Generator().manual_seed(9)
     A = torch.randint(0, 8, (1, M, K), generator=g).to(dtype).cuda()
