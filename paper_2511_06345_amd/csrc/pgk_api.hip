@@ -623,42 +623,75 @@ FusedPlan plan_fused(bool aligned, int64_t M, int64_t N, int64_t K, int64_t batc
     return fp;
 }
 
+// K tiles of a workgroup (one slice): those of the main loop, and those at its end that are loaded with waits and run-time
+// checks (the loop goes in trips of six; the last two load nothing any more).  whole: the last K tile is no edge.
+struct LoopTiles { double steady, tail; };
+
+LoopTiles loop_tiles(int64_t K, int count, bool whole)
+{
+    const int64_t n = ((K + 63) / 64 + count - 1) / count, m = n - (whole ? 0 : 1);
+    const int64_t rest = n - (m > 7 ? (m - 2) / 6 * 6 : 0);
+    return {(double)(n - std::max<int64_t>(rest - 2, 0)), (double)std::max<int64_t>(rest - 2, 0)};
+}
+
 // Whether operands with odd rows are copied through registers (pgk_gemm_mfma_reg.hip) or first into rows padded to whole
-// chunks (pack_dims).  Loads and LDS writes of their own cost the main loop's matrix work: with one operand on the large
-// tile 0.7 of the loop's time in the round model (4096 x 4096 x 4096 direct 102 us, A 108, B 107, with rows off the grid 114 and 121;
-// with K odd as well as in shorter loops more), on the small tile, which always takes both that way, 1.4, and 1.6 where both
-// are odd or B is transposed; a CU with a single workgroup has nothing to cover them with and loses 0.7 of a full round's.
-// The copies cost two passes over memory at 4 TB/s (an odd K: both operands, rows of a plain B: B alone) and 5 us a launch.
-// Output rows off the 128-byte grid are stored plainly by the register instances, which gains 0.16 us a megabyte.
-// Fitted to 600 shapes (33 ... 16384 x 33 ... 50257 x 33 ... 65536, batches up to 64, both layouts of B, splits): of the choices
-// 15 are more than 5 % slower than the copies, 17 than the registers, 0.8 % above the better of both in the geometric mean.
-// Copied first / through registers: 512 x 50257 x 768 84 / 65 us, 128 x 256 x 32371, 16 entries, 233 / 100, 9800 x 12713 x 64
-// 139 / 90, 1024 x 2048 x 255 (B transposed) 19 / 12; 2048 x 2047 x 2048 35 / 49, 4096 x 4095 x 4095 126 / 180, 16 x [1501 x 1501 x 1501] 199 / 215.
+// chunks (pack_dims): both ways as they would be planned, in microseconds on the measured part.  A round of workgroups takes a
+// fixed time and so much per K tile, more for those at a loop's end, and a last round with one workgroup on its busiest CU a time of its own.  K tiles
+// through registers take 1.25 to 1.5 times as long, and 1.1 times that with A so on the large tile, with both operands odd or B
+// transposed on the small one; the copies read and write at 5 TB/s, an odd K both operands, rows of a plain B it alone, and take 2.4 us a launch.
+// Output rows off the 16-byte grid take 0.14 us a megabyte more, 0.03 with the plain stores of the register instances.
+// Fitted to 6400 fused calls (33 ... 16384 x 33 ... 50257 x 33 ... 16384, batches up to 64, both layouts of B, up to 1.5 TFLOP).  On 2000 others: 0.6 %
+// above the better of both ways in the geometric mean (copies always 16 %, registers always 5 %), 50 of the choices more than 5 % slower
+// than the copies, 50 than the registers; 600 split calls 1.2 %.
+// Copied first / through registers: 512 x 50257 x 768 83 / 70 us, 128 x 256 x 32371, 16 entries, 228 / 96, 9800 x 12713 x 64
+// 139 / 89, 1024 x 2048 x 255 (B transposed) 14 / 11; 2048 x 2047 x 2048 34 / 46, 4096 x 4095 x 4095 132 / 213, 16 x [1501 x 1501 x 1501] 182 / 237,
+// 832 x 1440 x 379 (B transposed), 32 entries, 78 / 120, 960 x 3433 x 257, 16 entries, 99 / 120.
 bool reg_copies_pay(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, Slices slices)
 {
-    struct Estimate { int kind, count; double time; };
-    auto estimate = [&](int64_t k, int64_t ldb) {
-        Estimate e{slices.kind, slices.count, 0.0};
-        if (!e.count) {
-            const FusedPlan fp = plan_fused(true, M, N, k, batch, dtype, b_trans, ldb);
-            e.count = fp.split ? fp.slices.splits : 1;
-            e.kind = fp.split ? fp.split_small_tile : fp.path.kind;
+    // a round: fixed + steady and tail K tiles; the last one: with one workgroup on its busiest CU, and with two, as a share
+    struct Cost { double fixed, steady, tail, lone_fixed, lone_steady, lone_tail, two; };
+    auto time = [](const Cost& c, LoopTiles t, Rounds r, double loop) {
+        const double round = c.fixed + loop * (c.steady * t.steady + c.tail * t.tail);
+        const double lone = c.lone_fixed + loop * (c.lone_steady * t.steady + c.lone_tail * t.tail);
+        return round * (r.full + (r.rest > 1 ? c.two : 0.0)) + (r.rest == 1 ? lone : 0.0);
+    };
+    auto packed_cost = [](int kind) -> Cost {
+        switch (kind) {
+        case pgk::TILE_LARGE: return {5.5, 1.24, 1.86, 6.4, 1.07, 2.21, 1.0};
+        case pgk::TILE_TALL: return {5.3, 0.95, 1.51, 4.1, 0.74, 1.18, 1.0};
+        case pgk::TILE_WIDE: return {3.3, 0.84, 1.33, 3.5, 0.88, 1.41, 1.0};
+        default: return {3.0, 0.85, 2.02, 1.8, 0.52, 1.24, 0.84};
         }
-        e.kind = choose_path(true, M, N, k, dtype, batch * e.count, e.kind, b_trans, ldb).kind;
-        const double second_pass = e.count > 1 ? 2.0 * e.count * (double)M * (double)N * (double)batch * 4.0 / 4.0e6 + 5.0 : 0.0;
-        e.time = estimated_rounds_time(M, N, (k + e.count - 1) / e.count, dtype, batch * e.count, e.kind) + second_pass;
-        return e;
+    };
+    auto reg_cost = [](int kind) -> Cost {
+        if (kind == pgk::TILE_LARGE) return {4.6, 1.53, 2.43, 4.5, 1.45, 2.16, 1.0};
+        return {2.5, 1.23, 2.30, 2.1, 0.78, 1.84, 0.93};
+    };
+    struct Planned { int kind, count; Rounds rounds; };
+    auto plan = [&](int64_t k, int64_t ldb) {
+        Planned p{slices.kind, slices.count, {}};
+        if (!p.count) {
+            const FusedPlan fp = plan_fused(true, M, N, k, batch, dtype, b_trans, ldb);
+            p.count = fp.split ? fp.slices.splits : 1;
+            p.kind = fp.split ? fp.split_small_tile : fp.path.kind;
+        }
+        p.kind = choose_path(true, M, N, k, dtype, batch * p.count, p.kind, b_trans, ldb).kind;
+        p.rounds = rounds_of(M, N, dtype, batch * p.count, p.kind);
+        return p;
     };
     const OddRows odd = odd_rows(K, dtype, b_trans, N);
     const int64_t epc = chunk_elems(dtype), k = odd.a ? round_up64(K, epc) : K;
-    const Estimate reg = estimate(K, 0), packed = estimate(k, b_trans ? k : round_up64(N, epc));
-    const Rounds r = rounds_of(M, N, dtype, batch * reg.count, reg.kind);
-    const double loops = tile_cost(dtype, reg.kind).per_k * (double)K / (1024.0 * reg.count) * (r.full + (r.rest == 1 ? 0.7 : r.rest > 1 ? 1.0 : 0.0));
-    const double lost = reg.kind == pgk::TILE_LARGE ? 0.7 : (odd.a && odd.b) ? 1.6 : 1.4;
-    const double bytes = 4.0 * (double)K * (double)batch * ((odd.a ? (double)M : 0.0) + (double)N);
-    const double off_grid = reg.count == 1 && N % 64 != 0 ? 2.0 * (double)M * (double)N * (double)batch : 0.0;
-    // (where the registers need another tile than the copies would have, no less than that one takes)
-    return std::max(reg.time, packed.time) + lost * loops < packed.time + bytes / 4.0e6 + (odd.a ? 10.0 : 5.0) + 0.16e-6 * off_grid;
+    const Planned reg = plan(K, 0), packed = plan(k, b_trans ? k : round_up64(N, epc));
+    const double in = (double)K * (double)batch * 2.0e-6, out = (double)M * (double)N * (double)batch * 2.0e-6;    // MB (in: a row's)
+    const double partials = 0.6 * out;                                     // (a slice's, written and read)
+
+    const double loop = reg.kind == pgk::TILE_LARGE ? (odd.a ? 1.09 : 1.0) : b_trans ? 1.13 : odd.a && odd.b ? 1.11 : 1.0;
+    const double by_reg = time(reg_cost(reg.kind), loop_tiles(K, reg.count, false), reg.rounds, loop) +
+                          in * (0.17 * (double)M + 0.14 * (double)N) + (N % 8 != 0 ? 0.17 : 0.14) * out + (reg.count > 1 ? reg.count * partials : 0.0);
+    const double by_copies = time(packed_cost(packed.kind), loop_tiles(k, packed.count, k % 64 == 0), packed.rounds, 1.0) +
+                             in * ((odd.a ? 0.41 * (double)M : 0.0) + (b_trans ? 0.39 : 0.34) * (double)N) +
+                             (odd.a ? 4.8 : 2.2) + (N % 8 != 0 ? 0.20 : 0.06) * out + (packed.count > 1 ? packed.count * partials : 0.0);
+    return by_reg < by_copies;
 }
 
 // ---- The caller's workspace.  Everything a call needs beyond its inputs and outputs is cut from

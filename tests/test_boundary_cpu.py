@@ -478,10 +478,16 @@ def test_odd_rows_are_copied_first_where_that_is_faster(lib):
     assert copied(6528, 192, 3941, 1, True)             # 64 / 77
     assert copied(1501, 1501, 1501, 16)                 # 199 / 215: the copies' launches are paid once, the loop's loss per entry
     assert copied(2944, 20352, 2763, 1, True)           # 335 / 542
+    # few K tiles: those at a loop's end cost registers most
+    assert copied(832, 1440, 379, 32, True)             # 78 / 120
+    assert copied(960, 3433, 257, 16)                   # 99 / 120
+    assert copied(791, 513, 511, 1, True)               # 15 / 22
+    assert copied(4608, 271, 374)                       # 18.7 / 21.0
+    assert not copied(217, 701, 5568, 32)               # 199 / 125
     assert not copied(512, 50257, 768)                  # 84 / 65
     assert not copied(128, 256, 32371, 16)              # 233 / 100
     assert not copied(9800, 12713, 64)                  # 139 / 90
-    assert not copied(4096, 4096, 511)                  # 36 / 29
+    assert not copied(2799, 4096, 559)                  # 31 / 25
     assert not copied(1024, 2048, 255, 1, True)         # 19 / 12
     # both operands through registers: the small tile, also where slices and rounds are counted (the large one does not exist)
     assert binding.gemm_plan(528, 223, 30575, 12, gen.BF16)["tile"] == (128, 128, 64)

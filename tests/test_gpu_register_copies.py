@@ -72,7 +72,7 @@ def test_odd_rows_copied_first_exact(pgk, M, N, K, batch, bt):
 
 
 # every instance at one, two, three and many K tiles, whole and partial last ones
-LARGE_A = [(600, 16400, 63), (600, 16400, 127), (3900, 4100, 129), (3900, 4100, 577), (4096, 4096, 511)]
+LARGE_A = [(600, 16400, 63), (600, 16400, 127), (3900, 4100, 129), (3900, 4100, 577), (2255, 6400, 487)]
 LARGE_B = [(500, 50257, 64), (500, 50257, 62), (500, 50257, 128), (500, 50257, 190), (300, 20001, 640), (500, 50257, 646)]
 SMALL = [(1000, 2303, 63), (1000, 2303, 65), (1000, 2303, 191), (1000, 2303, 575), (3000, 4999, 129)]
 INSTANCES = ([(256, *s, 1, False) for s in LARGE_A + LARGE_B] + [(128, *s, 1, bt) for s in SMALL for bt in (False, True)] +
