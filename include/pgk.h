@@ -105,7 +105,7 @@ typedef enum {
  * multiply-adds on, tiles are copied through registers where that is estimated to cost less than the copies that
  * follow (short K, large operands for their outputs, grids of many workgroups); else, when the problem has at least 64^3 multiply-adds, the operands are first copied into the
  * workspace with rows padded with zeros to whole 16-byte chunks (up to batch*(M*K' + K'*N')
- * elements, K' and N' the next multiples of 8).  Products of at most 32 rows by 256 columns and more run, over
+ * elements, K' and N' the next multiples of 8; with a smaller workspace, registers if there is a kernel for it).  Products of at most 32 rows by 256 columns and more run, over
  * the range where that is the faster way, on a kernel whose workgroups take all of K: one pass, operands in
  * place at any alignment of their elements, row sums per 16 (B transposed) or up to 128 columns (with a smaller
  * workspace that holds the row sums of the 32 x 128 tiles, per 128 columns, those run instead).  C, bias and rowsum are always used in place,
@@ -128,8 +128,8 @@ typedef enum {
  * enough for at least two slices; or fewer than 192 large tiles and K of at least 512 K
  * tiles; pgk_gemm_plan tells) -- the partial products of an automatic K split, computed
  * exactly as by pgk_gemm_splitk with splits = 0 (at most 256 MiB; larger cases are not
- * split).  Which route a problem takes depends on its shape and on the alignment of A and B
- * only, so results stay bit-reproducible.
+ * split).  Which route a problem takes depends on its shape, on the alignment of A and B and on whether
+ * the workspace has the bytes of the query only, so results stay bit-reproducible.
  */
 int pgk_gemm_fused(const void* A, const void* B, const float* bias, void* C, float* rowsum,
                    int64_t M, int64_t N, int64_t K, int64_t batch,

@@ -106,8 +106,9 @@ bool mfma_shape_ok(int64_t M, int64_t N, int64_t K, int dtype, bool b_trans = fa
     return true;
 }
 
-// The slices of a split call (0: the fused call's own plan) and the tile that an automatic count comes with (-1: by the grid)
-struct Slices { int count, kind; };
+// The slices of a split call (0: the fused call's own plan) and the tile that an automatic count comes with (-1: by the grid).
+// no_copies: registers wherever there is a kernel for them (a workspace without room for padded copies)
+struct Slices { int count, kind; bool no_copies; };
 
 bool reg_copies_pay(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, Slices slices);
 
@@ -116,7 +117,7 @@ bool reg_copies_pay(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, b
 bool needs_packing(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, Slices slices)
 {
     const OddRows odd = odd_rows(K, dtype, b_trans, N);
-    return (odd.a || odd.b) && !(reg_copies_exist(M, N, K) && reg_copies_pay(M, N, K, batch, dtype, b_trans, slices));
+    return (odd.a || odd.b) && !(reg_copies_exist(M, N, K) && (slices.no_copies || reg_copies_pay(M, N, K, batch, dtype, b_trans, slices)));
 }
 
 // The dimensions the kernels see for a problem that is packed first: K and the row length of B,
@@ -147,7 +148,7 @@ PackDims pack_dims(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bo
 // cores, one way or the other, with either layout
 bool mfma_route(int64_t M, int64_t N, int64_t K, int dtype)
 {
-    const Slices fused{0, -1};
+    const Slices fused{0, -1, false};
     return mfma_shape_ok(M, N, K, dtype) || pack_dims(M, N, K, 1, dtype, false, fused).pack ||
            mfma_shape_ok(M, N, K, dtype, true) || pack_dims(M, N, K, 1, dtype, true, fused).pack;
 }
@@ -544,14 +545,19 @@ size_t split_part_bytes(int64_t M, int64_t N, int64_t batch, bool rowsum)
 //    columns (8 x 11008 x 4096 40.3 / 32.7, 14 x 13248 x 4224 54 / 44; 15 x 12933 x 4352 48 / 57, 9 x 5228 x 4672 29 / 43, 13 x 18048 x 2210 40 / 47).
 // Beyond a K of 8192 only odd rows gain (bf16, B transposed, 6 x 14592 x 8704 55 / 59; fp32 9 x 12544 x 10368 94 / 105). A second
 // row block (17 ... 32 rows) loses but for odd rows.
-bool stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, pgk::StreamPlan* pl)
+//
+// no_copies: odd rows whose operands would be copied first, for a workspace without room for that: whatever the kernel takes.
+bool stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, pgk::StreamPlan* pl, bool no_copies = false)
 {
     const bool f32 = dtype == PGK_DTYPE_F32;
     const bool odd = !f32 && (K % 2 != 0 || (!b_trans && N % 2 != 0));
     if (M > 32 || K < 64 || K > (odd ? 16384 : 8192) || N < 256) return false;
     if (M > 16 && (b_trans || !odd)) return false;
     const int64_t tiles = (N + 127) / 128 * batch;
-    if (b_trans) {
+    const bool any = no_copies && odd;
+    if (b_trans && any) {
+        pl->blocks = 1;
+    } else if (b_trans) {
         if (!f32 && !odd && K < 256) return false;
         const int64_t most = odd ? (K >= 512 ? 192 : 128) : f32 ? (K >= 1024 ? 192 : K >= 256 ? 128 : 64) : K >= 1024 ? 160 : K >= 512 ? 96 : 48;
         if (tiles > most || N > 16384 || (K < 1024 && N > 8192)) return false;
@@ -559,7 +565,7 @@ bool stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool
         if (f32 && (K > 4096 || (K > 2048 && N > 12288))) return false;
         pl->blocks = 1;
     } else if (!f32) {
-        if (odd ? K > 4096 && (N < 4096 || 5 * N < 3 * K) : tiles >= 128 || K > 4096 || (N <= 4096 && K > 1024)) return false;
+        if (any ? false : odd ? K > 4096 && (N < 4096 || 5 * N < 3 * K) : tiles >= 128 || K > 4096 || (N <= 4096 && K > 1024)) return false;
         pl->blocks = N >= 16384 && K <= 8192 ? 8 : 4;   // (8 / 4: 24 x 16387 x 4095 58 / 78 us, 16 x 11008 x 4095 38 / 31; 15001 x 2048 19 / 21)
     } else {
         if (tiles > 320 || N > 32768 || (K > 1024 && (N <= 4096 || N > 16384))) return false;
@@ -742,19 +748,21 @@ bool pack_needs(WsNeeds& w, int64_t M, int64_t N, int64_t K, int64_t batch, int 
     return true;
 }
 
-// allow_stream: false = the tiles in any case
+// How a fused call may run: the fastest way, the tiles in any case, or with no copies of operands that only their odd rows ask for
+enum class Way { fastest, tiles, no_copies };
+
 WsNeeds fused_needs(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, bool want_rowsum, bool a_mis,
-                    bool b_mis, bool allow_stream = true)
+                    bool b_mis, Way way = Way::fastest)
 {
     WsNeeds w{};
-    if (allow_stream && stream_plan(M, N, K, batch, dtype, b_trans, &w.sp)) {
+    if (way != Way::tiles && stream_plan(M, N, K, batch, dtype, b_trans, &w.sp, way == Way::no_copies)) {
         w.ok = w.stream = true;
         w.d = PackDims{false, K, 0, false, b_trans};
         w.rs_part = (want_rowsum && w.sp.groups > 1) ? (size_t)batch * (size_t)w.sp.groups * (size_t)M * sizeof(float) : 0;
         lay_out(w);
         return w;
     }
-    w.ok = pack_needs(w, M, N, K, batch, dtype, b_trans, a_mis, b_mis, Slices{0, -1});
+    w.ok = pack_needs(w, M, N, K, batch, dtype, b_trans, a_mis, b_mis, Slices{0, -1, way == Way::no_copies});
     if (!w.ok) return w;
     // the problem as the kernels see it
     const bool packed = w.d.pack;
@@ -785,15 +793,28 @@ WsNeeds splitk_needs(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, 
     return w;
 }
 
-// What a fused call with `workspace_bytes` does.  The kernel for few rows has row sums per 16 to 128 columns where the tiles
-// have them per 128: a workspace with room for the tiles' alone is still enough, and the tiles run.
+// What calls with `workspace_bytes` do.  The kernel for few rows has row sums per 16 to 128 columns where the tiles have them
+// per 128, and odd rows that are copied first may be read in place as well: a workspace with room for the slower way is enough for it.
 WsNeeds fused_needs_within(size_t workspace_bytes, int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans,
                            bool want_rowsum, bool a_mis, bool b_mis)
 {
     const WsNeeds w = fused_needs(M, N, K, batch, dtype, b_trans, want_rowsum, a_mis, b_mis);
-    if (!w.stream || w.total <= workspace_bytes) return w;
-    const WsNeeds tiles = fused_needs(M, N, K, batch, dtype, b_trans, want_rowsum, a_mis, b_mis, false);
-    return tiles.ok && tiles.total <= workspace_bytes ? tiles : w;
+    if (!w.ok || w.total <= workspace_bytes) return w;
+    for (const Way way : {Way::tiles, Way::no_copies}) {
+        const WsNeeds other = fused_needs(M, N, K, batch, dtype, b_trans, want_rowsum, a_mis, b_mis, way);
+        if (other.ok && other.total <= workspace_bytes) return other;
+    }
+    return w;
+}
+
+WsNeeds splitk_needs_within(size_t workspace_bytes, int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, Slices slices, bool b_trans,
+                            bool want_rowsum, bool a_mis, bool b_mis)
+{
+    const WsNeeds w = splitk_needs(M, N, K, batch, dtype, slices, b_trans, want_rowsum, a_mis, b_mis);
+    if (!w.ok || w.total <= workspace_bytes) return w;
+    slices.no_copies = true;
+    const WsNeeds other = splitk_needs(M, N, K, batch, dtype, slices, b_trans, want_rowsum, a_mis, b_mis);
+    return other.ok && other.total <= workspace_bytes ? other : w;
 }
 
 bool sizes_valid(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype)
@@ -986,7 +1007,7 @@ int pgk_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, int
         out[5] = (int32_t)tiles;
         return PGK_OK;
     }
-    const PackDims d = pack_dims(M, N, K, batch, dtype, b_transposed != 0, Slices{0, -1});      // as pgk_gemm_fused sees the problem
+    const PackDims d = pack_dims(M, N, K, batch, dtype, b_transposed != 0, Slices{0, -1, false});      // as pgk_gemm_fused sees the problem
     K = d.k;
     const FusedPlan fp = plan_fused(true, M, N, K, batch, dtype, d.b_trans, d.ldb);
     Path path = fp.path;
@@ -1020,7 +1041,7 @@ size_t pgk_gemm_splitk_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t 
     const int s = pgk_splitk_auto_splits(M, N, K, batch, dtype, splits);
     if (s <= 0) return 0;
     const bool mis = (flags & PGK_WS_UNALIGNED) != 0;
-    const WsNeeds w = splitk_needs(M, N, K, batch, dtype, Slices{s, split_tile_kind(M, N, K, batch, dtype, splits)}, (flags & PGK_WS_B_TRANSPOSED) != 0, (flags & PGK_WS_ROWSUM) != 0, mis, mis);
+    const WsNeeds w = splitk_needs(M, N, K, batch, dtype, Slices{s, split_tile_kind(M, N, K, batch, dtype, splits), false}, (flags & PGK_WS_B_TRANSPOSED) != 0, (flags & PGK_WS_ROWSUM) != 0, mis, mis);
     return w.ok ? w.total : 0;
 }
 
@@ -1046,7 +1067,8 @@ int gemm_splitk_impl(const void* A, const void* B, const float* bias, void* C, f
     const SplitPlan plan = plan_splits(M, N, K, batch, dtype, splits);
     const int tile_kind = split_tile_kind(M, N, K, batch, dtype, splits);
     const bool a_mis = !aligned16(A), b_mis = !aligned16(B);
-    const WsNeeds w = splitk_needs(M, N, K, batch, dtype, Slices{plan.splits, tile_kind}, b_trans, rowsum != nullptr, a_mis, b_mis);
+    const WsNeeds w = splitk_needs_within(workspace ? workspace_bytes : 0, M, N, K, batch, dtype, Slices{plan.splits, tile_kind, false}, b_trans,
+                                          rowsum != nullptr, a_mis, b_mis);
     if (!w.ok) return PGK_ERR_UNSUPPORTED;
     rc = check_workspace(w, workspace, workspace_bytes);
     if (rc != PGK_OK) return rc;

@@ -146,3 +146,41 @@ def test_row_sums_are_no_less_exact_than_of_padded_operands(pgk, M, N, K):
     odd, even = (pgk.gemm_fused_bt(x, y, None, ACT_NONE, rowsum=True)[1][0].double() for x, y in ((A, B), (pad(A, (0, 1)), pad(B, (0, 1)))))
     # (the errors of a few hundred rows: their norms agree to a tenth where both are sums of the same kind)
     assert float((odd - ref).norm()) <= 1.2 * float((even - ref).norm())
+
+
+@pytest.mark.parametrize("M,N,K,batch,bt", [
+    (1024, 2048, 1023, 1, True), (832, 1440, 379, 32, True), (2048, 2047, 320, 1, False), (700, 513, 511, 2, False), (4096, 4095, 512, 1, False),
+    (4096, 4096, 511, 1, False),
+    (32, 3072, 4429, 1, False), (9, 1000, 8191, 1, True),        # few rows
+])
+def test_without_room_for_copies_operands_are_read_in_place(pgk, M, N, K, batch, bt):
+    assert _copied(pgk, M, N, K, batch, bt)
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.randint(-7, 8, (batch, M, K), generator=g, device="cuda").to(torch.bfloat16)
+    B = torch.randint(-7, 8, (batch, N, K) if bt else (batch, K, N), generator=g, device="cuda").to(torch.bfloat16)
+    ws = torch.empty(16, dtype=torch.uint8, device="cuda")
+    C, _ = (pgk.gemm_fused_bt if bt else pgk.gemm_fused)(_inside(A), _inside(B), None, ACT_NONE, rowsum=False, workspace=ws)
+    ref = torch.stack([A[b].double() @ (B[b].double().t() if bt else B[b].double()) for b in range(batch)])
+    assert torch.equal(C, ref.to(torch.bfloat16))
+
+
+def test_split_call_with_room_for_its_partial_products_only(pgk):
+    M, N, K, splits = 512, 500, 8191, 4
+    q = pgk.gemm_splitk_workspace_bytes
+    products = splits * M * N * 4
+    assert q(M, N, K, 1, BF16, splits, 0) > products
+    g = torch.Generator(device="cuda").manual_seed(3)
+    A = torch.randint(-7, 8, (1, M, K), generator=g, device="cuda").to(torch.bfloat16)
+    B = torch.randint(-7, 8, (1, K, N), generator=g, device="cuda").to(torch.bfloat16)
+    ws = torch.full((products + 256,), 255, dtype=torch.uint8, device="cuda")
+    C, _ = pgk.gemm_splitk(_inside(A), _inside(B), None, ACT_NONE, splits=splits, rowsum=False, workspace=ws[:products])
+    assert torch.equal(C[0], (A[0].double() @ B[0].double()).to(torch.bfloat16))
+    assert bool((ws[products:] == 255).all())
+    with pytest.raises(pgk.PgkError):
+        pgk.gemm_splitk(A, B, None, ACT_NONE, splits=splits, rowsum=False, workspace=ws[:products - 256])
+
+
+def test_without_room_and_without_a_kernel_the_call_is_refused(pgk):
+    A, B = torch.ones((1, 500, 1001), dtype=torch.bfloat16, device="cuda"), torch.ones((1, 30, 1001), dtype=torch.bfloat16, device="cuda")
+    with pytest.raises(pgk.PgkError):
+        pgk.gemm_fused_bt(A, B, None, ACT_NONE, rowsum=False, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
