@@ -312,8 +312,8 @@ size_t pgk_reduce_max_workspace_bytes(int64_t outer, int64_t red, int64_t inner,
  *     shifted by one element for bfloat16 taps at odd offsets), channels padded with zeros to a multiple of the K tile.
  * These need `workspace`
  * (device memory, 256-byte aligned, contents destroyed) of pgk_conv1d_workspace_bytes(...)
- * bytes for the regrouped weights and the strips or copies.  Too small or NULL gives
- * PGK_ERR_WORKSPACE.  Every other case needs no workspace (the query then returns 0): few input
+ * bytes for the regrouped weights and the strips or copies.  Too small (also for the way through
+ * registers, if there is one) or NULL gives PGK_ERR_WORKSPACE.  Every other case needs no workspace (the query then returns 0): few input
  * channels under a large enough output run on a matrix-core kernel of their own, the rest (tiny
  * outputs) on a bounds-checked kernel; both read the input in place.
  */

@@ -1177,8 +1177,9 @@ struct ConvPlan {
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// no_copies: registers wherever there is a kernel for them (a workspace without room for copies of the input)
 ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw, int64_t stride, int64_t pad,
-                     int64_t dilation, int dtype)
+                     int64_t dilation, int dtype, bool no_copies = false)
 {
     ConvPlan pl{};
     if (B <= 0 || Cin <= 0 || L <= 0 || Cout <= 0 || Kw <= 0 || stride <= 0 || pad < 0 || dilation <= 0) return pl;
@@ -1216,7 +1217,7 @@ ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw
         const double lost = pl.kind == pgk::TILE_LARGE ? 0.35 : pl.kind == pgk::TILE_SMALL ? 0.5 : 0.7;
         return lost * loops < 6.0 * (double)B * (double)Cin * (double)L / 3.5e6 + 1.5;
     };
-    const bool reg = !bases_even && pl.kind != pgk::TILE_FLAT && Cout * Kw <= 3000 && reg_pays();
+    const bool reg = !bases_even && pl.kind != pgk::TILE_FLAT && Cout * Kw <= 3000 && (no_copies || reg_pays());
     // Reading the input in place needs the halo and the padding to be no wider than a tile.
     const bool strips = ((bases_even && (pl.Lout % epc == 0 || pl.kind != pgk::TILE_FLAT)) || reg) && halo <= bn && pad <= bn &&
                         (long double)B * Cin * 3 * ((bn + halo) / 256 + 2) < 2.0e9L;
@@ -1308,6 +1309,10 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
             (dtype == PGK_DTYPE_F32 || dtype == PGK_DTYPE_BF16) && pgk_conv1d_out_len(L, Kw, stride, pad, dilation) > 0)
             return PGK_ERR_UNSUPPORTED;
         return PGK_ERR_INVALID_ARG;
+    }
+    if (pl.fast && workspace && workspace_bytes < pl.w_bytes + pl.x_bytes) {
+        const ConvPlan in_place = plan_conv1d(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype, true);
+        if (in_place.fast && in_place.w_bytes + in_place.x_bytes <= workspace_bytes) pl = in_place;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t es = dtype == PGK_DTYPE_BF16 ? 2 : 4;

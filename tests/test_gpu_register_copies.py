@@ -184,3 +184,20 @@ def test_without_room_and_without_a_kernel_the_call_is_refused(pgk):
     A, B = torch.ones((1, 500, 1001), dtype=torch.bfloat16, device="cuda"), torch.ones((1, 30, 1001), dtype=torch.bfloat16, device="cuda")
     with pytest.raises(pgk.PgkError):
         pgk.gemm_fused_bt(A, B, None, ACT_NONE, rowsum=False, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+
+
+def test_convolution_without_room_for_copies_reads_its_input_in_place(pgk):
+    B, Cin, L, Cout, Kw, pad = 7, 384, 1656, 265, 10, 3
+    need = pgk.conv1d_workspace_bytes(B, Cin, L, Cout, Kw, 1, pad, 1, BF16)
+    assert need > 2 * 2 * B * Cin * L                       # two copies of the input
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randint(-3, 4, (B, Cin, L), generator=g, device="cuda").to(torch.bfloat16)
+    w = torch.randint(-3, 4, (Cout, Cin, Kw), generator=g, device="cuda").to(torch.bfloat16)
+    ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+    y = pgk.conv1d(_inside(x), _inside(w), None, ACT_NONE, 1, pad, 1, workspace=ws[:need // 2])
+    assert torch.equal(y, pgk.conv1d(x, w, None, ACT_NONE, 1, pad, 1))
+    xp = torch.nn.functional.pad(x.double(), (pad, pad))
+    ref = torch.stack([sum(w[:, :, k].double() @ xp[b, :, k:k + y.shape[2]].contiguous() for k in range(Kw)) for b in range(B)])
+    assert torch.equal(y, ref.to(torch.bfloat16)) and bool((ws[need // 2:] == 255).all())
+    with pytest.raises(pgk.PgkError):
+        pgk.conv1d(x, w, None, ACT_NONE, 1, pad, 1, workspace=ws[:256])
