@@ -103,7 +103,7 @@ typedef enum {
  * The matrix-core kernels read operands in place when their rows start on 4-byte boundaries
  * (float32 always; bfloat16 when K -- and, for B as [K][N], N -- is even).  Otherwise, from 2^25
  * multiply-adds on, tiles are copied through registers where that is estimated to cost less than the copies that
- * follow (short K, large operands for their outputs, grids of many workgroups); else, when the problem has at least 64^3 multiply-adds, the operands are first copied into the
+ * follow; else, when the problem has at least 64^3 multiply-adds, the operands are first copied into the
  * workspace with rows padded with zeros to whole 16-byte chunks (up to batch*(M*K' + K'*N')
  * elements, K' and N' the next multiples of 8; with a smaller workspace, registers if there is a kernel for it).  Products of at most 32 rows by 256 columns and more run, over
  * the range where that is the faster way, on a kernel whose workgroups take all of K: one pass, operands in
