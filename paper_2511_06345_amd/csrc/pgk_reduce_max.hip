@@ -11,7 +11,9 @@
 //   * inner == 1 (the reduced dimension is contiguous): a wave (short rows) or a
 //     256-thread workgroup (long rows) sweeps one row in 16-byte chunks; lanes are
 //     combined with cross-lane shuffles, waves through LDS.
-//   * inner > 1: lanes lie along the contiguous inner dimension, 16 bytes each; the four
+//   * 1 < inner, up to about half of what a workgroup loads at once: a workgroup sweeps its block of whole r as it
+//     lies in memory, 16 bytes per lane, and combines the lanes of equal inner position through LDS.
+//   * inner beyond that: lanes lie along the contiguous inner dimension, 16 bytes each; the four
 //     waves of a workgroup take every fourth r and are combined through LDS.
 // Every combination step compares (value, position) pairs, so the result does not depend
 // on how the work was split.  When there are too few outputs to fill the chip the reduced
@@ -373,8 +375,7 @@ __global__ __launch_bounds__(256) void reduce_max_short_rows_kernel(const void* 
 }
 
 // ---------------------------------------------------------------------------------
-// 1 < inner <= 64.  The strided kernel below would use inner / VEC of its 64 lanes.  Here
-// one wave owns one outer index (and the r range of one segment) and sweeps that contiguous
+// 1 < inner <= 64, many small blocks (the others go to the kernel after this one).  One wave owns one outer index (and the r range of one segment) and sweeps that contiguous
 // block of red x inner elements: R = 64 / inner consecutive r at a time, lane l at inner
 // position l % inner of r number l / inner of the sweep -- 64 (or R * inner) consecutive
 // elements per load instruction, eight sweeps in flight.  The lanes that share an inner
@@ -440,6 +441,153 @@ __global__ __launch_bounds__(256) void reduce_max_small_inner_kernel(const void*
             const size_t at = ((size_t)o * segs + seg) * (size_t)inner + lane;
             pv[at] = v;
             pi[at] = p;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------
+// inner up to about half the elements a workgroup loads at once.  A workgroup owns one outer index (and the r range of one
+// segment), a contiguous block of elements, and sweeps it in periods of R x inner of them, R whole r: 16 bytes per
+// lane, all lanes side by side whatever inner is, UNROLL periods in flight.  What a lane's element e of every period has in
+// common is its inner position, so it keeps the best (value, period) of it; the R entries that share an inner position
+// are combined at the end through LDS, a quarter of the rows left at a time.  A period that is a multiple of the
+// chunk starts on 16-byte boundaries wherever X starts (`lead` elements before the block); others are read from
+// any element on.
+// Bound by memory: bf16 [220, 50560, 7] 35 us (112 with a wave per segment and one element per load, which the address path
+// bounds), [128, 24742, 88] 90 (322 in the strided kernel, of whose lanes inner / (64 VEC) are at work: 6.3 TB/s), fp32 [200, 20000, 40] 105 (260).
+template <bool BF16, int NT>
+__global__ __launch_bounds__(NT) void reduce_max_block_kernel(const void* __restrict__ X, void* __restrict__ out,
+                                                              int* __restrict__ idx, float* __restrict__ pv,
+                                                              int* __restrict__ pi, int red, int inner, int segs,
+                                                              int r_per_seg, int R)
+{
+    constexpr int VEC = Elem<BF16>::VEC, ES = Elem<BF16>::BYTES, UNROLL = 4;
+    __shared__ float sv[NT * VEC];
+    __shared__ int si[NT * VEC];
+    const int tid = threadIdx.x;
+    const long long o = blockIdx.x / (unsigned int)segs;
+    const int seg = (int)(blockIdx.x - (unsigned int)o * (unsigned int)segs);
+    const int r0 = seg * r_per_seg;
+    const int r1 = r0 + r_per_seg < red ? r0 + r_per_seg : red;
+    const long long n = (long long)(r1 - r0) * inner;             // elements of this block
+    const int P = R * inner;
+    const size_t first = ((size_t)o * (size_t)red + (size_t)r0) * (size_t)inner;
+    const unsigned char* const at0 = (const unsigned char*)X + first * ES;
+    const bool whole = P % VEC == 0;
+    const int lead = whole ? (int)((size_t)at0 & 15u) / ES : 0;
+    const int f0 = tid * VEC - lead;                              // this lane's first element of period 0
+    const bool mine = tid * VEC < P;
+    const int periods = (int)((n + lead + P - 1) / P);
+    // periods before this one lie inside the block to the last chunk (but for the first one, which may start before it)
+    const int full_end = whole ? periods - 1 : periods - 2;
+
+    float bv[VEC];
+    int bk[VEC];                                                  // period of the best element, -1: none seen
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) { bv[e] = kNegInf; bk[e] = -1; }
+
+    if (mine) {
+        auto consume = [&](const u32x4& w, int s, bool ok) __attribute__((always_inline)) {
+            float x[VEC];
+            unpack<BF16>(w, x);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e)
+                if (ok && (bk[e] < 0 || replaces(x[e], bv[e]))) { bv[e] = x[e]; bk[e] = s; }
+        };
+        // UNROLL periods, of which the block may hold some of the chunks: their loads together all the same
+        auto guarded = [&](int s) __attribute__((always_inline)) {
+            u32x4 w[UNROLL];
+            bool ok[UNROLL];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                const long long g = (long long)(s + u) * P + f0;
+                ok[u] = g >= 0 && g + VEC <= n;
+                w[u] = u32x4{0u, 0u, 0u, 0u};
+                if (ok[u]) w[u] = load_chunk<BF16, true>(at0 + g * ES);
+            }
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) consume(w[u], s + u, ok[u]);
+        };
+        guarded(0);                                               // (from here on every slot has seen an element, if there is a fifth period)
+        int s = UNROLL;
+        const unsigned char* src = at0 + ((long long)s * P + f0) * ES;
+        const long long step = (long long)P * ES;
+        auto sweeps = [&](auto any_start) __attribute__((always_inline)) {
+            for (; s + UNROLL <= full_end; s += UNROLL, src += UNROLL * step) {
+                u32x4 w[UNROLL];
+#pragma unroll
+                for (int u = 0; u < UNROLL; ++u) w[u] = load_chunk<BF16, decltype(any_start)::value>(src + u * step);
+#pragma unroll
+                for (int u = 0; u < UNROLL; ++u) {
+                    float x[VEC];
+                    unpack<BF16>(w[u], x);
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e)
+                        if (replaces(x[e], bv[e])) { bv[e] = x[e]; bk[e] = s + u; }
+                }
+            }
+        };
+        if (whole) sweeps(std::false_type{});
+        else sweeps(std::true_type{});
+        for (; s < periods; s += UNROLL) guarded(s);
+        // chunks that the block's ends cut, one element per load: this lane's first one, and its last
+        auto cut = [&](int s) __attribute__((always_inline)) {
+            const long long g = (long long)s * P + f0;
+            if ((g >= 0 && g + VEC <= n) || g + VEC <= 0 || g >= n) return;
+            float x[VEC];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {                       // (an element there is in any case in place of one that is not)
+                const long long ge = g + e < 0 ? 0 : g + e < n ? g + e : n - 1;
+                x[e] = load_one<BF16>(at0, (size_t)ge);
+            }
+#pragma unroll
+            for (int e = 0; e < VEC; ++e)
+                if (g + e >= 0 && g + e < n && beats(x[e], s, bv[e], bk[e] < 0 ? kNoPos : bk[e])) { bv[e] = x[e]; bk[e] = s; }
+        };
+        cut(0);
+        if (periods > 1) cut(periods - 1);
+        if (!whole && periods > 2) cut(periods - 2);              // (its last chunk reaches into the last period)
+        // element f of the period (those before the block: of the period before) is r number f / inner, position f % inner
+        int q = f0 < 0 ? -((-f0 + inner - 1) / inner) : f0 / inner, i = f0 - q * inner;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const int f = f0 + e, k = f < 0 ? f + P : f;
+            if (k < P) {
+                sv[k] = bv[e];
+                si[k] = bk[e] < 0 ? kNoPos : r0 + bk[e] * R + q;
+            }
+            if (++i == inner) { i = 0; ++q; }
+        }
+    }
+    __syncthreads();
+    for (int rows = R; rows > 1;) {
+        const int left = (rows + 3) / 4, n_left = left * inner, n_rows = rows * inner;
+        for (int k = tid; k < n_left; k += NT) {
+            float v = sv[k];
+            int p = si[k];
+#pragma unroll
+            for (int j = 1; j < 4; ++j) {
+                const int kk = k + j * n_left;
+                if (kk < n_rows) {
+                    const float ov = sv[kk];
+                    const int op = si[kk];
+                    if (beats(ov, op, v, p)) { v = ov; p = op; }
+                }
+            }
+            sv[k] = v;
+            si[k] = p;
+        }
+        rows = left;
+        __syncthreads();
+    }
+    for (int k = tid; k < inner; k += NT) {
+        if (segs == 1) {
+            store_one<BF16>(out, (size_t)o * inner + k, sv[k]);
+            if (idx) idx[(size_t)o * inner + k] = si[k];
+        } else {
+            const size_t at = ((size_t)o * segs + seg) * (size_t)inner + k;
+            pv[at] = sv[k];
+            pi[at] = si[k];
         }
     }
 }
@@ -538,6 +686,53 @@ constexpr long long kShortRowChunks = 128;        // rows of at most this many c
 constexpr long long kSmallInner = 64;             // inner dimensions up to this: the flattened-sweep kernel
 constexpr long long kTinyBlock = 128;             // red x inner up to this: several outer indices per workgroup
 
+// The workgroups and the periods of reduce_max_block_kernel (the plan's `group` is minus its threads, `tiles_i` the r of a period),
+// or false where another kernel is faster:
+//  * blocks of at most two periods with many of them: a workgroup each is mostly its own start and end (bf16 [3000, 300, 9] 17.5 us
+//    here, 16 with a wave each; [20000, 40, 20] 47 and 20);
+//  * inner positions enough for the lanes of the strided kernel (bf16 [64, 4096, 1024] 87.5 and 88.5, 1536 149 and 132; fp32
+//    [64, 4096, 512] 83.6 and 82.4), also from one tile of that kernel on where whole r leave more than a quarter of the lanes idle here (bf16 [177, 1088, 721] 77 and
+//    71; [100, 4000, 520] 81 and 104) or the segments it may have are too few workgroups (fp32 [63, 8606, 384] 191 and 153).
+// A block of at most kOneLaunchBytes under too few outer indices: 1024 threads and no second pass, which costs more
+// than the chip's idle part gives (fp32 [29, 3712, 22], 327 KB, 12.9 us so, 15.5 in two launches; [16, 48054, 5], 961 KB, 25 and 15.8).
+// Else 512 workgroups, or 768 or 1024 where these are a whole number for every CU and 512 are not; segments of four periods at
+// least, and never more of them than the kernels before this one took, so that the workspace a call needs has not grown.
+constexpr long long kOneLaunchBytes = 256 << 10;
+
+bool plan_block(ReducePlan& pl, long long outer, long long red, long long inner, int dtype)
+{
+    const long long es = dtype == DT_BF16 ? 2 : 4, vec = 16 / es;
+    const bool one_launch = outer < 512 && red * inner * es <= kOneLaunchBytes && inner <= 512 * vec && (inner <= 128 * vec || red >= 64);
+    if (!one_launch && inner > 128 * vec) return false;
+    if (outer >= 1024 && red * inner <= 2 * 256 * vec) return false;
+    const long long nt = one_launch ? 1024 : 256;
+    long long R = nt * vec / inner;
+    const long long common = (inner & -inner) < vec ? (inner & -inner) : vec;      // (greatest common divisor: vec is a power of two)
+    if (R >= 4 * (vec / common)) R -= R % (vec / common);
+    if (!one_launch && inner > 64 * vec && 4 * R * inner < 3 * nt * vec) return false;
+    long long segs = 1;
+    if (!one_launch && outer < 512) {
+        const long long per_outer = (target_workgroups(dtype) * (inner <= kSmallInner ? 4 : 1) + outer - 1) / outer;
+        const long long former = inner <= 64 * vec ? per_outer : (per_outer + 1) / 2;
+        const long long most = red / (4 * R) < former ? red / (4 * R) : former;
+        double best = 0.0;
+        for (long long target = 512; target <= 1024; target += 256) {
+            const long long n = target / outer < most ? target / outer : most;
+            const double filled = (double)(n * outer) / (double)target;
+            if (n >= 1 && filled > best + 0.05) { best = filled; segs = n; }
+        }
+        if (inner > 64 * vec && segs == former && segs * outer < 448) return false;
+    }
+    pl.vec = (int)vec;
+    pl.group = (int)-nt;
+    pl.per_seg = (int)((red + segs - 1) / segs);
+    pl.segs = (int)((red + pl.per_seg - 1) / pl.per_seg);
+    pl.tiles_i = (int)(R < pl.per_seg ? R : pl.per_seg);
+    pl.blocks = outer * pl.segs;
+    pl.partial_elems = pl.segs > 1 ? (size_t)outer * pl.segs * (size_t)inner : 0;
+    return true;
+}
+
 }  // namespace
 
 ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int dtype, bool x_aligned)
@@ -583,6 +778,8 @@ ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int 
         pl.per_seg = (int)red;
         const long long q = 256 / (red * inner);
         pl.blocks = (outer + q - 1) / q;
+    } else if (plan_block(pl, outer, red, inner, dtype)) {
+        return pl;
     } else if (inner <= kSmallInner) {
         // one wave per (outer index, segment); group = 0 marks this kernel
         pl.vec = 1;
@@ -646,6 +843,12 @@ hipError_t launch_reduce_max(const ReducePlan& pl, const void* X, void* out, int
         if (bf) { if (pl.vec == 1) PGK_SHORT(true, 1, false); else if (pl.unaligned) PGK_SHORT(true, 8, true); else PGK_SHORT(true, 8, false); }
         else { if (pl.vec == 1) PGK_SHORT(false, 1, false); else if (pl.unaligned) PGK_SHORT(false, 4, true); else PGK_SHORT(false, 4, false); }
 #undef PGK_SHORT
+    } else if (inner > 1 && pl.group <= -256) {
+#define PGK_BLOCK(BF, NT) \
+    hipLaunchKernelGGL((reduce_max_block_kernel<BF, NT>), grid, dim3(NT), 0, s, X, out, idx, pv, pi, (int)red, (int)inner, pl.segs, pl.per_seg, pl.tiles_i)
+        if (bf) { if (pl.group == -256) PGK_BLOCK(true, 256); else PGK_BLOCK(true, 1024); }
+        else { if (pl.group == -256) PGK_BLOCK(false, 256); else PGK_BLOCK(false, 1024); }
+#undef PGK_BLOCK
     } else if (inner > 1 && pl.group == -1) {
         if (bf) hipLaunchKernelGGL(reduce_max_tiny_block_kernel<true>, grid, block, 0, s, X, out, idx, outer, (int)red, (int)inner);
         else hipLaunchKernelGGL(reduce_max_tiny_block_kernel<false>, grid, block, 0, s, X, out, idx, outer, (int)red, (int)inner);
