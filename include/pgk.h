@@ -310,12 +310,14 @@ size_t pgk_reduce_max_workspace_bytes(int64_t outer, int64_t red, int64_t inner,
  *  3. Otherwise -- stride > 1, any Cin of at least half a K tile's multiple (Cin >= its round-up / 2), odd
  *     dilations in bfloat16 -- with Kw <= 32: of copies of the input, one per phase of the stride (and a second one
  *     shifted by one element for bfloat16 taps at odd offsets), channels padded with zeros to a multiple of the K tile.
+ * Float32 also, where it is faster (Lout of at least 16, entries of x below 4 GiB), without any of these, in one launch: x and w on any
+ * element, read in place as they are.  Sizes that 1 to 3 need a workspace for ask for it all the same.
  * These need `workspace`
  * (device memory, 256-byte aligned, contents destroyed) of pgk_conv1d_workspace_bytes(...)
  * bytes for the regrouped weights and the strips or copies.  Too small (also for the way through
  * registers, if there is one) or NULL gives PGK_ERR_WORKSPACE.  Every other case needs no workspace (the query then returns 0): few input
  * channels under a large enough output run on a matrix-core kernel of their own, the rest (tiny
- * outputs) on a bounds-checked kernel; both read the input in place.
+ * outputs of bfloat16, or of fewer than 16 positions) on a bounds-checked kernel; both read the input in place.
  */
 int pgk_conv1d(const void* x, const void* w, const float* bias, void* y,
                int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw,

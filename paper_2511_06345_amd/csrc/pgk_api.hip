@@ -1173,12 +1173,14 @@ struct ConvPlan {
     int kind;            // tile shape (TILE_*), chosen as for a plain GEMM of Cout x Lout
     pgk::TileShape tile;
     size_t w_bytes, x_bytes;   // workspace parts: regrouped weights; copies of the input or strips
+    int in_place_rows;         // fp32, x and w read in place by tiles of so many output channels and 128 positions, whatever the rest says (0: not so)
 };
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// The kernels that read views of the input, or copies of it.
 // no_copies: registers wherever there is a kernel for them (a workspace without room for copies of the input)
-ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw, int64_t stride, int64_t pad,
+ConvPlan plan_conv_views(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw, int64_t stride, int64_t pad,
                      int64_t dilation, int dtype, bool no_copies = false)
 {
     ConvPlan pl{};
@@ -1278,6 +1280,59 @@ ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw
     return pl;
 }
 
+// How long a grid of `wgs` workgroups takes whose K loops have `steps` steps of 32, in us: fixed + (steps + ends) times what a step takes
+// a workgroup alone on its CU, or times `shared` for each of the CU's where these are more.
+struct StepCost { double fixed, ends, alone, shared; int per_cu; };
+
+double stepped_time(const StepCost& c, int64_t steps, double wgs)
+{
+    const double per = wgs / kNumCUs, on_busiest = per <= c.per_cu ? std::ceil(per) : per + 0.3;
+    return c.fixed + ((double)steps + c.ends) * std::max(c.alone, c.shared * on_busiest);
+}
+
+// fp32: the input and the weights read in place (pgk_gemm_f32_terms.h, VIEW_INPUT), without a launch that copies or regroups,
+// K = Cin * Kw without padding channels and tiles of 128, 64 or 32 output channels.  Bound like that kernel by issue slots, of which the loads take
+// more than from a matrix, so that few workgroups with long sums are slower than the fp32 instruction's small tiles.  The constants
+// were fitted to 400 drawn convolutions with each way forced, both off by a tenth in the root mean square: of the choices one is
+// over 2 % slower than the views, the mean is 1.21 times as fast, 0.97 of what the best way each time gives.  [10, 152, 53120] x
+// [19, 152, 7] 450 us in the views, 305 here; [16, 57, 36868] x [67, 57, 5] 314 and 246; [2, 463, 2816] x [24, 463, 5], 46 workgroups and 73 steps,
+// 51 and 82.  What has neither views nor enough to do for pgk_conv_few.hip was on the bounds-checked kernel: of 76 shapes none is
+// slower here, the mean 1.27 times as fast.
+int conv_rows_in_place(const ConvPlan& views, int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw, int64_t stride, int64_t pad,
+                       int64_t dilation)
+{
+    // byte offsets inside a row with its padding, inside a batch entry, and inside a tile of the weights
+    if (views.Lout < 16 || L + 2 * pad >= (1LL << 29) || Cin * L + pad >= (1LL << 30) - 4 || Cin * Kw * 128 >= (1LL << 30)) return 0;
+    const int64_t tiles_n = (views.Lout + 127) / 128;
+    auto wgs = [&](int64_t rows, int64_t tiles) { return (double)((Cout + rows - 1) / rows) * (double)tiles * (double)B; };
+    if (wgs(32, tiles_n) > 2.0e9) return 0;
+    const struct { int rows; StepCost cost; } kinds[] = {{128, {4.84, 2.28, 1.82, 1.37, 2}}, {64, {5.46, 1.31, 1.27, 0.88, 3}}, {32, {4.79, 1.18, 1.06, 0.66, 3}}};
+    int best = 0;
+    double best_time = 0.0;
+    for (const auto& k : kinds) {
+        const double t = stepped_time(k.cost, (Cin * Kw + 31) / 32, wgs(k.rows, tiles_n));
+        if (!best || t < best_time) { best = k.rows; best_time = t; }
+    }
+    if (!views.fast) return pgk::conv_few_channels_fits(B, Cin, Cout, Kw, stride, dilation, views.Lout) ? 0 : best;
+    const bool copied = views.table || views.Lp > 0;
+    const double copies = copied ? 0.17e-6 * 4.0 * (double)B * ((double)Cin * (double)L + (double)((Cin + 31) / 32 * 32) * (double)views.Lout * (double)stride) : 0.0;
+    // (the views' large tile is this kernel too: equal within what the runs differ where nothing is copied or padded, [16, 64, 65536] x [128, 64, 3] 341
+    // in the views, 345 here, with rows of 65538 360 and 340)
+    const StepCost cost = views.kind == pgk::TILE_FLAT    ? StepCost{7.2, 2.0, 0.56, 0.56, 4}
+                          : views.kind == pgk::TILE_SMALL ? StepCost{7.4, 1.7, 0.51, 0.51, 4}
+                                                          : StepCost{7.0, 2.2, 1.89, 1.38, 2};
+    const double in_views = copies + stepped_time(cost, Kw * ((Cin + 31) / 32), wgs(views.tile.bm, (views.Lout + views.tile.bn - 1) / views.tile.bn));
+    return best_time < 0.97 * in_views ? best : 0;
+}
+
+ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw, int64_t stride, int64_t pad, int64_t dilation, int dtype,
+                     bool no_copies = false)
+{
+    ConvPlan pl = plan_conv_views(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype, no_copies);
+    if (pl.valid && dtype == PGK_DTYPE_F32) pl.in_place_rows = conv_rows_in_place(pl, B, Cin, L, Cout, Kw, stride, pad, dilation);
+    return pl;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1336,9 +1391,22 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
     a.bias_per_row = 1;                   // one bias per output channel = per row
     a.act = act; a.splits = 1;
 
+    // (asked for by the sizes alone, whichever way the call then takes)
+    if (pl.fast && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < pl.w_bytes + pl.x_bytes))
+        return PGK_ERR_WORKSPACE;
+    if (pl.in_place_rows) {
+        const int64_t rows = pl.in_place_rows;
+        a.A = w; a.B = x;
+        a.b_batch_stride = Cin * L;
+        a.ldb = (int)L;
+        a.conv_kw = (int)Kw; a.conv_stride = (int)stride; a.conv_pad = (int)pad; a.conv_dil = (int)dilation; a.conv_len = (int)L;
+        a.k_slice = (a.K + 31) / 32 * 32;
+        a.tiles_m = (int)((Cout + rows - 1) / rows);
+        a.tiles_n = (int)((pl.Lout + 127) / 128);
+        a.group_m = group_m_for(a.tiles_m, a.tiles_n);
+        return pgk::launch_conv_f32_terms(a, (int)rows, st) == hipSuccess ? PGK_OK : PGK_ERR_HIP;
+    }
     if (pl.fast) {
-        if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < pl.w_bytes + pl.x_bytes)
-            return PGK_ERR_WORKSPACE;
         unsigned char* wr = static_cast<unsigned char*>(workspace);
         unsigned char* xp = wr + pl.w_bytes;
         const void* bsrc = x;

@@ -60,6 +60,13 @@
 //  * v_mfma_f32_16x16x32_bf16: with 32x32x16 two LDS stages of 16 k fit, a step takes 3724 cycles per
 //    pair of workgroups (3072 are matrix instructions), but the board's power limit then holds the
 //    clock at 1.63 GHz (4096^3 in 714 us).
+//  * 64 and 32 rows (three workgroups a CU) for outputs of fewer rows: a step of 64 x 128 takes 0.64 of the whole tile's time, of 32 x 128
+//    0.48, as the columns are split once for fewer rows (0.88, 0.66 and 1.37 us a step for each workgroup of a full CU, a
+//    convolution's input; [16, 448, 704] x [320, 448, 3] 116 us on 128 rows, 80 on 64).
+//  * A convolution's input in place (VIEW_INPUT): rows of B are rows of x at an offset, any alignment, so a K step is 32 products whatever
+//    the channels and taps, without copies, padding channels or regrouped weights.  Eight lanes follow the wave's eight rows, and a
+//    load gets its row by readlane: with the rows in scalar registers of their own the bookkeeping took a third of the issue slots
+//    ([11, 256, 24580] x [50, 256, 3] dilation 2: 214 us, 174 so).
 // LDS layout: fragments in the order the lanes read them -- sixteen rows x 32 k of one plane are
 // one contiguous KiB, lane (k chunk g, row r) reading 16 bytes of 256 g + ... (frag_pos) -- so that
 // operand reads need one address register; even rows before odd ones, XORed with the chunk, keeps
@@ -87,20 +94,25 @@ __device__ __forceinline__ void static_for(F&& f)
     }
 }
 
+// B is the input x of a convolution, x [batch][K / conv_kw][conv_len], read in place: row k of B is the row k / conv_kw of x,
+// its element n at n * conv_stride + (k % conv_kw) * conv_dil - conv_pad, zero outside
+constexpr int VIEW_INPUT = 2;
+
 template <bool BT_, int BM_, int BN_, int WAVES_PER_SIMD_>
 struct TermsCfg {
     static constexpr bool BT = BT_;                    // B given as [N][K]
     static constexpr int BM = BM_, BN = BN_, BK = 32;
     static constexpr int WAVES_PER_SIMD = WAVES_PER_SIMD_;
-    static constexpr int WGM = 2, WGN = 2, NW = 4, NT = 256;
+    static constexpr int WGM = BM >= 64 ? 2 : 1, NW = 4, WGN = NW / WGM, NT = 256;
     static constexpr int WM = BM / WGM, WN = BN / WGN;
     static constexpr int TM16 = WM / 16, TN16 = WN / 16;       // 16 x 16 accumulator blocks per wave
     static constexpr int PLANES = 3;
+    static constexpr int BIAS_N = BM > BN ? BM : BN;
     static constexpr int A_PLANE = BM * BK * 2, B_PLANE = BN * BK * 2;     // bytes of one plane
     static constexpr int A_BYTES = PLANES * A_PLANE, B_BYTES = PLANES * B_PLANE;
-    // chunks of eight k values per thread: rows of A (of a transposed B), columns of a plain B
-    static constexpr int A_CH = BM * 4 / NT, B_CH = BN * 4 / NT;
-    static_assert(A_CH == 2 && B_CH == 2, "two neighbouring rows and columns per thread");
+    // a thread copies two neighbouring rows of A (of a transposed B), columns of a plain B, so many k values of each
+    static constexpr int A_KV = BM * BK / NT / 2, B_KV = BN * BK / NT / 2;
+    static_assert((A_KV == 8 || A_KV == 4 || A_KV == 2) && B_KV == 8, "pairs of k values; of B a whole chunk");
     // the epilogue stages sixteen rows of a wave's part at a time
     static constexpr int PIECE_BYTES = 16 * WN * 4;
     static_assert(2 * PIECE_BYTES <= A_BYTES && 2 * PIECE_BYTES <= B_BYTES, "epilogue staging");
@@ -187,19 +199,15 @@ __device__ __forceinline__ void epilogue_terms(f32x4 (&acc)[Cfg::TM16][Cfg::TN16
     }
 }
 
-template <typename Cfg, int VIEW, bool TIMED = false>
-__global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_kernel(const GemmArgs p, const int out_mode)
+// INSIDE (of a convolution's input): every position that the tile reads lies inside the rows, and a thread's two columns side by side
+template <typename Cfg, int VIEW, bool TIMED, bool INSIDE>
+__device__ __forceinline__ void terms_tile(const GemmArgs& p, const int out_mode, unsigned char* const lds_a, unsigned char* const lds_b,
+                                           float* const rs_buf)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK;
-    constexpr int TM16 = Cfg::TM16, TN16 = Cfg::TN16, A_CH = Cfg::A_CH, B_CH = Cfg::B_CH;
+    constexpr int TM16 = Cfg::TM16, TN16 = Cfg::TN16, A_KV = Cfg::A_KV, A_CH = 2, B_CH = 2;
     constexpr bool BT = Cfg::BT;
-    constexpr int BIAS_N = BM > BN ? BM : BN;
-    __shared__ __attribute__((aligned(1024))) unsigned char lds_a[Cfg::A_BYTES];
-    __shared__ __attribute__((aligned(1024))) unsigned char lds_b[Cfg::B_BYTES];
-    // row sums of the two wave columns, then the tile's column biases, then its row biases
-    __shared__ __attribute__((aligned(16))) float rs_buf[Cfg::WGN * BM + 2 * BIAS_N];
-
+    constexpr int BIAS_N = Cfg::BIAS_N;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -280,28 +288,38 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     const int m_rem = (p.M - tm * BM) < BM ? (p.M - tm * BM) : BM;
     const int n_rem = (p.N - tn * BN) < BN ? (p.N - tn * BN) : BN;
 
-    constexpr bool BIAS_PER_ROW = VIEW == VIEW_CONV;
+    constexpr bool BIAS_PER_ROW = VIEW != VIEW_GEMM;
     float bias_pre = 0.0f;
     if (p.bias && out_mode == 0) {
         if constexpr (BIAS_PER_ROW) { if (tid < m_rem) bias_pre = p.bias[(size_t)tm * BM + tid]; }
         else if (tid < n_rem) bias_pre = p.bias[(size_t)tn * BN + tid];
     }
 
-    // ---- what this thread copies: of A (and of a transposed B) the eight k values of chunk tid % 4 of
-    // two neighbouring rows; of a plain B the eight k rows 8 wave .. of two neighbouring columns.
-    // Rows and columns past the edge re-read the last ones.
+    // ---- what this thread copies: of a transposed B the eight k values of chunk tid % 4 of
+    // two neighbouring rows, of A the same or (fewer rows) a half or a quarter of a chunk; of a plain B the eight k rows
+    // 8 wave .. of two neighbouring columns.  Rows and columns past the edge re-read the last ones.
+    constexpr int A_PER_ROW = BK / A_KV;                          // threads per row of A
     const int my_row = 2 * (tid >> 2), my_chunk = tid & 3;
-    unsigned int voff_a[A_CH], voff_b[BT ? B_CH : 1];
+    const int a_row = 2 * (tid / A_PER_ROW), a_k0 = (tid % A_PER_ROW) * A_KV;
+    // (a convolution's weights: the rows past the last one lie behind the end of A and read as zero)
+    unsigned int voff_a[A_CH], voff_b[BT || VIEW == VIEW_INPUT ? B_CH : 1];
 #pragma unroll
     for (int t = 0; t < A_CH; ++t) {
-        const int r = my_row + t;
-        voff_a[t] = (unsigned int)(r < m_rem ? r : m_rem - 1) * (unsigned int)p.K * 4u + (unsigned int)my_chunk * 32u;
+        const int r = a_row + t;
+        voff_a[t] = (unsigned int)(VIEW == VIEW_INPUT || r < m_rem ? r : m_rem - 1) * (unsigned int)p.K * 4u + (unsigned int)a_k0 * 4u;
     }
     if constexpr (BT) {
 #pragma unroll
         for (int t = 0; t < B_CH; ++t) {
             const int r = my_row + t;
             voff_b[t] = (unsigned int)(r < n_rem ? r : n_rem - 1) * (unsigned int)ldb * 4u + (unsigned int)my_chunk * 32u;
+        }
+    } else if constexpr (VIEW == VIEW_INPUT) {
+#pragma unroll
+        for (int t = 0; t < B_CH; ++t) {
+            const int c = 2 * lane + t;
+            voff_b[t] = (((unsigned int)tn * BN + (unsigned int)(c < n_rem ? c : n_rem - 1)) * (unsigned int)p.conv_stride -
+                         (INSIDE ? 0u : (unsigned int)p.conv_pad)) * 4u;
         }
     } else {
         const int c = 2 * lane, last = (n_rem - 1) / 2 * 2;
@@ -312,15 +330,14 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     auto frag_pos = [](int row, int g) __attribute__((always_inline)) {
         return (row >> 4) * 1024 + g * 256 + (((((row & 15) >> 1) + 8 * (row & 1)) ^ (6 * g & 7)) * 16);
     };
-    int wpos_a[A_CH], wpos_b[B_CH];
-#pragma unroll
-    for (int t = 0; t < A_CH; ++t) wpos_a[t] = frag_pos(my_row + t, my_chunk);
-#pragma unroll
-    for (int t = 0; t < B_CH; ++t) wpos_b[t] = BT ? frag_pos(my_row + t, my_chunk) : frag_pos(2 * lane + t, wave);
+    // (the odd row of a pair lies kOddRow bytes behind the even one, whose index has that bit clear)
+    constexpr int kOddRow = 128;
+    const int wpos_a = frag_pos(a_row, a_k0 >> 3) + (a_k0 & 7) * 2;
+    const int wpos_b = BT ? frag_pos(my_row, my_chunk) : frag_pos(2 * lane, wave);
 
-    // ---- global -> registers, one step: ra[t] = eight k values of a row of A, rb[t] = of a column of B.
+    // ---- global -> registers, one step: ra[t] = k values of a row of A, rb[t] = of a column of B.
     // Where the next step starts is running state, as in pgk_gemm_mfma_kernel.h.
-    float ra[A_CH][8], rb[B_CH][8];
+    float ra[A_CH][A_KV], rb[B_CH][8];
     size_t a_off = 0, b_off = 0;
     int next_step = 0, b_row_step = 0, b_taps_done = 0;
     long long tap_of_lane = 0;
@@ -336,7 +353,25 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
         return (long long)(((unsigned long long)hi << 32) | lo);
     };
     const long long b_tap_jump = VIEW == VIEW_CONV ? (long long)p.b_tap_step * 4 - (long long)p.b_tiles_per_tap * (long long)b_step : 0;
+    // A convolution's input: lane e (of eight, and again in the other lanes) follows the wave's k row e of the step that is being
+    // loaded: its tap, and where it starts in x, in bytes, without the padding.  What a load needs of it comes from readlane.
+    const unsigned int in_row_bytes = (unsigned int)p.conv_len * 4u, in_dil = (unsigned int)p.conv_dil * 4u;
+    const int in_taps = VIEW == VIEW_INPUT ? p.conv_kw : 1;
+    const int in_step_ch = __builtin_amdgcn_readfirstlane(BK / in_taps), in_step_tap = BK - in_step_ch * in_taps;
+    const unsigned int in_step_off = (unsigned int)in_step_ch * in_row_bytes + (unsigned int)in_step_tap * in_dil;
+    const unsigned int in_next_ch = in_row_bytes - (unsigned int)in_taps * in_dil;
+    // (the padding is taken off here, or off the lanes' positions)
+    const unsigned char* const in_base = (const unsigned char*)p.B + ((long long)b * p.b_batch_stride - (INSIDE ? p.conv_pad : 0)) * 4;
+    int in_tap = 0;
+    unsigned int in_off = 0;
     auto rewind = [&]() __attribute__((always_inline)) {
+        if constexpr (VIEW == VIEW_INPUT) {
+            // (a step before the first one)
+            const int ch = (8 * wave + (lane & 7)) / in_taps;
+            in_tap = 8 * wave + (lane & 7) - ch * in_taps;
+            in_off = (unsigned int)ch * in_row_bytes + (unsigned int)in_tap * in_dil - in_step_off;
+            in_tap -= in_step_tap;
+        }
         a_off = (size_t)k_rot * a_step;
         b_off = VIEW == VIEW_CONV ? (p.b_use_tap_table ? (size_t)p.b_tap_off[0] : 0) : (size_t)k_rot * b_step;
         next_step = k_rot;
@@ -350,7 +385,18 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
         bbase = Bg + b_off;
         a_off += a_step;
         b_off += b_step;
-        if constexpr (VIEW == VIEW_GEMM) {
+        if constexpr (VIEW == VIEW_INPUT) {
+            in_tap += in_step_tap;
+            in_off += in_step_off;
+            const bool over = in_tap >= in_taps;
+            in_tap -= over ? in_taps : 0;
+            in_off += over ? in_next_ch : 0u;
+            // (rows past the last one, which clear_k_tail takes out: the first one instead)
+            const bool there = next_step * BK + 8 * wave + (lane & 7) < p.K;
+            in_tap = there ? in_tap : 0;
+            in_off = there ? in_off : 0u;
+            ++next_step;
+        } else if constexpr (VIEW == VIEW_GEMM) {
             if (++next_step == KT) { next_step = 0; a_off = 0; b_off = 0; }
         } else {
             const bool new_tap = ++b_row_step == p.b_tiles_per_tap;
@@ -370,16 +416,53 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             x[e] = __builtin_bit_cast(float, w);
         }
     };
-    // chunk t of A: two instructions
+    // this thread's part of row t of A
     auto load_a = [&](int t) __attribute__((always_inline)) {
         auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)abase, 0, records(abase, A_end), 0x00020000);
-        four(rs, voff_a[t], ra[t]);
-        four(rs, voff_a[t] + 16, ra[t] + 4);
+        unsigned int at = voff_a[VIEW == VIEW_INPUT ? 0 : t];
+        if (VIEW == VIEW_INPUT && t == 1) {
+            // (a register of its own would be one too many for three waves per SIMD)
+            asm volatile("" : "+v"(at));
+            at += (unsigned int)p.K * 4u;
+        }
+        if constexpr (A_KV == 2) {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, at, 0, 0);
+            const unsigned int w0 = v[0], w1 = v[1];
+            ra[t][0] = __builtin_bit_cast(float, w0);
+            ra[t][1] = __builtin_bit_cast(float, w1);
+        } else {
+            four(rs, at, ra[t]);
+            if constexpr (A_KV == 8) four(rs, at + 16, ra[t] + 4);
+        }
     };
     // part q (of 4 B_CH) of B: of a transposed B half a chunk every other time, of a plain B the
     // k rows that part q completes when the parts are split in order (see `split`)
     auto load_b = [&](auto q_tag) __attribute__((always_inline)) {
         constexpr int q = decltype(q_tag)::value;
+        if constexpr (VIEW == VIEW_INPUT) {
+            if constexpr (q % 2 == 0) return;
+#pragma unroll
+            for (int e = q - 1; e <= q; ++e) {
+                const unsigned int off = (unsigned int)__builtin_amdgcn_readlane((int)in_off, e);
+                if constexpr (INSIDE) {
+                    auto all = __builtin_amdgcn_make_buffer_rsrc((void*)in_base, 0, (int)0xffffffffu, 0x00020000);
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(all, voff_b[0], off, 0);
+                    const unsigned int w0 = v[0], w1 = v[1];
+                    rb[0][e] = __builtin_bit_cast(float, w0);
+                    rb[1][e] = __builtin_bit_cast(float, w1);
+                } else {
+                    // a resource per row, outside of which all is zero
+                    const unsigned int tap = (unsigned int)__builtin_amdgcn_readlane(in_tap, e) * in_dil;
+                    auto row = __builtin_amdgcn_make_buffer_rsrc((void*)(in_base + (off - tap)), 0, (int)in_row_bytes, 0x00020000);
+#pragma unroll
+                    for (int t = 0; t < B_CH; ++t) {
+                        const unsigned int w = __builtin_amdgcn_raw_buffer_load_b32(row, voff_b[t] + tap, 0, 0);
+                        rb[t][e] = __builtin_bit_cast(float, w);
+                    }
+                }
+            }
+            return;
+        }
         auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)bbase, 0, VIEW == VIEW_CONV ? (int)0xffffffffu : records(bbase, B_end), 0x00020000);
         if constexpr (BT) {
             if constexpr (q % 2 == 1) four(rs, voff_b[q / 4] + 16u * (q / 2 % 2), rb[q / 4] + 4 * (q / 2 % 2));
@@ -405,11 +488,11 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     // k values of a partial last step that do not exist: whatever was read in their place (the start
     // of the next row; a NaN there must not reach this one) counts as zero
     auto clear_k_tail = [&]() __attribute__((always_inline)) {
-        const int ka = k_last - 8 * my_chunk, kb = BT ? ka : k_last - 8 * wave;
+        const int ka = k_last - a_k0, kb = k_last - 8 * (BT ? my_chunk : wave);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
 #pragma unroll
-            for (int t = 0; t < A_CH; ++t) ra[t][e] = e < ka ? ra[t][e] : 0.0f;
+            for (int t = 0; t < A_CH; ++t) { if (e < A_KV) ra[t][e] = e < ka ? ra[t][e] : 0.0f; }
 #pragma unroll
             for (int t = 0; t < B_CH; ++t) rb[t][e] = e < kb ? rb[t][e] : 0.0f;
         }
@@ -417,7 +500,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     // columns past the edge that are loaded all the same -- the neighbour of an odd row's last column, in a
     // convolution every position past the row's end -- hold other rows' values: zero, so that these do not
     // decide how this tile is computed
-    const bool edge_cols = !BT && (VIEW == VIEW_CONV ? n_rem < BN : n_rem % 2 != 0);
+    const bool edge_cols = !BT && VIEW != VIEW_INPUT && (VIEW == VIEW_CONV ? n_rem < BN : n_rem % 2 != 0);
     auto clear_edge_cols = [&]() __attribute__((always_inline)) {
         const int left = n_rem - 2 * lane;
 #pragma unroll
@@ -436,15 +519,16 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     // then of B's (of column pairs both columns at one k); OPS operations of two or three
     // instructions each take it apart.
     unsigned int lost = 0u;                       // what the values leave after two terms, or-ed together
-    u32x4 pa[A_CH][3], pb[B_CH][3];               // the packed terms
-    constexpr int PARTS = 4 * (A_CH + B_CH), OPS = 5;
+    unsigned int pa[A_CH][3][A_KV / 2];           // the packed terms
+    u32x4 pb[B_CH][3];
+    constexpr int A_PAIRS = A_KV / 2, A_PARTS = A_CH * A_PAIRS, PARTS = A_PARTS + 4 * B_CH, OPS = 5;
     auto bits = [](float x) __attribute__((always_inline)) { return __builtin_bit_cast(unsigned int, x); };
     auto value = [](unsigned int u) __attribute__((always_inline)) { return __builtin_bit_cast(float, u); };
     float t0 = 0.0f, t1 = 0.0f;
     auto split = [&](auto n_tag, auto op_tag) __attribute__((always_inline)) {
-        constexpr int n = decltype(n_tag)::value, op = decltype(op_tag)::value, nb = n - 4 * A_CH;
+        constexpr int n = decltype(n_tag)::value, op = decltype(op_tag)::value, nb = n - A_PARTS;
         constexpr bool of_a = nb < 0;
-        constexpr int t = of_a ? n / 4 : BT ? nb / 4 : nb % 2, q = of_a ? n % 4 : BT ? nb % 4 : nb / 2;
+        constexpr int t = of_a ? n / A_PAIRS : BT ? nb / 4 : nb % 2, q = of_a ? n % A_PAIRS : BT ? nb % 4 : nb / 2;
         float* x;
         if constexpr (of_a) x = &ra[t][2 * q]; else x = &rb[t][2 * q];
         auto put = [&](int plane, unsigned int w) __attribute__((always_inline)) {
@@ -485,9 +569,14 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
 #pragma unroll
-            for (int t = 0; t < A_CH; ++t) *(__attribute__((address_space(3))) u32x4*)PGK_LDS(lds_a + q * Cfg::A_PLANE + wpos_a[t]) = pa[t][q];
+            for (int t = 0; t < A_CH; ++t) {
+                unsigned char* const to = lds_a + q * Cfg::A_PLANE + wpos_a + kOddRow * t;
+                if constexpr (A_KV == 8) *(__attribute__((address_space(3))) u32x4*)PGK_LDS(to) = u32x4{pa[t][q][0], pa[t][q][1], pa[t][q][2], pa[t][q][3]};
+                else if constexpr (A_KV == 4) *(__attribute__((address_space(3))) u32x2*)PGK_LDS(to) = u32x2{pa[t][q][0], pa[t][q][1]};
+                else *(__attribute__((address_space(3))) unsigned int*)PGK_LDS(to) = pa[t][q][0];
+            }
 #pragma unroll
-            for (int t = 0; t < B_CH; ++t) *(__attribute__((address_space(3))) u32x4*)PGK_LDS(lds_b + q * Cfg::B_PLANE + wpos_b[t]) = pb[t][q];
+            for (int t = 0; t < B_CH; ++t) *(__attribute__((address_space(3))) u32x4*)PGK_LDS(lds_b + q * Cfg::B_PLANE + wpos_b + kOddRow * t) = pb[t][q];
         }
     };
 
@@ -512,11 +601,15 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     constexpr int PER_J = 6 * TM16, SLOTS = PER_J * TN16;
     auto step = [&](auto next_tag, auto ahead_tag) __attribute__((always_inline)) {
         constexpr bool NEXT = decltype(next_tag)::value != 0, AHEAD = decltype(ahead_tag)::value != 0;
-        bf16x8 fa[3][TM16], fb[2][3];
+        // two column blocks' fragments in turn; with fewer rows and three waves per SIMD only of term 0, the others into the same
+        // place once it is free (two places each take seven registers more than there are)
+        constexpr bool TWO = BM == 128;
+        bf16x8 fa[3][TM16], fb[TWO ? 6 : 4];
         f32x4 sum[TM16];            // of this step's products of one column block (see "Rounding")
         if constexpr (NEXT && !BT) { if (edge_cols) clear_edge_cols(); }
         auto fetch_a = [&](int q, int i) __attribute__((always_inline)) { fa[q][i] = *(const __attribute__((address_space(3))) bf16x8*)PGK_LDS(as + q * Cfg::A_PLANE + i * 1024); };
-        auto fetch_b = [&](int j, int q) __attribute__((always_inline)) { fb[j & 1][q] = *(const __attribute__((address_space(3))) bf16x8*)PGK_LDS(bs + q * Cfg::B_PLANE + j * 1024); };
+        auto slot_b = [](int j, int q) constexpr { return TWO ? 3 * (j & 1) + q : q == 0 ? 2 + (j & 1) : q - 1; };
+        auto fetch_b = [&](int j, int q) __attribute__((always_inline)) { fb[slot_b(j, q)] = *(const __attribute__((address_space(3))) bf16x8*)PGK_LDS(bs + q * Cfg::B_PLANE + j * 1024); };
         // (term of A, term of B) of the six products, the small ones first
         constexpr int QA[6] = {0, 2, 1, 0, 1, 0}, QB[6] = {2, 0, 1, 1, 0, 0};
         // the fragments of the first column block, in the order they are needed
@@ -539,18 +632,24 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
             // the small products' sum is complete before the large ones, theirs a column block later
             if constexpr (u == 5) acc[i][j] += sum[i];
             if constexpr (u == 0 && j > 0) acc[i][j - 1] += sum[i];
-            sum[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j & 1][QB[u]], fa[QA[u]][i],
+            sum[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[slot_b(j, QB[u])], fa[QA[u]][i],
                                                              u == 0 || u == 5 ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : sum[i], 0, 0, 0);
-            // the next column block's fragments, into the other buffer
-            if constexpr (j + 1 < TN16 && m % PER_J >= TM16 && m % PER_J < TM16 + 3) fetch_b(j + 1, QB[m % PER_J - TM16]);
+            // the next column block's fragments (term 2 is free behind the first product, term 1 behind the fourth)
+            if constexpr (j + 1 < TN16) {
+                constexpr int at = m % PER_J - TM16;
+                if constexpr (TWO) { if constexpr (at >= 0 && at < 3) fetch_b(j + 1, QB[at]); }
+                else if constexpr (at == 0) fetch_b(j + 1, 2);
+                else if constexpr (at == 1) fetch_b(j + 1, 0);
+                else if constexpr (at == 3 * TM16) fetch_b(j + 1, 1);
+            }
             if constexpr (NEXT) {
                 static_for<ops_before(m), ops_before(m + 1)>([&](auto o_tag) __attribute__((always_inline)) {
                     constexpr int o = decltype(o_tag)::value, part = o / OPS;
                     split(IC<part>{}, IC<o % OPS>{});
                     // a part's registers are free once it is split: what is to fill them next
                     if constexpr (AHEAD && o % OPS == OPS - 1) {
-                        if constexpr (part < 4 * A_CH) { if constexpr (part % 4 == 3) load_a(part / 4); }
-                        else load_b(IC<part - 4 * A_CH>{});
+                        if constexpr (part < A_PARTS) { if constexpr (part % A_PAIRS == A_PAIRS - 1) load_a(part / A_PAIRS); }
+                        else load_b(IC<part - A_PARTS>{});
                     }
                 });
             }
@@ -573,6 +672,16 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
     if constexpr (!BT) { if (edge_cols) clear_edge_cols(); }
     static_for<0, OPS * PARTS>([&](auto o) __attribute__((always_inline)) { split(IC<decltype(o)::value / OPS>{}, IC<decltype(o)::value % OPS>{}); });
     write_step();
+    float* const bias_lds = rs_buf + Cfg::WGN * BM;
+    float* const bias_lds_row = bias_lds + BIAS_N;
+    auto write_biases = [&]() __attribute__((always_inline)) {
+        if (tid < BIAS_N) {
+            bias_lds[tid] = BIAS_PER_ROW ? 0.0f : bias_pre;
+            if constexpr (BIAS_PER_ROW) bias_lds_row[tid] = bias_pre;
+        }
+    };
+    // (now, with three waves per SIMD: a register held through the loop is one too many)
+    if constexpr (BM < 128) write_biases();
     if (KT > 1) load_step();
     meet();
     stamp(1);
@@ -616,9 +725,17 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
                     *(f32x4*)(base + (row >> 4) * 2048 + c * 256 + (row & 15) * 16) = f32x4{x[0], x[1], x[2], x[3]};
                 };
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
+                for (int t = 0; t < A_CH; ++t) {
+                    if constexpr (A_KV >= 4) {
 #pragma unroll
-                    for (int t = 0; t < A_CH; ++t) put(lds_a, my_row + t, 2 * my_chunk + h, &ra[t][4 * h]);
+                        for (int h = 0; h < A_KV / 4; ++h) put(lds_a, a_row + t, a_k0 / 4 + h, &ra[t][4 * h]);
+                    } else {
+                        const int row = a_row + t;
+                        *(float2*)(lds_a + (row >> 4) * 2048 + (a_k0 >> 2) * 256 + (row & 15) * 16 + (a_k0 & 3) * 4) = float2{ra[t][0], ra[t][1]};
+                    }
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
 #pragma unroll
                     for (int t = 0; t < B_CH; ++t) {
                         if constexpr (BT) put(lds_b, my_row + t, 2 * my_chunk + h, &rb[t][4 * h]);
@@ -665,12 +782,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
         return;
     }
     float* const rs_lds = p.rs_part ? rs_buf : nullptr;
-    float* const bias_lds = rs_buf + Cfg::WGN * BM;
-    float* const bias_lds_row = bias_lds + BIAS_N;
-    if (tid < BIAS_N) {
-        bias_lds[tid] = BIAS_PER_ROW ? 0.0f : bias_pre;
-        if constexpr (BIAS_PER_ROW) bias_lds_row[tid] = bias_pre;
-    }
+    if constexpr (BM == 128) write_biases();
     __syncthreads();
     stamp(3);
     unsigned char* c_tile = (unsigned char*)p.C + ((size_t)b * p.M * p.N + (size_t)tm * BM * (size_t)p.N + (size_t)tn * BN) * 4;
@@ -684,7 +796,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
         default: epilogue_terms<ACT_NONE, KIND, Cfg, true, true>(acc, bias_lds, br, c_tile, (size_t)p.N * 4, m_rem, n_rem, wm, wn, lane, piece, rs_lds); break;
         }
     };
-    if constexpr (VIEW == VIEW_CONV) {
+    if constexpr (BIAS_PER_ROW) {
         if (p.bias) run_epilogue(IC<EPI_ROWBIAS>{});
         else run_epilogue(IC<EPI_PLAIN>{});
     } else {
@@ -696,7 +808,10 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
         __syncthreads();
         if (tid < m_rem) {
             // the wave columns' partial row sums, in order
-            p.rs_part[((size_t)b * p.tiles_n + tn) * (size_t)p.M + (size_t)tm * BM + tid] = rs_buf[tid] + rs_buf[BM + tid];
+            float sum = rs_buf[tid];
+#pragma unroll
+            for (int w = 1; w < Cfg::WGN; ++w) sum += rs_buf[w * BM + tid];
+            p.rs_part[((size_t)b * p.tiles_n + tn) * (size_t)p.M + (size_t)tm * BM + tid] = sum;
         }
     }
     stamp(4);
@@ -705,12 +820,41 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_k
         __syncthreads();
         stamp(5);
     }
+}
+
+template <typename Cfg, int VIEW, bool TIMED = false>
+__global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_f32_terms_kernel(const GemmArgs p, const int out_mode)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_a[Cfg::A_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_b[Cfg::B_BYTES];
+    // row sums of the wave columns, then the tile's column biases, then its row biases
+    __shared__ __attribute__((aligned(16))) float rs_buf[Cfg::WGN * Cfg::BM + 2 * Cfg::BIAS_N];
+    if constexpr (VIEW == VIEW_INPUT) {
+        // (the whole tile once for each way: with the branch inside the loop, or a loop for each, registers that cross it are
+        // copied and, with 128 rows, spilled)
+        const unsigned int tiles = (unsigned int)p.tiles_m * (unsigned int)p.tiles_n;
+        int tm, tn;
+        tile_coords(xcd_remap(blockIdx.x, gridDim.x) % tiles, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+        const long long from = (long long)tn * Cfg::BN - p.conv_pad;
+        const long long to = from + Cfg::BN - 1 + (long long)(p.conv_kw - 1) * p.conv_dil;
+        if (p.conv_stride == 1 && from >= 0 && to < p.conv_len && (tn + 1) * Cfg::BN <= p.N)
+            terms_tile<Cfg, VIEW, TIMED, true>(p, out_mode, lds_a, lds_b, rs_buf);
+        else
+            terms_tile<Cfg, VIEW, TIMED, false>(p, out_mode, lds_a, lds_b, rs_buf);
+    } else {
+        terms_tile<Cfg, VIEW, TIMED, true>(p, out_mode, lds_a, lds_b, rs_buf);
+    }
 #endif
 }
 
 // 128 x 128 tiles: 48 KiB of LDS for operands, two workgroups per CU
 using CfgTerms = TermsCfg<false, 128, 128, 2>;
 using CfgTermsT = TermsCfg<true, 128, 128, 2>;
+// 64 and 32 rows
+using CfgTerms64 = TermsCfg<false, 64, 128, 3>;
+using CfgTerms64T = TermsCfg<true, 64, 128, 2>;
+using CfgTerms32 = TermsCfg<false, 32, 128, 3>;
 
 template <typename Cfg, int VIEW, bool TIMED = false>
 static hipError_t launch_terms(const GemmArgs& a, int out_mode, hipStream_t s)

@@ -53,7 +53,7 @@ struct GemmArgs {
     int edge_tn[3];
     int edge_ldb;
     long long edge_batch_stride;
-    // Bounds-checked kernel, convolution read in place: conv_kw > 0 means B is the input
+    // Bounds-checked kernel and the fp32 convolution read in place: conv_kw > 0 means B is the input
     // x [batch][K / conv_kw][conv_len] and B[k][n] stands for
     // x[k / conv_kw][n * conv_stride + (k % conv_kw) * conv_dil - conv_pad], zero outside.
     int conv_kw, conv_stride, conv_pad, conv_dil, conv_len;
@@ -134,6 +134,9 @@ hipError_t launch_gemm_tiny(const GemmArgs& a, hipStream_t s);
 // The large fp32 tile, plain operand views and a convolution's, on the bf16 matrix cores
 // (pgk_gemm_f32_terms.h); reached through launch_gemm_mfma.
 hipError_t launch_gemm_f32_terms(const GemmArgs& a, int out_mode, hipStream_t s);
+// A convolution whose input and weights are read in place (A = w [Cout][Cin * Kw], conv_* set, bias_per_row), on tiles of 128, 64 or 32
+// output channels and 128 positions.
+hipError_t launch_conv_f32_terms(const GemmArgs& a, int rows, hipStream_t s);
 hipError_t launch_gemm_f32_terms_timed(const GemmArgs& a, hipStream_t s);
 
 // The large tile of either type, plain operand views, out_mode 0, with phase stamps (a.stamps set).
