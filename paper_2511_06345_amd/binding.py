@@ -33,6 +33,11 @@ EXPORTS = ("pgk_gemm_fused", "pgk_gemm_splitk", "pgk_gemm_fused_bt", "pgk_gemm_s
 WS_ROWSUM, WS_B_TRANSPOSED, WS_UNALIGNED = 1, 2, 4
 
 _lib = None
+# the ordinary calls in native code (csrc/pgk_torch.cpp), bound to the library when that is loaded
+_native = None
+_NATIVE_ENTRIES = ("pgk_gemm_fused", "pgk_gemm_fused_bt", "pgk_gemm_splitk", "pgk_gemm_splitk_bt", "pgk_gemm_fused_workspace_bytes",
+                   "pgk_gemm_splitk_workspace_bytes", "pgk_reduce_max", "pgk_reduce_max_workspace_bytes", "pgk_conv1d",
+                   "pgk_conv1d_workspace_bytes", "pgk_conv1d_out_len")
 
 # the handle of torch.cuda.current_stream() without the Python object around it: 0.3 us, not 2.8, of a small
 # call that takes 20 us of which the host bounds all.  Not a public name: None where torch does not have it.
@@ -49,7 +54,7 @@ class PgkError(RuntimeError):
 
 def load_library() -> ctypes.CDLL:
     """dlopen libpgk.so (built in-tree by ``build.build_library``)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -105,6 +110,9 @@ def load_library() -> ctypes.CDLL:
     lib.pgk_status_string.argtypes = [ci]
     lib.pgk_version.restype = ci
     lib.pgk_version.argtypes = []
+    from . import _pgk_torch
+    _pgk_torch.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in _NATIVE_ENTRIES))
+    _native = _pgk_torch
     _lib = lib
     return lib
 
@@ -247,6 +255,13 @@ def _ws_flags(A, B, rowsum: bool, b_transposed: bool) -> int:
     return flags
 
 
+def _checked(done, where: str):
+    """What an ordinary call in native code gave: its outputs, or the library's status."""
+    if type(done) is int:
+        raise PgkError(done, where)
+    return done
+
+
 def gemm_fused(A: torch.Tensor, B: torch.Tensor, bias: Optional[torch.Tensor], act: int,
                rowsum: bool = True, out: Optional[torch.Tensor] = None,
                rowsum_out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
@@ -261,6 +276,10 @@ def gemm_fused(A: torch.Tensor, B: torch.Tensor, bias: Optional[torch.Tensor], a
     and the problem needs one.
     """
     lib = load_library()
+    if out is None and rowsum_out is None and workspace is None and stream is None:
+        done = _native.gemm(A, B, bias, act, rowsum, b_transposed, None)
+        if done is not None:
+            return _checked(done, "pgk_gemm_fused_bt" if b_transposed else "pgk_gemm_fused")
     batch, M, N, K, dtype = _shape(A, B, b_transposed)
     entry = lib.pgk_gemm_fused_bt if b_transposed else lib.pgk_gemm_fused
     dev = A.device
@@ -317,6 +336,10 @@ def gemm_splitk(A: torch.Tensor, B: torch.Tensor, bias: Optional[torch.Tensor], 
     ``workspace`` is a uint8 device tensor of at least ``gemm_splitk_workspace_bytes(...)`` bytes
     (``splitk_workspace_bytes(...)`` is enough for aligned operands); allocated here when None."""
     lib = load_library()
+    if out is None and rowsum_out is None and workspace is None and stream is None and splits is not None:
+        done = _native.gemm(A, B, bias, act, rowsum, b_transposed, splits)
+        if done is not None:
+            return _checked(done, "pgk_gemm_splitk_bt" if b_transposed else "pgk_gemm_splitk")
     batch, M, N, K, dtype = _shape(A, B, b_transposed)
     entry = lib.pgk_gemm_splitk_bt if b_transposed else lib.pgk_gemm_splitk
     dev = A.device
@@ -352,6 +375,10 @@ def reduce_max(X: torch.Tensor, dim: int, want_idx: bool = True, out: Optional[t
     (values in the dtype of X with ``dim`` removed, int32 positions or None).  ``workspace``: uint8
     device tensor of at least ``reduce_max_workspace_bytes(...)`` bytes, allocated here when None."""
     lib = load_library()
+    if out is None and idx_out is None and workspace is None and stream is None:
+        done = _native.reduce_max(X, dim, want_idx)
+        if done is not None:
+            return _checked(done, "pgk_reduce_max")
     if not (X.is_cuda and X.is_contiguous()):
         raise ValueError("X must be a contiguous device tensor")
     if X.dtype == torch.float32:
@@ -468,6 +495,10 @@ def conv1d(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor], act: 
     float32 or bfloat16 device tensors; bias float32 [Cout] or None.  ``workspace``: uint8 device
     tensor of at least ``conv1d_workspace_bytes(...)`` bytes, allocated here when None."""
     lib = load_library()
+    if out is None and workspace is None and stream is None:
+        done = _native.conv1d(x, w, bias, act, stride, pad, dilation)
+        if done is not None:
+            return _checked(done, "pgk_conv1d")
     if x.dim() != 3 or w.dim() != 3 or x.shape[1] != w.shape[1]:
         raise ValueError("expected x [B, Cin, L] and w [Cout, Cin, Kw]")
     if not (x.is_cuda and w.is_cuda and x.is_contiguous() and w.is_contiguous() and x.device == w.device):

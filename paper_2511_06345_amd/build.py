@@ -11,6 +11,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpgk.so")
+# the binding's ordinary calls in native code (host only, against the torch that is installed)
+TORCH_EXT = os.path.join(HERE, "_pgk_torch.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 # what the compiler reports per kernel (registers, scratch, LDS, waves per SIMD), written at
 # build time next to the library; the profile harness reads it
@@ -20,11 +22,11 @@ BUILT_FROM = os.path.join(HERE, "libpgk.built_from")
 
 
 def source_hash() -> str:
-    """A short hash of csrc/*.hip and *.h as they stand."""
+    """A short hash of csrc/*.hip, *.h and *.cpp as they stand."""
     import glob
     import hashlib
     h = hashlib.sha256()
-    for path in sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.h"))):
+    for path in sorted(p for kind in ("*.hip", "*.h", "*.cpp") for p in glob.glob(os.path.join(CSRC, kind))):
         h.update(os.path.basename(path).encode())
         with open(path, "rb") as f:
             h.update(f.read())
@@ -87,6 +89,22 @@ def _compile(src: str):
     return obj, parse_resource_remarks(res.stderr)
 
 
+def _build_torch_ext() -> None:
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    includes = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-I{d}" for d in includes),
+           os.path.join(CSRC, "pgk_torch.cpp"), "-o", TORCH_EXT, "-L" + os.path.join(root, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"compiling pgk_torch.cpp failed:\n{res.stderr}")
+
+
 def build_library(verbose: bool = False) -> str:
     """Compile every HIP source for gfx950 and link libpgk.so.  Always recompiles."""
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -94,7 +112,9 @@ def build_library(verbose: bool = False) -> str:
     if os.path.exists(BUILT_FROM):
         os.remove(BUILT_FROM)
     with ThreadPoolExecutor(max_workers=6) as ex:
+        ext = ex.submit(_build_torch_ext)
         compiled = list(ex.map(_compile, SOURCES))
+        ext.result()
     objs = [c[0] for c in compiled]
     resources = {}
     for _, r in compiled:
