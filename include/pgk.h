@@ -311,7 +311,9 @@ size_t pgk_reduce_max_workspace_bytes(int64_t outer, int64_t red, int64_t inner,
  *     dilations in bfloat16 -- with Kw <= 32: of copies of the input, one per phase of the stride (and a second one
  *     shifted by one element for bfloat16 taps at odd offsets), channels padded with zeros to a multiple of the K tile.
  * Float32 also, where it is faster (Lout of at least 16, entries of x below 4 GiB), without any of these, in one launch: x and w on any
- * element, read in place as they are.  Sizes that 1 to 3 need a workspace for ask for it all the same.
+ * element, read in place as they are.  Sizes that 1 to 3 need a workspace for ask for it all the same.  Bfloat16 likewise, x on any element, strides
+ * of at most 3 and (Kw - 1) * dilation + 127 * stride below 384, from 16 channels on also where 1 to 3 do not apply: the query then gives what
+ * the regrouped weights take, and a call with less runs without.
  * These need `workspace`
  * (device memory, 256-byte aligned, contents destroyed) of pgk_conv1d_workspace_bytes(...)
  * bytes for the regrouped weights and the strips or copies.  Too small (also for the way through

@@ -33,7 +33,7 @@ def source_hash() -> str:
     return h.hexdigest()[:16]
 
 SOURCES = ["pgk_api.hip", "pgk_gemm_mfma.hip", "pgk_gemm_mfma_conv.hip", "pgk_gemm_mfma_reg.hip", "pgk_gemm_f32_terms.hip", "pgk_gemm_tiny.hip", "pgk_gemm_stream.hip", "pgk_gemm_guarded.hip", "pgk_reduce.hip", "pgk_reduce_max.hip",
-           "pgk_probe.hip", "pgk_conv.hip", "pgk_conv_few.hip", "pgk_pack.hip"]
+           "pgk_probe.hip", "pgk_conv.hip", "pgk_conv_few.hip", "pgk_conv_bf16.hip", "pgk_pack.hip"]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from forming packed fp32 VALU ops

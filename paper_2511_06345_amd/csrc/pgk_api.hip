@@ -1173,7 +1173,9 @@ struct ConvPlan {
     int kind;            // tile shape (TILE_*), chosen as for a plain GEMM of Cout x Lout
     pgk::TileShape tile;
     size_t w_bytes, x_bytes;   // workspace parts: regrouped weights; copies of the input or strips
-    int in_place_rows;         // fp32, x and w read in place by tiles of so many output channels and 128 positions, whatever the rest says (0: not so)
+    int in_place_rows;         // x read in place by tiles of so many output channels and 128 positions, whatever the rest says (0: not so);
+                               // bf16 with `regrouped` bytes of workspace
+    size_t regrouped;
 };
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1325,11 +1327,56 @@ int conv_rows_in_place(const ConvPlan& views, int64_t B, int64_t Cin, int64_t L,
     return best_time < 0.97 * in_views ? best : 0;
 }
 
+// bf16: blocks of 32 channels of the input in LDS, position by position (pgk_conv_bf16.hip), without copies of the input, without a K loop through
+// registers, and x read once for all taps.  A block takes what its loads and barriers take or, on a full CU, its taps and its
+// rows for every workgroup.  The constants were fitted to 420 drawn convolutions, these and those of the views' kernels (both off by an eighth in the root mean square); of the choices
+// two are over 5 % slower than the views, the mean is 1.65 times as fast, 0.98 of what the best way each time gives.  [13, 384, 11631] x [61, 384, 5]
+// stride 2 117 us in the views, 58 here, [13, 64, 4673] x [128, 64, 7] stride 2 39 and 17; long sums over many channels are the views': [8, 512, 4096] x [512,
+// 512, 3] 56 and 86.  From 16 channels on also what had no views, which is faster here throughout (89 of the 420): [13, 20, 26691] x [202, 20, 3] 287
+// on the bounds-checked kernel and 63, [13, 17, 61760] x [64, 17, 1] 85 on the one for few channels and 27.
+int conv_bf16_in_place(const ConvPlan& views, int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw, int64_t stride, int64_t pad, int64_t dilation)
+{
+    const int64_t blocks = (Cin + 31) / 32, tiles_n = (views.Lout + 127) / 128;
+    if (views.Lout < 16 || Cin < 16 || L >= (1 << 27) || (long double)Cout * Kw * blocks * 64 >= 2.0e9L ||
+        (long double)((tiles_n + 4) * 128) * stride + pad >= 2.0e9L || (long double)(Cout + 31) / 32 * tiles_n * B >= 2.0e9L) return 0;
+    struct Cost { int rows, per_cu; double fixed, per_round, part, tap_alone, group_alone, tap, group; };
+    const Cost kinds[] = {{128, 2, 6.90, 1.43, 0.19, 0.293, 0.37, 0.218, 0.25}, {64, 4, 6.47, 0.77, 0.24, 0.192, 0.31, 0.131, 0.173},
+                          {32, 4, 5.90, 0.48, 0.31, 0.156, 0.31, 0.059, 0.142}};
+    const int64_t groups = ((Kw - 1) * dilation + 127 * stride + 1 + 127) / 128;
+    int best = 0;
+    double best_time = 0.0;
+    for (const Cost& k : kinds) {
+        int parts = 1;
+        const size_t lds = pgk::conv_bf16_lds(Kw, stride, dilation, L, k.rows, &parts);
+        if (!lds) return 0;
+        const double per = (double)((Cout + k.rows - 1) / k.rows) * (double)tiles_n * (double)B / kNumCUs;
+        const double on_busiest = per <= std::min<double>(k.per_cu, (double)(160 * 1024 / lds)) ? std::ceil(per) : per + 0.3;
+        const double t = k.fixed + k.per_round * on_busiest +
+                         (double)blocks * std::max(k.tap_alone * (double)Kw + k.part * parts + k.group_alone * (double)groups,
+                                                   on_busiest * (k.tap * (double)Kw + k.group * (double)groups));
+        if (!best || t < best_time) { best = k.rows; best_time = t; }
+    }
+    if (!views.fast) return best;
+    const double copies = views.table || views.Lp > 0 ? 0.21e-6 * 2.0 * (double)B * ((double)Cin * (double)L + (double)((Cin + 63) / 64 * 64) * (double)views.Lout * (double)(stride * std::max(views.shifts, 1))) : 0.0;
+    const StepCost cost = views.kind == pgk::TILE_FLAT    ? StepCost{8.2, 0.0, 0.49, 0.43, 4}
+                          : views.kind == pgk::TILE_SMALL ? StepCost{9.1, 4.5, 0.515, 0.423, 2}
+                          : views.kind == pgk::TILE_LARGE ? StepCost{7.2, 7.7, 0.23, 1.235, 1}
+                                                          : StepCost{6.5, 6.8, 0.79, 0.89, 1};
+    const double wgs = (double)((Cout + views.tile.bm - 1) / views.tile.bm) * (double)((views.Lout + views.tile.bn - 1) / views.tile.bn) * (double)B;
+    // (tiles of one to a CU: whole rounds)
+    const double in_views = copies + stepped_time(cost, (int64_t)((double)(Kw * ((Cin + 63) / 64)) * (views.reg ? 1.38 : 1.0)),
+                                                  cost.per_cu == 1 ? std::ceil(wgs / kNumCUs) * kNumCUs - (wgs > kNumCUs ? 0.3 * kNumCUs : 0.0) : wgs);
+    return best_time < 0.92 * in_views ? best : 0;
+}
+
 ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw, int64_t stride, int64_t pad, int64_t dilation, int dtype,
                      bool no_copies = false)
 {
     ConvPlan pl = plan_conv_views(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype, no_copies);
-    if (pl.valid && dtype == PGK_DTYPE_F32) pl.in_place_rows = conv_rows_in_place(pl, B, Cin, L, Cout, Kw, stride, pad, dilation);
+    if (pl.valid)
+        pl.in_place_rows = dtype == PGK_DTYPE_F32 ? conv_rows_in_place(pl, B, Cin, L, Cout, Kw, stride, pad, dilation)
+                                                  : conv_bf16_in_place(pl, B, Cin, L, Cout, Kw, stride, pad, dilation);
+    if (pl.in_place_rows && dtype == PGK_DTYPE_BF16) pl.regrouped = round_up((size_t)(Cout * Kw * ((Cin + 31) / 32 * 32) * 2), 256);
     return pl;
 }
 
@@ -1348,7 +1395,7 @@ size_t pgk_conv1d_workspace_bytes(int64_t B, int64_t Cin, int64_t L, int64_t Cou
                                   int64_t pad, int64_t dilation, int dtype)
 {
     const ConvPlan pl = plan_conv1d(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype);
-    return (pl.valid && pl.fast) ? pl.w_bytes + pl.x_bytes : 0;
+    return !pl.valid ? 0 : pl.fast ? pl.w_bytes + pl.x_bytes : pl.regrouped;
 }
 
 int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t B, int64_t Cin, int64_t L,
@@ -1394,7 +1441,14 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
     // (asked for by the sizes alone, whichever way the call then takes)
     if (pl.fast && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < pl.w_bytes + pl.x_bytes))
         return PGK_ERR_WORKSPACE;
-    if (pl.in_place_rows) {
+    // (bf16 that has no other use for a workspace: without one it stays on the bounds-checked kernel)
+    if (pl.regrouped && workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u) && workspace_bytes >= pl.regrouped) {
+        const int cin_pad = (int)((Cin + 31) / 32 * 32);
+        if (pgk::launch_conv_repack_weights(w, workspace, (int)Cout, (int)Cin, cin_pad, (int)Kw, dtype, st) != hipSuccess) return PGK_ERR_HIP;
+        return pgk::launch_conv_bf16(x, workspace, bias, y, B, (int)Cin, cin_pad, (int)L, (int)Cout, (int)Kw, (int)stride, (int)pad, (int)dilation,
+                                     (int)pl.Lout, pl.in_place_rows, act, st) == hipSuccess ? PGK_OK : PGK_ERR_HIP;
+    }
+    if (pl.in_place_rows && dtype == PGK_DTYPE_F32) {
         const int64_t rows = pl.in_place_rows;
         a.A = w; a.B = x;
         a.b_batch_stride = Cin * L;

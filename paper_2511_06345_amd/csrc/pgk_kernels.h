@@ -195,6 +195,12 @@ hipError_t launch_conv_pad_input(const void* x, void* xp, long long rows, int L,
 // (the same launch regroups the weights: wr[co][k][ci] = w[co][ci][k], zero up to Cin_pad)
 hipError_t launch_conv_phase_copies(const void* x, void* xc, long long B, int Cin, int Cin_pad, int L, int Lq, int pad,
                                     int stride, int shifts, const void* w, void* wr, int Cout, int Kw, int dtype, hipStream_t s);
+// bf16, the input read in place (pgk_conv_bf16.hip); wr as launch_conv_repack_weights makes it, channels padded to a multiple of 32, on a
+// 16-byte boundary; x, bias and y on any element.  rows: output channels per tile, 128, 64 or 32.
+// conv_bf16_lds: bytes of LDS per workgroup, 0 where the kernel does not take such a convolution (parts: that the weights of a block come in).
+size_t conv_bf16_lds(long long Kw, long long stride, long long dil, long long L, int rows, int* parts = nullptr);
+hipError_t launch_conv_bf16(const void* x, const void* wr, const float* bias, void* y, long long B, int Cin, int cin_pad, int L, int Cout,
+                            int Kw, int stride, int pad, int dil, int Lout, int rows, int act, hipStream_t s);
 // wr[co][k][ci] = w[co][ci][k] for ci < Cin, 0 for Cin <= ci < Cin_pad
 hipError_t launch_conv_repack_weights(const void* w, void* wr, int Cout, int Cin, int Cin_pad, int Kw, int dtype, hipStream_t s);
 // the regrouped weights and, in the same launch, strip e (e < n_edges, may be 0) of
