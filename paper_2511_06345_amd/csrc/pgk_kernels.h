@@ -180,6 +180,7 @@ struct ReducePlan {
     int vec, group, segs, per_seg, tiles_i;
     long long blocks;
     size_t partial_elems;
+    bool held;             // rows in registers, per_seg chunks a lane
 };
 ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int dtype, bool x_aligned);
 // pv / pi: partial_elems floats / ints of scratch (unused when partial_elems == 0).

@@ -8,9 +8,8 @@
 // and several of them in flight per lane.  Where rows do not start on 16-byte boundaries, long ones are
 // read in aligned chunks with the elements at their ends apart, shorter and strided ones in chunks from any element on,
 // and small problems one element per load (plan_reduce_max).
-//   * inner == 1 (the reduced dimension is contiguous): a wave (short rows) or a
-//     256-thread workgroup (long rows) sweeps one row in 16-byte chunks; lanes are
-//     combined with cross-lane shuffles, waves through LDS.
+//   * inner == 1 (the reduced dimension is contiguous): some lanes of a wave (short rows), a wave or a workgroup hold a row in
+//     registers, in 16-byte chunks all loaded at once; longer ones are swept by a workgroup.  The maximum comes first, its position after.
 //   * 1 < inner, up to about half of what a workgroup loads at once: a workgroup sweeps its block of whole r as it
 //     lies in memory, 16 bytes per lane, and combines the lanes of equal inner position through LDS.
 //   * inner beyond that: lanes lie along the contiguous inner dimension, 16 bytes each; the four
@@ -97,109 +96,266 @@ __device__ __forceinline__ void store_one(void* out, size_t e, float v)
 }
 
 // ---------------------------------------------------------------------------------
-// inner == 1.  G lanes (one wave, or the whole workgroup of 256) sweep the chunks
-// [c0, c1) of one row; lane l takes chunks c0 + l, c0 + l + G, ...  LEAD: the rows do not all start on
-// 16-byte boundaries; the elements before a row's first boundary and those behind its last
-// whole chunk are taken one per lane (bf16 [2048, 50257]: 105 us with one element per load, 39 so).
-// Result: direct to out / idx when segs == 1, else to the segment partials.
-template <bool BF16, bool LEAD, int G>
-__global__ __launch_bounds__(256) void reduce_max_rows_kernel(const void* __restrict__ X, void* __restrict__ out,
-                                                              int* __restrict__ idx, float* __restrict__ pv,
-                                                              int* __restrict__ pi, long long outer, int red,
-                                                              int segs, int chunks_per_seg)
+// Rows (inner == 1): the largest value first, then where it is.  A compare, a select of the value and one of its position per element
+// are four to six operations, and bound rows by the vector ALU: bf16 ones of 520 elements streamed at 3.3 TB/s, of 100 at 1.1.
+// v_maximum3_f32 takes two elements at a time and hands NaN on, and the position is looked up once, in what the maximum came
+// from: both stream at 5.3 to 7.0.  (Its maximum orders -0 below +0: what is looked up is the first element that compares equal.)
+__device__ __forceinline__ float maximum(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
+template <bool BF16>
+__device__ __forceinline__ float chunk_maximum(const u32x4& w)
 {
     constexpr int VEC = Elem<BF16>::VEC;
-    constexpr int ROWS = 256 / G;                 // rows (or row segments) per workgroup
-    constexpr int UNROLL = 4;
+    float x[VEC];
+    unpack<BF16>(w, x);
+    float m = x[0];
+#pragma unroll
+    for (int e = 1; e < VEC; ++e) m = maximum(m, x[e]);
+    return m;
+}
+template <bool BF16>
+__device__ __forceinline__ float chunk_maximum(float x) { return x; }
+
+// Is x what the maximum m stands for?  NANS: where m may be one.
+template <bool NANS>
+__device__ __forceinline__ bool is_maximum(float x, float m) { return NANS ? x == m || (x != x && m != m) : x == m; }
+
+// Of U chunks in ascending position with their maxima, the first element that m stands for: its value, its chunk and its place there
+// (false: none).
+template <bool BF16, bool NANS, int U>
+__device__ __forceinline__ bool first_of(const u32x4 (&w)[U], const float (&cm)[U], float m, float& v, int& chunk, int& e0)
+{
+    constexpr int VEC = Elem<BF16>::VEC;
+    u32x4 sel = w[U - 1];
+    chunk = U - 1;
+#pragma unroll
+    for (int u = U - 2; u >= 0; --u)
+        if (is_maximum<NANS>(cm[u], m)) { sel = w[u]; chunk = u; }
+    float x[VEC];
+    unpack<BF16>(sel, x);
+    e0 = -1;
+    v = 0.0f;
+#pragma unroll
+    for (int e = VEC - 1; e >= 0; --e)
+        if (is_maximum<NANS>(x[e], m)) { e0 = e; v = x[e]; }
+    return e0 >= 0;
+}
+template <bool BF16, bool NANS, int U>
+__device__ __forceinline__ bool first_of(const float (&w)[U], const float (&cm)[U], float m, float& v, int& chunk, int& e0)
+{
+    chunk = -1;
+    v = 0.0f;
+    e0 = 0;
+#pragma unroll
+    for (int u = U - 1; u >= 0; --u)
+        if (is_maximum<NANS>(cm[u], m)) { v = w[u]; chunk = u; }
+    return chunk >= 0;
+}
+
+// `combine` over the 1 << lg lanes of a group, in every one of them
+template <typename T, typename F>
+__device__ __forceinline__ T across(T v, int lg, F combine)
+{
+    auto dpp = [&](auto ctrl) { return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, true)); };
+    if (lg >= 1) v = combine(v, dpp(std::integral_constant<int, 0xB1>{}));       // quad_perm [1, 0, 3, 2]
+    if (lg >= 2) v = combine(v, dpp(std::integral_constant<int, 0x4E>{}));       // quad_perm [2, 3, 0, 1]
+    if (lg >= 3) v = combine(v, dpp(std::integral_constant<int, 0x141>{}));      // row_half_mirror
+    if (lg >= 4) v = combine(v, dpp(std::integral_constant<int, 0x140>{}));      // row_mirror
+    if (lg >= 5) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned int, v), __builtin_bit_cast(unsigned int, v), false, false);
+        const unsigned int s0 = s[0], s1 = s[1];
+        v = combine(__builtin_bit_cast(T, s0), __builtin_bit_cast(T, s1));
+    }
+    if (lg >= 6) {
+        const auto s = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned int, v), __builtin_bit_cast(unsigned int, v), false, false);
+        const unsigned int s0 = s[0], s1 = s[1];
+        v = combine(__builtin_bit_cast(T, s0), __builtin_bit_cast(T, s1));
+    }
+    return v;
+}
+__device__ __forceinline__ float across_max(float v, int lg) { return across(v, lg, [](float a, float b) { return maximum(a, b); }); }
+__device__ __forceinline__ int across_min(int v, int lg) { return across(v, lg, [](int a, int b) { return a < b ? a : b; }); }
+
+// Rows held in registers: g = 1 << lg lanes of a wave (G == 64), or the workgroup (256, 512 or 1024 threads), share a row, U chunks of 16 bytes
+// per lane, all loaded at once.  ANY: rows start on any element.  Either way a chunk that would reach past the row's end is moved back to end with it: the
+// elements it shares with others are found at the same positions.  LEAD: aligned chunks, the last one in place of those past it, the elements at the
+// row's ends apart, one per lane (bf16 rows of 9999 elements: 56 us with ANY, 44 so; in a wave's lanes ANY is faster, of 333: 48 and 60; fp32 alike).
+// VEC == 1: rows shorter than a chunk, one lane each.
+enum { ALIGNED, ANY, LEAD };
+
+template <bool BF16, int VEC, int FORM, int U, int G>
+__global__ __launch_bounds__(G > 64 ? G : 256) void reduce_max_held_rows_kernel(const void* __restrict__ X, void* __restrict__ out,
+                                                                   int* __restrict__ idx, long long outer, int red, int lg)
+{
+    __shared__ float sv[G > 64 ? G / 64 : 1];
+    __shared__ int si[G > 64 ? G / 64 : 1];
+    const int tid = threadIdx.x;
+    const int g = G > 64 ? G : 1 << lg;
+    const int gl = tid & (g - 1);
+    const long long row = G > 64 ? (long long)blockIdx.x : (long long)blockIdx.x * (256 >> lg) + (tid >> lg);
+    const bool active = row < outer;              // whole groups only
+    const size_t row_base = (size_t)(active ? row : outer - 1) * (size_t)red;
+    const unsigned char* const row_at = (const unsigned char*)X + row_base * Elem<BF16>::BYTES;
+    const int lead = FORM == LEAD ? (int)((0u - (unsigned int)(size_t)row_at) & 15u) / Elem<BF16>::BYTES : 0;
+    const int nch = (red - lead) / VEC, rest = red - lead - nch * VEC;      // (with LEAD)
+    auto start = [&](int c) __attribute__((always_inline)) {
+        if constexpr (FORM == LEAD) return lead + (c < nch ? c : nch - 1) * VEC;
+        else return c * VEC < red - VEC ? c * VEC : red - VEC;
+    };
+    using loaded = typename std::conditional<VEC == 1, float, u32x4>::type;
+    loaded w[U];
+    float cm[U];
+    float lead_v = kNegInf, rest_v = kNegInf;
+    if constexpr (FORM == LEAD) {
+        if (gl < lead) lead_v = load_one<BF16>(X, row_base + gl);
+        if (gl < rest) rest_v = load_one<BF16>(X, row_base + red - rest + gl);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if constexpr (VEC == 1) w[u] = load_one<BF16>(X, row_base + start(gl + u * g));
+        else w[u] = load_chunk<BF16, FORM == ANY>(row_at + (size_t)start(gl + u * g) * Elem<BF16>::BYTES);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) cm[u] = chunk_maximum<BF16>(w[u]);
+    float m = cm[0];
+#pragma unroll
+    for (int u = 1; u < U; ++u) m = maximum(m, cm[u]);
+    if constexpr (FORM == LEAD) m = maximum(m, maximum(lead_v, rest_v));
+    const int wave_lg = G > 64 ? 6 : lg;
+    m = across_max(m, wave_lg);
+    float v;
+    int chunk, e;
+    bool found;
+    if (__any(m != m)) found = first_of<BF16, true, U>(w, cm, m, v, chunk, e);
+    else found = first_of<BF16, false, U>(w, cm, m, v, chunk, e);
+    int pos = found ? start(gl + chunk * g) + e : kNoPos;
+    if constexpr (FORM == LEAD) {
+        if (!found && gl < rest && is_maximum<true>(rest_v, m)) { v = rest_v; pos = red - rest + gl; }
+        if (gl < lead && is_maximum<true>(lead_v, m)) { v = lead_v; pos = gl; }
+    }
+    const int first = across_min(pos, wave_lg);
+    if constexpr (G > 64) {
+        if (pos == first) { sv[tid >> 6] = v; si[tid >> 6] = pos; }      // (lanes that share an element write the same)
+        __syncthreads();
+        if (tid == 0) {
+            v = sv[0];
+            pos = si[0];
+#pragma unroll
+            for (int q = 1; q < G / 64; ++q)
+                if (beats(sv[q], si[q], v, pos)) { v = sv[q]; pos = si[q]; }
+            store_one<BF16>(out, (size_t)row, v);
+            if (idx) idx[row] = pos;
+        }
+    } else if (active && pos == first) {
+        store_one<BF16>(out, (size_t)row, v);
+        if (idx) idx[row] = pos;
+    }
+}
+
+// Longer rows: the workgroup sweeps the chunks [c0, c1) of one row, UNROLL sweeps at a time (the last chunk in place of those past
+// it); a lane keeps its maximum and the sweeps it came from, and the first of those that have the row's read theirs again for the position.
+// ENDS: the rows do not all start on 16-byte boundaries; the elements before a row's first boundary and those behind its last
+// whole chunk are taken one per lane (bf16 [2048, 50257]: 105 us with one element per load, 39 so).
+// Result: direct to out / idx when segs == 1, else to the segment partials.
+template <bool BF16, bool ENDS, int UNROLL>
+__global__ __launch_bounds__(256) void reduce_max_rows_kernel(const void* __restrict__ X, void* __restrict__ out,
+                                                              int* __restrict__ idx, float* __restrict__ pv,
+                                                              int* __restrict__ pi, int red, int segs, int chunks_per_seg)
+{
+    constexpr int VEC = Elem<BF16>::VEC, G = 256;
     __shared__ float sv[4];
     __shared__ int si[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int gl = tid % G;                       // lane within the group
-    const long long unit = (long long)blockIdx.x * ROWS + tid / G;      // row * segs + seg
-    const bool active = unit < outer * segs;      // whole groups only: uniform per wave
-    const long long row = active ? unit / segs : 0;
-    const int seg = active ? (int)(unit - row * segs) : 0;
+    const int gl = threadIdx.x;
+    const long long unit = blockIdx.x;            // row * segs + seg
+    const long long row = unit / segs;
+    const int seg = (int)(unit - row * segs);
     const size_t row_base = (size_t)row * (size_t)red;
     const unsigned char* const row_at = (const unsigned char*)X + row_base * Elem<BF16>::BYTES;
     // elements before the first 16-byte boundary (red is larger than that), whole chunks, elements left
-    const int lead = LEAD ? (int)((0u - (unsigned int)(size_t)row_at) & 15u) / Elem<BF16>::BYTES : 0;
+    const int lead = ENDS ? (int)((0u - (unsigned int)(size_t)row_at) & 15u) / Elem<BF16>::BYTES : 0;
     const int nch = (red - lead) / VEC;
-    const int rest = LEAD ? red - lead - nch * VEC : 0;
+    const int rest = ENDS ? red - lead - nch * VEC : 0;
     const int c0 = seg * chunks_per_seg;
-    const int c1 = active ? (c0 + chunks_per_seg < nch ? c0 + chunks_per_seg : nch) : c0;
+    const int c1 = c0 + chunks_per_seg < nch ? c0 + chunks_per_seg : nch;
+    const u32x4* const src = (const u32x4*)(row_at + lead * Elem<BF16>::BYTES);
 
-    float bv[VEC];
-    int bk[VEC];                                  // sweep number of the best element per slot
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) { bv[e] = kNegInf; bk[e] = 0; }
-
-    int c = c0 + gl, k = 0;
-    const u32x4* src = (const u32x4*)(row_at + lead * Elem<BF16>::BYTES);
-    for (; c + (UNROLL - 1) * G < c1; c += UNROLL * G, k += UNROLL) {
-        u32x4 w[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) w[u] = __builtin_nontemporal_load(src + c + u * G);
+    // (the elements at the row's ends: the first segment's lanes and the last one's)
+    float lead_v = kNegInf, rest_v = kNegInf;
+    const bool has_lead = ENDS && seg == 0 && gl < lead, has_rest = ENDS && seg == segs - 1 && gl < rest;
+    if constexpr (ENDS) {
+        if (has_lead) lead_v = load_one<BF16>(X, row_base + gl);
+        if (has_rest) rest_v = load_one<BF16>(X, row_base + red - rest + gl);
+    }
+    // chunks first + gl, first + gl + G, ... (past the end: the last one)
+    auto load = [&](int first, u32x4 (&w)[UNROLL]) __attribute__((always_inline)) {
+        const int at = first < c1 ? first : c1 - 1, left = c1 - 1 - at;
+        const unsigned char* const from = (const unsigned char*)(src + at);
+        const unsigned int most = 16u * (unsigned int)(left < UNROLL * G ? left : UNROLL * G);
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-            float x[VEC];
-            unpack<BF16>(w[u], x);
+            const unsigned int off = 16u * (unsigned int)(gl + u * G);
+            w[u] = __builtin_nontemporal_load((const u32x4*)(from + (off < most ? off : most)));
+        }
+    };
+    float best = kNegInf;
+    int best_first = c0;                          // the sweeps it came from
+    auto take = [&](int first, const u32x4 (&w)[UNROLL]) __attribute__((always_inline)) {
+        float m = chunk_maximum<BF16>(w[0]);
 #pragma unroll
-            for (int e = 0; e < VEC; ++e)
-                if (replaces(x[e], bv[e])) { bv[e] = x[e]; bk[e] = k + u; }
+        for (int u = 1; u < UNROLL; ++u) m = maximum(m, chunk_maximum<BF16>(w[u]));
+        if (replaces(m, best)) { best = m; best_first = first; }
+    };
+    if (c0 < c1) {                                // (as many sweeps are on their way as are looked at)
+        u32x4 w0[UNROLL], w1[UNROLL];
+        load(c0, w0);
+        for (int c = c0; c < c1; c += 2 * UNROLL * G) {
+            load(c + UNROLL * G, w1);
+            take(c, w0);
+            if (c + UNROLL * G >= c1) break;
+            load(c + 2 * UNROLL * G, w0);
+            take(c + UNROLL * G, w1);
         }
     }
-    for (; c < c1; c += G, ++k) {
-        float x[VEC];
-        unpack<BF16>(__builtin_nontemporal_load(src + c), x);
+    float m = maximum(maximum(lead_v, rest_v), best);
+    m = across_max(m, 6);
+    int pos = kNoPos;
+    float v = m;
+    const bool has = c0 < c1 && is_maximum<true>(best, m);
+    // (of the wave's lanes that have it those of the earliest sweeps: bf16 values tie often)
+    const int earliest = across_min(has ? best_first : kNoPos, 6);
+    if (has && best_first == earliest) {
+        u32x4 w[UNROLL];
+        float cm[UNROLL];
+        load(best_first, w);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e)
-            if (replaces(x[e], bv[e])) { bv[e] = x[e]; bk[e] = k; }
-    }
-    // this lane's best: slot e of sweep k is element (lead + (c0 + gl + k G) VEC + e) of the row
-    const bool any = c0 + gl < c1;
-    float v = kNegInf;
-    int p = kNoPos;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-        const int pos = any ? lead + (c0 + gl + bk[e] * G) * VEC + e : kNoPos;
-        if (beats(bv[e], pos, v, p)) { v = bv[e]; p = pos; }
-    }
-    if constexpr (LEAD) {
-        // the first segment's lanes take the elements before the chunks, the last segment's those behind
-        if (active && seg == 0 && gl < lead) {
-            const float x = load_one<BF16>(X, row_base + gl);
-            if (beats(x, gl, v, p)) { v = x; p = gl; }
-        }
-        if (active && seg == segs - 1 && gl < rest) {
-            const int pos = red - rest + gl;
-            const float x = load_one<BF16>(X, row_base + pos);
-            if (beats(x, pos, v, p)) { v = x; p = pos; }
+        for (int u = 0; u < UNROLL; ++u) cm[u] = chunk_maximum<BF16>(w[u]);
+        int chunk, e;
+        float x;
+        if (first_of<BF16, true, UNROLL>(w, cm, m, x, chunk, e)) {
+            const int c = best_first + gl + chunk * G;
+            v = x;
+            pos = lead + (c < c1 ? c : c1 - 1) * VEC + e;
         }
     }
-    // across the lanes of the wave
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(v, off, 64);
-        const int op = __shfl_xor(p, off, 64);
-        if (beats(ov, op, v, p)) { v = ov; p = op; }
+    if constexpr (ENDS) {
+        if (has_rest && pos == kNoPos && is_maximum<true>(rest_v, m)) { v = rest_v; pos = red - rest + gl; }
+        if (has_lead && is_maximum<true>(lead_v, m)) { v = lead_v; pos = gl; }
     }
-    if constexpr (G == 256) {
-        if (lane == 0) { sv[wave] = v; si[wave] = p; }
-        __syncthreads();
-        if (tid == 0) {
+    const int first = across_min(pos, 6);
+    if (pos == first) { sv[gl >> 6] = v; si[gl >> 6] = pos; }            // (lanes that share an element write the same)
+    __syncthreads();
+    if (gl != 0) return;
+    v = sv[0];
+    pos = si[0];
 #pragma unroll
-            for (int w = 1; w < 4; ++w)
-                if (beats(sv[w], si[w], v, p)) { v = sv[w]; p = si[w]; }
-        }
-    }
-    if (gl == 0 && active) {
-        if (segs == 1) {
-            store_one<BF16>(out, (size_t)row, v);
-            if (idx) idx[row] = p;
-        } else {
-            pv[unit] = v;
-            pi[unit] = p;
-        }
+    for (int q = 1; q < 4; ++q)
+        if (beats(sv[q], si[q], v, pos)) { v = sv[q]; pos = si[q]; }
+    if (segs == 1) {
+        store_one<BF16>(out, (size_t)row, v);
+        if (idx) idx[row] = pos;
+    } else {
+        pv[unit] = v;
+        pi[unit] = pos;
     }
 }
 
@@ -307,70 +463,6 @@ __global__ __launch_bounds__(256) void reduce_max_cols_kernel(const void* __rest
                 pi[at] = bp[e];
             }
         }
-    }
-}
-
-// ---------------------------------------------------------------------------------
-// inner == 1, short rows (at most 128 chunks): a wave per row would leave most lanes idle,
-// so g = 1, 2, ... 32 lanes (a power of two, 1 << lg) share a row and a wave takes 64 / g
-// rows; every lane has at most four chunks, fetched together.  No segments.  VEC == 1: rows of at most 128
-// elements that do not start on 16-byte boundaries; UNALIGNED: longer ones, read in 16-byte chunks from
-// any element on, the elements behind the last whole chunk one by one by the lane whose chunk they
-// would be.
-template <bool BF16, int VEC, bool UNALIGNED>
-__global__ __launch_bounds__(256) void reduce_max_short_rows_kernel(const void* __restrict__ X, void* __restrict__ out,
-                                                                    int* __restrict__ idx, long long outer, int red, int lg)
-{
-    const int tid = threadIdx.x;
-    const int g = 1 << lg;
-    const int gl = tid & (g - 1);
-    const long long row = (long long)blockIdx.x * (256 >> lg) + (tid >> lg);
-    const bool active = row < outer;              // whole groups only
-    const int nch = red / VEC;
-    const size_t row_base = (size_t)(active ? row : 0) * (size_t)red;
-
-    float x[4][VEC];
-    bool have[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int c = gl + u * g;
-        have[u] = active && c < nch;
-        if constexpr (VEC > 1) {
-            u32x4 w = {0u, 0u, 0u, 0u};
-            if (have[u]) w = load_chunk<BF16, UNALIGNED>((const unsigned char*)X + row_base * Elem<BF16>::BYTES + (size_t)c * 16);
-            unpack<BF16>(w, x[u]);
-        } else {
-            x[u][0] = have[u] ? load_one<BF16>(X, row_base + c) : 0.0f;
-        }
-    }
-    // this lane's best over its chunks, in increasing position; the first one it has starts the scan
-    float v = kNegInf;
-    int p = kNoPos;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            const int pos = (gl + u * g) * VEC + e;
-            if (have[u] && (p == kNoPos || replaces(x[u][e], v))) { v = x[u][e]; p = pos; }
-        }
-    }
-    if constexpr (UNALIGNED) {
-        if (active && gl == (nch & (g - 1))) {
-            for (int pos = nch * VEC; pos < red; ++pos) {
-                const float r = load_one<BF16>(X, row_base + pos);
-                if (p == kNoPos || replaces(r, v)) { v = r; p = pos; }
-            }
-        }
-    }
-    // across the g lanes of the row
-    for (int off = g >> 1; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(v, off, 64);
-        const int op = __shfl_xor(p, off, 64);
-        if (beats(ov, op, v, p)) { v = ov; p = op; }
-    }
-    if (gl == 0 && active) {
-        store_one<BF16>(out, (size_t)row, v);
-        if (idx) idx[row] = p;
     }
 }
 
@@ -682,7 +774,12 @@ __global__ __launch_bounds__(256) void reduce_max_finish_wave_kernel(const float
 // strided 5080 / 6450 / 5970; fp32 long rows 6940 / 6670 / 6620.
 constexpr int target_workgroups(int dtype) { return dtype == DT_BF16 ? 1024 : 512; }
 constexpr int kWaveFinishMinSegs = 16;
-constexpr long long kShortRowChunks = 128;        // rows of at most this many chunks: several rows per wave
+// Rows are held in registers up to so many chunks by some lanes of a wave or all of them, by a workgroup of 256, eight chunks a lane at most
+// (300 MB of fp32 rows of 2112 elements 43 us so, 63 swept by a wave each; bf16 of 8192 44 and 50), and by 512 threads, sixteen chunks a lane (bf16
+// [2048, 50257] 33 us so, 37 swept by 256; fp32 rows of 14400 36 and 39).  With too few rows for every CU 1024 threads hold
+// as many, also where rows would be cut into segments: the second pass is a launch of its own (bf16 [128, 50257] 9.5 us
+// so, 5.8 here; [400, 65536] 13.4 and 9.7; but [1000, 24001], one segment, 9.1 and 10.4).
+constexpr long long kHeldWave = 512, kHeldWorkgroup = 2048, kHeldMost = 8192;
 constexpr long long kSmallInner = 64;             // inner dimensions up to this: the flattened-sweep kernel
 constexpr long long kTinyBlock = 128;             // red x inner up to this: several outer indices per workgroup
 
@@ -741,33 +838,37 @@ ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int 
     const int es = dtype == DT_BF16 ? 2 : 4;
     const int vec16 = 16 / es;
     if (inner == 1) {
-        // rows that do not all start on 16-byte boundaries: read in chunks all the same, except where
-        // they are so short that one element per lane is as good
         pl.unaligned = !(x_aligned && red % vec16 == 0);
-        pl.vec = pl.unaligned && red <= kShortRowChunks ? 1 : vec16;
-        const long long nch = red / pl.vec;
-        if (nch <= kShortRowChunks) {              // very short rows: g lanes each, at most four chunks per lane
+        pl.vec = red < vec16 ? 1 : vec16;
+        const long long all = (red + pl.vec - 1) / pl.vec;
+        const bool few = outer <= 256 || (outer < target_workgroups(dtype) && all >= 2 * kHeldWorkgroup);
+        if (all <= kHeldMost) {
+            // The fewest lanes that hold the row: with two chunks each, so that short rows are read in pieces of 128 bytes, from eight lanes on
+            // with four (fp32 rows of 64 elements 50 us on four lanes, 44 on eight; bf16 of 520 47 on 32 lanes, 72 on 64).
             int g = 1;
-            while (4 * g < nch) g *= 2;
+            if (all > kHeldWorkgroup) g = few ? 1024 : 512;
+            else if (all > kHeldWave) g = 256;
+            else if (pl.vec > 1) while ((all <= 16 ? 2 : 4) * g < all && g < 64) g *= 2;
             pl.group = g;
+            pl.held = true;
             pl.segs = 1;
-            pl.per_seg = (int)nch;
+            pl.per_seg = (int)((all + g - 1) / g);
             pl.tiles_i = 1;
-            pl.blocks = (outer + 256 / g - 1) / (256 / g);
+            pl.blocks = g > 64 ? outer : (outer + 256 / g - 1) / (256 / g);
             pl.partial_elems = 0;
             return pl;
         }
-        pl.group = nch <= 64 * 8 ? 64 : 256;       // short rows: one wave each
+        const long long nch = red / pl.vec;
+        pl.group = 256;
         pl.segs = 1;
-        if (pl.group == 256 && outer < target_workgroups(dtype)) {
+        if (outer < target_workgroups(dtype)) {
             const long long want = (target_workgroups(dtype) + outer - 1) / outer;
             const long long most = nch / (256 * 8) > 0 ? nch / (256 * 8) : 1;   // eight sweeps per segment at least
             pl.segs = (int)(want < most ? want : most);
         }
         pl.per_seg = (int)((nch + pl.segs - 1) / pl.segs);
         pl.segs = (int)((nch + pl.per_seg - 1) / pl.per_seg);
-        const long long units = outer * pl.segs, per_wg = 256 / pl.group;
-        pl.blocks = (units + per_wg - 1) / per_wg;
+        pl.blocks = outer * pl.segs;
         pl.tiles_i = 1;
     } else if (red * inner <= kTinyBlock) {
         // several outer indices per workgroup; group = -1 marks this kernel
@@ -829,20 +930,52 @@ ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int 
     return pl;
 }
 
+namespace {
+
+template <bool BF16, int VEC, int FORM, int G, int U = 8>
+void launch_held(const ReducePlan& pl, const void* X, void* out, int* idx, long long outer, int red, hipStream_t s)
+{
+    if (pl.per_seg != U) {
+        if constexpr (U > (G == 512 ? 5 : G > 64 ? 3 : 1)) launch_held<BF16, VEC, FORM, G, U - 1>(pl, X, out, idx, outer, red, s);
+        return;
+    }
+    int lg = 0;
+    while ((1 << lg) < pl.group) ++lg;
+    hipLaunchKernelGGL((reduce_max_held_rows_kernel<BF16, VEC, FORM, U, G>), dim3((unsigned int)pl.blocks), dim3(G > 64 ? G : 256), 0, s, X, out, idx,
+                       outer, red, lg);
+}
+
+template <bool BF16>
+void launch_held(const ReducePlan& pl, const void* X, void* out, int* idx, long long outer, int red, hipStream_t s)
+{
+    constexpr int VEC = Elem<BF16>::VEC, OFF = BF16 ? LEAD : ANY;
+    if (pl.vec == 1) launch_held<BF16, 1, ALIGNED, 64, VEC - 1>(pl, X, out, idx, outer, red, s);
+    else if (pl.group <= 64) {
+        if (pl.unaligned) launch_held<BF16, VEC, ANY, 64>(pl, X, out, idx, outer, red, s);
+        else launch_held<BF16, VEC, ALIGNED, 64>(pl, X, out, idx, outer, red, s);
+    } else if (pl.group == 256) {
+        if (pl.unaligned) launch_held<BF16, VEC, OFF, 256>(pl, X, out, idx, outer, red, s);
+        else launch_held<BF16, VEC, ALIGNED, 256>(pl, X, out, idx, outer, red, s);
+    } else if (pl.group == 512) {
+        if (pl.unaligned) launch_held<BF16, VEC, OFF, 512, 16>(pl, X, out, idx, outer, red, s);
+        else launch_held<BF16, VEC, ALIGNED, 512, 16>(pl, X, out, idx, outer, red, s);
+    } else {
+        if (pl.unaligned) launch_held<BF16, VEC, OFF, 1024>(pl, X, out, idx, outer, red, s);
+        else launch_held<BF16, VEC, ALIGNED, 1024>(pl, X, out, idx, outer, red, s);
+    }
+}
+
+}  // namespace
+
 hipError_t launch_reduce_max(const ReducePlan& pl, const void* X, void* out, int* idx, float* pv, int* pi,
                              long long outer, long long red, long long inner, int dtype, hipStream_t s)
 {
     if (pl.blocks <= 0 || pl.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned int)pl.blocks), block(256);
     const bool bf = dtype == DT_BF16;
-    if (inner == 1 && pl.group < 64) {
-        int lg = 0;
-        while ((1 << lg) < pl.group) ++lg;
-#define PGK_SHORT(BF, VEC, UN) \
-    hipLaunchKernelGGL((reduce_max_short_rows_kernel<BF, VEC, UN>), grid, block, 0, s, X, out, idx, outer, (int)red, lg)
-        if (bf) { if (pl.vec == 1) PGK_SHORT(true, 1, false); else if (pl.unaligned) PGK_SHORT(true, 8, true); else PGK_SHORT(true, 8, false); }
-        else { if (pl.vec == 1) PGK_SHORT(false, 1, false); else if (pl.unaligned) PGK_SHORT(false, 4, true); else PGK_SHORT(false, 4, false); }
-#undef PGK_SHORT
+    if (pl.held) {
+        if (bf) launch_held<true>(pl, X, out, idx, outer, (int)red, s);
+        else launch_held<false>(pl, X, out, idx, outer, (int)red, s);
     } else if (inner > 1 && pl.group <= -256) {
 #define PGK_BLOCK(BF, NT) \
     hipLaunchKernelGGL((reduce_max_block_kernel<BF, NT>), grid, dim3(NT), 0, s, X, out, idx, pv, pi, (int)red, (int)inner, pl.segs, pl.per_seg, pl.tiles_i)
@@ -856,15 +989,13 @@ hipError_t launch_reduce_max(const ReducePlan& pl, const void* X, void* out, int
         if (bf) hipLaunchKernelGGL(reduce_max_small_inner_kernel<true>, grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, (int)inner, pl.segs, pl.per_seg);
         else hipLaunchKernelGGL(reduce_max_small_inner_kernel<false>, grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, (int)inner, pl.segs, pl.per_seg);
     } else if (inner == 1) {
-#define PGK_ROWS(BF, LEAD, G) \
-    hipLaunchKernelGGL((reduce_max_rows_kernel<BF, LEAD, G>), grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, pl.segs, pl.per_seg)
-        if (bf) {
-            if (pl.unaligned) { if (pl.group == 64) PGK_ROWS(true, true, 64); else PGK_ROWS(true, true, 256); }
-            else { if (pl.group == 64) PGK_ROWS(true, false, 64); else PGK_ROWS(true, false, 256); }
-        } else {
-            if (pl.unaligned) { if (pl.group == 64) PGK_ROWS(false, true, 64); else PGK_ROWS(false, true, 256); }
-            else { if (pl.group == 64) PGK_ROWS(false, false, 64); else PGK_ROWS(false, false, 256); }
-        }
+        // (sweeps at a time: two, but fp32 rows in one piece four -- with 512 workgroups two are too few loads under way: [512, 200000] 70 us, 59;
+        // cut into more of them fp32 [396, 1077376] 250 us with two, 274 with four, bf16 [1195, 101129] 40.7 and 41.4, with 2048 threads a CU)
+#define PGK_ROWS(BF, ENDS, N) \
+    hipLaunchKernelGGL((reduce_max_rows_kernel<BF, ENDS, N>), grid, block, 0, s, X, out, idx, pv, pi, (int)red, pl.segs, pl.per_seg)
+        if (bf) { if (pl.unaligned) PGK_ROWS(true, true, 2); else PGK_ROWS(true, false, 2); }
+        else if (pl.segs > 1) { if (pl.unaligned) PGK_ROWS(false, true, 2); else PGK_ROWS(false, false, 2); }
+        else { if (pl.unaligned) PGK_ROWS(false, true, 4); else PGK_ROWS(false, false, 4); }
 #undef PGK_ROWS
     } else {
 #define PGK_COLS(BF, VEC, UN) \
