@@ -630,13 +630,13 @@ FusedPlan plan_fused(bool aligned, int64_t M, int64_t N, int64_t K, int64_t batc
 }
 
 // K tiles of a workgroup (one slice): those of the main loop, and those at its end that are loaded with waits and run-time
-// checks (the loop goes in trips of six; the last two load nothing any more).  whole: the last K tile is no edge.
+// checks (the loop goes in trips of six, or of two; the last two load nothing any more).  whole: the last K tile is no edge.
 struct LoopTiles { double steady, tail; };
 
-LoopTiles loop_tiles(int64_t K, int count, bool whole)
+LoopTiles loop_tiles(int64_t K, int count, bool whole, int trip)
 {
     const int64_t n = ((K + 63) / 64 + count - 1) / count, m = n - (whole ? 0 : 1);
-    const int64_t rest = n - (m > 7 ? (m - 2) / 6 * 6 : 0);
+    const int64_t rest = n - (m > trip + 1 ? (m - 2) / trip * trip : 0);
     return {(double)(n - std::max<int64_t>(rest - 2, 0)), (double)std::max<int64_t>(rest - 2, 0)};
 }
 
@@ -652,6 +652,9 @@ LoopTiles loop_tiles(int64_t K, int count, bool whole)
 // Copied first / through registers: 512 x 50257 x 768 83 / 70 us, 128 x 256 x 32371, 16 entries, 228 / 96, 9800 x 12713 x 64
 // 139 / 89, 1024 x 2048 x 255 (B transposed) 14 / 11; 2048 x 2047 x 2048 34 / 46, 4096 x 4095 x 4095 132 / 213, 16 x [1501 x 1501 x 1501] 182 / 237,
 // 832 x 1440 x 379 (B transposed), 32 entries, 78 / 120, 960 x 3433 x 257, 16 entries, 99 / 120.
+// The fit is of main loops in trips of six; all but the large tile's with A through registers now go in trips of two, which spares some of the tiles at their
+// end.  From seven K tiles on that is counted, with a margin for what has not been fitted: 70 drawn products whose choice it turns to registers
+// are 1.05 to 1.44 times as fast, 1.20 in the mean (435 x 37339 x 429, B transposed, 73 copied, 56 through registers; 7616 x 53 x 1225 37 and 26).
 bool reg_copies_pay(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, bool b_trans, Slices slices)
 {
     // a round: fixed + steady and tail K tiles; the last one: with one workgroup on its busiest CU, and with two, as a share
@@ -692,12 +695,16 @@ bool reg_copies_pay(int64_t M, int64_t N, int64_t K, int64_t batch, int dtype, b
     const double partials = 0.6 * out;                                     // (a slice's, written and read)
 
     const double loop = reg.kind == pgk::TILE_LARGE ? (odd.a ? 1.09 : 1.0) : b_trans ? 1.13 : odd.a && odd.b ? 1.11 : 1.0;
-    const double by_reg = time(reg_cost(reg.kind), loop_tiles(K, reg.count, false), reg.rounds, loop) +
-                          in * (0.17 * (double)M + 0.14 * (double)N) + (N % 8 != 0 ? 0.17 : 0.14) * out + (reg.count > 1 ? reg.count * partials : 0.0);
-    const double by_copies = time(packed_cost(packed.kind), loop_tiles(k, packed.count, k % 64 == 0), packed.rounds, 1.0) +
+    auto by_reg = [&](int trip) {
+        return time(reg_cost(reg.kind), loop_tiles(K, reg.count, false, trip), reg.rounds, loop) +
+               in * (0.17 * (double)M + 0.14 * (double)N) + (N % 8 != 0 ? 0.17 : 0.14) * out + (reg.count > 1 ? reg.count * partials : 0.0);
+    };
+    const double by_copies = time(packed_cost(packed.kind), loop_tiles(k, packed.count, k % 64 == 0, 6), packed.rounds, 1.0) +
                              in * ((odd.a ? 0.41 * (double)M : 0.0) + (b_trans ? 0.39 : 0.34) * (double)N) +
                              (odd.a ? 4.8 : 2.2) + (N % 8 != 0 ? 0.20 : 0.06) * out + (packed.count > 1 ? packed.count * partials : 0.0);
-    return by_reg < by_copies;
+    if (by_reg(6) < by_copies) return true;
+    const bool long_enough = (K + 63) / 64 >= 7 * (int64_t)reg.count;
+    return long_enough && !(reg.kind == pgk::TILE_LARGE && odd.a) && by_reg(2) < 0.95 * by_copies;
 }
 
 // ---- The caller's workspace.  Everything a call needs beyond its inputs and outputs is cut from

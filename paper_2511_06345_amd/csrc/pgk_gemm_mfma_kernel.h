@@ -103,7 +103,7 @@ struct MfmaCfgBt : MfmaCfgBase<true, BF16_, BM_, BN_, BK_, WGM_, WGN_, A_STAGES_
 // ... bf16 with A and / or B copied through registers
 template <bool BT_, int BM_, int BN_, int BK_, int WGM_, int WGN_, int A_STAGES_, int WAVES_PER_SIMD_, bool REG_A_, bool REG_B_>
 struct MfmaCfgReg : MfmaCfgBase<BT_, true, BM_, BN_, BK_, WGM_, WGN_, A_STAGES_, WAVES_PER_SIMD_, REG_A_, REG_B_> {
-    static_assert(A_STAGES_ == 3 || (REG_A_ && REG_B_), "the two-deep A ring's copies are interleaved with B's");
+    static_assert(A_STAGES_ == 3 || REG_B_, "beside a two-deep A ring direct copies of B are issued a tile later than the prologue here expects");
 };
 
 // A tile: rows of CPR chunks; 16 consecutive rows read the same logical chunk
@@ -728,7 +728,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_SIMD) void gemm_mfma_kernel
     // whole is read anywhere and cleared (zero_k_tail).
     // The loads and LDS writes take issue slots and the rows off the 16-byte grid extra requests: a K tile of the large tile
     // 1.5 us in the loop instead of 1.2, of the small one 1.2 instead of 0.85, and 2.4 and 2.3 among the last ones, which are loaded under
-    // run-time checks; what they spare is a padded copy of the operand (512 x 50257 x 768 83 -> 70 us).
+    // run-time checks; what they spare is a padded copy of the operand (512 x 50257 x 768 83 -> 67 us).
     u32x4 ra[Cfg::REG_A ? Cfg::A_CPW : 1], rb[Cfg::REG_B ? Cfg::B_CPW : 1];
     const unsigned char *ra_base = Ag, *rb_base = Bg;         // where the tile in registers starts
     auto past_end = [](const unsigned char* base, const unsigned char* end, unsigned int off) __attribute__((always_inline)) -> long long {

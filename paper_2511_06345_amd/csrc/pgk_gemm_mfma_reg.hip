@@ -6,18 +6,22 @@
 namespace pgk {
 
 namespace {
-// The large tile has registers for one operand's pieces beside its accumulators, and not quite: of 256 three spill
-// with B's pieces, six in the convolution's form and sixteen with A's (scratch of 16, 28 and 68 bytes a lane).
+// The large tile has registers for one operand's pieces beside its accumulators, and not quite: of 256 five spill
+// with B's pieces, eight in the convolution's form and sixteen with A's (scratch of 24, 36 and 68 bytes a lane).
 // The small tile takes both operands that way, also where only one needs it; the half tiles have no such
 // instances, as the small one is as fast or faster on what they are planned for (reg_tile_kind).
+// With B through registers the A ring is two deep: the main loop then goes in trips of two K tiles instead of six (the rings'
+// common period), which leaves at most four tiles to the loop's end, where loads are checked at run time, not eight.  The third stage gave A's
+// direct copies more time, which does not show.  512 x 50257 x 768 70.9 -> 67 us, x 512 60.5 -> 55, 128 x 128 x 5443, 10 entries, 30.7 -> 22, 1000 x
+// 2048 x 257 (B transposed) 16.0 -> 14.3, convolution [8, 512, 4096] x [512, 512, 3] 64 -> 61; 92 products and 14 convolutions: none over 1 % slower.
 template <bool REG_A, bool REG_B>
-using RegLarge = MfmaCfgReg<false, 256, 256, 64, 4, 2, 3, 2, REG_A, REG_B>;
+using RegLarge = MfmaCfgReg<false, 256, 256, 64, 4, 2, REG_B ? 2 : 3, 2, REG_A, REG_B>;
 template <bool BT>
-using RegSmall = MfmaCfgReg<BT, 128, 128, 64, 2, 2, 3, 2, true, true>;
+using RegSmall = MfmaCfgReg<BT, 128, 128, 64, 2, 2, 2, 2, true, true>;
 // (a convolution's weights are regrouped and always copied directly)
-using ConvSmall = MfmaCfgReg<false, 128, 128, 64, 2, 2, 3, 2, false, true>;
-using ConvTall = MfmaCfgReg<false, 256, 128, 64, 4, 2, 3, 2, false, true>;
-using ConvWide = MfmaCfgReg<false, 128, 256, 64, 2, 4, 3, 2, false, true>;
+using ConvSmall = MfmaCfgReg<false, 128, 128, 64, 2, 2, 2, 2, false, true>;
+using ConvTall = MfmaCfgReg<false, 256, 128, 64, 4, 2, 2, 2, false, true>;
+using ConvWide = MfmaCfgReg<false, 128, 256, 64, 2, 4, 2, 2, false, true>;
 
 }  // namespace
 
