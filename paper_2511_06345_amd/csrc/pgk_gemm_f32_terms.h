@@ -519,7 +519,8 @@ __device__ __forceinline__ void terms_tile(const GemmArgs& p, const int out_mode
     // then of B's (of column pairs both columns at one k); OPS operations of two or three
     // instructions each take it apart.
     unsigned int lost = 0u;                       // what the values leave after two terms, or-ed together
-    unsigned int pa[A_CH][3][A_KV / 2];           // the packed terms
+    // the packed terms (of whole chunks as vectors: as single registers the loop had four waits more)
+    typename std::conditional<A_KV == 8, u32x4, unsigned int[A_KV / 2]>::type pa[A_CH][3];
     u32x4 pb[B_CH][3];
     constexpr int A_PAIRS = A_KV / 2, A_PARTS = A_CH * A_PAIRS, PARTS = A_PARTS + 4 * B_CH, OPS = 5;
     auto bits = [](float x) __attribute__((always_inline)) { return __builtin_bit_cast(unsigned int, x); };
@@ -571,7 +572,7 @@ __device__ __forceinline__ void terms_tile(const GemmArgs& p, const int out_mode
 #pragma unroll
             for (int t = 0; t < A_CH; ++t) {
                 unsigned char* const to = lds_a + q * Cfg::A_PLANE + wpos_a + kOddRow * t;
-                if constexpr (A_KV == 8) *(__attribute__((address_space(3))) u32x4*)PGK_LDS(to) = u32x4{pa[t][q][0], pa[t][q][1], pa[t][q][2], pa[t][q][3]};
+                if constexpr (A_KV == 8) *(__attribute__((address_space(3))) u32x4*)PGK_LDS(to) = pa[t][q];
                 else if constexpr (A_KV == 4) *(__attribute__((address_space(3))) u32x2*)PGK_LDS(to) = u32x2{pa[t][q][0], pa[t][q][1]};
                 else *(__attribute__((address_space(3))) unsigned int*)PGK_LDS(to) = pa[t][q][0];
             }
