@@ -989,12 +989,14 @@ hipError_t launch_reduce_max(const ReducePlan& pl, const void* X, void* out, int
         if (bf) hipLaunchKernelGGL(reduce_max_small_inner_kernel<true>, grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, (int)inner, pl.segs, pl.per_seg);
         else hipLaunchKernelGGL(reduce_max_small_inner_kernel<false>, grid, block, 0, s, X, out, idx, pv, pi, outer, (int)red, (int)inner, pl.segs, pl.per_seg);
     } else if (inner == 1) {
-        // (sweeps at a time: two, but fp32 rows in one piece four -- with 512 workgroups two are too few loads under way: [512, 200000] 70 us, 59;
-        // cut into more of them fp32 [396, 1077376] 250 us with two, 274 with four, bf16 [1195, 101129] 40.7 and 41.4, with 2048 threads a CU)
+        // (sweeps at a time: two, but of fp32 four with at most two workgroups a CU, where two are too few loads under way -- [512, 200000]
+        // 70 us, 59, [16, 2^24] 175 and 151 --, and with more than four; between, [396, 1077376] takes 250 us with two, 274 with
+        // four.  bf16 [1195, 101129] 40.7 and 41.4)
+        const bool two = pl.blocks > 512 && pl.blocks <= 1024;
 #define PGK_ROWS(BF, ENDS, N) \
     hipLaunchKernelGGL((reduce_max_rows_kernel<BF, ENDS, N>), grid, block, 0, s, X, out, idx, pv, pi, (int)red, pl.segs, pl.per_seg)
         if (bf) { if (pl.unaligned) PGK_ROWS(true, true, 2); else PGK_ROWS(true, false, 2); }
-        else if (pl.segs > 1) { if (pl.unaligned) PGK_ROWS(false, true, 2); else PGK_ROWS(false, false, 2); }
+        else if (two) { if (pl.unaligned) PGK_ROWS(false, true, 2); else PGK_ROWS(false, false, 2); }
         else { if (pl.unaligned) PGK_ROWS(false, true, 4); else PGK_ROWS(false, false, 4); }
 #undef PGK_ROWS
     } else {
