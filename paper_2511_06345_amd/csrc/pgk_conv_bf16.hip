@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "pgk_device.h"
@@ -33,6 +34,7 @@ namespace {
 constexpr int kBlock = 32;                 // channels per block
 constexpr int kCols = 128;                 // positions per tile
 constexpr int kGroups = 3;                 // of 128 rows of LDS, at most
+constexpr int kMostLds = 80 * 1024;        // bytes of LDS per workgroup, at most (taps_at_a_time)
 
 struct ConvArgs {
     const unsigned short* x;
@@ -301,9 +303,18 @@ template <int BM, int GROUPS, bool PARTS>
 hipError_t launch_tile(const ConvArgs& p, unsigned int wgs, size_t lds, hipStream_t s)
 {
     if (lds > 64 * 1024) {
-        // (more than the runtime grants unasked)
-        const hipError_t e = hipFuncSetAttribute((const void*)conv_bf16_kernel<BM, GROUPS, PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        // More than the runtime grants unasked.  The grant is the kernel's and not the call's, so it is the most that any call takes: a
+        // thread with a smaller convolution must not lower it between another one's grant and its launch.  Once per device.
+        static std::atomic<unsigned long long> granted{0};
+        int device = 0;
+        hipError_t e = hipGetDevice(&device);
         if (e != hipSuccess) return e;
+        const unsigned long long bit = device < 64 ? 1ull << device : 0;
+        if (!(granted.load(std::memory_order_acquire) & bit)) {
+            e = hipFuncSetAttribute((const void*)conv_bf16_kernel<BM, GROUPS, PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize, kMostLds);
+            if (e != hipSuccess) return e;
+            granted.fetch_or(bit, std::memory_order_release);
+        }
     }
     hipLaunchKernelGGL((conv_bf16_kernel<BM, GROUPS, PARTS>), dim3(wgs), dim3(256), lds, s, p);
     return hipGetLastError();
@@ -348,7 +359,7 @@ hipError_t launch_conv_bf16(const void* x, const void* wr, const float* bias, vo
                             int Kw, int stride, int pad, int dil, int Lout, int rows, int act, hipStream_t s)
 {
     const size_t lds = conv_bf16_lds(Kw, stride, dil, L, rows);      // (128 rows of input and more: the epilogue's pieces fit)
-    if (!lds || cin_pad % kBlock != 0 || cin_pad < Cin || (uintptr_t)wr % 16 != 0) return hipErrorInvalidValue;
+    if (!lds || lds > (size_t)kMostLds || cin_pad % kBlock != 0 || cin_pad < Cin || (uintptr_t)wr % 16 != 0) return hipErrorInvalidValue;
     ConvArgs p{};
     p.x = (const unsigned short*)x; p.w = (const unsigned short*)wr; p.bias = bias; p.y = (unsigned short*)y;
     p.Cin = Cin; p.cin_pad = cin_pad; p.L = L; p.Cout = Cout; p.Kw = Kw; p.stride = stride; p.pad = pad; p.dil = dil; p.Lout = Lout; p.act = act;

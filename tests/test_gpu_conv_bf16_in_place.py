@@ -112,3 +112,33 @@ def test_replays_of_a_graph(pgk):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, pgk.conv1d(x, w, None, RELU, 2, 2, 1))
+
+
+def test_threads_with_different_needs_of_lds(pgk):
+    """Calls that share a kernel and differ in the LDS they take (6 and 7 taps of 64 rows: 65 and 73 KB), from several threads."""
+    import threading
+
+    import torch
+    x = torch.randint(-2, 3, (8, 384, 9000), device="cuda").bfloat16()
+    weights = [torch.randint(-2, 3, (64, 384, Kw), device="cuda").bfloat16() for Kw in (6, 7)]
+    want = [pgk.conv1d(x, w, None, NONE, 1, 0, 1) for w in weights]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(first):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for k in range(40):
+                    which = (first + k) % 2
+                    y = pgk.conv1d(x, weights[which], None, NONE, 1, 0, 1)
+                    torch.cuda.current_stream().synchronize()
+                    if not torch.equal(y, want[which]):
+                        wrong.append((first, k))
+        except Exception as e:
+            wrong.append(e)
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong[:3]
