@@ -783,8 +783,62 @@ constexpr long long kHeldWave = 512, kHeldWorkgroup = 2048, kHeldMost = 8192;
 constexpr long long kSmallInner = 64;             // inner dimensions up to this: the flattened-sweep kernel
 constexpr long long kTinyBlock = 128;             // red x inner up to this: several outer indices per workgroup
 
+// Strided reductions (inner > 1) that reduce_max_block_kernel leaves to the kernels before it
+ReducePlan plan_strided(long long outer, long long red, long long inner, int dtype, bool x_aligned)
+{
+    ReducePlan pl{};
+    const int vec16 = dtype == DT_BF16 ? 8 : 4;
+    if (inner <= kSmallInner) {
+        // one wave per (outer index, segment); group = 0 marks this kernel
+        pl.vec = 1;
+        pl.group = 0;
+        pl.tiles_i = 1;
+        pl.segs = 1;
+        const long long waves = 4LL * target_workgroups(dtype);
+        if (outer < waves) {
+            const long long want = (waves + outer - 1) / outer;
+            const long long sweep = 64 / inner;                                  // r per sweep
+            const long long most = red / (8 * sweep) > 0 ? red / (8 * sweep) : 1;   // eight sweeps per segment at least
+            pl.segs = (int)(want < most ? want : most);
+        }
+        pl.per_seg = (int)((red + pl.segs - 1) / pl.segs);
+        pl.segs = (int)((red + pl.per_seg - 1) / pl.per_seg);
+        pl.blocks = (outer * pl.segs + 3) / 4;
+    } else {
+        pl.unaligned = !(x_aligned && inner % vec16 == 0);
+        // One element per load for unaligned rows while the problem is small: the chip is not full then, and
+        // 64 VEC positions per workgroup leave fewer and longer ones (fp32 [53, 67, 845] 10.1 us, in chunks 15.3;
+        // bf16 [580, 101, 83] 10.0 and 15.4); bf16 also with few positions per row, where most lanes have
+        // no chunk ([484, 279, 102] 19.3 and 22.9).  Of 20000 unaligned shapes 0.8 % stay more than
+        // 5 % behind one element per load everywhere, without these lines 5 %; the mean is 1.25 (bf16) and 1.38
+        // (fp32) times as fast as with one element everywhere.
+        const long double elements = (long double)outer * red * inner;
+        const bool single = pl.unaligned && (elements < (dtype == DT_BF16 ? 1.0e7L : 4.0e6L) ||
+                                             (dtype == DT_BF16 && inner <= 128 && red < 512));
+        pl.vec = single ? 1 : vec16;
+        pl.group = 256;
+        pl.tiles_i = (int)((inner + 64 * pl.vec - 1) / (64 * pl.vec));
+        const long long wg0 = outer * pl.tiles_i;
+        pl.segs = 1;
+        if (wg0 < target_workgroups(dtype)) {
+            const long long want = (target_workgroups(dtype) + wg0 - 1) / wg0;
+            // eight r per wave at least; unaligned chunks sixteen, fp32 ones (less work each) thirty-two, else the second pass
+            // costs more than the segments give (fp32 [42, 72, 1901]: 13.7 us in one pass, 18.5 in two; [11, 135, 2959] 10.5
+            // and 15.8; bf16 [59, 254, 438], 26.9 and 16.0)
+            const long long least = !pl.unaligned || single ? 32 : dtype == DT_BF16 ? 64 : 128;
+            const long long most = red / least > 0 ? red / least : 1;
+            pl.segs = (int)(want < most ? want : most);
+        }
+        pl.per_seg = (int)((red + pl.segs - 1) / pl.segs);
+        pl.segs = (int)((red + pl.per_seg - 1) / pl.per_seg);
+        pl.blocks = wg0 * pl.segs;
+    }
+    pl.partial_elems = pl.segs > 1 ? (size_t)outer * pl.segs * (size_t)inner : 0;
+    return pl;
+}
+
 // The workgroups and the periods of reduce_max_block_kernel (the plan's `group` is minus its threads, `tiles_i` the r of a period),
-// or false where another kernel is faster:
+// where that kernel is the faster one.  It is not for
 //  * blocks of at most two periods with many of them: a workgroup each is mostly its own start and end (bf16 [3000, 300, 9] 17.5 us
 //    here, 16 with a wave each; [20000, 40, 20] 47 and 20);
 //  * inner positions enough for the lanes of the strided kernel (bf16 [64, 4096, 1024] 87.5 and 88.5, 1536 149 and 132; fp32
@@ -793,33 +847,37 @@ constexpr long long kTinyBlock = 128;             // red x inner up to this: sev
 // A block of at most kOneLaunchBytes under too few outer indices: 1024 threads and no second pass, which costs more
 // than the chip's idle part gives (fp32 [29, 3712, 22], 327 KB, 12.9 us so, 15.5 in two launches; [16, 48054, 5], 961 KB, 25 and 15.8).
 // Else 512 workgroups, or 768 or 1024 where these are a whole number for every CU and 512 are not; segments of four periods at
-// least, and never more of them than the kernels before this one took, so that the workspace a call needs has not grown.
+// least, and never more of them than the kernels before this one take, so that no call needs more workspace than with those. Where they take
+// fewer than 512 workgroups would be, they are the faster ones by themselves: of 70 such shapes 0.64 to 1.08 of the time here with the segments
+// they take, 0.7 on average (fp32 [240, 218, 479] none, bf16 [5, 4283, 282] 41: 11.1 us, 14.5 here), and no slower than with more of them here.
 constexpr long long kOneLaunchBytes = 256 << 10;
 
-bool plan_block(ReducePlan& pl, long long outer, long long red, long long inner, int dtype)
+// pl: the plan of the kernels before this one, left as it is where they are faster.
+void plan_block(ReducePlan& pl, long long outer, long long red, long long inner, int dtype)
 {
     const long long es = dtype == DT_BF16 ? 2 : 4, vec = 16 / es;
     const bool one_launch = outer < 512 && red * inner * es <= kOneLaunchBytes && inner <= 512 * vec && (inner <= 128 * vec || red >= 64);
-    if (!one_launch && inner > 128 * vec) return false;
-    if (outer >= 1024 && red * inner <= 2 * 256 * vec) return false;
+    if (!one_launch && inner > 128 * vec) return;
+    if (outer >= 1024 && red * inner <= 2 * 256 * vec) return;
     const long long nt = one_launch ? 1024 : 256;
     long long R = nt * vec / inner;
     const long long common = (inner & -inner) < vec ? (inner & -inner) : vec;      // (greatest common divisor: vec is a power of two)
     if (R >= 4 * (vec / common)) R -= R % (vec / common);
-    if (!one_launch && inner > 64 * vec && 4 * R * inner < 3 * nt * vec) return false;
+    if (!one_launch && inner > 64 * vec && 4 * R * inner < 3 * nt * vec) return;
     long long segs = 1;
     if (!one_launch && outer < 512) {
-        const long long per_outer = (target_workgroups(dtype) * (inner <= kSmallInner ? 4 : 1) + outer - 1) / outer;
-        const long long former = inner <= 64 * vec ? per_outer : (per_outer + 1) / 2;
-        const long long most = red / (4 * R) < former ? red / (4 * R) : former;
+        const long long periods = red / (4 * R), wanted = 512 / outer < periods ? 512 / outer : periods;
+        if (wanted > pl.segs) return;
+        const long long most = periods < pl.segs ? periods : pl.segs;
         double best = 0.0;
         for (long long target = 512; target <= 1024; target += 256) {
             const long long n = target / outer < most ? target / outer : most;
             const double filled = (double)(n * outer) / (double)target;
             if (n >= 1 && filled > best + 0.05) { best = filled; segs = n; }
         }
-        if (inner > 64 * vec && segs == former && segs * outer < 448) return false;
+        if (inner > 64 * vec && segs == pl.segs && segs * outer < 448) return;
     }
+    pl.unaligned = false;
     pl.vec = (int)vec;
     pl.group = (int)-nt;
     pl.per_seg = (int)((red + segs - 1) / segs);
@@ -827,7 +885,6 @@ bool plan_block(ReducePlan& pl, long long outer, long long red, long long inner,
     pl.tiles_i = (int)(R < pl.per_seg ? R : pl.per_seg);
     pl.blocks = outer * pl.segs;
     pl.partial_elems = pl.segs > 1 ? (size_t)outer * pl.segs * (size_t)inner : 0;
-    return true;
 }
 
 }  // namespace
@@ -879,52 +936,10 @@ ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int 
         pl.per_seg = (int)red;
         const long long q = 256 / (red * inner);
         pl.blocks = (outer + q - 1) / q;
-    } else if (plan_block(pl, outer, red, inner, dtype)) {
-        return pl;
-    } else if (inner <= kSmallInner) {
-        // one wave per (outer index, segment); group = 0 marks this kernel
-        pl.vec = 1;
-        pl.group = 0;
-        pl.tiles_i = 1;
-        pl.segs = 1;
-        const long long waves = 4LL * target_workgroups(dtype);
-        if (outer < waves) {
-            const long long want = (waves + outer - 1) / outer;
-            const long long sweep = 64 / inner;                                  // r per sweep
-            const long long most = red / (8 * sweep) > 0 ? red / (8 * sweep) : 1;   // eight sweeps per segment at least
-            pl.segs = (int)(want < most ? want : most);
-        }
-        pl.per_seg = (int)((red + pl.segs - 1) / pl.segs);
-        pl.segs = (int)((red + pl.per_seg - 1) / pl.per_seg);
-        pl.blocks = (outer * pl.segs + 3) / 4;
     } else {
-        pl.unaligned = !(x_aligned && inner % vec16 == 0);
-        // One element per load for unaligned rows while the problem is small: the chip is not full then, and
-        // 64 VEC positions per workgroup leave fewer and longer ones (fp32 [53, 67, 845] 10.1 us, in chunks 15.3;
-        // bf16 [580, 101, 83] 10.0 and 15.4); bf16 also with few positions per row, where most lanes have
-        // no chunk ([484, 279, 102] 19.3 and 22.9).  Of 20000 unaligned shapes 0.8 % stay more than
-        // 5 % behind one element per load everywhere, without these lines 5 %; the mean is 1.25 (bf16) and 1.38
-        // (fp32) times as fast as with one element everywhere.
-        const long double elements = (long double)outer * red * inner;
-        const bool single = pl.unaligned && (elements < (dtype == DT_BF16 ? 1.0e7L : 4.0e6L) ||
-                                             (dtype == DT_BF16 && inner <= 128 && red < 512));
-        pl.vec = single ? 1 : vec16;
-        pl.group = 256;
-        pl.tiles_i = (int)((inner + 64 * pl.vec - 1) / (64 * pl.vec));
-        const long long wg0 = outer * pl.tiles_i;
-        pl.segs = 1;
-        if (wg0 < target_workgroups(dtype)) {
-            const long long want = (target_workgroups(dtype) + wg0 - 1) / wg0;
-            // eight r per wave at least; unaligned chunks sixteen, fp32 ones (less work each) thirty-two, else the second pass
-            // costs more than the segments give (fp32 [42, 72, 1901]: 13.7 us in one pass, 18.5 in two; [11, 135, 2959] 10.5
-            // and 15.8; bf16 [59, 254, 438], 26.9 and 16.0)
-            const long long least = !pl.unaligned || single ? 32 : dtype == DT_BF16 ? 64 : 128;
-            const long long most = red / least > 0 ? red / least : 1;
-            pl.segs = (int)(want < most ? want : most);
-        }
-        pl.per_seg = (int)((red + pl.segs - 1) / pl.segs);
-        pl.segs = (int)((red + pl.per_seg - 1) / pl.per_seg);
-        pl.blocks = wg0 * pl.segs;
+        pl = plan_strided(outer, red, inner, dtype, x_aligned);
+        plan_block(pl, outer, red, inner, dtype);
+        return pl;
     }
     pl.partial_elems = pl.segs > 1 ? (size_t)outer * pl.segs * (size_t)inner : 0;
     return pl;

@@ -1,9 +1,11 @@
 """The C-ABI library without a GPU: it loads, exports every declared symbol, and
 rejects bad arguments on the host before any device work (no compute calls here)."""
 import ctypes
+import math
 
 import numpy as np
 import os
+import random
 import re
 
 import pytest
@@ -274,6 +276,39 @@ def test_reduce_max_rejects_bad_arguments_on_the_host(lib):
     assert call(outer=16, red=1 << 24, inner=1, ws=0x8000, ws_bytes=need - 8) == WORKSPACE
     assert call(outer=16, red=1 << 24, inner=1, ws=0x8002, ws_bytes=need) == WORKSPACE
     assert q(0, 3, 4, gen.F32) == 0 and q(2, 3, 4, 5) == 0
+
+
+def test_strided_reductions_ask_for_no_more_than_their_segments(lib):
+    """Workspace of a strided reduction: at most the segments that the kernels with lanes along the inner dimension take (a wave, or
+    64 lanes times the load's width, per workgroup), whichever kernel runs, so that a workspace sized for those is always enough."""
+    def segments(outer, red, inner, dtype, aligned):
+        target, vec = (1024, 8) if dtype == gen.BF16 else (512, 4)
+        if red * inner <= 128:
+            return 1
+        if inner <= 64:
+            units, least, target = outer, 8 * (64 // inner), 4 * target
+        else:
+            unaligned = not (aligned and inner % vec == 0)
+            single = unaligned and (outer * red * inner < (1e7 if dtype == gen.BF16 else 4e6) or (dtype == gen.BF16 and inner <= 128 and red < 512))
+            units = outer * -(-inner // (64 * (1 if single else vec)))
+            least = 32 if not unaligned or single else 64 if dtype == gen.BF16 else 128
+        if units >= target:
+            return 1
+        per_seg = -(-red // min(-(-target // units), max(red // least, 1)))
+        return -(-red // per_seg)
+
+    def most(outer, red, inner, dtype):
+        n = max(segments(outer, red, inner, dtype, aligned) for aligned in (False, True))
+        return 8 * outer * inner * n if n > 1 else 0
+
+    q = binding.reduce_max_workspace_bytes
+    assert q(240, 218, 479, gen.F32) == 0 and q(33, 179, 839, gen.BF16) <= 664488 and q(4, 12606, 181, gen.F32) <= 567616
+    rng = random.Random(7)
+    for _ in range(20000):
+        outer, red, inner = (int(math.exp(rng.uniform(0, math.log(top)))) for top in (600, 1 << 20, 4097))
+        for dtype in (gen.F32, gen.BF16):
+            if inner > 1:
+                assert q(outer, red, inner, dtype) <= most(outer, red, inner, dtype), (outer, red, inner, dtype)
 
 
 def test_conv1d_host_arithmetic_and_validation(lib):
