@@ -20,6 +20,7 @@
 // segment results in order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "pgk_device.h"
@@ -838,15 +839,20 @@ ReducePlan plan_strided(long long outer, long long red, long long inner, int dty
 }
 
 // The workgroups and the periods of reduce_max_block_kernel (the plan's `group` is minus its threads, `tiles_i` the r of a period),
-// where that kernel is the faster one.  It is not for
-//  * blocks of at most two periods with many of them: a workgroup each is mostly its own start and end (bf16 [3000, 300, 9] 17.5 us
-//    here, 16 with a wave each; [20000, 40, 20] 47 and 20);
-//  * inner positions enough for the lanes of the strided kernel (bf16 [64, 4096, 1024] 87.5 and 88.5, 1536 149 and 132; fp32
-//    [64, 4096, 512] 83.6 and 82.4), also from one tile of that kernel on where whole r leave more than a quarter of the lanes idle here (bf16 [177, 1088, 721] 77 and
-//    71; [100, 4000, 520] 81 and 104) or the segments it may have are too few workgroups (fp32 [63, 8606, 384] 191 and 153).
-// A block of at most kOneLaunchBytes under too few outer indices: 1024 threads and no second pass, which costs more
-// than the chip's idle part gives (fp32 [29, 3712, 22], 327 KB, 12.9 us so, 15.5 in two launches; [16, 48054, 5], 961 KB, 25 and 15.8).
-// Else 512 workgroups, or 768 or 1024 where these are a whole number for every CU and 512 are not; segments of four periods at
+// where that kernel is the faster one.  What decides it (calls queued one after the other; of 4500 drawn shapes 1409 are more than a twentieth faster than
+// without this kernel, 1.59 times in the mean, five are more than a tenth slower, 0.88 the worst; the figures: the other kernels' time / this one's):
+//  * A workgroup starts, ends and combines its lanes once per block (or segment): many small blocks are not for it.  Of 512 blocks and more
+//    it takes fp32 ones from 14 bytes per block of them on, 64 KB at most ([9015, 359, 7] 0.65, [1436, 3222, 3] 1.37), 256 KB where inner is over 64
+//    ([7361, 20, 207] 0.66, up to 1.66 from there); bf16 ones, which a wave reads element by element, from 2 KB, 8 KB of 1024 and more ([976, 21, 25] 0.67,
+//    [570, 830, 2] 1.52), where lanes of the strided kernel read them 32 KB, and there not if these are mostly at work ([1430, 421, 415] 0.80).
+//  * Fewer blocks of up to 256 KB: 1024 threads a block and no second pass, instead of segments and one.  A launch is 3 us, a block of 50 KB as
+//    long, so the line is at a size of block that grows with all of the input, which the two launches have to read as well (bf16 [249, 461, 63] 2.35, fp32
+//    [5, 8632, 7] 0.58; [77, 2865, 3] 1.2).  Where the other kernels make no segments theirs is one launch too and the faster one throughout
+//    (bf16 [261, 55, 285] 0.45).
+//  * Fewer, larger blocks in segments: two launches either way, from 3 (bf16, inner up to 64) to 36 MB on ([14, 2533, 47] fp32 0.81, [178, 3508, 25]
+//    1.62); with inner over 64 where at most half of the strided kernel's lanes are at work in fp32 ([16, 19619, 244] 0.96, [28, 49714, 67] 1.91), for
+//    bf16 also beyond unless the blocks are over 80, where that kernel has the workgroups that it needs ([111, 1589, 413] 0.84, [29, 22832, 138] 2.12).
+// Segments: 512 workgroups, or 768 or 1024 where these are a whole number for every CU and 512 are not; four periods at
 // least, and never more of them than the kernels before this one take, so that no call needs more workspace than with those. Where they take
 // fewer than 512 workgroups would be, they are the faster ones by themselves: of 70 such shapes 0.64 to 1.08 of the time here with the segments
 // they take, 0.7 on average (fp32 [240, 218, 479] none, bf16 [5, 4283, 282] 41: 11.1 us, 14.5 here), and no slower than with more of them here.
@@ -856,9 +862,26 @@ constexpr long long kOneLaunchBytes = 256 << 10;
 void plan_block(ReducePlan& pl, long long outer, long long red, long long inner, int dtype)
 {
     const long long es = dtype == DT_BF16 ? 2 : 4, vec = 16 / es;
-    const bool one_launch = outer < 512 && red * inner * es <= kOneLaunchBytes && inner <= 512 * vec && (inner <= 128 * vec || red >= 64);
-    if (!one_launch && inner > 128 * vec) return;
-    if (outer >= 1024 && red * inner <= 2 * 256 * vec) return;
+    const long long bytes = red * inner * es, lanes = 64 * vec;
+    const bool bf16 = dtype == DT_BF16, waves = inner <= kSmallInner;      // (waves: the other kernel is the one with a wave per segment)
+    const double all = 1.0e-6 * (double)outer * (double)bytes;
+    const double busy = (double)inner / (double)((inner + lanes - 1) / lanes * lanes);      // share of the strided kernel's lanes that have positions
+    const bool one_launch = outer < 512 && bytes <= kOneLaunchBytes;
+    if (one_launch) {
+        if (pl.segs == 1 || inner > 512 * vec || (inner > 128 * vec && red < 64)) return;
+        if (outer > 256) { if (!bf16 || !waves || all < 3.0) return; }
+        else if ((double)bytes > 1024.0 * (bf16 ? 13.0 + (waves ? 17.0 : 10.0) * all : 42.0 + 4.5 * all)) return;
+    } else {
+        if (inner > 128 * vec) return;
+        if (outer >= 512) {
+            const long long least = bf16 ? (waves ? (outer < 1024 ? 2 : 8) : inner <= lanes ? 32 : 8) * 1024 : waves ? std::min(14 * outer, 65536LL) : 256 * 1024;
+            if (bytes < least || (bf16 && !waves && inner <= lanes && busy > 0.7)) return;
+        } else if (waves) {
+            if (all < (bf16 ? 3.0 : pl.segs >= 650 ? 2.5 : 32.0)) return;
+        } else if (bf16 ? all < 20.0 || (outer > 80 && busy > 0.7) : all < 36.0 || busy > 0.5) {
+            return;
+        }
+    }
     const long long nt = one_launch ? 1024 : 256;
     long long R = nt * vec / inner;
     const long long common = (inner & -inner) < vec ? (inner & -inner) : vec;      // (greatest common divisor: vec is a power of two)

@@ -52,8 +52,34 @@ def test_edges_of_periods(pgk, oracle, dtype, inner):
             check(pgk, oracle, gen.f32_to_bf16_bits(x) if dtype == BF16 else x, start, dtype)
 
 
+# edges of periods, batches of periods and blocks on the block kernel itself (test_kernels_reached_cpu.py): blocks enough for 1024 threads each
+# instead of two launches, and a workgroup of 256 each (r per period, then outer and inner)
+EDGES = {F32: [(584, 200, 7), (100, 200, 40), (40, 200, 100), (144, 520, 7), (28, 520, 36)],
+         BF16: [(1168, 200, 7), (204, 100, 40), (32, 100, 250), (288, 520, 7), (56, 520, 36)]}
+
+
+def edges(dtype, R, outer, inner):
+    """Those of the edges where the block kernel is the one that runs."""
+    es = 2 if dtype == BF16 else 4
+    least = (7400 if dtype == F32 else 2048) if outer == 520 else 64 * es * inner if inner >= 100 else 0
+    return [red for red in (R - 1, R, R + 1, 2 * R, 4 * R - 1, 4 * R, 4 * R + 1, 5 * R, 8 * R + 1, 9 * R) if red * inner * es >= least]
+
+
+@pytest.mark.parametrize("dtype,R,outer,inner", [(dtype, *e) for dtype in (F32, BF16) for e in EDGES[dtype]])
+def test_edges_of_periods_in_many_blocks(pgk, oracle, dtype, R, outer, inner):
+    reds = edges(dtype, R, outer, inner)
+    assert len(reds) >= 4
+    for red in reds:
+        x = gen.small_ints(gen.tensor_seed(99, 4, red), outer * red * inner, -2, 2).reshape(outer, red, inner)
+        x[:2] = 0.0
+        x[:2, np.arange(inner) % red, np.arange(inner)] = 1.0
+        x[0, red - 1, inner - 1] = 2.0
+        for start in (0, 1, 3):
+            check(pgk, oracle, gen.f32_to_bf16_bits(x) if dtype == BF16 else x, start, dtype)
+
+
 @pytest.mark.parametrize("dtype", [F32, BF16])
-@pytest.mark.parametrize("shape", [(4, 3000, 6), (3, 50000, 11), (2, 30011, 65), (530, 200, 33)])
+@pytest.mark.parametrize("shape", [(4, 3000, 6), (3, 50000, 11), (2, 30011, 65), (530, 200, 33), (60, 400, 9), (12, 17003, 65)])
 def test_special_values(pgk, oracle, dtype, shape):
     """Slices of nothing but -inf, signed zeros, maxima and NaNs in the first and last places."""
     outer, red, inner = shape

@@ -1,0 +1,41 @@
+"""The kernels behind the dispatch (no GPU: tests/launches.py): which one a size goes to where two were measured, and that the sizes of
+the GPU tests reach the kernels they are meant for."""
+import pytest
+
+import test_gpu_reduce_block as blocks
+from launches import traced
+from paper_2511_06345_amd import inputs as gen
+
+F32, BF16 = gen.F32, gen.BF16
+
+
+def first_kernels(calls, **how):
+    return [call if isinstance(call, int) else call[0].kernel for call in traced(calls, **how)]
+
+
+# us in the kernels with lanes along the inner dimension / with a workgroup per block
+BLOCK_OR_LANES = [
+    (F32, (5, 8632, 7), 7.2, 12.4), (F32, (11, 1969, 13), 7.3, 10.2), (F32, (77, 2865, 3), 8.9, 7.4), (BF16, (249, 461, 63), 21.4, 9.1),
+    (BF16, (9, 585, 199), 8.0, 11.8), (BF16, (261, 55, 285), 6.1, 13.4), (BF16, (446, 21, 87), 4.6, 8.6), (F32, (164, 52, 339), 5.4, 8.1),
+    (F32, (5299, 342, 7), 14.1, 24.8), (F32, (1436, 3222, 3), 1.37, 1.0), (F32, (7361, 20, 207), 25.4, 38.5), (BF16, (976, 21, 25), 0.67, 1.0),
+    (BF16, (570, 830, 2), 1.52, 1.0), (BF16, (303, 861, 873), 92.9, 123.8), (BF16, (29, 22832, 138), 2.12, 1.0), (F32, (14, 2533, 47), 0.81, 1.0),
+    (F32, (178, 3508, 25), 1.62, 1.0), (BF16, (1, 39012, 5), 9.2, 27.5), (F32, (28, 49714, 67), 1.91, 1.0), (BF16, (5, 4283, 282), 11.1, 14.5),
+]
+
+
+def test_blocks_where_they_are_faster():
+    kernels = first_kernels([("reduce_max", dtype, *shape) for dtype, shape, _, _ in BLOCK_OR_LANES])
+    for (dtype, shape, lanes, block), kernel in zip(BLOCK_OR_LANES, kernels):
+        assert kernel.startswith("reduce_max_block_kernel") == (block < lanes), (dtype, shape, kernel)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_sizes_for_the_block_kernel_reach_it(dtype):
+    name = "reduce_max_block_kernel<%s, " % ("true" if dtype == BF16 else "false")
+    for R, outer, inner in blocks.EDGES[dtype]:
+        calls = [("reduce_max", dtype, outer, red, inner) for red in blocks.edges(dtype, R, outer, inner)]
+        for off in (0, 1):
+            reached = [kernel == name + ("256>" if outer == 520 else "1024>") for kernel in first_kernels(calls, x_off=off)]
+            assert all(reached) if off == 0 else sum(reached) >= 4, (off, list(zip(calls, reached)))
+    in_segments = [len(call) == 2 for call in traced([("reduce_max", dtype, *shape) for shape in blocks.SHAPES]) if call[0].kernel == name + "256>"]
+    assert in_segments.count(True) >= 2 and in_segments.count(False) >= 2
