@@ -779,7 +779,9 @@ constexpr int kWaveFinishMinSegs = 16;
 // (300 MB of fp32 rows of 2112 elements 43 us so, 63 swept by a wave each; bf16 of 8192 44 and 50), and by 512 threads, sixteen chunks a lane (bf16
 // [2048, 50257] 33 us so, 37 swept by 256; fp32 rows of 14400 36 and 39).  With too few rows for every CU 1024 threads hold
 // as many, also where rows would be cut into segments: the second pass is a launch of its own (bf16 [128, 50257] 9.5 us
-// so, 5.8 here; [400, 65536] 13.4 and 9.7; but [1000, 24001], one segment, 9.1 and 10.4).
+// so, 5.8 here; [400, 65536] 13.4 and 9.7; but [1000, 24001], one segment, 9.1 and 10.4).  So they do for fp32 rows of 3072 to 6400 chunks, unless
+// their last one is less than half used: 512 threads keep more rows under way than the memory takes well (600 MB of rows of 16384 elements 94 us, 89 so,
+// 20480 89 and 88; 16448 93 and 95, 28672 90.6 and 91.2).
 constexpr long long kHeldWave = 512, kHeldWorkgroup = 2048, kHeldMost = 8192;
 constexpr long long kSmallInner = 64;             // inner dimensions up to this: the flattened-sweep kernel
 constexpr long long kTinyBlock = 128;             // red x inner up to this: several outer indices per workgroup
@@ -926,7 +928,7 @@ ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int 
             // The fewest lanes that hold the row: with two chunks each, so that short rows are read in pieces of 128 bytes, from eight lanes on
             // with four (fp32 rows of 64 elements 50 us on four lanes, 44 on eight; bf16 of 520 47 on 32 lanes, 72 on 64).
             int g = 1;
-            if (all > kHeldWorkgroup) g = few ? 1024 : 512;
+            if (all > kHeldWorkgroup) g = few || (dtype == DT_F32 && all >= 3072 && all <= 6400 && (all - 1) % 1024 >= 512) ? 1024 : 512;
             else if (all > kHeldWave) g = 256;
             else if (pl.vec > 1) while ((all <= 16 ? 2 : 4) * g < all && g < 64) g *= 2;
             pl.group = g;

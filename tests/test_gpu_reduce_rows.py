@@ -33,7 +33,7 @@ def rows(rng, outer, red, kind):
 
 
 # chunks of a row: on each side of the number of lanes, of chunks per lane, of waves and workgroups, of registers and sweeps
-CHUNKS = [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 64, 65, 128, 129, 255, 256, 257, 320, 321, 512, 513, 1024, 1025, 1793, 2048, 2049, 2561, 3073, 4097, 7681, 8192, 8193, 9000]
+CHUNKS = [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 64, 65, 128, 129, 255, 256, 257, 320, 321, 512, 513, 1024, 1025, 1793, 2048, 2049, 2561, 3072, 3073, 4096, 4097, 6400, 7681, 8192, 8193, 9000]
 
 
 @pytest.mark.parametrize("chunks", CHUNKS)

@@ -29,6 +29,13 @@ def test_blocks_where_they_are_faster():
         assert kernel.startswith("reduce_max_block_kernel") == (block < lanes), (dtype, shape, kernel)
 
 
+def test_long_fp32_rows_in_the_faster_workgroup():
+    """us at 600 MB with 512 threads / 1024: 12288 elements 89.3 / 87.5, 16384 94 / 89, 20480 89 / 88; 16448 93 / 95, 28672 90.6 / 91.2; 512 for bf16."""
+    rows = [(F32, 12288, 1024), (F32, 16384, 1024), (F32, 20480, 1024), (F32, 16448, 512), (F32, 28672, 512), (F32, 8448, 512), (BF16, 32768, 512)]
+    for (dtype, red, threads), (launch,) in zip(rows, traced([("reduce_max", dtype, 150000000 // red, red, 1) for dtype, red, _ in rows])):
+        assert launch.kernel.startswith("reduce_max_held_rows_kernel") and launch.block == threads, (dtype, red, launch)
+
+
 @pytest.mark.parametrize("dtype", [F32, BF16])
 def test_sizes_for_the_block_kernel_reach_it(dtype):
     name = "reduce_max_block_kernel<%s, " % ("true" if dtype == BF16 else "false")
