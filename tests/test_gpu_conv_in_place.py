@@ -98,3 +98,19 @@ def test_replays_of_a_graph(pgk):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, pgk.conv1d(x, w, None, RELU, 1, 2, 1))
+
+
+@pytest.mark.parametrize("Cin,Kw", [(1, 1), (2, 1), (1, 3), (5, 1), (3, 3), (11, 1)])
+def test_short_sums_round_like_multiply_adds(pgk, Cin, Kw):
+    """Sums of fewer than 12 products, heavy-tailed: each product's error is at most a rounding of it and of the sums that follow
+    (a single product: correctly rounded)."""
+    import torch
+    for B, L, Cout in ((1, 300, 40), (2, 3001, 70)):
+        g = torch.Generator(device="cuda").manual_seed(Cin * 10 + Kw)
+        x, w = (torch.exp(4 * torch.randn(s, device="cuda", generator=g)) * torch.randn(s, device="cuda", generator=g).sign() for s in ((B, Cin, L), (Cout, Cin, Kw)))
+        y = pgk.conv1d(x, w, None, NONE)
+        taps = x.double().unfold(2, Kw, 1).permute(0, 1, 3, 2).reshape(B, Cin * Kw, -1)
+        ref, scale = torch.matmul(w.double().reshape(Cout, -1), taps), torch.matmul(w.double().abs().reshape(Cout, -1), taps.abs())
+        if Cin * Kw == 1:
+            assert torch.equal(y, ref.float())
+        assert bool(((y.double() - ref).abs() <= Cin * Kw * 2.0 ** -24 * scale).all())

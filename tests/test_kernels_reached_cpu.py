@@ -46,3 +46,13 @@ def test_sizes_for_the_block_kernel_reach_it(dtype):
             assert all(reached) if off == 0 else sum(reached) >= 4, (off, list(zip(calls, reached)))
     in_segments = [len(call) == 2 for call in traced([("reduce_max", dtype, *shape) for shape in blocks.SHAPES]) if call[0].kernel == name + "256>"]
     assert in_segments.count(True) >= 2 and in_segments.count(False) >= 2
+
+
+def test_short_fp32_sums_are_plain_multiply_adds():
+    """Convolutions with fewer than 12 products per output stay off the kernel of three terms, which rounds a single product worse."""
+    calls = [("conv1d", F32, B, Cin, L, Cout, Kw, stride, 1, 1) for Cin, Kw in ((1, 1), (2, 1), (1, 3), (5, 1), (2, 5), (11, 1), (12, 1), (4, 3), (16, 1))
+             for B, L, Cout, stride in ((1, 300, 40, 1), (3, 5000, 33, 2), (2, 20000, 200, 1))]
+    for call, kernel in zip(calls, first_kernels(calls)):
+        if call[3] * call[6] < 12:
+            assert "f32_terms" not in kernel, (call, kernel)
+    assert any("f32_terms" in kernel for kernel in first_kernels(calls[-9:]))
