@@ -310,26 +310,28 @@ size_t pgk_reduce_max_workspace_bytes(int64_t outer, int64_t red, int64_t inner,
  *  3. Otherwise -- stride > 1, any Cin of at least half a K tile's multiple (Cin >= its round-up / 2), odd
  *     dilations in bfloat16 -- with Kw <= 32: of copies of the input, one per phase of the stride (and a second one
  *     shifted by one element for bfloat16 taps at odd offsets), channels padded with zeros to a multiple of the K tile.
- * Float32 also, where it is faster (Lout of at least 16, entries of x below 4 GiB), without any of these, in one launch: x and w on any
- * element, read in place as they are.  Sizes that 1 to 3 need a workspace for ask for it all the same.  Bfloat16 likewise, x on any element, strides
- * of at most 3 and (Kw - 1) * dilation + 127 * stride below 384, from 16 channels on also where 1 to 3 do not apply: the query then gives what
- * the regrouped weights take, and a call with less runs without.
- * These need `workspace`
- * (device memory, 256-byte aligned, contents destroyed) of pgk_conv1d_workspace_bytes(...)
- * bytes for the regrouped weights and the strips or copies.  Too small (also for the way through
- * registers, if there is one) or NULL gives PGK_ERR_WORKSPACE.  Every other case needs no workspace (the query then returns 0): few input
+ * Float32 also, where it is faster (Lout of at least 16, 12 products per output and more, entries of x below 4 GiB), without any of these, in
+ * one launch and without a workspace: x and w on any element, read in place as they are.  Bfloat16 likewise, x on any element, strides
+ * of at most 3 and (Kw - 1) * dilation + 127 * stride below 384, from 16 channels on also where 1 to 3 do not apply: with the regrouped weights
+ * alone in the workspace.
+ * `workspace`: device memory, 256-byte aligned, contents destroyed.  pgk_conv1d_workspace_bytes(...) bytes are enough whichever way the
+ * call takes, the regrouped weights and the strips or copies of 1 to 3 included; pgk_conv1d_workspace_least_bytes(...) are what it takes on the
+ * way that it goes, up to all of them less.  With fewer (also for the way through registers, if there is one) or NULL a call in the sizes of 1 to 3
+ * gives PGK_ERR_WORKSPACE; bfloat16 beyond them then runs without.  Every other case needs no workspace (both queries then return 0): few input
  * channels under a large enough output run on a matrix-core kernel of their own, the rest (tiny
- * outputs of bfloat16, or of fewer than 16 positions) on a bounds-checked kernel; both read the input in place.
+ * outputs of bfloat16, short sums of float32, fewer than 16 positions) on a bounds-checked kernel; both read the input in place.
  */
 int pgk_conv1d(const void* x, const void* w, const float* bias, void* y,
                int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw,
                int64_t stride, int64_t pad, int64_t dilation, int act, int dtype,
                void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace pgk_conv1d needs for this problem (0: none).  Pure host arithmetic,
- * assuming 16-byte aligned pointers; 0 also for invalid arguments. */
+/* Bytes of workspace that are enough for pgk_conv1d on this problem (0: none), and the least with which it runs the same way.  Pure
+ * host arithmetic, assuming 16-byte aligned pointers; 0 also for invalid arguments. */
 size_t pgk_conv1d_workspace_bytes(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw,
                                   int64_t stride, int64_t pad, int64_t dilation, int dtype);
+size_t pgk_conv1d_workspace_least_bytes(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw,
+                                        int64_t stride, int64_t pad, int64_t dilation, int dtype);
 
 /* Output length of the convolution, or 0 when the arguments give none.  Host arithmetic. */
 int64_t pgk_conv1d_out_len(int64_t L, int64_t Kw, int64_t stride, int64_t pad, int64_t dilation);

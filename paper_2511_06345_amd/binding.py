@@ -25,7 +25,7 @@ EXPORTS = ("pgk_gemm_fused", "pgk_gemm_splitk", "pgk_gemm_fused_bt", "pgk_gemm_s
            "pgk_gemm_fused_workspace_bytes", "pgk_gemm_splitk_workspace_bytes", "pgk_splitk_workspace_bytes",
            "pgk_gemm_fused_static", "pgk_gemm_fused_static_max_bytes",
            "pgk_splitk_auto_splits", "pgk_reduce_max", "pgk_reduce_max_workspace_bytes", "pgk_conv1d",
-           "pgk_conv1d_workspace_bytes", "pgk_conv1d_out_len", "pgk_probe_mfma", "pgk_probe_stream_read",
+           "pgk_conv1d_workspace_bytes", "pgk_conv1d_workspace_least_bytes", "pgk_conv1d_out_len", "pgk_probe_mfma", "pgk_probe_stream_read",
            "pgk_probe_gemm_phases", "pgk_probe_mfma_fed",
            "pgk_status_string", "pgk_version")
 
@@ -37,7 +37,7 @@ _lib = None
 _native = None
 _NATIVE_ENTRIES = ("pgk_gemm_fused", "pgk_gemm_fused_bt", "pgk_gemm_splitk", "pgk_gemm_splitk_bt", "pgk_gemm_fused_workspace_bytes",
                    "pgk_gemm_splitk_workspace_bytes", "pgk_reduce_max", "pgk_reduce_max_workspace_bytes", "pgk_conv1d",
-                   "pgk_conv1d_workspace_bytes", "pgk_conv1d_out_len")
+                   "pgk_conv1d_workspace_least_bytes", "pgk_conv1d_out_len")
 
 # the handle of torch.cuda.current_stream() without the Python object around it: 0.3 us, not 2.8, of a small
 # call that takes 20 us of which the host bounds all.  Not a public name: None where torch does not have it.
@@ -94,6 +94,8 @@ def load_library() -> ctypes.CDLL:
     lib.pgk_conv1d.argtypes = [vp, vp, vp, vp] + [i64] * 8 + [ci, ci, vp, ctypes.c_size_t, vp]
     lib.pgk_conv1d_workspace_bytes.restype = ctypes.c_size_t
     lib.pgk_conv1d_workspace_bytes.argtypes = [i64] * 8 + [ci]
+    lib.pgk_conv1d_workspace_least_bytes.restype = ctypes.c_size_t
+    lib.pgk_conv1d_workspace_least_bytes.argtypes = [i64] * 8 + [ci]
     lib.pgk_conv1d_out_len.restype = i64
     lib.pgk_conv1d_out_len.argtypes = [i64] * 5
     lib.pgk_probe_mfma.restype = ci
@@ -481,11 +483,18 @@ def conv1d_out_len(L: int, Kw: int, stride: int = 1, pad: int = 0, dilation: int
 
 def conv1d_workspace_bytes(B: int, Cin: int, L: int, Cout: int, Kw: int, stride: int, pad: int, dilation: int,
                            dtype: int) -> int:
+    """Enough whichever way the call takes."""
     return int(load_library().pgk_conv1d_workspace_bytes(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype))
 
 
+def conv1d_workspace_least_bytes(B: int, Cin: int, L: int, Cout: int, Kw: int, stride: int, pad: int, dilation: int,
+                                 dtype: int) -> int:
+    """What the call takes on the way that it goes."""
+    return int(load_library().pgk_conv1d_workspace_least_bytes(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype))
+
+
 _conv1d_len = functools.lru_cache(maxsize=4096)(conv1d_out_len)
-_conv1d_bytes = functools.lru_cache(maxsize=4096)(conv1d_workspace_bytes)
+_conv1d_bytes = functools.lru_cache(maxsize=4096)(conv1d_workspace_least_bytes)
 
 
 def conv1d(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor], act: int = ACT_NONE, stride: int = 1,
@@ -493,7 +502,7 @@ def conv1d(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor], act: 
            workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """y = act(conv1d(x, w) + bias) via pgk_conv1d.  x [B, Cin, L], w [Cout, Cin, Kw]: contiguous
     float32 or bfloat16 device tensors; bias float32 [Cout] or None.  ``workspace``: uint8 device
-    tensor of at least ``conv1d_workspace_bytes(...)`` bytes, allocated here when None."""
+    tensor of at least ``conv1d_workspace_least_bytes(...)`` bytes, allocated here when None."""
     lib = load_library()
     if out is None and workspace is None and stream is None:
         done = _native.conv1d(x, w, bias, act, stride, pad, dilation)
@@ -516,7 +525,7 @@ def conv1d(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor], act: 
     if Lout <= 0:
         raise ValueError("the convolution has no output for these sizes")
     dev = x.device
-    need = (_conv1d_bytes if plain else conv1d_workspace_bytes)(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype)
+    need = (_conv1d_bytes if plain else conv1d_workspace_least_bytes)(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype)
     with _on_stream(stream):
         if workspace is None and need:
             workspace = torch.empty((need,), dtype=torch.uint8, device=dev)

@@ -1392,6 +1392,12 @@ ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw
     return pl;
 }
 
+// What the call writes to: in place nothing but a bf16 kernel's regrouped weights, whatever the views would take.
+size_t touched_workspace(const ConvPlan& pl)
+{
+    return !pl.valid ? 0 : pl.fast && !pl.in_place_rows ? pl.w_bytes + pl.x_bytes : pl.regrouped;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1410,6 +1416,12 @@ size_t pgk_conv1d_workspace_bytes(int64_t B, int64_t Cin, int64_t L, int64_t Cou
     return !pl.valid ? 0 : pl.fast ? pl.w_bytes + pl.x_bytes : pl.regrouped;
 }
 
+size_t pgk_conv1d_workspace_least_bytes(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw, int64_t stride,
+                                        int64_t pad, int64_t dilation, int dtype)
+{
+    return touched_workspace(plan_conv1d(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype));
+}
+
 int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t B, int64_t Cin, int64_t L,
                int64_t Cout, int64_t Kw, int64_t stride, int64_t pad, int64_t dilation, int act, int dtype,
                void* workspace, size_t workspace_bytes, void* stream)
@@ -1424,9 +1436,9 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
             return PGK_ERR_UNSUPPORTED;
         return PGK_ERR_INVALID_ARG;
     }
-    if (pl.fast && workspace && workspace_bytes < pl.w_bytes + pl.x_bytes) {
+    if (pl.fast && workspace && workspace_bytes < touched_workspace(pl)) {
         const ConvPlan in_place = plan_conv1d(B, Cin, L, Cout, Kw, stride, pad, dilation, dtype, true);
-        if (in_place.fast && in_place.w_bytes + in_place.x_bytes <= workspace_bytes) pl = in_place;
+        if (in_place.fast && touched_workspace(in_place) <= workspace_bytes) pl = in_place;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t es = dtype == PGK_DTYPE_BF16 ? 2 : 4;
@@ -1450,9 +1462,8 @@ int pgk_conv1d(const void* x, const void* w, const float* bias, void* y, int64_t
     a.bias_per_row = 1;                   // one bias per output channel = per row
     a.act = act; a.splits = 1;
 
-    // (asked for by the sizes alone, whichever way the call then takes)
-    if (pl.fast && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < pl.w_bytes + pl.x_bytes))
-        return PGK_ERR_WORKSPACE;
+    if (const size_t least = touched_workspace(pl);
+        pl.fast && least && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < least)) return PGK_ERR_WORKSPACE;
     // (bf16 that has no other use for a workspace: without one it stays on the bounds-checked kernel)
     if (pl.regrouped && workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u) && workspace_bytes >= pl.regrouped) {
         const int cin_pad = (int)((Cin + 31) / 32 * 32);

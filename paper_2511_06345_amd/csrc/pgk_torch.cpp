@@ -29,7 +29,7 @@ struct Library {
     decltype(&pgk_reduce_max) reduce_max;
     decltype(&pgk_reduce_max_workspace_bytes) reduce_max_bytes;
     decltype(&pgk_conv1d) conv1d;
-    decltype(&pgk_conv1d_workspace_bytes) conv1d_bytes;
+    decltype(&pgk_conv1d_workspace_least_bytes) conv1d_bytes;
     decltype(&pgk_conv1d_out_len) conv1d_out_len;
 };
 Library lib{};

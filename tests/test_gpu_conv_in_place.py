@@ -114,3 +114,20 @@ def test_short_sums_round_like_multiply_adds(pgk, Cin, Kw):
         if Cin * Kw == 1:
             assert torch.equal(y, ref.float())
         assert bool(((y.double() - ref).abs() <= Cin * Kw * 2.0 ** -24 * scale).all())
+
+
+def test_ordinary_calls_allocate_what_they_write_to(pgk):
+    """No room for copies of the input that the way taken does not make (137 MB of them here; the weights regrouped for bf16 0.2 MB)."""
+    import torch
+    for dtype, (B, Cin, L, Cout, Kw, stride) in ((torch.float32, (4, 152, 53120, 19, 7, 1)), (torch.bfloat16, (8, 384, 11631, 61, 5, 2))):
+        x, w = torch.zeros((B, Cin, L), dtype=dtype, device="cuda"), torch.zeros((Cout, Cin, Kw), dtype=dtype, device="cuda")
+        code = gen.F32 if dtype == torch.float32 else gen.BF16
+        assert pgk.conv1d_workspace_bytes(B, Cin, L, Cout, Kw, stride, 0, 1, code) > x.numel() * x.element_size() // 2
+        lout = (L - Kw) // stride + 1
+        for out in (None, torch.empty((B, Cout, lout), dtype=dtype, device="cuda")):
+            torch.cuda.synchronize()
+            torch.cuda.reset_peak_memory_stats()
+            before = torch.cuda.memory_allocated()
+            y = pgk.conv1d(x, w, None, RELU, stride, 0, 1, out=out)
+            assert torch.cuda.max_memory_allocated() - before <= (y.numel() * y.element_size() if out is None else 0) + (1 << 20)
+            del y

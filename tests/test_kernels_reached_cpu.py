@@ -56,3 +56,20 @@ def test_short_fp32_sums_are_plain_multiply_adds():
         if call[3] * call[6] < 12:
             assert "f32_terms" not in kernel, (call, kernel)
     assert any("f32_terms" in kernel for kernel in first_kernels(calls[-9:]))
+
+
+def test_convolutions_in_place_take_no_more_workspace_than_they_write_to():
+    """fp32 none, bf16 the regrouped weights, though the views of such sizes would take copies of the input; with less the call is refused
+    where the views are another way, and the views take what they took."""
+    from paper_2511_06345_amd import binding
+    fp32, bf16 = (F32, 10, 152, 53120, 19, 7, 1, 0, 1), (BF16, 13, 384, 11631, 61, 5, 2, 0, 1)
+    assert binding.conv1d_workspace_bytes(*fp32[1:], F32) > 300e6 and binding.conv1d_workspace_least_bytes(*fp32[1:], F32) == 0
+    least = binding.conv1d_workspace_least_bytes(*bf16[1:], BF16)
+    assert binding.conv1d_workspace_bytes(*bf16[1:], BF16) > 200e6 and 61 * 384 * 5 * 2 <= least < 61 * 384 * 5 * 2 + 256
+    for call, room in ((fp32, 0), (bf16, least)):
+        (with_all,), (with_least,) = traced([("conv1d", *call)]), traced([("conv1d", *call)], workspace=room)
+        assert with_all == with_least and ("f32_terms" in with_all[-1].kernel or "conv_bf16" in with_all[-1].kernel), (with_all, with_least)
+    assert traced([("conv1d", *bf16)], workspace=least - 256) == [-3]
+    views = (F32, 2, 64, 1024, 32, 3, 1, 1, 1)
+    assert binding.conv1d_workspace_bytes(*views[1:], F32) == binding.conv1d_workspace_least_bytes(*views[1:], F32) > 0
+    assert traced([("conv1d", *views)], workspace=0) == [-3]
