@@ -12,6 +12,7 @@ import ctypes
 import functools
 import math
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -33,7 +34,7 @@ EXPORTS = ("pgk_gemm_fused", "pgk_gemm_splitk", "pgk_gemm_fused_bt", "pgk_gemm_s
 WS_ROWSUM, WS_B_TRANSPOSED, WS_UNALIGNED = 1, 2, 4
 
 _lib = None
-# the ordinary calls in native code (csrc/pgk_torch.cpp), bound to the library when that is loaded
+# the ordinary calls in native code (csrc/pgk_torch.cpp), bound to the library when that is loaded; None where they do not load
 _native = None
 _NATIVE_ENTRIES = ("pgk_gemm_fused", "pgk_gemm_fused_bt", "pgk_gemm_splitk", "pgk_gemm_splitk_bt", "pgk_gemm_fused_workspace_bytes",
                    "pgk_gemm_splitk_workspace_bytes", "pgk_reduce_max", "pgk_reduce_max_workspace_bytes", "pgk_conv1d",
@@ -112,9 +113,14 @@ def load_library() -> ctypes.CDLL:
     lib.pgk_status_string.argtypes = [ci]
     lib.pgk_version.restype = ci
     lib.pgk_version.argtypes = []
-    from . import _pgk_torch
-    _pgk_torch.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in _NATIVE_ENTRIES))
-    _native = _pgk_torch
+    try:
+        from . import _pgk_torch
+        _pgk_torch.bind(*(ctypes.cast(getattr(lib, name), vp).value for name in _NATIVE_ENTRIES))
+        _native = _pgk_torch
+    except ImportError as e:
+        # built against one torch; without it the same calls go the general way, some microseconds later
+        warnings.warn(f"no native calls ({e}): build again for this torch (build.build_library); until then calls are marshalled in Python",
+                      RuntimeWarning, stacklevel=2)
     _lib = lib
     return lib
 
@@ -278,7 +284,7 @@ def gemm_fused(A: torch.Tensor, B: torch.Tensor, bias: Optional[torch.Tensor], a
     and the problem needs one.
     """
     lib = load_library()
-    if out is None and rowsum_out is None and workspace is None and stream is None:
+    if _native is not None and out is None and rowsum_out is None and workspace is None and stream is None:
         done = _native.gemm(A, B, bias, act, rowsum, b_transposed, None)
         if done is not None:
             return _checked(done, "pgk_gemm_fused_bt" if b_transposed else "pgk_gemm_fused")
@@ -338,7 +344,7 @@ def gemm_splitk(A: torch.Tensor, B: torch.Tensor, bias: Optional[torch.Tensor], 
     ``workspace`` is a uint8 device tensor of at least ``gemm_splitk_workspace_bytes(...)`` bytes
     (``splitk_workspace_bytes(...)`` is enough for aligned operands); allocated here when None."""
     lib = load_library()
-    if out is None and rowsum_out is None and workspace is None and stream is None and splits is not None:
+    if _native is not None and out is None and rowsum_out is None and workspace is None and stream is None and splits is not None:
         done = _native.gemm(A, B, bias, act, rowsum, b_transposed, splits)
         if done is not None:
             return _checked(done, "pgk_gemm_splitk_bt" if b_transposed else "pgk_gemm_splitk")
@@ -377,7 +383,7 @@ def reduce_max(X: torch.Tensor, dim: int, want_idx: bool = True, out: Optional[t
     (values in the dtype of X with ``dim`` removed, int32 positions or None).  ``workspace``: uint8
     device tensor of at least ``reduce_max_workspace_bytes(...)`` bytes, allocated here when None."""
     lib = load_library()
-    if out is None and idx_out is None and workspace is None and stream is None:
+    if _native is not None and out is None and idx_out is None and workspace is None and stream is None:
         done = _native.reduce_max(X, dim, want_idx)
         if done is not None:
             return _checked(done, "pgk_reduce_max")
@@ -504,7 +510,7 @@ def conv1d(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor], act: 
     float32 or bfloat16 device tensors; bias float32 [Cout] or None.  ``workspace``: uint8 device
     tensor of at least ``conv1d_workspace_least_bytes(...)`` bytes, allocated here when None."""
     lib = load_library()
-    if out is None and workspace is None and stream is None:
+    if _native is not None and out is None and workspace is None and stream is None:
         done = _native.conv1d(x, w, bias, act, stride, pad, dilation)
         if done is not None:
             return _checked(done, "pgk_conv1d")

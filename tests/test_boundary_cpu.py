@@ -278,6 +278,27 @@ def test_reduce_max_rejects_bad_arguments_on_the_host(lib):
     assert q(0, 3, 4, gen.F32) == 0 and q(2, 3, 4, 5) == 0
 
 
+def test_without_the_native_calls_the_general_way_serves(lib, monkeypatch):
+    """The extension is built against one torch: where it does not load, the library does all the same, with a warning, and the
+    calls go the general way (whose checks of their operands show here)."""
+    import sys
+
+    import paper_2511_06345_amd as package
+    import torch
+    with monkeypatch.context() as m:
+        m.setattr(binding, "_lib", None)
+        m.setattr(binding, "_native", None)
+        m.delattr(package, "_pgk_torch", raising=False)
+        m.setitem(sys.modules, package.__name__ + "._pgk_torch", None)
+        with pytest.warns(RuntimeWarning, match="build again"):
+            assert binding.load_library().pgk_version() == lib.pgk_version()
+        A, x = torch.ones(4, 4), torch.ones(1, 2, 9)
+        for call in (lambda: binding.gemm_fused(A, A, None, 0), lambda: binding.gemm_splitk(A, A, None, 0), lambda: binding.reduce_max(A, 0),
+                     lambda: binding.conv1d(x, torch.ones(3, 2, 3), None)):
+            with pytest.raises(ValueError, match="device"):
+                call()
+
+
 def test_strided_reductions_ask_for_no_more_than_their_segments(lib):
     """Workspace of a strided reduction: at most the segments that the kernels with lanes along the inner dimension take (a wave, or
     64 lanes times the load's width, per workgroup), whichever kernel runs, so that a workspace sized for those is always enough."""
