@@ -671,3 +671,17 @@ def test_kernels_that_spill_registers_are_known(lib):
         table = json.load(f)
     spilled = {name: use["vgpr_spills"] for name, use in table.items() if use.get("vgpr_spills")}
     assert all("MfmaCfgReg<false, 256, 256, 64" in name and n <= 16 for name, n in spilled.items()), spilled
+
+
+def test_convolution_views_keep_their_scalars_in_registers(lib):
+    """The fp32 kernel in three terms on a convolution's views: scalar registers spilled to lanes of vector ones cost every tile's start
+    and end 1.5 % of a call of six steps a tile."""
+    import json
+
+    from paper_2511_06345_amd import build
+    if not os.path.exists(build.RESOURCES):
+        pytest.skip("no resource table: the library was not built here")
+    with open(build.RESOURCES) as f:
+        table = json.load(f)
+    views = [use for name, use in table.items() if "gemm_f32_terms_kernel<pgk::TermsCfg<false, 128, 128, 2>, 1, " in name]
+    assert views and all(use["sgpr_spills"] == 0 for use in views), views
