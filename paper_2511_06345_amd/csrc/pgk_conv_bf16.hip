@@ -323,7 +323,9 @@ hipError_t launch_tile(const ConvArgs& p, unsigned int wgs, size_t lds, hipStrea
 template <int BM, int GROUPS>
 hipError_t launch_groups(const ConvArgs& p, unsigned int wgs, size_t lds, hipStream_t s)
 {
-    return p.taps < p.Kw ? launch_tile<BM, GROUPS, true>(p, wgs, lds, s) : launch_tile<BM, GROUPS, false>(p, wgs, lds, s);
+    // (one group of positions is a single tap at stride 1, whose weights are one part)
+    if constexpr (GROUPS > 1) { if (p.taps < p.Kw) return launch_tile<BM, GROUPS, true>(p, wgs, lds, s); }
+    return launch_tile<BM, GROUPS, false>(p, wgs, lds, s);
 }
 
 template <int BM>

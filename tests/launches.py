@@ -73,7 +73,9 @@ def _run():
 
 
 def traced(calls, workspace=None, x_off=0):
-    """Launches and grants of each call, in order; a call that is refused gives its status instead of the list."""
+    """Launches and grants of each call, in order; a call that is refused gives its status instead of the list.  workspace: bytes, of all
+    calls or of each."""
+    room = workspace if isinstance(workspace, list) else [workspace] * len(calls)
     from paper_2511_06345_amd import binding, build
     with tempfile.TemporaryDirectory() as folder:
         source, lib = os.path.join(folder, "hip.c"), os.path.join(folder, "hip.so")
@@ -82,7 +84,7 @@ def traced(calls, workspace=None, x_off=0):
         subprocess.run(["gcc", "-shared", "-fPIC", "-o", lib, source], check=True)
         env = dict(os.environ, LD_PRELOAD=" ".join(filter(None, [lib, os.environ.get("LD_PRELOAD")])))
         run = subprocess.run([sys.executable, os.path.abspath(__file__), binding.LIB_PATH], capture_output=True, text=True, cwd=ROOT, env=env,
-                             input=json.dumps([[*map(lambda v: v if isinstance(v, str) else int(v), call), workspace, x_off] for call in calls]))
+                             input=json.dumps([[*map(lambda v: v if isinstance(v, str) else int(v), call), r, x_off] for call, r in zip(calls, room)]))
     assert run.returncode == 0, run.stderr
     names, out = {}, []
     for line in run.stdout.splitlines():

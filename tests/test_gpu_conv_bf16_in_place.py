@@ -19,18 +19,42 @@ def pgk():
     return binding
 
 
-# B, Cin, L, Cout, Kw, stride, pad, dilation
+# B, Cin, L, Cout, Kw, stride, pad, dilation (two with few outputs and channels are the views', which are the faster way there)
 CASES = [
-    # 32 output channels: one, two and three groups of positions, one block of channels and several, whole and partly filled
+    # up to 32 output channels: one, two and three groups of positions, one block of channels and several, whole and partly filled
     (20, 17, 2600, 18, 3, 1, 1, 1), (12, 64, 1025, 32, 1, 1, 0, 1), (10, 90, 1537, 31, 3, 2, 0, 2), (14, 33, 900, 24, 10, 1, 4, 1),
-    # 64
+    # up to 64
     (30, 20, 3001, 64, 3, 1, 1, 1), (16, 96, 4097, 60, 5, 2, 2, 1), (24, 31, 2049, 64, 1, 2, 0, 1), (16, 100, 3000, 190, 10, 1, 9, 2),
-    # 128
+    # more
     (40, 20, 2700, 202, 3, 1, 1, 1), (30, 66, 2100, 257, 5, 2, 2, 2), (40, 24, 2000, 128, 1, 1, 0, 1), (20, 40, 3001, 384, 7, 1, 3, 1),
     # rows shorter than a tile, padding wider than the row, halos and strides at their widest, rows of two elements
     (30, 16, 18, 40, 3, 1, 1, 1), (20, 24, 30, 33, 5, 1, 70, 9), (9, 40, 1500, 20, 2, 1, 0, 255), (9, 17, 1300, 40, 1, 3, 0, 1), (6, 48, 2, 32, 3, 1, 10, 1),
     # one workgroup
     (1, 16, 130, 16, 3, 1, 1, 1), (1, 37, 64, 20, 4, 1, 0, 1),
+]
+
+
+# Each instance of the kernel, (output channels of a tile, groups of 128 positions, weights of a block in parts), which test_kernels_reached_cpu.py
+# asserts: one block of channels and several, whole and partly filled, ends of rows, strides, with the padding wider than the row
+INSTANCES = [
+    ((32, 1, False), (1, 18, 16, 18, 1, 1, 0, 2)), ((32, 1, False), (1, 46, 2, 22, 1, 1, 7, 3)), ((32, 1, False), (1, 79, 17, 71, 1, 1, 1, 2)),
+    ((32, 2, False), (1, 20, 2, 16, 1, 2, 18, 3)), ((32, 2, False), (1, 48, 2, 35, 1, 2, 15, 3)), ((32, 2, False), (1, 96, 50, 35, 1, 2, 1, 3)),
+    ((32, 2, True), (1, 17, 40, 20, 10, 1, 0, 1)), ((32, 2, True), (1, 36, 17, 19, 10, 1, 13, 3)), ((32, 2, True), (1, 84, 2, 26, 10, 1, 12, 1)),
+    ((32, 3, False), (1, 18, 22, 23, 1, 3, 23, 3)), ((32, 3, False), (1, 45, 63, 33, 1, 3, 1, 2)), ((32, 3, False), (1, 70, 52, 36, 1, 3, 1, 1)),
+    ((32, 3, True), (1, 32, 47, 18, 2, 3, 0, 1)), ((32, 3, True), (1, 28, 51, 19, 3, 3, 1, 1)), ((32, 3, True), (1, 90, 2, 18, 12, 2, 22, 1)),
+    ((64, 1, False), (43, 48, 2091, 34, 1, 1, 1, 163)), ((64, 1, False), (15, 32, 3032, 103, 1, 1, 0, 1)), ((64, 1, False), (5, 102, 1572, 357, 1, 1, 59, 1)),
+    ((64, 2, False), (43, 25, 2186, 34, 1, 2, 0, 9)), ((64, 2, False), (54, 34, 28, 476, 2, 1, 1, 3)), ((64, 2, False), (40, 81, 778, 133, 1, 2, 1, 3)),
+    ((64, 2, True), (55, 16, 298, 172, 12, 1, 16, 3)), ((64, 2, True), (54, 48, 2, 462, 10, 1, 48, 2)),
+    ((64, 3, False), (1, 48, 59, 45, 3, 3, 1, 1)), ((64, 3, False), (1, 87, 5, 36, 2, 3, 45, 1)), ((64, 3, False), (56, 29, 164, 130, 3, 2, 0, 64)),
+    ((64, 3, True), (1, 32, 33, 46, 7, 2, 60, 20)), ((64, 3, True), (2, 20, 268, 30, 7, 1, 0, 41)), ((64, 3, True), (1, 77, 223, 43, 7, 1, 0, 34)),
+    ((64, 3, True), (13, 64, 4673, 128, 7, 2, 0, 1)),
+    ((128, 1, False), (37, 32, 1451, 118, 1, 1, 0, 1)), ((128, 1, False), (7, 35, 3855, 225, 1, 1, 7, 1)), ((128, 1, False), (57, 68, 287, 380, 1, 1, 0, 2)),
+    ((128, 2, False), (35, 21, 892, 368, 1, 2, 0, 37)), ((128, 2, False), (53, 30, 1636, 235, 1, 2, 5, 1)), ((128, 2, False), (39, 48, 3146, 92, 1, 2, 0, 1)),
+    ((128, 2, True), (19, 24, 3438, 103, 4, 1, 0, 9)), ((128, 2, True), (38, 44, 1350, 98, 5, 1, 9, 9)),
+    ((128, 3, False), (46, 21, 1928, 236, 1, 3, 38, 3)), ((128, 3, False), (35, 56, 2460, 237, 1, 3, 0, 3)), ((128, 3, False), (46, 85, 2155, 105, 2, 2, 0, 73)),
+    ((128, 3, True), (37, 25, 2023, 209, 3, 2, 9, 9)), ((128, 3, True), (44, 48, 2601, 97, 3, 2, 63, 3)), ((128, 3, True), (59, 70, 1507, 70, 3, 1, 30, 127)),
+    # 384 positions exactly, the last of three groups whole (also 28 channels above)
+    ((64, 3, False), (1, 48, 59, 45, 3, 3, 1, 1)), ((128, 3, True), (34, 19, 3329, 499, 3, 3, 0, 1)),
 ]
 
 
@@ -142,3 +166,34 @@ def test_threads_with_different_needs_of_lds(pgk):
     for t in threads:
         t.join()
     assert not wrong, wrong[:3]
+
+
+@pytest.mark.parametrize("instance,case", INSTANCES)
+def test_instances(pgk, instance, case):
+    """Integers exactly, from even and odd starts; uniform values within the bound of test_against_the_oracle."""
+    import torch
+    B, Cin, L, Cout, Kw, stride, pad, dilation = case
+    g = torch.Generator(device="cuda").manual_seed(Cin * Kw)
+
+    def in_64_bits(x, w, bias):
+        xp = torch.nn.functional.pad(x.double(), (pad, pad))
+        lout = (L + 2 * pad - dilation * (Kw - 1) - 1) // stride + 1
+        y = bias.double().view(1, -1, 1).expand(B, -1, lout).clone()
+        for b in range(B):
+            for k in range(Kw):
+                y[b] += w[:, :, k].double().contiguous() @ xp[b, :, k * dilation:k * dilation + (lout - 1) * stride + 1:stride].contiguous()
+        return y
+    x = torch.randint(-3, 4, (B, Cin, L), generator=g, device="cuda").bfloat16()
+    w = torch.randint(-3, 4, (Cout, Cin, Kw), generator=g, device="cuda").bfloat16()
+    bias = torch.randint(-7, 8, (Cout,), generator=g, device="cuda").float()
+    want = in_64_bits(x, w, bias).float().bfloat16()
+    for start in (0, 1):
+        placed = torch.cat([x.new_full((start,), float("nan")), x.reshape(-1)])[start:].view(x.shape)
+        assert torch.equal(pgk.conv1d(placed, w, bias, NONE, stride, pad, dilation), want), start
+    x = torch.empty((B, Cin, L), device="cuda").uniform_(-1, 1, generator=g).bfloat16()
+    w = torch.empty((Cout, Cin, Kw), device="cuda").normal_(0, (Cin * Kw) ** -0.5, generator=g).bfloat16()
+    bias = torch.empty(Cout, device="cuda").normal_(0, 0.5, generator=g)
+    got = pgk.conv1d(x, w, bias, SILU, stride, pad, dilation).double()
+    ref = in_64_bits(x, w, bias)
+    ref, scale = ref * torch.sigmoid(ref), in_64_bits(x.abs(), w.abs(), bias.abs())
+    assert bool(((got - ref).abs() <= (Cin * Kw + 12) * 2.0 ** -24 * 1.13 * scale + 2.0 ** -8 * ref.abs() + 1e-30).all())

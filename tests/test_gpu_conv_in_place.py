@@ -23,14 +23,18 @@ def pgk():
 
 # B, Cin, L, Cout, Kw, stride, pad, dilation
 CASES = [
-    # 128 output channels and more, whole tiles and rows and one more or less of each; one, two and many K steps
+    # tiles of 128 or 64 output channels, whole tiles and rows and one more or less of each; one, two and many K steps
     (30, 32, 2050, 128, 3, 1, 0, 1), (30, 33, 2049, 129, 3, 1, 1, 1), (9, 20, 3000, 383, 5, 1, 2, 1), (24, 7, 1400, 300, 4, 1, 0, 1),
-    # 64
+    (28, 17, 2200, 102, 1, 1, 1, 2), (51, 38, 2302, 69, 1, 2, 5, 2), (39, 66, 1379, 67, 1, 1, 0, 1), (22, 34, 4624, 67, 3, 2, 5, 2),
+    (50, 120, 902, 68, 2, 1, 5, 1),
+    # of 64 or 32
     (20, 57, 1801, 64, 5, 1, 2, 1), (20, 31, 1700, 63, 1, 1, 0, 1), (12, 100, 1537, 192, 3, 2, 1, 1), (16, 40, 3001, 50, 3, 1, 2, 2),
-    # 32
+    # of 32 (the last one is the views', the faster way there)
     (20, 53, 2500, 19, 3, 1, 1, 1), (24, 18, 1300, 32, 10, 1, 0, 1), (14, 37, 3300, 26, 5, 1, 2, 1), (10, 90, 1900, 30, 3, 2, 0, 2),
-    # rows of less than a tile, padding wider than the row, wide halos, strides beyond the tap count, one channel
+    # rows of less than a tile, padding wider than the row, wide halos, strides beyond the tap count, one channel (with five taps on the
+    # bounds-checked kernel: too few products)
     (40, 16, 20, 24, 3, 1, 1, 1), (30, 24, 30, 40, 5, 1, 70, 9), (8, 24, 900, 40, 3, 7, 2, 40), (6, 5, 4001, 48, 9, 3, 4, 2), (3, 1, 700, 16, 5, 1, 2, 1),
+    (3, 1, 700, 16, 13, 1, 2, 1), (9, 1, 900, 40, 20, 1, 5, 1), (11, 130, 1201, 128, 2, 1, 1, 1),
 ]
 
 

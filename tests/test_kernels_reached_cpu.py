@@ -2,7 +2,10 @@
 the GPU tests reach the kernels they are meant for."""
 import pytest
 
+import test_gpu_conv_bf16_in_place as in_place
+import test_gpu_conv_in_place as in_place_fp32
 import test_gpu_reduce_block as blocks
+import test_gpu_register_trips as trips
 from launches import traced
 from paper_2511_06345_amd import inputs as gen
 
@@ -73,3 +76,44 @@ def test_convolutions_in_place_take_no_more_workspace_than_they_write_to():
     views = (F32, 2, 64, 1024, 32, 3, 1, 1, 1)
     assert binding.conv1d_workspace_bytes(*views[1:], F32) == binding.conv1d_workspace_least_bytes(*views[1:], F32) > 0
     assert traced([("conv1d", *views)], workspace=0) == [-3]
+
+
+def last_kernels(calls, **how):
+    return [call if isinstance(call, int) else call[-1].kernel for call in traced(calls, **how)]
+
+
+def test_sizes_for_each_instance_of_the_bf16_convolution_reach_it():
+    for off in (0, 1):
+        kernels = last_kernels([("conv1d", BF16, *case) for _, case in in_place.INSTANCES], x_off=off)
+        for ((rows, groups, parts), case), kernel in zip(in_place.INSTANCES, kernels):
+            assert kernel == f"conv_bf16_kernel<{rows}, {groups}, {str(parts).lower()}>", (case, kernel)
+    reached = {instance for instance, _ in in_place.INSTANCES}
+    assert reached == {(rows, groups, parts) for rows in (32, 64, 128) for groups in (1, 2, 3) for parts in (False, True)} - {(r, 1, True) for r in (32, 64, 128)}
+    # with one workgroup, rows of two elements, 384 positions
+    alone = traced([("conv1d", BF16, *case) for instance, case in in_place.INSTANCES if case[0] == 1])
+    assert sum(call[-1].grid == 1 for call in alone) >= 6
+    assert any((case[4] - 1) * case[7] + 127 * case[5] + 1 == 384 for _, case in in_place.INSTANCES) and any(case[2] == 2 for _, case in in_place.INSTANCES)
+
+
+def test_sizes_for_each_tile_through_registers_reach_it():
+    for off in (0, 1):
+        sizes = [(tile, case) for tile, case in trips.CONVOLUTIONS.items() if case[-1] == off]
+        kernels = last_kernels([("conv1d", BF16, B, Cin, L, Cout, Kw, 1, pad, dil) for _, (B, Cin, L, Cout, Kw, pad, dil, _) in sizes], x_off=off)
+        for (((rows, cols, tiles), case), kernel) in zip(sizes, kernels):
+            assert kernel.startswith(f"gemm_mfma_kernel<MfmaCfgReg<false, {rows}, {cols}, 64") and case[1] // 64 * case[4] == tiles, (case, kernel)
+    from paper_2511_06345_amd import binding
+    B, Cin, L, Cout, Kw = trips.WITHOUT_ROOM
+    need = binding.conv1d_workspace_least_bytes(B, Cin, L, Cout, Kw, 1, 0, 1, BF16)
+    copies, registers = last_kernels([("conv1d", BF16, B, Cin, L, Cout, Kw, 1, 0, 1)] * 2, workspace=[need, need // 2 // 256 * 256])
+    assert "MfmaCfg<" in copies and "MfmaCfgReg<" in registers
+
+
+def test_sizes_for_the_fp32_convolution_in_place_reach_each_tile():
+    for off in (0, 1):
+        kernels = last_kernels([("conv1d", F32, *case) for case in in_place_fp32.CASES], x_off=off)
+        steps = {}
+        for case, kernel in zip(in_place_fp32.CASES, kernels):
+            steps.setdefault(kernel, set()).add(-(-case[1] * case[4] // 32))
+        for rows in (128, 64, 32):
+            reached = [n for kernel, n in steps.items() if kernel.startswith(f"conv_f32_terms_kernel<TermsCfg<false, {rows}, 128")]
+            assert reached and len(reached[0]) >= 3, (rows, steps)
