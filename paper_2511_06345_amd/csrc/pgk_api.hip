@@ -1322,8 +1322,15 @@ int conv_rows_in_place(const ConvPlan& views, int64_t B, int64_t Cin, int64_t L,
     const struct { int rows; StepCost cost; } kinds[] = {{128, {4.84, 2.28, 1.82, 1.37, 2}}, {64, {5.46, 1.31, 1.27, 0.88, 3}}, {32, {4.79, 1.18, 1.06, 0.66, 3}}};
     int best = 0;
     double best_time = 0.0;
+    // A strided load takes a line for every few lanes, and starts its lanes on few of the cache's banks if the stride is even: so much more of a
+    // step for each workgroup (with many on a CU, strides 2, 3, 4, 5 and 8: 0.26, 0.2, 0.9, 0.6 and 1.4, with one or two, which the
+    // cache holds, less; [1, 256, 131200] x [19, 256, 10] stride 2 162 us in the views, 229 here).  Of 1200 drawn convolutions of strides 2 to
+    // 11 without it 45 were over 5 % slower than before there was this way, 0.56 the worst.
+    const double apart = (stride % 2 != 0 ? 0.11 : 0.2) * (double)(std::min<int64_t>(stride, 4) - 1);
     for (const auto& k : kinds) {
-        const double t = stepped_time(k.cost, (Cin * Kw + 31) / 32, wgs(k.rows, tiles_n));
+        StepCost cost = k.cost;
+        cost.shared += apart;
+        const double t = stepped_time(cost, (Cin * Kw + 31) / 32, wgs(k.rows, tiles_n));
         if (!best || t < best_time) { best = k.rows; best_time = t; }
     }
     if (!views.fast) return pgk::conv_few_channels_fits(B, Cin, Cout, Kw, stride, dilation, views.Lout) ? 0 : best;

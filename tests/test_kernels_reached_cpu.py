@@ -117,3 +117,17 @@ def test_sizes_for_the_fp32_convolution_in_place_reach_each_tile():
         for rows in (128, 64, 32):
             reached = [n for kernel, n in steps.items() if kernel.startswith(f"conv_f32_terms_kernel<TermsCfg<false, {rows}, 128")]
             assert reached and len(reached[0]) >= 3, (rows, steps)
+
+
+# us in the views or copies of the input / in place
+VIEWS_OR_IN_PLACE = [
+    (F32, (1, 256, 131200, 19, 10, 2, 0, 1), 162, 229), (F32, (3, 767, 6239, 512, 3, 4, 0, 1), 148, 261), (F32, (22, 256, 3515, 1, 10, 2, 0, 3), 107, 156),
+    (F32, (9, 95, 8505, 16, 10, 2, 0, 1), 47, 61), (F32, (10, 152, 53120, 19, 7, 1, 0, 1), 450, 305), (F32, (16, 57, 36868, 67, 5, 1, 0, 1), 314, 246),
+    (F32, (2, 463, 2816, 24, 5, 1, 0, 1), 51, 82),
+]
+
+
+def test_convolutions_in_place_where_that_is_faster():
+    kernels = last_kernels([("conv1d", dtype, *case) for dtype, case, _, _ in VIEWS_OR_IN_PLACE])
+    for (dtype, case, views, in_place_us), kernel in zip(VIEWS_OR_IN_PLACE, kernels):
+        assert kernel.startswith(("conv_f32_terms", "conv_bf16")) == (in_place_us < views), (dtype, case, kernel)
