@@ -1347,8 +1347,10 @@ int conv_rows_in_place(const ConvPlan& views, int64_t B, int64_t Cin, int64_t L,
 
 // bf16: blocks of 32 channels of the input in LDS, position by position (pgk_conv_bf16.hip), without copies of the input, without a K loop through
 // registers, and x read once for all taps.  A block takes what its loads and barriers take or, on a full CU, its taps and its
-// rows for every workgroup.  The constants were fitted to 420 drawn convolutions, these and those of the views' kernels (both off by an eighth in the root mean square); of the choices
-// two are over 5 % slower than the views, the mean is 1.65 times as fast, 0.98 of what the best way each time gives.  [13, 384, 11631] x [61, 384, 5]
+// rows for every workgroup; up to six of them a CU go in whole rounds.  The constants were fitted to 420 drawn convolutions, these and those of the
+// views' kernels (both off by an eighth in the root mean square), and the line lies where few choices are wrong: of 2400 others, half of them with long
+// sums, nine are over 5 % slower than before there was this way, 0.82 the worst (46 with the line at 0.92 of the views' time and without whole
+// rounds, 0.63: [2, 665, 11631] x [392, 665, 10] stride 2 113 us, 180 here), the mean is 1.60 times as fast, 1.14 with long sums.  [13, 384, 11631] x [61, 384, 5]
 // stride 2 117 us in the views, 58 here, [13, 64, 4673] x [128, 64, 7] stride 2 39 and 17; long sums over many channels are the views': [8, 512, 4096] x [512,
 // 512, 3] 56 and 86.  From 16 channels on also what had no views, which is faster here throughout (89 of the 420): [13, 20, 26691] x [202, 20, 3] 287
 // on the bounds-checked kernel and 63, [13, 17, 61760] x [64, 17, 1] 85 on the one for few channels and 27; the outputs' rounding covers what the
@@ -1369,7 +1371,7 @@ int conv_bf16_in_place(const ConvPlan& views, int64_t B, int64_t Cin, int64_t L,
         const size_t lds = pgk::conv_bf16_lds(Kw, stride, dilation, L, k.rows, &parts);
         if (!lds) return 0;
         const double per = (double)((Cout + k.rows - 1) / k.rows) * (double)tiles_n * (double)B / kNumCUs;
-        const double on_busiest = per <= std::min<double>(k.per_cu, (double)(160 * 1024 / lds)) ? std::ceil(per) : per + 0.3;
+        const double on_busiest = per <= std::max(6.0, std::min<double>(k.per_cu, (double)(160 * 1024 / lds))) ? std::ceil(per) : per + 0.3;
         const double t = k.fixed + k.per_round * on_busiest +
                          (double)blocks * std::max(k.tap_alone * (double)Kw + k.part * parts + k.group_alone * (double)groups,
                                                    on_busiest * (k.tap * (double)Kw + k.group * (double)groups));
@@ -1385,7 +1387,7 @@ int conv_bf16_in_place(const ConvPlan& views, int64_t B, int64_t Cin, int64_t L,
     // (tiles of one to a CU: whole rounds)
     const double in_views = copies + stepped_time(cost, (int64_t)((double)(Kw * ((Cin + 63) / 64)) * (views.reg ? 1.38 : 1.0)),
                                                   cost.per_cu == 1 ? std::ceil(wgs / kNumCUs) * kNumCUs - (wgs > kNumCUs ? 0.3 * kNumCUs : 0.0) : wgs);
-    return best_time < 0.92 * in_views ? best : 0;
+    return best_time < 0.85 * in_views ? best : 0;
 }
 
 ConvPlan plan_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Kw, int64_t stride, int64_t pad, int64_t dilation, int dtype,

@@ -123,7 +123,9 @@ def test_sizes_for_the_fp32_convolution_in_place_reach_each_tile():
 VIEWS_OR_IN_PLACE = [
     (F32, (1, 256, 131200, 19, 10, 2, 0, 1), 162, 229), (F32, (3, 767, 6239, 512, 3, 4, 0, 1), 148, 261), (F32, (22, 256, 3515, 1, 10, 2, 0, 3), 107, 156),
     (F32, (9, 95, 8505, 16, 10, 2, 0, 1), 47, 61), (F32, (10, 152, 53120, 19, 7, 1, 0, 1), 450, 305), (F32, (16, 57, 36868, 67, 5, 1, 0, 1), 314, 246),
-    (F32, (2, 463, 2816, 24, 5, 1, 0, 1), 51, 82),
+    (F32, (2, 463, 2816, 24, 5, 1, 0, 1), 51, 82), (BF16, (2, 665, 11631, 392, 10, 2, 4, 1), 113, 180), (BF16, (1, 256, 16069, 557, 7, 2, 3, 1), 40, 58),
+    (BF16, (19, 512, 836, 256, 7, 1, 3, 1), 66, 79), (BF16, (27, 275, 1422, 233, 10, 2, 36, 8), 55, 72), (BF16, (13, 384, 11631, 61, 5, 2, 0, 1), 117, 58),
+    (BF16, (13, 64, 4673, 128, 7, 2, 0, 1), 39, 17), (BF16, (8, 512, 4096, 512, 3, 1, 1, 1), 56, 86), (BF16, (13, 17, 61760, 64, 1, 1, 0, 1), 85, 27),
 ]
 
 
