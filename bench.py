@@ -56,7 +56,7 @@ REDUCE_DESCR = {
 CONV_DESCR = {
     "v1": "v1: fp32 conv1d [16, 64, 65536] * [128, 64, 3], stride 1, pad 1, bias + ReLU (matrix-core path)",
     "v2": "v2: bf16 conv1d [8, 256, 16384] * [256, 256, 5], stride 1, pad 4, dilation 2, bias + SiLU (matrix-core path)",
-    "v3": "v3: fp32 conv1d [4, 48, 32768] * [64, 48, 5], stride 2, pad 2, bias (matrix-core path on per-phase copies of the input)",
+    "v3": "v3: fp32 conv1d [4, 48, 32768] * [64, 48, 5], stride 2, pad 2, bias (matrix-core path)",
 }
 
 
@@ -445,8 +445,11 @@ def conv_main(args, name, pgk, gen, torch):
     fast = head["workspace_bytes"] > 0
     # the matrix-core path is priced against the matrix peak of its type, the bounds-checked
     # path (plain fp32 FMA) against the fp32 vector peak
-    # (fp32 with more than 64 output channels runs on the 128 x 128 tile)
-    terms = fast and dtype_key == "f32" and cw.Cout > 64
+    # (what is read in place writes to less of the workspace than the views would; fp32 so, and with more than 64 output channels in
+    # the views, runs in three bf16 terms)
+    in_place = fast and pgk.conv1d_workspace_least_bytes(cw.B, cw.Cin, cw.L, cw.Cout, cw.Kw, cw.stride, cw.pad, cw.dilation,
+                                                         cw.dtype) < head["workspace_bytes"]
+    terms = fast and dtype_key == "f32" and (in_place or cw.Cout > 64)
     peak = PEAK_F32_TERMS_TFLOPS if terms else PEAK_TFLOPS[dtype_key] if fast else 157.3
     achieved = cw.flops / (head["call_ms_avg"] * 1e-3) / 1e12
     out = {
@@ -459,7 +462,8 @@ def conv_main(args, name, pgk, gen, torch):
                    "stride": cw.stride, "pad": cw.pad, "dilation": cw.dilation, "flops_per_step": cw.flops,
                    "algorithmic_bytes_per_step": cw.algorithmic_bytes, "workspace_bytes": head["workspace_bytes"]},
         "roofline": {"bound": "mfma" if fast else "alu",
-                     "kernel": ("pgk::gemm_f32_terms_kernel" if terms else "pgk::gemm_mfma_kernel") + " on shifted views (+ pad and weight regrouping kernels)" if fast
+                     "kernel": ("pgk::conv_f32_terms_kernel" if terms else "pgk::conv_bf16_kernel (+ weight regrouping kernel)") + ", the input read in place" if in_place
+                               else ("pgk::gemm_f32_terms_kernel" if terms else "pgk::gemm_mfma_kernel") + " on shifted views (+ pad and weight regrouping kernels)" if fast
                                else "pgk::gemm_guarded_kernel reading the input in place",
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                      "launch_ms_avg": head["call_ms_avg"], "traffic": None,

@@ -1302,8 +1302,8 @@ double stepped_time(const StepCost& c, int64_t steps, double wgs)
 // fp32: the input and the weights read in place (pgk_gemm_f32_terms.h, VIEW_INPUT), without a launch that copies or regroups,
 // K = Cin * Kw without padding channels and tiles of 128, 64 or 32 output channels.  Bound like that kernel by issue slots, of which the loads take
 // more than from a matrix, so that few workgroups with long sums are slower than the fp32 instruction's small tiles.  The constants
-// were fitted to 400 drawn convolutions with each way forced, both off by a tenth in the root mean square: of the choices one is
-// over 2 % slower than the views, the mean is 1.21 times as fast, 0.97 of what the best way each time gives.  [10, 152, 53120] x
+// were fitted to 400 drawn convolutions of strides 1 and 2 with each way forced, both off by a tenth in the root mean square: of the choices one is
+// over 2 % slower than the views (what larger strides and more workgroups add: `apart` below), the mean is 1.21 times as fast, 0.97 of what the best way each time gives.  [10, 152, 53120] x
 // [19, 152, 7] 450 us in the views, 305 here; [16, 57, 36868] x [67, 57, 5] 314 and 246; [2, 463, 2816] x [24, 463, 5], 46 workgroups and 73 steps,
 // 51 and 82.  What has neither views nor enough to do for pgk_conv_few.hip was on the bounds-checked kernel: of 76 shapes none is
 // slower here, the mean 1.27 times as fast.

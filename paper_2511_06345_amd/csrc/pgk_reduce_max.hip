@@ -10,9 +10,9 @@
 // and small problems one element per load (plan_reduce_max).
 //   * inner == 1 (the reduced dimension is contiguous): some lanes of a wave (short rows), a wave or a workgroup hold a row in
 //     registers, in 16-byte chunks all loaded at once; longer ones are swept by a workgroup.  The maximum comes first, its position after.
-//   * 1 < inner, up to about half of what a workgroup loads at once: a workgroup sweeps its block of whole r as it
+//   * 1 < inner, up to about half of what a workgroup loads at once, blocks large enough (plan_block): a workgroup sweeps its block of whole r as it
 //     lies in memory, 16 bytes per lane, and combines the lanes of equal inner position through LDS.
-//   * inner beyond that: lanes lie along the contiguous inner dimension, 16 bytes each; the four
+//   * inner beyond that, and smaller blocks: lanes lie along the contiguous inner dimension, 16 bytes each; the four
 //     waves of a workgroup take every fourth r and are combined through LDS.
 // Every combination step compares (value, position) pairs, so the result does not depend
 // on how the work was split.  When there are too few outputs to fill the chip the reduced
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(256) void reduce_max_cols_kernel(const void* __rest
 }
 
 // ---------------------------------------------------------------------------------
-// 1 < inner <= 64, many small blocks (the others go to the kernel after this one).  One wave owns one outer index (and the r range of one segment) and sweeps that contiguous
+// 1 < inner <= 64 (the blocks that plan_block does not give to the kernel after this one).  One wave owns one outer index (and the r range of one segment) and sweeps that contiguous
 // block of red x inner elements: R = 64 / inner consecutive r at a time, lane l at inner
 // position l % inner of r number l / inner of the sweep -- 64 (or R * inner) consecutive
 // elements per load instruction, eight sweeps in flight.  The lanes that share an inner

@@ -1,7 +1,7 @@
 // The binding's ordinary calls in native code: operands are plain contiguous device tensors, outputs and workspace come from
 // torch's allocator, the stream is the current one.  What binding.py does for such a call, in the same order, without the
 // interpreter: a small call is bound by the host (fp32 256^3 with row sums, two launches and three
-// allocations, 15.7 us through the interpreter and 7.7 so, calls of one launch and one allocation 8.5 and 5.1).  Everything else -- a caller's outputs, workspace or stream, operands that are to be refused, subclasses and
+// allocations, 15.4 us through the interpreter and 7.7 to 9.2 so, calls of one launch and one allocation 8.5 and 5.1).  Everything else -- a caller's outputs, workspace or stream, operands that are to be refused, subclasses and
 // wrapped tensors, numbers that are no plain ints -- is answered with None, and binding.py goes its general way.
 //
 // Functions return a tensor or a tuple of them, the library's status (an int) where that is not zero, or None.
