@@ -268,7 +268,8 @@ int pgk_splitk_auto_splits(int64_t M, int64_t N, int64_t K, int64_t batch,
  * are few outputs and a long reduced dimension the range is reduced in segments and a
  * second small kernel combines them; the segment results (value, position) live in
  * `workspace`: pgk_reduce_max_workspace_bytes(...) bytes of device memory on a 4-byte
- * boundary, NULL / 0 when that is 0 (see "Workspace" at the top).
+ * boundary, NULL / 0 when that is 0 (see "Workspace" at the top).  With fewer, a strided reduction (inner > 1) of short or few
+ * blocks [red][inner] runs on a kernel that needs less or none, if that is enough; else PGK_ERR_WORKSPACE.
  * The result does not depend on how the work was split and is bit-reproducible.
  */
 int pgk_reduce_max(const void* X, void* out, int32_t* idx,

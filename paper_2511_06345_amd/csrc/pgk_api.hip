@@ -1135,7 +1135,13 @@ int pgk_reduce_max(const void* X, void* out, int32_t* idx, int64_t outer, int64_
     if ((long double)outer * (long double)inner >= 4.6e18L ||
         (long double)outer * (long double)inner * (long double)red >= 4.6e18L) return PGK_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const pgk::ReducePlan pl = pgk::plan_reduce_max(outer, red, inner, dtype, aligned16(X));
+    pgk::ReducePlan pl = pgk::plan_reduce_max(outer, red, inner, dtype, aligned16(X));
+    // (too little room for the faster way's segments: whole blocks, if that takes no more than there is)
+    const size_t room = workspace && !(reinterpret_cast<uintptr_t>(workspace) & 3u) ? workspace_bytes : 0;
+    if (pl.partial_elems * 8 > room) {
+        const pgk::ReducePlan blocks = pgk::plan_reduce_max_blocks(outer, red, inner, dtype, aligned16(X));
+        if (blocks.blocks > 0 && blocks.partial_elems * 8 <= room) pl = blocks;
+    }
     if (pl.blocks <= 0 || pl.blocks > 0x7fffffffLL) return PGK_ERR_UNSUPPORTED;
     float* pv = nullptr;
     int* pi = nullptr;

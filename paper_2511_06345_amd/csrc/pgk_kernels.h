@@ -183,6 +183,8 @@ struct ReducePlan {
     bool held;             // rows in registers, per_seg chunks a lane
 };
 ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int dtype, bool x_aligned);
+// The kernel that sweeps whole blocks wherever it goes, also where it is not the fastest: fewer partial results, or none (blocks == 0: it does not go).
+ReducePlan plan_reduce_max_blocks(long long outer, long long red, long long inner, int dtype, bool x_aligned);
 // pv / pi: partial_elems floats / ints of scratch (unused when partial_elems == 0).
 hipError_t launch_reduce_max(const ReducePlan& pl, const void* X, void* out, int* idx, float* pv, int* pi,
                              long long outer, long long red, long long inner, int dtype, hipStream_t s);

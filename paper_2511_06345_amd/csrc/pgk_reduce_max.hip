@@ -860,8 +860,9 @@ ReducePlan plan_strided(long long outer, long long red, long long inner, int dty
 // they take, 0.7 on average (fp32 [240, 218, 479] none, bf16 [5, 4283, 282] 41: 11.1 us, 14.5 here), and no slower than with more of them here.
 constexpr long long kOneLaunchBytes = 256 << 10;
 
-// pl: the plan of the kernels before this one, left as it is where they are faster.
-void plan_block(ReducePlan& pl, long long outer, long long red, long long inner, int dtype)
+// pl: the plan of the kernels before this one, left as it is where they are faster -- unless `anywhere`, with which it is left only where this kernel
+// does not go.
+void plan_block(ReducePlan& pl, long long outer, long long red, long long inner, int dtype, bool anywhere)
 {
     const long long es = dtype == DT_BF16 ? 2 : 4, vec = 16 / es;
     const long long bytes = red * inner * es, lanes = 64 * vec;
@@ -869,30 +870,30 @@ void plan_block(ReducePlan& pl, long long outer, long long red, long long inner,
     const double all = 1.0e-6 * (double)outer * (double)bytes;
     const double busy = (double)inner / (double)((inner + lanes - 1) / lanes * lanes);      // share of the strided kernel's lanes that have positions
     const bool one_launch = outer < 512 && bytes <= kOneLaunchBytes;
-    if (one_launch) {
-        if (pl.segs == 1 || inner > 512 * vec || (inner > 128 * vec && red < 64)) return;
+    if (one_launch ? inner > 512 * vec || (inner > 128 * vec && red < 64) : inner > 128 * vec) return;
+    if (anywhere) {
+        // (whatever it takes)
+    } else if (one_launch) {
+        if (pl.segs == 1) return;
         if (outer > 256) { if (!bf16 || !waves || all < 3.0) return; }
         else if ((double)bytes > 1024.0 * (bf16 ? 13.0 + (waves ? 17.0 : 10.0) * all : 42.0 + 4.5 * all)) return;
-    } else {
-        if (inner > 128 * vec) return;
-        if (outer >= 512) {
-            const long long least = bf16 ? (waves ? (outer < 1024 ? 2 : 8) : inner <= lanes ? 32 : 8) * 1024 : waves ? std::min(14 * outer, 65536LL) : 256 * 1024;
-            if (bytes < least || (bf16 && !waves && inner <= lanes && busy > 0.7)) return;
-        } else if (waves) {
-            if (all < (bf16 ? 3.0 : pl.segs >= 650 ? 2.5 : 32.0)) return;
-        } else if (bf16 ? all < 20.0 || (outer > 80 && busy > 0.7) : all < 36.0 || busy > 0.5) {
-            return;
-        }
+    } else if (outer >= 512) {
+        const long long least = bf16 ? (waves ? (outer < 1024 ? 2 : 8) : inner <= lanes ? 32 : 8) * 1024 : waves ? std::min(14 * outer, 65536LL) : 256 * 1024;
+        if (bytes < least || (bf16 && !waves && inner <= lanes && busy > 0.7)) return;
+    } else if (waves) {
+        if (all < (bf16 ? 3.0 : pl.segs >= 650 ? 2.5 : 32.0)) return;
+    } else if (bf16 ? all < 20.0 || (outer > 80 && busy > 0.7) : all < 36.0 || busy > 0.5) {
+        return;
     }
     const long long nt = one_launch ? 1024 : 256;
     long long R = nt * vec / inner;
     const long long common = (inner & -inner) < vec ? (inner & -inner) : vec;      // (greatest common divisor: vec is a power of two)
     if (R >= 4 * (vec / common)) R -= R % (vec / common);
-    if (!one_launch && inner > 64 * vec && 4 * R * inner < 3 * nt * vec) return;
+    if (!anywhere && !one_launch && inner > 64 * vec && 4 * R * inner < 3 * nt * vec) return;
     long long segs = 1;
     if (!one_launch && outer < 512) {
         const long long periods = red / (4 * R), wanted = 512 / outer < periods ? 512 / outer : periods;
-        if (wanted > pl.segs) return;
+        if (!anywhere && wanted > pl.segs) return;
         const long long most = periods < pl.segs ? periods : pl.segs;
         double best = 0.0;
         for (long long target = 512; target <= 1024; target += 256) {
@@ -900,7 +901,7 @@ void plan_block(ReducePlan& pl, long long outer, long long red, long long inner,
             const double filled = (double)(n * outer) / (double)target;
             if (n >= 1 && filled > best + 0.05) { best = filled; segs = n; }
         }
-        if (inner > 64 * vec && segs == pl.segs && segs * outer < 448) return;
+        if (!anywhere && inner > 64 * vec && segs == pl.segs && segs * outer < 448) return;
     }
     pl.unaligned = false;
     pl.vec = (int)vec;
@@ -963,11 +964,19 @@ ReducePlan plan_reduce_max(long long outer, long long red, long long inner, int 
         pl.blocks = (outer + q - 1) / q;
     } else {
         pl = plan_strided(outer, red, inner, dtype, x_aligned);
-        plan_block(pl, outer, red, inner, dtype);
+        plan_block(pl, outer, red, inner, dtype, false);
         return pl;
     }
     pl.partial_elems = pl.segs > 1 ? (size_t)outer * pl.segs * (size_t)inner : 0;
     return pl;
+}
+
+ReducePlan plan_reduce_max_blocks(long long outer, long long red, long long inner, int dtype, bool x_aligned)
+{
+    if (inner == 1 || red * inner <= kTinyBlock) return {};
+    ReducePlan pl = plan_strided(outer, red, inner, dtype, x_aligned);
+    plan_block(pl, outer, red, inner, dtype, true);
+    return pl.group <= -256 ? pl : ReducePlan{};
 }
 
 namespace {

@@ -98,3 +98,18 @@ def test_special_values(pgk, oracle, dtype, shape):
     x = gen.f32_to_bf16_bits(x) if dtype == BF16 else x
     for start in (0, 1, 3):
         check(pgk, oracle, x, start, dtype)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("shape", [(5, 8632, 7), (11, 1969, 13), (9, 585, 199), (4, 2000, 64), (2, 31, 250), (261, 55, 285)])
+def test_without_a_workspace(pgk, dtype, shape):
+    """The same result whether there is room for segments or not."""
+    import torch
+    outer, red, inner = shape
+    X = torch.randint(-50, 51, shape, device="cuda").to(torch.bfloat16 if dtype == BF16 else torch.float32)
+    want = pgk.reduce_max(X, 1)
+    v, i = torch.empty_like(want[0]), torch.empty_like(want[1])
+    rc = pgk.load_library().pgk_reduce_max(X.data_ptr(), v.data_ptr(), i.data_ptr(), outer, red, inner, dtype, None, 0,
+                                           torch.cuda.current_stream().cuda_stream or None)
+    torch.cuda.synchronize()
+    assert rc == 0 and torch.equal(v, want[0]) and torch.equal(i, want[1])

@@ -133,3 +133,20 @@ def test_convolutions_in_place_where_that_is_faster():
     kernels = last_kernels([("conv1d", dtype, *case) for dtype, case, _, _ in VIEWS_OR_IN_PLACE])
     for (dtype, case, views, in_place_us), kernel in zip(VIEWS_OR_IN_PLACE, kernels):
         assert kernel.startswith(("conv_f32_terms", "conv_bf16")) == (in_place_us < views), (dtype, case, kernel)
+
+
+def test_strided_reductions_with_little_workspace():
+    """Where the faster way needs segments and there is no room for them, whole blocks in one launch, or in fewer segments; refused where those
+    do not fit either."""
+    from paper_2511_06345_amd import binding
+    blocks_in_one = [(F32, 5, 8632, 7), (F32, 11, 1969, 13), (BF16, 9, 585, 199), (BF16, 4, 2000, 64)]
+    for call, full, (launch,) in zip(blocks_in_one, traced([("reduce_max", *c) for c in blocks_in_one]), traced([("reduce_max", *c) for c in blocks_in_one], workspace=0)):
+        assert binding.reduce_max_workspace_bytes(*call[1:], call[0]) > 0 and len(full) == 2 and "block" not in full[0].kernel
+        assert launch.kernel.startswith("reduce_max_block_kernel") and launch.block == 1024
+    # [4, 9811, 14]: 298 segments the faster way, 34 of whole blocks
+    few = ("reduce_max", F32, 4, 9811, 14)
+    enough = 34 * 4 * 14 * 8
+    assert binding.reduce_max_workspace_bytes(*few[2:], F32) > enough
+    segments, refused = traced([few, few], workspace=[enough, enough - 8])
+    assert segments[0].kernel.startswith("reduce_max_block_kernel") and len(segments) == 2 and refused == -3
+    assert traced([("reduce_max", BF16, 128, 24742, 88), ("reduce_max", F32, 16, 1 << 24, 1)], workspace=0) == [-3, -3]
