@@ -371,7 +371,9 @@ def stored_traffic(workload: str, kernel_substring: str, profiles_dir: Optional[
     figure would describe other code)."""
     now = kernel_source_hash()
     for rec in read_traffic_records(profiles_dir or os.path.join(ROOT, "profiles")):
-        if rec["workload"] == workload and rec["sources"] == now and _squash(kernel_substring) in _squash(rec["kernel"]):
+        # (the name as it is usually written, without the namespace inside the template's arguments)
+        if rec["workload"] == workload and rec["sources"] == now and \
+                _squash(kernel_substring).replace("pgk::", "") in _squash(rec["kernel"]).replace("pgk::", ""):
             return rec["bytes"]
     return None
 

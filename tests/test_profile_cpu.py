@@ -167,6 +167,7 @@ def test_traffic_records_round_trip(tmp_path):
     assert [r["workload"] for r in recs] == ["c3", "c4"] and recs[0]["bytes"] == 1745802240 and recs[0]["kernel"] == kern
     assert profile.stored_traffic("c3", "MfmaCfg<true, 256, 256, 64, 4, 2, 3, 2>, 0, false>", str(tmp_path)) == 1745802240
     assert profile.stored_traffic("c3", "MfmaCfg<true,256,256,64,4,2,3,2>,0,false>", str(tmp_path)) == 1745802240   # white space
+    assert profile.stored_traffic("c3", "pgk::gemm_mfma_kernel<MfmaCfg<true, 256, 256, 64, 4, 2, 3, 2>, 0, false>", str(tmp_path)) == 1745802240   # namespaces
     assert profile.stored_traffic("c4", "MfmaCfg<true, 256, 256, 64, 4, 2, 3, 2>, 0, false>", str(tmp_path)) is None  # other sources
     assert profile.stored_traffic("c3", "MfmaCfg<false, 128, 128", str(tmp_path)) is None
     assert profile.stored_traffic("c2", "MfmaCfg", str(tmp_path)) is None
