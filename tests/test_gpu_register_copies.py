@@ -101,8 +101,8 @@ def test_convolution_of_an_input_on_any_element_exact(pgk, dtype, offset, B, Cin
 @pytest.mark.parametrize("B,Cin,L,Cout,Kw,pad,dil", [
     (2, 64, 1000, 64, 3, 1, 1), (1, 128, 4096, 256, 3, 1, 1), (2, 64, 777, 100, 5, 2, 1), (1, 64, 513, 48, 4, 0, 1),
     (3, 192, 300, 130, 3, 3, 3), (1, 64, 129, 64, 7, 3, 1), (1, 64, 2001, 512, 1, 0, 1), (2, 64, 640, 64, 3, 101, 1),
-    # the tiles of 256 x 256, 256 x 128 (outputs of at most 128 positions) and 128 x 256 (at most 128 channels), enough of them
-    # to be chosen
+    # large grids (most of these read their input in place, through LDS: sizes that reach each tile through registers are in
+    # test_gpu_register_trips.py, asserted by test_kernels_reached_cpu.py)
     (8, 128, 4097, 512, 3, 1, 1), (9, 64, 4001, 500, 5, 2, 1), (97, 64, 101, 512, 3, 1, 1), (49, 128, 130, 1000, 3, 0, 1),
     (12, 64, 4097, 128, 3, 1, 1), (13, 128, 3900, 100, 7, 3, 1),
 ])
@@ -187,6 +187,7 @@ def test_without_room_and_without_a_kernel_the_call_is_refused(pgk):
 
 
 def test_convolution_without_room_for_copies_reads_its_input_in_place(pgk):
+    # (through LDS at this size; through registers: test_convolution_without_room_for_copies_goes_through_registers)
     B, Cin, L, Cout, Kw, pad = 7, 384, 1656, 265, 10, 3
     need = pgk.conv1d_workspace_bytes(B, Cin, L, Cout, Kw, 1, pad, 1, BF16)
     assert need > 2 * 2 * B * Cin * L                       # two copies of the input
